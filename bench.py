@@ -172,7 +172,7 @@ def measure(cfg, inp, steps: int, warmup: int, cold: bool = True):
     res = {
         "workload": workload_name(cfg, C), "filled_slots": R, "slots": E * C,
         "ms_per_step": round(ms_per_step, 5), "tokens_per_s": round(T / (ms_per_step * 1e-3), 1),
-        "roofline": {"bound": "mfma" if bf16 else "alu", "kernel": "grouped_gemm_mfma_kernel" if bf16 else "gemm_generic_kernel",
+        "roofline": {"bound": "mfma" if bf16 else "alu", "kernel": "grouped_gemm_mfma_kernel" if bf16 else "grouped_gemm_tile_kernel",
                      "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                      "flop_per_launch": flop_per_gemm, "avg_launch_ms": round(gemm_ms, 5),
                      "traffic": recorded_gemm_traffic(cfg.name)},

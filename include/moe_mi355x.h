@@ -168,7 +168,7 @@ int moe_encode(const void* x, int dtype, const int32_t* idx, const int32_t* loc,
  *   Y[e] = act(Z[e] * W1[e] + b1[e]) * W2[e] + b2[e]     for every expert e.
  *   Z [E,C,M], W1 [E,M,H], W2 [E,H,M], Y [E,C,M], hidden [E,C,H] (scratch) in `dtype`; b1 [E,H], b2 [E,M] in
  *   `dtype` or NULL.  bf16: products accumulate in fp32 on the matrix cores, the hidden activations are rounded to
- *   bf16 once after the activation and Y once at the end.  fp32: plain fp32 FMA accumulation.
+ *   bf16 once after the activation and Y once at the end.  fp32: fp32 products and sums on the matrix cores.
  *   counts [E] int32 or NULL: if given, only the first min(counts[e], C) rows of each expert are computed and the
  *   remaining rows of Y and hidden are left untouched (decode never reads them); if NULL all C rows are computed.
  *   act: ReLU, GeLU (the erf form v * Phi(v); the bf16 matrix-core path evaluates Phi to within 6e-7) or SiLU. */
@@ -219,8 +219,8 @@ int moe_expert_ffn_train(const void* Z, const void* W1, const void* b1, const vo
                          const int32_t* counts, int64_t E, int64_t C, int64_t M, int64_t H, void* pre, void* hidden, void* Y,
                          void* stream);
 
-/* Bytes of workspace moe_expert_ffn_backward needs (recomputed pre-activations, dP, one transposed weight matrix,
- * one transposed and one row-padded activation slab).  0 on invalid arguments. */
+/* Bytes of workspace moe_expert_ffn_backward needs (recomputed pre-activations, dP, the zero-padded last rows of two
+ * operands).  0 on invalid arguments. */
 size_t moe_ffn_backward_workspace_bytes(int64_t E, int64_t C, int64_t M, int64_t H, int dtype);
 
 /* Backward of the local experts' feed-forward layer (Sec. 3.2: in the backward pass "the computation becomes the

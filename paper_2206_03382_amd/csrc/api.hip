@@ -5,26 +5,6 @@
 #include "common.h"
 
 namespace moe {
-hipError_t launch_grouped_gemm_generic(const void* A, const void* B, const void* bias, int act, int dtype,
-                                       const int32_t* counts, int64_t E, int64_t C, int64_t K, int64_t N, void* out,
-                                       hipStream_t s);
-hipError_t launch_grouped_gemm_mfma(const void* A, const void* B, const void* bias, int act, const int32_t* counts,
-                                    int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s,
-                                    const int32_t* gather = nullptr, int64_t gather_rows = 0, void* pre_out = nullptr);
-bool grouped_gemm_mfma_supports(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows = 0);
-
-hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, int act, int dtype, const int32_t* counts,
-                               int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, void* pre_out) {
-  if (act < 0) pre_out = nullptr;                                   // nothing to tell apart
-  if (dtype == MOE_BF16 && grouped_gemm_mfma_supports(E, C, K, N))
-    return launch_grouped_gemm_mfma(A, B, bias, act, counts, E, C, K, N, out, s, nullptr, 0, pre_out);
-  if (pre_out) {                                                    // the plain kernel has one output: run it twice
-    const hipError_t err = launch_grouped_gemm_generic(A, B, bias, -1, dtype, counts, E, C, K, N, pre_out, s);
-    if (err != hipSuccess) return err;
-  }
-  return launch_grouped_gemm_generic(A, B, bias, act, dtype, counts, E, C, K, N, out, s);
-}
-
 namespace {
 
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -312,9 +292,9 @@ int moe_expert_ffn_gather(const void* x, const int32_t* slot_src, int64_t T, con
   if (int st = row_shape_status(M)) return st;
   if (int st = row_shape_status(H)) return st;
   if (!aligned(x, 16) || !aligned(W1, 16) || !aligned(W2, 16) || !aligned(hidden, 16) || !aligned(Y, 16)) return MOE_UNSUPPORTED;
-  if (dtype != MOE_BF16 || !grouped_gemm_mfma_supports(E, C, M, H, T)) return MOE_UNSUPPORTED;
+  if (dtype != MOE_BF16 || !grouped_gemm_gathers_on_large_tile(E, C, M, H, T)) return MOE_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
-  if (launch_grouped_gemm_mfma(x, W1, b1, act, counts, E, C, M, H, hidden, s, slot_src, T) != hipSuccess) return MOE_HIP_ERROR;
+  if (launch_grouped_gemm(x, W1, b1, act, dtype, counts, E, C, M, H, hidden, s, nullptr, slot_src, T) != hipSuccess) return MOE_HIP_ERROR;
   if (launch_grouped_gemm(hidden, W2, b2, -1, dtype, counts, E, C, H, M, Y, s) != hipSuccess) return MOE_HIP_ERROR;
   return MOE_OK;
 }
@@ -404,7 +384,7 @@ struct TrainState {
 // The training step reads the experts' input rows straight from the token matrix through the slot -> token map (first
 // GEMM of the forward, first layer's weight gradient of the backward) wherever the matrix-core kernels take the shape.
 bool train_fuses_dispatch(int64_t T, int64_t M, int64_t H, int64_t E, int64_t C, int dtype) {
-  return dtype == MOE_BF16 && grouped_gemm_mfma_supports(E, C, M, H, T) && ffn_backward_gather_supports(E, C, M, H, T, dtype);
+  return dtype == MOE_BF16 && grouped_gemm_gathers_on_large_tile(E, C, M, H, T) && grouped_gemm_tn_gathers(E, C, M, H, T);
 }
 
 TrainState train_layout(int64_t T, int64_t M, int64_t H, int64_t E, int k, int64_t C, int dtype) {
@@ -469,10 +449,10 @@ int layer_forward(const void* x, const void* Wg, const float* gate_bias, const v
   if (run_gate(x, Wg, gate_bias, dtype, T, M, E, k, C, normalize, d_logits, d_idx, d_gw, d_loc, d_counts, d_src, d_gws, s, mark) != hipSuccess ||
       !mark())
     return MOE_HIP_ERROR;
-  if (fuse_dispatch && dtype == MOE_BF16 && grouped_gemm_mfma_supports(E, C, M, H, T)) {
+  if (fuse_dispatch && dtype == MOE_BF16 && grouped_gemm_gathers_on_large_tile(E, C, M, H, T)) {
     // the first expert GEMM gathers its rows from x through slot_src: the dispatch buffer is never materialised
     if (!mark()) return MOE_HIP_ERROR;
-    if (launch_grouped_gemm_mfma(x, W1, b1, act, d_counts, E, C, M, H, d_hidden, s, d_src, T) != hipSuccess || !mark())
+    if (launch_grouped_gemm(x, W1, b1, act, dtype, d_counts, E, C, M, H, d_hidden, s, nullptr, d_src, T) != hipSuccess || !mark())
       return MOE_HIP_ERROR;
   } else {
     // the dispatch buffer is internal here and the expert GEMM skips rows past an expert's fill: no zero rows needed
@@ -646,7 +626,7 @@ int moe_layer_forward_train(const void* x, const void* Wg, const float* gate_bia
                [] { return true; }) != hipSuccess)
     return MOE_HIP_ERROR;
   if (w.fused) {
-    if (launch_grouped_gemm_mfma(x, W1, b1, act, counts, E, C, M, H, base + w.hidden, s, src, T, base + w.pre) != hipSuccess)
+    if (launch_grouped_gemm(x, W1, b1, act, dtype, counts, E, C, M, H, base + w.hidden, s, base + w.pre, src, T) != hipSuccess)
       return MOE_HIP_ERROR;
   } else {
     // the slabs are internal and every later stage stops at an expert's fill: no zero rows needed

@@ -141,19 +141,23 @@ hipError_t launch_encode(const void* x, int dtype, const int32_t* idx, const int
 hipError_t launch_decode(const void* Y, int dtype, const int32_t* idx, const int32_t* loc, const float* gate_w,
                          int64_t T, int64_t M, int64_t E, int k, int64_t C, void* out, hipStream_t s,
                          const int64_t* C_dev = nullptr);
-// One grouped GEMM: out[e] = epilogue(A[e] (rows_e x K) * B[e] (K x N) + bias[e]); A [E,C,K], B [E,K,N], out [E,C,N].
+// Grouped GEMMs (ffn_mfma.hip), any K and N that are multiples of 8, bf16 or fp32.
+// out[e] = epilogue(A[e] (rows_e x K) * B[e] (K x N) + bias[e]); A [E,C,K], B [E,K,N], out [E,C,N].
 // act < 0 means no activation.  With `pre_out` [E,C,N] the values before the activation are written there as well.
+// With `gather` [E, C] row c of A[e] is row gather[e, c] of one matrix [gather_rows, K].
 hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, int act, int dtype, const int32_t* counts,
-                               int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, void* pre_out = nullptr);
-
-// Matrix-core GEMM with transposed operands (ffn_mfma.hip), bf16 only; see there for the argument meaning.
-bool grouped_gemm_mfma_supports_backward(int64_t E, int64_t C, int64_t M, int64_t H);
-bool grouped_gemm_mfma_supports_nt(int64_t rows, int64_t K, int64_t N);
-hipError_t launch_grouped_gemm_mfma_nt(const void* A, const void* Bt, const int32_t* counts, int64_t E, int64_t C,
-                                       int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s);
-hipError_t launch_grouped_gemm_mfma_tn(const void* At, const void* B, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
-                                       int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s,
-                                       const int32_t* gather = nullptr, int64_t gather_rows = 0);
+                               int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, void* pre_out = nullptr,
+                               const int32_t* gather = nullptr, int64_t gather_rows = 0);
+// The products of the backward, with an operand used transposed; see ffn_mfma.hip for the arguments.
+hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, const int32_t* counts, int64_t E, int64_t C,
+                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s);
+hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
+                                  int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s,
+                                  const int32_t* gather = nullptr, int64_t gather_rows = 0);
+size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W);
+// bf16 shapes whose first product, or whose products in both directions, read A through `gather` on the large tile
+bool grouped_gemm_gathers_on_large_tile(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows);
+bool grouped_gemm_tn_gathers(int64_t E, int64_t C, int64_t M, int64_t H, int64_t gather_rows);
 
 size_t gate_backward_workspace_bytes(int64_t T, int64_t M, int64_t E);
 hipError_t launch_gate_backward(const void* x, const void* Wg, const float* logits, const int32_t* idx, const float* dgate_w,
@@ -162,8 +166,7 @@ hipError_t launch_gate_backward(const void* x, const void* Wg, const float* logi
 
 // Backward of the expert feed-forward layer (ffn_backward.hip): byte offsets of its workspace pieces
 struct FfnBackwardWorkspace {
-  size_t pre, dP, Wt, At, Bp, total;
-  int64_t Cp;                                             // capacity padded to the GEMM's K step
+  size_t pre, dP, a_tail, b_tail, total;
 };
 FfnBackwardWorkspace ffn_backward_layout(int64_t E, int64_t C, int64_t M, int64_t H, int dtype);
 hipError_t launch_expert_ffn_backward(const void* Z, const void* W1, const void* b1, const void* W2, const void* pre,
@@ -171,7 +174,6 @@ hipError_t launch_expert_ffn_backward(const void* Z, const void* W1, const void*
                                       int64_t C, int64_t M, int64_t H, void* ws, void* dZ, void* dW1, void* db1, void* dW2,
                                       void* db2, hipStream_t s, const int32_t* gather = nullptr, int64_t gather_rows = 0);
 // With `gather` [E, C] (slot -> token) `Z` is the token matrix [gather_rows, M] itself (fused dispatch: the slabs of
-// dispatched rows were never written); needs saved pre-activations and shapes the matrix-core backward takes.
-bool ffn_backward_gather_supports(int64_t E, int64_t C, int64_t M, int64_t H, int64_t gather_rows, int dtype);
+// dispatched rows were never written); needs saved pre-activations and shapes grouped_gemm_tn_gathers takes.
 
 }  // namespace moe

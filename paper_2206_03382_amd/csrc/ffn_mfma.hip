@@ -67,6 +67,10 @@ constexpr int kNN = 0, kNT = 1, kTN = 2;    // operand layouts, see the head of 
 __device__ __forceinline__ void global_to_lds_16(const char* base, uint32_t voff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
+// The same from an address of the lane's own.
+__device__ __forceinline__ void global_to_lds_16(const char* addr, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(addr), "s"(lds_addr) : "memory", "m0");
+}
 
 // Branch-free activations for the bf16 epilogue.  gelu(v) = v Phi(v) with Phi(-y) = erfc(y / sqrt 2) / 2 for y = |v|:
 // e = 2^-P(y) with a degree-5 polynomial P fitted to -log2 erfc(y / sqrt 2) (weighted least squares on [0, 9] with P(0) = 0;
@@ -132,6 +136,93 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
 }
 
 }  // namespace
+
+// A weight-gradient product (kTN) reduces over an expert's slots: K-steps of 64 slots, the last one (whole or not) read
+// from the side buffers, which also covers an expert without any slot (one K-step of zeros).
+__host__ __device__ inline int slot_ksteps(int64_t fill) { return fill > 0 ? (int)((fill + BK - 1) / BK) : 1; }
+
+// Tiles per group of the block numbering (log2): 32 when the launch has several rounds of tiles for every compute unit;
+// fewer when it has not, so that the groups, which are dealt whole to the XCDs, still spread evenly over them.
+__host__ __device__ inline int group_size_log2(int64_t live_tiles) { return live_tiles >= 1024 ? 5 : (live_tiles >= 512 ? 4 : 3); }
+
+// Blocks to launch so that every tile is reached whatever the fills turn out to be and whichever group size they select.
+static inline int64_t tile_grid(int64_t E, int64_t MT, int64_t NT) {
+  int64_t blocks = 0;
+  for (int gs = 3; gs <= 5; ++gs) {
+    const int64_t G = (int64_t)1 << gs, groups = E * ceil_div(MT * NT, G);      // upper bound: every expert full
+    const int64_t b = ceil_div(groups, 8) * 8 * G;                              // G blocks per group, groups dealt to 8 XCDs
+    blocks = b > blocks ? b : blocks;
+  }
+  return blocks;
+}
+
+// Which tile block number b works on (see the numbering described in the kernel below).  Returns kTileNone past the last
+// live group, kTileIdle for an idle slot of a short group, kTileLive otherwise with the expert, its row and column tile and
+// the expert's number of real rows.
+constexpr int kTileLive = 0, kTileIdle = 1, kTileNone = 2;
+template <int TILE_ROWS>
+__device__ __forceinline__ int find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
+                                         int& e_out, int& mt_out, int& nt_out, int& rows_out) {
+  auto live_rows = [&](int el) -> int {                             // rows of expert el that exist (its fill, at most C)
+    if (el >= E) return 0;
+    int64_t r = C;
+    if (counts) { const int64_t c = counts[el]; r = c < C ? (c > 0 ? c : 0) : C; }
+    return (int)r;
+  };
+  constexpr int kChunks = kMaxExperts / 64;
+  int rowsv[kChunks], mtv[kChunks];                                 // lane l of chunk c: rows / live row tiles of expert 64 c + l
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) rowsv[c] = c * 64 < E ? live_rows(c * 64 + lane) : 0;      // all loads in flight at once
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) mtv[c] = (rowsv[c] + TILE_ROWS - 1) / TILE_ROWS;
+  int live_tiles = 0;                                               // live tiles of all experts
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) {
+    if (c * 64 >= E) break;
+    live_tiles += __builtin_amdgcn_readlane(wave_inclusive_scan(mtv[c] * NT), 63);
+  }
+  const int gs = group_size_log2(live_tiles), G = 1 << gs;          // tiles per group
+  const int group = ((b / 8) >> gs) * 8 + b % 8, slot = (b / 8) & (G - 1);
+  int total_full = 0;                                               // full groups of all experts
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) {
+    if (c * 64 >= E) break;
+    total_full += __builtin_amdgcn_readlane(wave_inclusive_scan((mtv[c] * NT) >> gs), 63);
+  }
+  const bool short_group = group >= total_full;
+  const int target = short_group ? group - total_full : group;
+  int e = -1, mte = 0, rank = 0, rows_e = 0;                        // expert, its live row tiles, group's rank among its own, its rows
+  int base = 0;
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) {
+    if (c * 64 >= E || e >= 0) break;
+    const int mt_l = mtv[c];
+    const int ng_l = short_group ? (((mt_l * NT) & (G - 1)) != 0 ? 1 : 0) : (mt_l * NT) >> gs;
+    const int inc = wave_inclusive_scan(ng_l);                      // inclusive prefix sum over the wave
+    const int tot = __builtin_amdgcn_readlane(inc, 63);
+    if (target < base + tot) {
+      const unsigned long long hit = __ballot(base + inc > target);
+      const int l = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
+      e = c * 64 + l;                                               // the same in every lane: keep them in scalar registers
+      mte = __builtin_amdgcn_readlane(mt_l, l);
+      rows_e = __builtin_amdgcn_readlane(rowsv[c], l);
+      rank = target - (base + __builtin_amdgcn_readlane(inc - ng_l, l));
+    }
+    base += tot;
+  }
+  if (e < 0) return kTileNone;                                      // past the last live group
+  const int q = ((short_group ? (mte * NT) >> gs : rank) << gs) + slot;
+  if (q >= mte * NT) return kTileIdle;                              // idle slot of a short group
+  const int full = (NT / 8) * mte * 8;                              // live tiles of this expert in full 8-column blocks
+  int mt, nt;
+  if (q < full) { mt = (q % (mte * 8)) / 8; nt = (q / (mte * 8)) * 8 + q % 8; }
+  else { const int w = NT % 8, r = q - full; mt = r / w; nt = (NT / 8) * 8 + r % w; }
+  e_out = e; mt_out = mt; nt_out = nt; rows_out = rows_e;
+  return kTileLive;
+}
+
+#include "ffn_tile.h"
+
 
 // ---- main loop -------------------------------------------------------------------------------------------------
 // K-step kt (64 wide) is four sub-steps of 16 MFMAs.  While sub-step s computes from one fragment buffer, the 12 LDS
@@ -344,89 +435,6 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
   }
 }
 
-// A weight-gradient product (kTN) reduces over an expert's slots: K-steps of 64 slots, the last one (whole or not) read
-// from the side buffers, which also covers an expert without any slot (one K-step of zeros).
-__host__ __device__ inline int slot_ksteps(int64_t fill) { return fill > 0 ? (int)((fill + BK - 1) / BK) : 1; }
-
-// Tiles per group of the block numbering (log2): 32 when the launch has several rounds of tiles for every compute unit;
-// fewer when it has not, so that the groups, which are dealt whole to the XCDs, still spread evenly over them.
-__host__ __device__ inline int group_size_log2(int64_t live_tiles) { return live_tiles >= 1024 ? 5 : (live_tiles >= 512 ? 4 : 3); }
-
-// Blocks to launch so that every tile is reached whatever the fills turn out to be and whichever group size they select.
-static inline unsigned tile_grid(int64_t E, int64_t MT, int64_t NT) {
-  int64_t blocks = 0;
-  for (int gs = 3; gs <= 5; ++gs) {
-    const int64_t G = (int64_t)1 << gs, groups = E * ceil_div(MT * NT, G);      // upper bound: every expert full
-    const int64_t b = ceil_div(groups, 8) * 8 * G;                              // G blocks per group, groups dealt to 8 XCDs
-    blocks = b > blocks ? b : blocks;
-  }
-  return (unsigned)blocks;
-}
-
-// Which tile block number b works on (see the numbering described in the kernel below).  Returns kTileNone past the last
-// live group, kTileIdle for an idle slot of a short group, kTileLive otherwise with the expert, its row and column tile and
-// the expert's number of real rows.
-constexpr int kTileLive = 0, kTileIdle = 1, kTileNone = 2;
-__device__ __forceinline__ int find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
-                                         int& e_out, int& mt_out, int& nt_out, int& rows_out) {
-  auto live_rows = [&](int el) -> int {                             // rows of expert el that exist (its fill, at most C)
-    if (el >= E) return 0;
-    int64_t r = C;
-    if (counts) { const int64_t c = counts[el]; r = c < C ? (c > 0 ? c : 0) : C; }
-    return (int)r;
-  };
-  constexpr int kChunks = kMaxExperts / 64;
-  int rowsv[kChunks], mtv[kChunks];                                 // lane l of chunk c: rows / live row tiles of expert 64 c + l
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) rowsv[c] = c * 64 < E ? live_rows(c * 64 + lane) : 0;      // all loads in flight at once
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) mtv[c] = (rowsv[c] + BM - 1) / BM;
-  int live_tiles = 0;                                               // live tiles of all experts
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) {
-    if (c * 64 >= E) break;
-    live_tiles += __builtin_amdgcn_readlane(wave_inclusive_scan(mtv[c] * NT), 63);
-  }
-  const int gs = group_size_log2(live_tiles), G = 1 << gs;          // tiles per group
-  const int group = ((b / 8) >> gs) * 8 + b % 8, slot = (b / 8) & (G - 1);
-  int total_full = 0;                                               // full groups of all experts
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) {
-    if (c * 64 >= E) break;
-    total_full += __builtin_amdgcn_readlane(wave_inclusive_scan((mtv[c] * NT) >> gs), 63);
-  }
-  const bool short_group = group >= total_full;
-  const int target = short_group ? group - total_full : group;
-  int e = -1, mte = 0, rank = 0, rows_e = 0;                        // expert, its live row tiles, group's rank among its own, its rows
-  int base = 0;
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) {
-    if (c * 64 >= E || e >= 0) break;
-    const int mt_l = mtv[c];
-    const int ng_l = short_group ? (((mt_l * NT) & (G - 1)) != 0 ? 1 : 0) : (mt_l * NT) >> gs;
-    const int inc = wave_inclusive_scan(ng_l);                      // inclusive prefix sum over the wave
-    const int tot = __builtin_amdgcn_readlane(inc, 63);
-    if (target < base + tot) {
-      const unsigned long long hit = __ballot(base + inc > target);
-      const int l = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
-      e = c * 64 + l;                                               // the same in every lane: keep them in scalar registers
-      mte = __builtin_amdgcn_readlane(mt_l, l);
-      rows_e = __builtin_amdgcn_readlane(rowsv[c], l);
-      rank = target - (base + __builtin_amdgcn_readlane(inc - ng_l, l));
-    }
-    base += tot;
-  }
-  if (e < 0) return kTileNone;                                      // past the last live group
-  const int q = ((short_group ? (mte * NT) >> gs : rank) << gs) + slot;
-  if (q >= mte * NT) return kTileIdle;                              // idle slot of a short group
-  const int full = (NT / 8) * mte * 8;                              // live tiles of this expert in full 8-column blocks
-  int mt, nt;
-  if (q < full) { mt = (q % (mte * 8)) / 8; nt = (q / (mte * 8)) * 8 + q % 8; }
-  else { const int w = NT % 8, r = q - full; mt = r / w; nt = (NT / 8) * 8 + r % w; }
-  e_out = e; mt_out = mt; nt_out = nt; rows_out = rows_e;
-  return kTileLive;
-}
-
 // GRAD (kNT only): the epilogue multiplies by act'(pre) read from `pre` [E,C,N], i.e. the product is the gradient with
 // respect to the pre-activations of a layer whose activation is ACT; with ACT < 0 it adds `pre` instead (a product
 // accumulated onto an existing matrix; `pre` may then be `out` itself, every element being read before it is written
@@ -461,7 +469,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
   // per group a handful of them would leave some XCDs with twice the work of others.
   const int lane = threadIdx.x & 63;
   int e, mt, nt, rows_e;
-  if (find_tile(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e) != kTileLive) return;
+  if (find_tile<BM>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e) != kTileLive) return;
   const int64_t rows = rows_e;                                      // already here from the search: no second trip to memory
   const int64_t m0 = (int64_t)mt * BM;
   if (m0 >= rows) return;                                           // cannot happen (mt < mte); keeps every access in the slab
@@ -658,7 +666,7 @@ __global__ __launch_bounds__(256) void tail_rows_kernel(const uint4* __restrict_
     dst[((int64_t)e * BK + j) * cpr + ch] = slot < fill ? src[row * cpr + ch] : make_uint4(0, 0, 0, 0);
 }
 
-bool grouped_gemm_mfma_supports(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows) {
+static bool large_tile_supports(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows) {
   if (K % BK != 0 || N % BN != 0 || E > kMaxExperts) return false;
   const int64_t tiles = E * ceil_div(C, BM) * (N / BN);
   // 32-bit byte offsets inside one expert's A slab (or the whole token matrix when gathering) and B matrix
@@ -667,11 +675,11 @@ bool grouped_gemm_mfma_supports(int64_t E, int64_t C, int64_t K, int64_t N, int6
          gather_rows < ((int64_t)1 << 31);
 }
 
-hipError_t launch_grouped_gemm_mfma(const void* A, const void* B, const void* bias, int act, const int32_t* counts,
-                                    int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s,
-                                    const int32_t* gather, int64_t gather_rows, void* pre_out) {
+static hipError_t launch_large_nn(const void* A, const void* B, const void* bias, int act, const int32_t* counts,
+                                  int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s,
+                                  const int32_t* gather, int64_t gather_rows, void* pre_out) {
   const int MT = (int)ceil_div(C, BM), NT = (int)(N / BN);
-  const dim3 grid(tile_grid(E, MT, NT)), block(kThreads);
+  const dim3 grid((unsigned)tile_grid(E, MT, NT)), block(kThreads);
 #define MOE_LAUNCH_GEMM(ACT, DUAL)                                                                                    \
   grouped_gemm_mfma_kernel<ACT, kNN, false, DUAL><<<grid, block, 0, s>>>(                                             \
       (const uint16_t*)A, (const uint16_t*)B, (const uint16_t*)bias, counts, gather, (int)gather_rows, (int)E, C,     \
@@ -697,10 +705,10 @@ hipError_t launch_grouped_gemm_mfma(const void* A, const void* B, const void* bi
 
 // out[e] = A[e] (rows_e x K) * Bt[e]^T, Bt [E, N, K]; with `pre` [E, C, N] the result is multiplied by act'(pre), or,
 // with act < 0, has `pre` added (pre == out accumulates in place).
-hipError_t launch_grouped_gemm_mfma_nt(const void* A, const void* Bt, const int32_t* counts, int64_t E, int64_t C,
-                                       int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s) {
+static hipError_t launch_large_nt(const void* A, const void* Bt, const int32_t* counts, int64_t E, int64_t C,
+                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s) {
   const int MT = (int)ceil_div(C, BM), NT = (int)(N / BN);
-  const dim3 grid(tile_grid(E, MT, NT)), block(kThreads);
+  const dim3 grid((unsigned)tile_grid(E, MT, NT)), block(kThreads);
 #define MOE_LAUNCH_GEMM(ACT, GRAD)                                                                                    \
   grouped_gemm_mfma_kernel<ACT, kNT, GRAD><<<grid, block, 0, s>>>(                                                    \
       (const uint16_t*)A, (const uint16_t*)Bt, nullptr, counts, nullptr, 0, (int)E, C, (int)K, (int)N, MT, NT,        \
@@ -720,16 +728,16 @@ hipError_t launch_grouped_gemm_mfma_nt(const void* A, const void* Bt, const int3
 // multiples of 256.  a_tail [E, 64, R] and b_tail [E, 64, N] are scratch for the zero-padded last K-step.
 // With `gather` [E, C] (slot -> row, as the dispatch builds it) At is one matrix [gather_rows, R] and slot c of expert e
 // is its row gather[e, c]; gather_rows * R * 2 must stay below 2^32.
-hipError_t launch_grouped_gemm_mfma_tn(const void* At, const void* B, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
-                                       int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s,
-                                       const int32_t* gather, int64_t gather_rows) {
+static hipError_t launch_large_tn(const void* At, const void* B, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
+                                  int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, const int32_t* gather,
+                                  int64_t gather_rows) {
   const int cprR = (int)(R / 8), cprN = (int)(N / 8);
   tail_rows_kernel<<<dim3(BK / 4, (unsigned)E), dim3(256), 0, s>>>((const uint4*)At, kfill, C, cprR, (uint4*)a_tail, gather, gather_rows);
   tail_rows_kernel<<<dim3(BK / 4, (unsigned)E), dim3(256), 0, s>>>((const uint4*)B, kfill, C, cprN, (uint4*)b_tail, nullptr, 0);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   const int MT = (int)(R / BM), NT = (int)(N / BN);
-  const dim3 grid(tile_grid(E, MT, NT)), block(kThreads);
+  const dim3 grid((unsigned)tile_grid(E, MT, NT)), block(kThreads);
   if (gather)
     grouped_gemm_mfma_kernel<-1, kTN, false, false, true><<<grid, block, 0, s>>>(
         (const uint16_t*)At, (const uint16_t*)B, nullptr, nullptr, gather, (int)gather_rows, (int)E, R, (int)C, (int)N, MT, NT,
@@ -741,17 +749,55 @@ hipError_t launch_grouped_gemm_mfma_tn(const void* At, const void* B, const int3
   return hipGetLastError();
 }
 
-// One [rows, K] x [N, K]^T product (a single "expert"): shapes the kNT layout takes.
-bool grouped_gemm_mfma_supports_nt(int64_t rows, int64_t K, int64_t N) {
-  return grouped_gemm_mfma_supports(1, rows, K, N, 0) && N * K * 2 < ((int64_t)1 << 32);
-}
-
-// Shapes for which the whole backward of the expert layer runs on the three layouts above.
-bool grouped_gemm_mfma_supports_backward(int64_t E, int64_t C, int64_t M, int64_t H) {
+// Shapes for which the three layouts of an expert layer's backward run on the large tile.
+static bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M, int64_t H) {
   const int64_t W = M > H ? M : H;
   const int64_t tiles = E * ceil_div(C > W ? C : W, BM) * (W / BN);
   return M % BN == 0 && H % BN == 0 && E <= kMaxExperts && tiles < ((int64_t)1 << 30) &&
          C * W * 2 < ((int64_t)1 << 32) && M * H * 2 < ((int64_t)1 << 32);
+}
+
+bool grouped_gemm_gathers_on_large_tile(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows) {
+  return large_tile_supports(E, C, K, N, gather_rows);
+}
+
+bool grouped_gemm_tn_gathers(int64_t E, int64_t C, int64_t M, int64_t H, int64_t gather_rows) {
+  return large_tile_supports_backward(E, C, M, H) && gather_rows > 0 && gather_rows * M * 2 < ((int64_t)1 << 32);
+}
+
+hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, int act, int dtype, const int32_t* counts,
+                               int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, void* pre_out,
+                               const int32_t* gather, int64_t gather_rows) {
+  if (act < 0) pre_out = nullptr;                                   // nothing to tell apart
+  if (dtype == MOE_BF16 && large_tile_supports(E, C, K, N, gather ? gather_rows : 0))
+    return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, gather, gather_rows, pre_out);
+  const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, out, nullptr, nullptr, pre_out, act};
+  return dtype == MOE_BF16 ? launch_tile<uint16_t, kNN>(p, C, s) : launch_tile<float, kNN>(p, C, s);
+}
+
+// out[e] = A[e] (rows_e x K) * Bt[e]^T, Bt [E, N, K]; with `pre` [E, C, N] the result is multiplied by act'(pre), or,
+// with act < 0, has `pre` added (pre == out accumulates in place).
+hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, const int32_t* counts, int64_t E, int64_t C,
+                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s) {
+  if (dtype == MOE_BF16 && large_tile_supports(E, C, K, N, 0) && N * K * 2 < ((int64_t)1 << 32))
+    return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s);
+  const TileArgs p = {A, Bt, nullptr, counts, nullptr, 0, C, K, (int)N, (int)E, 0, 0, out, nullptr, pre, nullptr, pre ? act : -1};
+  return dtype == MOE_BF16 ? launch_tile<uint16_t, kNT>(p, C, s) : launch_tile<float, kNT>(p, C, s);
+}
+
+size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W) { return (size_t)E * BK * W * 2; }
+
+// out[e] (R x N) = At[e]^T * B[e] over the first min(kfill[e], C) of the C slots; At [E, C, R], B [E, C, N].  a_tail and
+// b_tail: scratch of grouped_gemm_tn_tail_bytes(E, R) and (E, N).  With `gather` (grouped_gemm_tn_gathers shapes only) At
+// is one matrix [gather_rows, R] and slot c of expert e is its row gather[e, c].
+hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
+                                  int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, const int32_t* gather,
+                                  int64_t gather_rows) {
+  if (dtype == MOE_BF16 && large_tile_supports_backward(E, C, R, N))
+    return launch_large_tn(At, B, kfill, E, C, R, N, a_tail, b_tail, out, s, gather, gather_rows);
+  if (gather) return hipErrorInvalidValue;
+  const TileArgs p = {At, B, nullptr, nullptr, nullptr, 0, R, C, (int)N, (int)E, 0, 0, out, kfill, nullptr, nullptr, -1};
+  return dtype == MOE_BF16 ? launch_tile<uint16_t, kTN>(p, R, s) : launch_tile<float, kTN>(p, R, s);
 }
 
 }  // namespace moe

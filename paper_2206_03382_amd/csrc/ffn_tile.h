@@ -1,0 +1,346 @@
+// The grouped GEMM of ffn_mfma.hip for what its 256 x 256 tile does not cover or does not suit: fp32 storage, bf16 with any
+// K and N that are multiples of 8, and launches with few tiles.  Included by ffn_mfma.hip (same helpers, same operand layouts).
+//
+//   out[e] = epilogue(A[e] * B[e] + bias[e]) in the layouts kNN, kNT and kTN, bf16 (v_mfma_f32_32x32x16_bf16) or fp32
+//   (v_mfma_f32_32x32x2_f32: full fp32 products and sums), fp32 accumulation.
+//
+// One K-step is 128 bytes of k (64 bf16, 32 fp32), staged through an NS-deep LDS ring by direct global->LDS loads with an
+// address per lane, so that edges cost nothing inside: rows past the fill repeat the last live row, columns past N the
+// tile's first piece (neither is stored), and the pieces of the last K-step that lie past the end of the reduction come
+// from a 16-byte piece of zeros.  No operand is copied, padded or transposed in memory.  In bytes the LDS layouts and their
+// swizzles are the same for both types:
+//   k-contiguous operand: [rows][8 pieces of 16 bytes], piece g of row r at position g ^ ((r / 2) % 8)  (ds_read_b128)
+//   k-slow operand:       [k rows][width], bf16 pieces swizzled for ds_read_b64_tr_b16, fp32 read as single words
+// A K-step of a wave is one barrier, the loads of a later K-step, then its MFMAs; two blocks share a compute unit (64 KB of
+// LDS each), so that one block's matrix instructions cover the other's barrier, LDS latency and epilogue.
+//
+// What it replaced was an fp32 FMA kernel on operands transposed and padded in memory, at 12 TFLOP/s in either type.
+// Measured, training step of 17 experts x 353 rows, M = 776, H = 1544, bf16: the six products 645-700 us -> 35-57 us each,
+// step 5060 -> 453 us.  8 experts x 1024 rows, M = 512, H = 1024, fp32: products 166-228 us -> 83-132 us (102 TFLOP/s in
+// the weight gradients; fp32 matrix peak 157), step 1589 -> 722 us.
+
+namespace {
+
+struct TileArgs {
+  const void* A;
+  const void* B;
+  const void* bias;
+  const int32_t* counts;
+  const int32_t* gather;        // kNN: A's row r is row gather[e, r] of one matrix [gather_rows, K]
+  int64_t gather_rows;
+  int64_t C;                    // rows of A (kNN, kNT) or its width (kTN)
+  int64_t K;                    // length of the reduction; slots per expert (kTN)
+  int N, E, MT, NT;
+  void* out;
+  const int32_t* kfill;         // kTN: live slots per expert
+  const void* pre;              // kNT: multiply by act'(pre) (act >= 0) or add pre (act < 0)
+  void* pre_out;                // kNN: the values before the activation go here as well
+  int act;
+};
+
+// Waits until at most min(later, MOST) K-steps' loads, L of them each, are outstanding.
+template <int MOST, int L> __device__ __forceinline__ void wait_for_loads(int later) {
+  if constexpr (MOST > 0) {
+    if (later < MOST) { wait_for_loads<MOST - 1, L>(later); return; }
+  }
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(MOST * L) : "memory");
+}
+
+__device__ __align__(256) uint4 g_zero_piece[16];                   // stays zero: where pieces past the reduction's end are read
+
+template <typename ET, int MODE, int BM, int BN, int WR, int WC, int NS>
+__global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(const TileArgs p) {
+  constexpr int ES = (int)sizeof(ET), EC = 16 / ES;                 // elements per 16-byte piece
+  constexpr int BKE = 128 / ES;                                     // k per K-step
+  constexpr bool BF16 = ES == 2;
+  constexpr bool TRA = MODE == kTN, TRB = MODE != kNT;              // k-slow operands
+  constexpr int NW = WR * WC;
+  constexpr int WTM = BM / WR, WTN = BN / WC, TI = WTM / 32, TJ = WTN / 32;
+  constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+  constexpr int LA = A_BYTES / (NW * 1024), LB = BN * 128 / (NW * 1024);   // direct loads per wave and K-step
+  static_assert(LA >= 1 && LB >= 1 && TI >= 1 && TJ >= 1, "every wave loads and owns something");
+  static_assert(NW * WTM * WTN * ES <= NS * STAGE, "the epilogue's transpose fits into the stages");
+  __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WC, wn = wave % WC, kg = lane >> 5;
+
+  // ---- which tile: the search of the large kernel, or plain numbering for more experts than it takes ----------------
+  int e, mt, nt, rows;
+  if (p.E <= kMaxExperts) {
+    if (find_tile<BM>(blockIdx.x, lane, p.E, p.C, p.counts, p.NT, e, mt, nt, rows) != kTileLive) return;
+  } else {
+    const int per = p.MT * p.NT;
+    e = blockIdx.x / per;
+    mt = (blockIdx.x % per) / p.NT;
+    nt = blockIdx.x % p.NT;
+    int64_t r = p.C;
+    if (p.counts) { const int64_t c = p.counts[e]; r = c < p.C ? (c > 0 ? c : 0) : p.C; }
+    rows = (int)r;
+  }
+  const int64_t m0 = (int64_t)mt * BM;
+  if (m0 >= rows) return;
+  const int64_t n0 = (int64_t)nt * BN;
+  int64_t kend = p.K;                                               // k that exist
+  if (MODE == kTN && p.kfill) { const int64_t c = p.kfill[e]; kend = c < p.K ? (c > 0 ? c : 0) : p.K; }
+  const int KT = kend > 0 ? (int)((kend + BKE - 1) / BKE) : 1;
+
+  // ---- this lane's direct loads: address at K-step 0, and k of its piece (to tell what lies past the end) ---------------
+  const char* a_ptr[LA];
+  const char* b_ptr[LB];
+  int a_k[LA], b_k[LB];
+  // k-contiguous: block i*NW + wave = 8 rows, lane l row +l/8, position l%8.   k-slow: PB bytes per k row.
+  auto swz_slow = [](int kr, int width_bytes) -> int {              // bf16 only: see tr_off
+    return width_bytes >= 256 ? 4 * (kr & 3) : (width_bytes == 128 ? 4 * ((kr >> 1) & 1) : 0);
+  };
+  auto slow_source = [&](const char* base, int64_t ld, int64_t c0, int width, int i, int& k_out) -> const char* {
+    const int pb = width * ES, ppr = pb / 16, rpb = 1024 / pb;      // bytes and pieces per k row, k rows per 1 KB block
+    const int kr = (i * NW + wave) * rpb + lane / ppr;
+    const int c = (lane % ppr) ^ (BF16 ? swz_slow(kr, pb) : 0);
+    const int64_t col = c0 + c * EC;
+    k_out = kr;
+    return base + ((int64_t)kr * ld + (col < ld ? col : c0)) * ES;  // columns past the end: any piece of the row
+  };
+  auto fast_source = [&](const char* base, int64_t ld, int64_t row, int i, int& k_out) -> const char* {
+    const int r = (i * NW + wave) * 8 + (lane >> 3);
+    const int g = (lane & 7) ^ ((r >> 1) & 7);
+    k_out = g * EC;
+    return base + (row * ld + g * EC) * ES;
+  };
+#pragma unroll
+  for (int i = 0; i < LA; ++i) {
+    if (TRA) {
+      a_ptr[i] = slow_source((const char*)p.A + (int64_t)e * p.K * p.C * ES, p.C, m0, BM, i, a_k[i]);
+    } else {
+      int64_t row = m0 + (i * NW + wave) * 8 + (lane >> 3);
+      row = row < rows ? row : rows - 1;                            // rows past the fill repeat the last one
+      if (p.gather) {
+        const int64_t t = p.gather[(int64_t)e * p.C + row];
+        a_ptr[i] = fast_source((const char*)p.A, p.K, t >= 0 && t < p.gather_rows ? t : 0, i, a_k[i]);
+      } else {
+        a_ptr[i] = fast_source((const char*)p.A + (int64_t)e * p.C * p.K * ES, p.K, row, i, a_k[i]);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < LB; ++i) {
+    const char* base = (const char*)p.B + (int64_t)e * p.K * p.N * ES;
+    if (TRB) {
+      b_ptr[i] = slow_source(base, p.N, n0, BN, i, b_k[i]);
+    } else {
+      const int64_t row = n0 + (i * NW + wave) * 8 + (lane >> 3);
+      b_ptr[i] = fast_source(base, p.K, row < p.N ? row : p.N - 1, i, b_k[i]);
+    }
+  }
+  const int64_t a_step = TRA ? (int64_t)BKE * p.C * ES : 128, b_step = TRB ? (int64_t)BKE * p.N * ES : 128;
+  const uint32_t smem_addr = (uint32_t)(uintptr_t)LDS_PTR(char, smem);
+  const char* zero = (const char*)g_zero_piece;
+  auto issue = [&](int t) __attribute__((always_inline)) {          // K-step t -> stage t % NS; t ascends by one per call
+    const uint32_t dst = smem_addr + (uint32_t)((t % NS) * STAGE);
+    if (t == KT - 1) {                                              // pieces past the end of the reduction are zeros
+      const int64_t left = kend - (int64_t)t * BKE;
+#pragma unroll
+      for (int i = 0; i < LA; ++i) global_to_lds_16(a_k[i] < left ? a_ptr[i] : zero, dst + (i * NW + wave) * 1024);
+#pragma unroll
+      for (int i = 0; i < LB; ++i) global_to_lds_16(b_k[i] < left ? b_ptr[i] : zero, dst + A_BYTES + (i * NW + wave) * 1024);
+    } else {
+#pragma unroll
+      for (int i = 0; i < LA; ++i) { global_to_lds_16(a_ptr[i], dst + (i * NW + wave) * 1024); a_ptr[i] += a_step; }
+#pragma unroll
+      for (int i = 0; i < LB; ++i) { global_to_lds_16(b_ptr[i], dst + A_BYTES + (i * NW + wave) * 1024); b_ptr[i] += b_step; }
+    }
+  };
+
+  // ---- LDS read offsets of this lane's fragments (sub-tile 0; the others are constants apart) ---------------------------
+  const int swz = ((lane & 31) >> 1) & 7;
+  auto read_fast = [&](const char* tile, int w, int t, int s) -> u32x4 {   // pieces 2 s + kg of row w*.. + 32 t + lane % 32
+    return *LDS_PTR(u32x4, tile + (w + t * 32 + (lane & 31)) * 128 + (((2 * s + kg) ^ swz) << 4));
+  };
+  auto read_slow_bf16 = [&](const char* tile, int w, int t, int width, int s) -> bf16x8 {
+    const int pb = width * 2, kr = (lane & 15) >> 2;
+    const int c = w / 8 + t * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
+    const char* at = tile + (kg * 8 + kr) * pb + ((c ^ swz_slow(kr, pb)) << 4) + ((lane & 1) << 3);
+    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(short4v, at + 16 * s * pb));
+    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(short4v, at + (16 * s + 4) * pb));
+    return __builtin_bit_cast(bf16x8, (short8v)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  auto read_slow_fp32 = [&](const char* tile, int w, int t, int width, int s) -> u32x4 {
+    u32x4 v;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *LDS_PTR(uint32_t, tile + (8 * s + 4 * kg + u) * width * 4 + (w + t * 32 + (lane & 31)) * 4);
+    return v;
+  };
+
+  // ---- accumulators: the bias (register 4 g + u of tile (i, j) is column 32 j + 8 g + 4 kg + u of the wave's), or zero; its
+  // loads go out ahead of the first K-steps' and are used behind them
+  using Raw4 = std::conditional_t<BF16, u32x2, u32x4>;
+  Raw4 braw[TJ][4];
+  const bool has_bias = MODE == kNN && p.bias != nullptr;
+  const int64_t bcol = n0 + wn * WTN + 4 * kg;
+  if (has_bias) {
+    const ET* be = (const ET*)p.bias + (int64_t)e * p.N;
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int64_t col = bcol + j * 32 + 8 * g;
+        braw[j][g] = *reinterpret_cast<const Raw4*>(be + (col < p.N ? col : n0));
+      }
+  }
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t)
+    if (t < KT) issue(t);
+  f32x16 acc[TI][TJ];
+#pragma unroll
+  for (int j = 0; j < TJ; ++j)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        float b = 0.f;
+        if (has_bias) {
+          if constexpr (BF16) b = __uint_as_float((u & 1) ? braw[j][g][u >> 1] & 0xffff0000u : braw[j][g][u >> 1] << 16);
+          else b = __uint_as_float(braw[j][g][u]);
+        }
+#pragma unroll
+        for (int i = 0; i < TI; ++i) acc[i][j][4 * g + u] = b;
+      }
+
+  // 32-row sub-tiles of this wave that hold real rows
+  const int64_t live = rows - m0 - wm * WTM;
+  const int ni = live <= 0 ? 0 : (live >= WTM ? TI : (int)((live + 31) >> 5));
+
+  auto main_loop = [&](auto ni_tag) __attribute__((always_inline)) {
+    constexpr int NI = decltype(ni_tag)::value;
+    for (int kt = 0; kt < KT; ++kt) {
+      // K-step kt has landed when at most the loads of the later ones (issued after it) are outstanding
+      wait_for_loads<NS - 2, LA + LB>(KT - 1 - kt);
+      PIN();
+      asm volatile("s_barrier" ::: "memory");                       // every wave's loads are here; K-step kt - 1 is done with
+      PIN();
+      if (kt + NS - 1 < KT) issue(kt + NS - 1);
+      PIN();
+      const char* sa = smem + (kt % NS) * STAGE;
+      const char* sb = sa + A_BYTES;
+      if (NI > 0) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          if constexpr (BF16) {
+            bf16x8 a[TI], b[TJ];
+#pragma unroll
+            for (int i = 0; i < NI; ++i) a[i] = TRA ? read_slow_bf16(sa, wm * WTM, i, BM, s) : __builtin_bit_cast(bf16x8, read_fast(sa, wm * WTM, i, s));
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) b[j] = TRB ? read_slow_bf16(sb, wn * WTN, j, BN, s) : __builtin_bit_cast(bf16x8, read_fast(sb, wn * WTN, j, s));
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+              for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+          } else {
+            u32x4 a[TI], b[TJ];                                     // k = 8 s + 4 kg + u in register u of both operands
+#pragma unroll
+            for (int i = 0; i < NI; ++i) a[i] = TRA ? read_slow_fp32(sa, wm * WTM, i, BM, s) : read_fast(sa, wm * WTM, i, s);
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) b[j] = TRB ? read_slow_fp32(sb, wn * WTN, j, BN, s) : read_fast(sb, wn * WTN, j, s);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+              for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+                  acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(b[j][u]), __uint_as_float(a[i][u]), acc[i][j], 0, 0, 0);
+          }
+        }
+      }
+    }
+  };
+  if (ni == TI) main_loop(std::integral_constant<int, TI>{});
+  else if (TI > 1 && ni == 1) main_loop(std::integral_constant<int, 1>{});
+  else main_loop(std::integral_constant<int, 0>{});
+  static_assert(TI <= 2, "ragged waves are instantiated for 0 and 1 live sub-tiles");
+
+  // ---- epilogue: the wave's tile goes through its own piece of LDS, so that stores are 16 bytes per lane and whole row
+  // pieces; piece c of row r sits at position c ^ (r % pieces per row).
+  __syncthreads();                                                  // the stages are done with
+  constexpr int CPR = WTN * ES / 16, RPI = 64 / CPR;                // pieces per row, rows per store
+  char* wtile = smem + wave * (WTM * WTN * ES);
+  const int64_t nw = n0 + wn * WTN;
+  const int64_t out_at = ((int64_t)e * p.C + m0 + wm * WTM) * p.N + nw;
+  auto write_tile = [&](auto act_tag, ET* dst, const ET* pre) __attribute__((always_inline)) {
+    constexpr int ACT = decltype(act_tag)::value;
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      const int r = i * 32 + (lane & 31);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          float v[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            v[u] = acc[i][j][4 * g + u];
+            if (ACT >= 0 && !pre) v[u] = BF16 ? epilogue_act<ACT>(v[u]) : apply_act(v[u], ACT);
+          }
+          if constexpr (BF16) {
+            u32x2 pk;
+            pk.x = pack_bf16x2(v[0], v[1]);
+            pk.y = pack_bf16x2(v[2], v[3]);
+            *LDS_PTR(u32x2, wtile + r * (CPR * 16) + (((4 * j + g) ^ (r % CPR)) << 4) + 8 * kg) = pk;
+          } else {
+            const u32x4 pk = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+            *LDS_PTR(u32x4, wtile + r * (CPR * 16) + (((8 * j + 2 * g + kg) ^ (r % CPR)) << 4)) = pk;
+          }
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+    for (int it = 0; it < WTM / RPI; ++it) {
+      const int r = it * RPI + lane / CPR;
+      const int ch = (lane % CPR) ^ (r % CPR);
+      u32x4 q = *LDS_PTR(u32x4, wtile + r * (CPR * 16) + ((lane % CPR) << 4));
+      if (r < live && nw + ch * EC < p.N) {
+        const int64_t at = out_at + (int64_t)r * p.N + ch * EC;
+        if (pre) {                                                  // times act'(pre), both factors as stored; or plus `pre`
+          float g[EC], pv[EC];
+          Vec16<ET>::unpack(__builtin_bit_cast(uint4, q), g);
+          Vec16<ET>::unpack(*reinterpret_cast<const uint4*>(pre + at), pv);
+#pragma unroll
+          for (int u = 0; u < EC; ++u) g[u] = ACT < 0 ? g[u] + pv[u] : g[u] * (BF16 ? epilogue_act_grad<ACT>(pv[u]) : apply_act_grad(pv[u], ACT));
+          q = __builtin_bit_cast(u32x4, Vec16<ET>::pack(g));
+        }
+        *reinterpret_cast<u32x4*>(dst + at) = q;
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  ET* out = (ET*)p.out;
+  const ET* pre = MODE == kNT ? (const ET*)p.pre : nullptr;
+  if (MODE == kNN && p.pre_out) write_tile(std::integral_constant<int, -1>{}, (ET*)p.pre_out, nullptr);
+  if (MODE == kTN) write_tile(std::integral_constant<int, -1>{}, out, nullptr);
+  else switch (p.act) {
+    case MOE_ACT_RELU: write_tile(std::integral_constant<int, MOE_ACT_RELU>{}, out, pre); break;
+    case MOE_ACT_GELU: write_tile(std::integral_constant<int, MOE_ACT_GELU>{}, out, pre); break;
+    case MOE_ACT_SILU: write_tile(std::integral_constant<int, MOE_ACT_SILU>{}, out, pre); break;
+    default: write_tile(std::integral_constant<int, -1>{}, out, pre); break;
+  }
+}
+
+}  // namespace
+
+// Tile of a launch: 32 x 64 (two waves) where no expert has more than 32 rows, 128 x 128 where that leaves enough tiles for
+// two per compute unit, 64 x 64 otherwise.
+template <typename ET, int MODE>
+static hipError_t launch_tile(TileArgs p, int64_t rows, hipStream_t s) {
+  const int64_t big = p.E * ceil_div(rows, 128) * ceil_div(p.N, 128);
+  auto go = [&](auto kernel, int bm, int bn, int threads) {
+    p.MT = (int)ceil_div(rows, bm);
+    p.NT = (int)ceil_div(p.N, bn);
+    const int64_t blocks = p.E <= kMaxExperts ? tile_grid(p.E, p.MT, p.NT) : (int64_t)p.E * p.MT * p.NT;
+    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    kernel<<<dim3((unsigned)blocks), dim3(threads), 0, s>>>(p);
+    return hipGetLastError();
+  };
+  if (rows <= 32) return go(grouped_gemm_tile_kernel<ET, MODE, 32, 64, 1, 2, 6>, 32, 64, 128);
+  if (big >= 512) return go(grouped_gemm_tile_kernel<ET, MODE, 128, 128, 2, 2, 2>, 128, 128, 256);
+  return go(grouped_gemm_tile_kernel<ET, MODE, 64, 64, 2, 2, 4>, 64, 64, 256);
+}

@@ -291,7 +291,7 @@ static hipError_t gate_backward_t(const void* x, const void* Wg, const float* lo
   // runs in steps of 64 experts: other expert counts get zero-padded copies of both operands.
   const int64_t Ep = ceil_div(E, 64) * 64;
   const bool dx_mfma = dx && sizeof(ET) == 2 && E >= 32 && M % 256 == 0 && (reinterpret_cast<uintptr_t>(Wg) & 15) == 0 &&
-                       grouped_gemm_mfma_supports_nt(T, Ep, M);
+                       T * Ep < ((int64_t)1 << 31) && M * Ep < ((int64_t)1 << 31);
   if (dx_mfma) {
     char* extra = ws + align_up((size_t)T * E * 4, 256) + align_up((size_t)slices * M * E * 4, 256) + align_up((size_t)slices * E * 4, 256);
     uint16_t* dl16 = (uint16_t*)extra;
@@ -305,7 +305,7 @@ static hipError_t gate_backward_t(const void* x, const void* Wg, const float* lo
       if ((err = hipGetLastError()) != hipSuccess) return err;
       wgt = wg16;
     }
-    if ((err = launch_grouped_gemm_mfma_nt(dl16, wgt, nullptr, 1, T, Ep, M, dx, accumulate_dx ? dx : nullptr, -1, s)) != hipSuccess) return err;
+    if ((err = launch_grouped_gemm_nt(dl16, wgt, MOE_BF16, nullptr, 1, T, Ep, M, dx, accumulate_dx ? dx : nullptr, -1, s)) != hipSuccess) return err;
   } else if (dx) {
     const int cpr = (int)(M * sizeof(ET) / 16);
     gate_dx_kernel<ET><<<dim3((unsigned)ceil_div(T, kDxTokens), (unsigned)ceil_div(cpr, 256)), dim3(256), 0, s>>>(dl, (const ET*)Wg, T, cpr, (int)E, accumulate_dx, (uint4*)dx);
