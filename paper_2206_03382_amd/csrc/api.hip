@@ -19,6 +19,9 @@ inline int gate_shape_status(int64_t T, int64_t E, int k) {
   return MOE_OK;
 }
 
+// rows an expert holds on average if the choices spread evenly (a hint for the GEMM's tile)
+inline int64_t mean_fill(int64_t T, int64_t E, int k) { return ceil_div(T * k, E); }
+
 inline int row_shape_status(int64_t M) {
   if (M < 1 || M > kMaxDim) return MOE_INVALID_ARG;
   if (M % 8 != 0) return MOE_UNSUPPORTED;
@@ -278,7 +281,7 @@ int moe_expert_ffn_train(const void* Z, const void* W1, const void* b1, const vo
   if (!aligned(Z, 16) || !aligned(W1, 16) || !aligned(W2, 16) || !aligned(pre, 16) || !aligned(hidden, 16) || !aligned(Y, 16))
     return MOE_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
-  if (launch_grouped_gemm(Z, W1, b1, act, dtype, counts, E, C, M, H, hidden, s, pre) != hipSuccess) return MOE_HIP_ERROR;
+  if (launch_grouped_gemm(Z, W1, b1, act, dtype, counts, E, C, M, H, hidden, s, 0, pre) != hipSuccess) return MOE_HIP_ERROR;
   if (launch_grouped_gemm(hidden, W2, b2, -1, dtype, counts, E, C, H, M, Y, s) != hipSuccess) return MOE_HIP_ERROR;
   return MOE_OK;
 }
@@ -294,7 +297,7 @@ int moe_expert_ffn_gather(const void* x, const int32_t* slot_src, int64_t T, con
   if (!aligned(x, 16) || !aligned(W1, 16) || !aligned(W2, 16) || !aligned(hidden, 16) || !aligned(Y, 16)) return MOE_UNSUPPORTED;
   if (dtype != MOE_BF16 || !grouped_gemm_gathers_on_large_tile(E, C, M, H, T)) return MOE_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
-  if (launch_grouped_gemm(x, W1, b1, act, dtype, counts, E, C, M, H, hidden, s, nullptr, slot_src, T) != hipSuccess) return MOE_HIP_ERROR;
+  if (launch_grouped_gemm(x, W1, b1, act, dtype, counts, E, C, M, H, hidden, s, 0, nullptr, slot_src, T) != hipSuccess) return MOE_HIP_ERROR;
   if (launch_grouped_gemm(hidden, W2, b2, -1, dtype, counts, E, C, H, M, Y, s) != hipSuccess) return MOE_HIP_ERROR;
   return MOE_OK;
 }
@@ -449,17 +452,18 @@ int layer_forward(const void* x, const void* Wg, const float* gate_bias, const v
   if (run_gate(x, Wg, gate_bias, dtype, T, M, E, k, C, normalize, d_logits, d_idx, d_gw, d_loc, d_counts, d_src, d_gws, s, mark) != hipSuccess ||
       !mark())
     return MOE_HIP_ERROR;
+  const int64_t mean = mean_fill(T, E, k);
   if (fuse_dispatch && dtype == MOE_BF16 && grouped_gemm_gathers_on_large_tile(E, C, M, H, T)) {
     // the first expert GEMM gathers its rows from x through slot_src: the dispatch buffer is never materialised
     if (!mark()) return MOE_HIP_ERROR;
-    if (launch_grouped_gemm(x, W1, b1, act, dtype, d_counts, E, C, M, H, d_hidden, s, nullptr, d_src, T) != hipSuccess || !mark())
+    if (launch_grouped_gemm(x, W1, b1, act, dtype, d_counts, E, C, M, H, d_hidden, s, mean, nullptr, d_src, T) != hipSuccess || !mark())
       return MOE_HIP_ERROR;
   } else {
     // the dispatch buffer is internal here and the expert GEMM skips rows past an expert's fill: no zero rows needed
     if (launch_encode(x, dtype, d_idx, d_loc, d_src, T, M, E, k, C, d_Z, s, false) != hipSuccess || !mark()) return MOE_HIP_ERROR;
-    if (launch_grouped_gemm(d_Z, W1, b1, act, dtype, d_counts, E, C, M, H, d_hidden, s) != hipSuccess || !mark()) return MOE_HIP_ERROR;
+    if (launch_grouped_gemm(d_Z, W1, b1, act, dtype, d_counts, E, C, M, H, d_hidden, s, mean) != hipSuccess || !mark()) return MOE_HIP_ERROR;
   }
-  if (launch_grouped_gemm(d_hidden, W2, b2, -1, dtype, d_counts, E, C, H, M, d_Y, s) != hipSuccess || !mark()) return MOE_HIP_ERROR;
+  if (launch_grouped_gemm(d_hidden, W2, b2, -1, dtype, d_counts, E, C, H, M, d_Y, s, mean) != hipSuccess || !mark()) return MOE_HIP_ERROR;
   if (launch_decode(d_Y, dtype, d_idx, d_loc, d_gw, T, M, E, k, C, out, s) != hipSuccess || !mark()) return MOE_HIP_ERROR;
   return MOE_OK;
 }
@@ -590,8 +594,8 @@ int moe_layer_forward_dynamic(const void* x, const void* Wg, const float* gate_b
   // choices are kept (loc < C, read from device memory) and how many rows of a slab are filled
   if (launch_slot_sources(d_idx, d_loc, T, E, k, C_max, d_src, s, d_C) != hipSuccess) return MOE_HIP_ERROR;
   if (launch_encode(x, dtype, d_idx, d_loc, d_src, T, M, E, k, C_max, base + w.Z, s, false, d_C) != hipSuccess) return MOE_HIP_ERROR;
-  if (launch_grouped_gemm(base + w.Z, W1, b1, act, dtype, d_fills, E, C_max, M, H, base + w.hidden, s) != hipSuccess) return MOE_HIP_ERROR;
-  if (launch_grouped_gemm(base + w.hidden, W2, b2, -1, dtype, d_fills, E, C_max, H, M, base + w.Y, s) != hipSuccess) return MOE_HIP_ERROR;
+  if (launch_grouped_gemm(base + w.Z, W1, b1, act, dtype, d_fills, E, C_max, M, H, base + w.hidden, s, mean_fill(T, E, k)) != hipSuccess) return MOE_HIP_ERROR;
+  if (launch_grouped_gemm(base + w.hidden, W2, b2, -1, dtype, d_fills, E, C_max, H, M, base + w.Y, s, mean_fill(T, E, k)) != hipSuccess) return MOE_HIP_ERROR;
   if (launch_decode(base + w.Y, dtype, d_idx, d_loc, d_gw, T, M, E, k, C_max, out, s, d_C) != hipSuccess) return MOE_HIP_ERROR;
   return MOE_OK;
 }
@@ -626,15 +630,15 @@ int moe_layer_forward_train(const void* x, const void* Wg, const float* gate_bia
                [] { return true; }) != hipSuccess)
     return MOE_HIP_ERROR;
   if (w.fused) {
-    if (launch_grouped_gemm(x, W1, b1, act, dtype, counts, E, C, M, H, base + w.hidden, s, base + w.pre, src, T) != hipSuccess)
+    if (launch_grouped_gemm(x, W1, b1, act, dtype, counts, E, C, M, H, base + w.hidden, s, mean_fill(T, E, k), base + w.pre, src, T) != hipSuccess)
       return MOE_HIP_ERROR;
   } else {
     // the slabs are internal and every later stage stops at an expert's fill: no zero rows needed
     if (launch_encode(x, dtype, idx, loc, src, T, M, E, k, C, base + w.Z, s, false) != hipSuccess) return MOE_HIP_ERROR;
-    if (launch_grouped_gemm(base + w.Z, W1, b1, act, dtype, counts, E, C, M, H, base + w.hidden, s, base + w.pre) != hipSuccess)
+    if (launch_grouped_gemm(base + w.Z, W1, b1, act, dtype, counts, E, C, M, H, base + w.hidden, s, mean_fill(T, E, k), base + w.pre) != hipSuccess)
       return MOE_HIP_ERROR;
   }
-  if (launch_grouped_gemm(base + w.hidden, W2, b2, -1, dtype, counts, E, C, H, M, base + w.Y, s) != hipSuccess) return MOE_HIP_ERROR;
+  if (launch_grouped_gemm(base + w.hidden, W2, b2, -1, dtype, counts, E, C, H, M, base + w.Y, s, mean_fill(T, E, k)) != hipSuccess) return MOE_HIP_ERROR;
   if (launch_decode(base + w.Y, dtype, idx, loc, gw, T, M, E, k, C, out, s) != hipSuccess) return MOE_HIP_ERROR;
   return MOE_OK;
 }
@@ -668,7 +672,7 @@ int moe_layer_backward(const void* x, const void* Wg, const void* W1, const void
     return MOE_HIP_ERROR;
   // experts: dZ over the filled slots, parameter gradients
   if (launch_expert_ffn_backward(w.fused ? x : base + w.Z, W1, b1, W2, base + w.pre, base + w.hidden, base + w.dY, act, dtype,
-                                 counts, E, C, M, H, base + w.ffn_ws, base + w.dZ, dW1, db1, dW2, db2, s, w.fused ? src : nullptr,
+                                 counts, E, C, M, H, base + w.ffn_ws, base + w.dZ, dW1, db1, dW2, db2, s, mean_fill(T, E, k), w.fused ? src : nullptr,
                                  w.fused ? T : 0) != hipSuccess)
     return MOE_HIP_ERROR;
   // encode: dx = sum of a token's kept slot rows of dZ (decode with unit weights)

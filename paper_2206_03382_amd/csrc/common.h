@@ -145,14 +145,15 @@ hipError_t launch_decode(const void* Y, int dtype, const int32_t* idx, const int
 // out[e] = epilogue(A[e] (rows_e x K) * B[e] (K x N) + bias[e]); A [E,C,K], B [E,K,N], out [E,C,N].
 // act < 0 means no activation.  With `pre_out` [E,C,N] the values before the activation are written there as well.
 // With `gather` [E, C] row c of A[e] is row gather[e, c] of one matrix [gather_rows, K].
+// rows_hint: rows an expert holds on average as far as the caller knows (0: C); it only steers the choice of the tile.
 hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, int act, int dtype, const int32_t* counts,
-                               int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, void* pre_out = nullptr,
-                               const int32_t* gather = nullptr, int64_t gather_rows = 0);
+                               int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, int64_t rows_hint = 0,
+                               void* pre_out = nullptr, const int32_t* gather = nullptr, int64_t gather_rows = 0);
 // The products of the backward, with an operand used transposed; see ffn_mfma.hip for the arguments.
 hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, const int32_t* counts, int64_t E, int64_t C,
-                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s);
+                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s, int64_t rows_hint = 0);
 hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
-                                  int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s,
+                                  int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, int64_t rows_hint = 0,
                                   const int32_t* gather = nullptr, int64_t gather_rows = 0);
 size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W);
 // bf16 shapes whose first product, or whose products in both directions, read A through `gather` on the large tile
@@ -172,7 +173,8 @@ FfnBackwardWorkspace ffn_backward_layout(int64_t E, int64_t C, int64_t M, int64_
 hipError_t launch_expert_ffn_backward(const void* Z, const void* W1, const void* b1, const void* W2, const void* pre,
                                       const void* hidden, const void* dY, int act, int dtype, const int32_t* counts, int64_t E,
                                       int64_t C, int64_t M, int64_t H, void* ws, void* dZ, void* dW1, void* db1, void* dW2,
-                                      void* db2, hipStream_t s, const int32_t* gather = nullptr, int64_t gather_rows = 0);
+                                      void* db2, hipStream_t s, int64_t rows_hint = 0, const int32_t* gather = nullptr,
+                                      int64_t gather_rows = 0);
 // With `gather` [E, C] (slot -> token) `Z` is the token matrix [gather_rows, M] itself (fused dispatch: the slabs of
 // dispatched rows were never written); needs saved pre-activations and shapes grouped_gemm_tn_gathers takes.
 

@@ -76,7 +76,7 @@ template <typename ET>
 static hipError_t ffn_backward_t(const void* Z, const void* W1, const void* b1, const void* W2, const void* saved_pre,
                                  const void* hidden, const void* dY, int act, int dtype, const int32_t* counts, int64_t E, int64_t C, int64_t M,
                                  int64_t H, char* ws, void* dZ, void* dW1, void* db1, void* dW2, void* db2, hipStream_t s,
-                                 const int32_t* gather, int64_t gather_rows) {
+                                 int64_t rows_hint, const int32_t* gather, int64_t gather_rows) {
   const FfnBackwardWorkspace w = ffn_backward_layout(E, C, M, H, dtype);
   const int es = (int)sizeof(ET);
   void *dP = ws + w.dP, *a_tail = ws + w.a_tail, *b_tail = ws + w.b_tail;
@@ -86,7 +86,7 @@ static hipError_t ffn_backward_t(const void* Z, const void* W1, const void* b1, 
   // pre-activations: the caller's (kept by the training forward), else recomputed
   if (!saved_pre) {
     if (gather) return hipErrorInvalidValue;                       // a fused-dispatch training forward always keeps them
-    MOE_TRY(launch_grouped_gemm(Z, W1, b1, -1, dtype, counts, E, C, M, H, ws + w.pre, s));
+    MOE_TRY(launch_grouped_gemm(Z, W1, b1, -1, dtype, counts, E, C, M, H, ws + w.pre, s, rows_hint));
   }
   auto colsums = [&]() -> hipError_t {
     if (db1) {
@@ -100,10 +100,10 @@ static hipError_t ffn_backward_t(const void* Z, const void* W1, const void* b1, 
     return hipGetLastError();
   };
   // dP = (dY W2^T) * act'(pre);  dZ = dP W1^T;  dW2 = hidden^T dY;  dW1 = Z^T dP
-  MOE_TRY(launch_grouped_gemm_nt(dY, W2, dtype, counts, E, C, M, H, dP, pre, act, s));
-  if (dZ) MOE_TRY(launch_grouped_gemm_nt(dP, W1, dtype, counts, E, C, H, M, dZ, nullptr, -1, s));
-  if (dW2) MOE_TRY(launch_grouped_gemm_tn(hidden, dY, dtype, counts, E, C, H, M, a_tail, b_tail, dW2, s));
-  if (dW1) MOE_TRY(launch_grouped_gemm_tn(Z, dP, dtype, counts, E, C, M, H, a_tail, b_tail, dW1, s, gather, gather_rows));
+  MOE_TRY(launch_grouped_gemm_nt(dY, W2, dtype, counts, E, C, M, H, dP, pre, act, s, rows_hint));
+  if (dZ) MOE_TRY(launch_grouped_gemm_nt(dP, W1, dtype, counts, E, C, H, M, dZ, nullptr, -1, s, rows_hint));
+  if (dW2) MOE_TRY(launch_grouped_gemm_tn(hidden, dY, dtype, counts, E, C, H, M, a_tail, b_tail, dW2, s, rows_hint));
+  if (dW1) MOE_TRY(launch_grouped_gemm_tn(Z, dP, dtype, counts, E, C, M, H, a_tail, b_tail, dW1, s, rows_hint, gather, gather_rows));
   MOE_TRY(colsums());
 #undef MOE_TRY
   return hipSuccess;
@@ -112,12 +112,12 @@ static hipError_t ffn_backward_t(const void* Z, const void* W1, const void* b1, 
 hipError_t launch_expert_ffn_backward(const void* Z, const void* W1, const void* b1, const void* W2, const void* pre,
                                       const void* hidden, const void* dY, int act, int dtype, const int32_t* counts, int64_t E,
                                       int64_t C, int64_t M, int64_t H, void* ws, void* dZ, void* dW1, void* db1, void* dW2,
-                                      void* db2, hipStream_t s, const int32_t* gather, int64_t gather_rows) {
+                                      void* db2, hipStream_t s, int64_t rows_hint, const int32_t* gather, int64_t gather_rows) {
   if (dtype == MOE_F32)
     return ffn_backward_t<float>(Z, W1, b1, W2, pre, hidden, dY, act, dtype, counts, E, C, M, H, (char*)ws, dZ, dW1, db1, dW2, db2, s,
-                                 gather, gather_rows);
+                                 rows_hint, gather, gather_rows);
   return ffn_backward_t<uint16_t>(Z, W1, b1, W2, pre, hidden, dY, act, dtype, counts, E, C, M, H, (char*)ws, dZ, dW1, db1, dW2, db2, s,
-                                  gather, gather_rows);
+                                  rows_hint, gather, gather_rows);
 }
 
 }  // namespace moe

@@ -35,6 +35,7 @@
 // The two MFMA operands are passed swapped (B fragment first), so that a lane's accumulator registers hold four
 // consecutive output columns of one row: D'[n][m] with m = lane % 32, n = 8 (v/4) + 4 (lane/32) + v % 4.  The
 // epilogue packs them to 8 bytes, transposes the wave's 128 x 128 tile through LDS and stores whole 256-byte row pieces.
+#include <cmath>
 #include <type_traits>
 
 #include "common.h"
@@ -765,24 +766,28 @@ bool grouped_gemm_tn_gathers(int64_t E, int64_t C, int64_t M, int64_t H, int64_t
   return large_tile_supports_backward(E, C, M, H) && gather_rows > 0 && gather_rows * M * 2 < ((int64_t)1 << 32);
 }
 
+static double mean_or(int64_t rows_hint, int64_t C) { return (double)(rows_hint > 0 && rows_hint < C ? rows_hint : C); }
+
 hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, int act, int dtype, const int32_t* counts,
-                               int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, void* pre_out,
-                               const int32_t* gather, int64_t gather_rows) {
+                               int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, int64_t rows_hint,
+                               void* pre_out, const int32_t* gather, int64_t gather_rows) {
   if (act < 0) pre_out = nullptr;                                   // nothing to tell apart
-  if (dtype == MOE_BF16 && large_tile_supports(E, C, K, N, gather ? gather_rows : 0))
-    return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, gather, gather_rows, pre_out);
+  const bool large_ok = dtype == MOE_BF16 && large_tile_supports(E, C, K, N, gather ? gather_rows : 0);
+  const Tile tile = choose_tile(kNN, large_ok, E, C, mean_or(rows_hint, C), K, N);
+  if (tile == Tile::k256) return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, gather, gather_rows, pre_out);
   const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, out, nullptr, nullptr, pre_out, act};
-  return dtype == MOE_BF16 ? launch_tile<uint16_t, kNN>(p, C, s) : launch_tile<float, kNN>(p, C, s);
+  return launch_small<kNN>(dtype, tile, p, s);
 }
 
 // out[e] = A[e] (rows_e x K) * Bt[e]^T, Bt [E, N, K]; with `pre` [E, C, N] the result is multiplied by act'(pre), or,
 // with act < 0, has `pre` added (pre == out accumulates in place).
 hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, const int32_t* counts, int64_t E, int64_t C,
-                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s) {
-  if (dtype == MOE_BF16 && large_tile_supports(E, C, K, N, 0) && N * K * 2 < ((int64_t)1 << 32))
-    return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s);
+                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s, int64_t rows_hint) {
+  const bool large_ok = dtype == MOE_BF16 && large_tile_supports(E, C, K, N, 0) && N * K * 2 < ((int64_t)1 << 32);
+  const Tile tile = choose_tile(kNT, large_ok, E, C, mean_or(rows_hint, C), K, N);
+  if (tile == Tile::k256) return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s);
   const TileArgs p = {A, Bt, nullptr, counts, nullptr, 0, C, K, (int)N, (int)E, 0, 0, out, nullptr, pre, nullptr, pre ? act : -1};
-  return dtype == MOE_BF16 ? launch_tile<uint16_t, kNT>(p, C, s) : launch_tile<float, kNT>(p, C, s);
+  return launch_small<kNT>(dtype, tile, p, s);
 }
 
 size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W) { return (size_t)E * BK * W * 2; }
@@ -791,13 +796,13 @@ size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W) { return (size_t)E * BK 
 // b_tail: scratch of grouped_gemm_tn_tail_bytes(E, R) and (E, N).  With `gather` (grouped_gemm_tn_gathers shapes only) At
 // is one matrix [gather_rows, R] and slot c of expert e is its row gather[e, c].
 hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
-                                  int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, const int32_t* gather,
-                                  int64_t gather_rows) {
-  if (dtype == MOE_BF16 && large_tile_supports_backward(E, C, R, N))
-    return launch_large_tn(At, B, kfill, E, C, R, N, a_tail, b_tail, out, s, gather, gather_rows);
-  if (gather) return hipErrorInvalidValue;
+                                  int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, int64_t rows_hint,
+                                  const int32_t* gather, int64_t gather_rows) {
+  const bool large_ok = dtype == MOE_BF16 && large_tile_supports_backward(E, C, R, N);
+  const Tile tile = gather ? Tile::k256 : choose_tile(kTN, large_ok, E, R, mean_or(rows_hint, C), C, N);
+  if (tile == Tile::k256) return launch_large_tn(At, B, kfill, E, C, R, N, a_tail, b_tail, out, s, gather, gather_rows);
   const TileArgs p = {At, B, nullptr, nullptr, nullptr, 0, R, C, (int)N, (int)E, 0, 0, out, kfill, nullptr, nullptr, -1};
-  return dtype == MOE_BF16 ? launch_tile<uint16_t, kTN>(p, R, s) : launch_tile<float, kTN>(p, R, s);
+  return launch_small<kTN>(dtype, tile, p, s);
 }
 
 }  // namespace moe

@@ -11,13 +11,15 @@
 // swizzles are the same for both types:
 //   k-contiguous operand: [rows][8 pieces of 16 bytes], piece g of row r at position g ^ ((r / 2) % 8)  (ds_read_b128)
 //   k-slow operand:       [k rows][width], bf16 pieces swizzled for ds_read_b64_tr_b16, fp32 read as single words
-// A K-step of a wave is one barrier, the loads of a later K-step, then its MFMAs; two blocks share a compute unit (64 KB of
-// LDS each), so that one block's matrix instructions cover the other's barrier, LDS latency and epilogue.
+// Several blocks share a compute unit (64 KB of LDS or less each), so that one block's matrix instructions cover another's
+// barrier, load latency, tile search and epilogue; what is left binds by LDS reads (128 x 128: about three quarters of
+// the LDS rate at the matrix cores' peak) and, for few tiles, by how evenly they divide among the units.
 //
 // What it replaced was an fp32 FMA kernel on operands transposed and padded in memory, at 12 TFLOP/s in either type.
 // Measured, training step of 17 experts x 353 rows, M = 776, H = 1544, bf16: the six products 645-700 us -> 35-57 us each,
-// step 5060 -> 453 us.  8 experts x 1024 rows, M = 512, H = 1024, fp32: products 166-228 us -> 83-132 us (102 TFLOP/s in
-// the weight gradients; fp32 matrix peak 157), step 1589 -> 722 us.
+// step 5060 -> 417 us.  8 experts x 1024 rows, M = 512, H = 1024, fp32: products 166-228 us -> 72-95 us (117 TFLOP/s in
+// the weight gradients; fp32 matrix peak 157), step 1585 -> 630 us.  8 experts x 4 rows, M = H = 2048, bf16: 29 us on the
+// large tile -> 13 us (67 MB of weights: 5.1 TB/s), layer 121 -> 72 us.
 
 namespace {
 
@@ -136,20 +138,21 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   const int64_t a_step = TRA ? (int64_t)BKE * p.C * ES : 128, b_step = TRB ? (int64_t)BKE * p.N * ES : 128;
   const uint32_t smem_addr = (uint32_t)(uintptr_t)LDS_PTR(char, smem);
   const char* zero = (const char*)g_zero_piece;
-  auto issue = [&](int t) __attribute__((always_inline)) {          // K-step t -> stage t % NS; t ascends by one per call
+  auto issue_whole = [&](int t) __attribute__((always_inline)) {    // K-step t -> stage t % NS; t ascends by one per call
     const uint32_t dst = smem_addr + (uint32_t)((t % NS) * STAGE);
-    if (t == KT - 1) {                                              // pieces past the end of the reduction are zeros
-      const int64_t left = kend - (int64_t)t * BKE;
 #pragma unroll
-      for (int i = 0; i < LA; ++i) global_to_lds_16(a_k[i] < left ? a_ptr[i] : zero, dst + (i * NW + wave) * 1024);
+    for (int i = 0; i < LA; ++i) { global_to_lds_16(a_ptr[i], dst + (i * NW + wave) * 1024); a_ptr[i] += a_step; }
 #pragma unroll
-      for (int i = 0; i < LB; ++i) global_to_lds_16(b_k[i] < left ? b_ptr[i] : zero, dst + A_BYTES + (i * NW + wave) * 1024);
-    } else {
+    for (int i = 0; i < LB; ++i) { global_to_lds_16(b_ptr[i], dst + A_BYTES + (i * NW + wave) * 1024); b_ptr[i] += b_step; }
+  };
+  auto issue = [&](int t) __attribute__((always_inline)) {          // the same, with zeros past the end of the reduction
+    if (t < KT - 1) { issue_whole(t); return; }
+    const uint32_t dst = smem_addr + (uint32_t)((t % NS) * STAGE);
+    const int left = (int)(kend - (int64_t)t * BKE);
 #pragma unroll
-      for (int i = 0; i < LA; ++i) { global_to_lds_16(a_ptr[i], dst + (i * NW + wave) * 1024); a_ptr[i] += a_step; }
+    for (int i = 0; i < LA; ++i) global_to_lds_16(a_k[i] < left ? a_ptr[i] : zero, dst + (i * NW + wave) * 1024);
 #pragma unroll
-      for (int i = 0; i < LB; ++i) { global_to_lds_16(b_ptr[i], dst + A_BYTES + (i * NW + wave) * 1024); b_ptr[i] += b_step; }
-    }
+    for (int i = 0; i < LB; ++i) global_to_lds_16(b_k[i] < left ? b_ptr[i] : zero, dst + A_BYTES + (i * NW + wave) * 1024);
   };
 
   // ---- LDS read offsets of this lane's fragments (sub-tile 0; the others are constants apart) ---------------------------
@@ -157,19 +160,20 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   auto read_fast = [&](const char* tile, int w, int t, int s) -> u32x4 {   // pieces 2 s + kg of row w*.. + 32 t + lane % 32
     return *LDS_PTR(u32x4, tile + (w + t * 32 + (lane & 31)) * 128 + (((2 * s + kg) ^ swz) << 4));
   };
-  auto read_slow_bf16 = [&](const char* tile, int w, int t, int width, int s) -> bf16x8 {
-    const int pb = width * 2, kr = (lane & 15) >> 2;
-    const int c = w / 8 + t * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
-    const char* at = tile + (kg * 8 + kr) * pb + ((c ^ swz_slow(kr, pb)) << 4) + ((lane & 1) << 3);
-    const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(short4v, at + 16 * s * pb));
-    const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(short4v, at + (16 * s + 4) * pb));
-    return __builtin_bit_cast(bf16x8, (short8v)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-  };
-  auto read_slow_fp32 = [&](const char* tile, int w, int t, int width, int s) -> u32x4 {
-    u32x4 v;
+  auto read_slow = [&](const char* tile, int w, int t, int width, int s) -> u32x4 {
+    if constexpr (BF16) {
+      const int pb = width * 2, kr = (lane & 15) >> 2;
+      const int c = w / 8 + t * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
+      const char* at = tile + (kg * 8 + kr) * pb + ((c ^ swz_slow(kr, pb)) << 4) + ((lane & 1) << 3);
+      const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(short4v, at + 16 * s * pb));
+      const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(short4v, at + (16 * s + 4) * pb));
+      return __builtin_bit_cast(u32x4, (short8v)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    } else {
+      u32x4 v;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = *LDS_PTR(uint32_t, tile + (8 * s + 4 * kg + u) * width * 4 + (w + t * 32 + (lane & 31)) * 4);
-    return v;
+      for (int u = 0; u < 4; ++u) v[u] = *LDS_PTR(uint32_t, tile + (8 * s + 4 * kg + u) * width * 4 + (w + t * 32 + (lane & 31)) * 4);
+      return v;
+    }
   };
 
   // ---- accumulators: the bias (register 4 g + u of tile (i, j) is column 32 j + 8 g + 4 kg + u of the wave's), or zero; its
@@ -189,7 +193,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
       }
   }
 #pragma unroll
-  for (int t = 0; t < NS - 1; ++t)
+  for (int t = 0; t < NS; ++t)
     if (t < KT) issue(t);
   f32x16 acc[TI][TJ];
 #pragma unroll
@@ -211,48 +215,71 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   const int64_t live = rows - m0 - wm * WTM;
   const int ni = live <= 0 ? 0 : (live >= WTM ? TI : (int)((live + 31) >> 5));
 
+  // Fragments are read one sub-step (a quarter of a K-step) ahead of their MFMAs, across K-steps too: the barrier that hands
+  // a stage over sits ahead of the last sub-step's MFMAs, when every read of the stage is done, and the stage is refilled
+  // right behind it with the K-step NS ahead.
   auto main_loop = [&](auto ni_tag) __attribute__((always_inline)) {
     constexpr int NI = decltype(ni_tag)::value;
-    for (int kt = 0; kt < KT; ++kt) {
-      // K-step kt has landed when at most the loads of the later ones (issued after it) are outstanding
-      wait_for_loads<NS - 2, LA + LB>(KT - 1 - kt);
-      PIN();
-      asm volatile("s_barrier" ::: "memory");                       // every wave's loads are here; K-step kt - 1 is done with
-      PIN();
-      if (kt + NS - 1 < KT) issue(kt + NS - 1);
-      PIN();
-      const char* sa = smem + (kt % NS) * STAGE;
+    u32x4 fa[2][TI], fb[2][TJ];                                     // bf16: 8 k; fp32: k = 8 s + 4 kg + u in register u
+    auto read = [&](int d, const char* sa, int s) __attribute__((always_inline)) {
       const char* sb = sa + A_BYTES;
-      if (NI > 0) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          if constexpr (BF16) {
-            bf16x8 a[TI], b[TJ];
+      for (int i = 0; i < NI; ++i) fa[d][i] = TRA ? read_slow(sa, wm * WTM, i, BM, s) : read_fast(sa, wm * WTM, i, s);
 #pragma unroll
-            for (int i = 0; i < NI; ++i) a[i] = TRA ? read_slow_bf16(sa, wm * WTM, i, BM, s) : __builtin_bit_cast(bf16x8, read_fast(sa, wm * WTM, i, s));
+      for (int j = 0; j < TJ; ++j)
+        if (NI > 0) fb[d][j] = TRB ? read_slow(sb, wn * WTN, j, BN, s) : read_fast(sb, wn * WTN, j, s);
+    };
+    auto mfmas = [&](int d) __attribute__((always_inline)) {
+      if constexpr (BF16) {
 #pragma unroll
-            for (int j = 0; j < TJ; ++j) b[j] = TRB ? read_slow_bf16(sb, wn * WTN, j, BN, s) : __builtin_bit_cast(bf16x8, read_fast(sb, wn * WTN, j, s));
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
+          for (int j = 0; j < TJ; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fb[d][j]), __builtin_bit_cast(bf16x8, fa[d][i]), acc[i][j], 0, 0, 0);
+      } else {
 #pragma unroll
-              for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
-          } else {
-            u32x4 a[TI], b[TJ];                                     // k = 8 s + 4 kg + u in register u of both operands
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int i = 0; i < NI; ++i) a[i] = TRA ? read_slow_fp32(sa, wm * WTM, i, BM, s) : read_fast(sa, wm * WTM, i, s);
+          for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int j = 0; j < TJ; ++j) b[j] = TRB ? read_slow_fp32(sb, wn * WTN, j, BN, s) : read_fast(sb, wn * WTN, j, s);
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-              for (int i = 0; i < NI; ++i)
-#pragma unroll
-                for (int j = 0; j < TJ; ++j)
-                  acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(b[j][u]), __uint_as_float(a[i][u]), acc[i][j], 0, 0, 0);
-          }
-        }
+            for (int j = 0; j < TJ; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(fb[d][j][u]), __uint_as_float(fa[d][i][u]), acc[i][j], 0, 0, 0);
       }
-    }
+    };
+    auto kstep = [&](auto steady_tag, int kt) __attribute__((always_inline)) {
+      constexpr bool STEADY = decltype(steady_tag)::value;          // K-step kt + NS exists and is not the last
+      const char* cur = smem + (kt % NS) * STAGE;
+#pragma unroll
+      for (int s = 0; s < 3; ++s) {
+        read((s + 1) & 1, cur, s + 1);
+        PIN();
+        mfmas(s & 1);
+        PIN();
+      }
+      if (STEADY || kt + 1 < KT) {
+        if (STEADY) wait_for_loads<NS - 2, LA + LB>(NS);            // K-step kt + 1 has landed, later ones may be under way
+        else wait_for_loads<NS - 2, LA + LB>(KT - 2 - kt);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // this wave's reads of K-step kt are done
+        PIN();
+        asm volatile("s_barrier" ::: "memory");
+        PIN();
+        if (STEADY) issue_whole(kt + NS);
+        else if (kt + NS < KT) issue(kt + NS);
+        read(0, smem + ((kt + 1) % NS) * STAGE, 0);
+        PIN();
+      }
+      mfmas(1);
+      PIN();
+    };
+    wait_for_loads<NS - 1, LA + LB>(KT - 1);
+    PIN();
+    asm volatile("s_barrier" ::: "memory");
+    PIN();
+    read(0, smem, 0);
+    PIN();
+    int kt = 0;
+    for (; kt + NS < KT - 1; ++kt) kstep(std::true_type{}, kt);
+    for (; kt < KT; ++kt) kstep(std::false_type{}, kt);
   };
   if (ni == TI) main_loop(std::integral_constant<int, TI>{});
   else if (TI > 1 && ni == 1) main_loop(std::integral_constant<int, 1>{});
@@ -327,20 +354,45 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
 
 }  // namespace
 
-// Tile of a launch: 32 x 64 (two waves) where no expert has more than 32 rows, 128 x 128 where that leaves enough tiles for
-// two per compute unit, 64 x 64 otherwise.
-template <typename ET, int MODE>
-static hipError_t launch_tile(TileArgs p, int64_t rows, hipStream_t s) {
-  const int64_t big = p.E * ceil_div(rows, 128) * ceil_div(p.N, 128);
-  auto go = [&](auto kernel, int bm, int bn, int threads) {
-    p.MT = (int)ceil_div(rows, bm);
-    p.NT = (int)ceil_div(p.N, bn);
-    const int64_t blocks = p.E <= kMaxExperts ? tile_grid(p.E, p.MT, p.NT) : (int64_t)p.E * p.MT * p.NT;
-    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    kernel<<<dim3((unsigned)blocks), dim3(threads), 0, s>>>(p);
-    return hipGetLastError();
+template <typename ET, int MODE, int BM, int BN, int NS>
+static hipError_t launch_tile(TileArgs p, hipStream_t s) {
+  p.MT = (int)ceil_div(p.C, BM);
+  p.NT = (int)ceil_div(p.N, BN);
+  const int64_t blocks = p.E <= kMaxExperts ? tile_grid(p.E, p.MT, p.NT) : (int64_t)p.E * p.MT * p.NT;
+  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  grouped_gemm_tile_kernel<ET, MODE, BM, BN, 2, 2, NS><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(p);
+  return hipGetLastError();
+}
+
+// Which tile a bf16 launch takes.  The three shapes differ in how much of the chip a launch of few tiles uses, how finely its
+// work divides among the 256 compute units, and how fast a full unit runs: 256 x 256 (one block per unit) is 1.2-1.3 times
+// as fast as 128 x 128 (two) and 1.7-1.9 times as fast as 64 x 64 (three) once every unit has several tiles, and the
+// slowest by up to 3 times where it leaves most units idle.  Estimated time of a launch in microseconds:
+//   base + fix * rounds + ksteps * max(lat * rounds, thr * tiles per unit),    rounds = tiles per unit / blocks per unit
+// with constants fitted to 694 measured launches (4-128 experts, 8-4096 rows each, K and N 768-4096, with and without a
+// transposed A).  Over those the choice is 2.8 % (2.3 % for weight gradients) off the best of the three on average, against
+// 21 % (24 %) for always taking the largest tile.
+enum class Tile { k256, k128, k64 };
+static Tile choose_tile(int mode, bool large_ok, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
+  const double ksteps = (mode == kTN ? mean_rows : (double)K) / 64 + 0.5;
+  auto cost = [&](int bm, int per_unit, double base, double fix, double lat, double thr) {
+    const double row_tiles = mode == kTN ? (double)ceil_div(rows, bm) : (mean_rows / bm + 0.5 > 1.0 ? mean_rows / bm + 0.5 : 1.0);
+    double q = (double)E * row_tiles * (double)ceil_div(N, bm) / 256.0;             // tiles per compute unit
+    q = q <= 4.0 * per_unit ? ceil(q - 0.02) : q + 0.5;
+    const double rounds = q > per_unit ? q / per_unit : 1.0;
+    return base + fix * rounds + ksteps * (lat * rounds > thr * q ? lat * rounds : thr * q);
   };
-  if (rows <= 32) return go(grouped_gemm_tile_kernel<ET, MODE, 32, 64, 1, 2, 6>, 32, 64, 128);
-  if (big >= 512) return go(grouped_gemm_tile_kernel<ET, MODE, 128, 128, 2, 2, 2>, 128, 128, 256);
-  return go(grouped_gemm_tile_kernel<ET, MODE, 64, 64, 2, 2, 4>, 64, 64, 256);
+  // the weight gradients' large kernel comes with two launches that pad its last K-step
+  const double c256 = large_ok ? cost(256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 1.1) : 1e30;
+  const double c128 = cost(128, 2, 1.5, 3.5, 0.3, 0.56), c64 = cost(64, 3, 3.0, 1.5, 0.3, 0.235);
+  return c256 <= c128 && c256 <= c64 ? Tile::k256 : (c128 <= c64 ? Tile::k128 : Tile::k64);
+}
+
+// The launches below the large tile.  fp32: the matrix instruction is 16 times slower, loads hardly matter, and the finest
+// tile divides best (64 x 64, five blocks per unit: within 2-4 % of the best of four shapes over 442 launches).
+template <int MODE>
+static hipError_t launch_small(int dtype, Tile tile, const TileArgs& p, hipStream_t s) {
+  if (dtype == MOE_F32) return launch_tile<float, MODE, 64, 64, 2>(p, s);
+  if (tile == Tile::k64) return launch_tile<uint16_t, MODE, 64, 64, 3>(p, s);
+  return launch_tile<uint16_t, MODE, 128, 128, 2>(p, s);
 }

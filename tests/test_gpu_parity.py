@@ -466,7 +466,7 @@ def test_expert_ffn_backward(moe, dtype, E, C, M, H, act, bias, use_counts):
             assert_close(got, ref[name], dtype, name)
 
 
-# The small-tile GEMM in its three operand layouts: rows, columns and reduction lengths around its tiles (32 x 64, 64 x 64,
+# The small-tile GEMM in its three operand layouts: rows, columns and reduction lengths around its tiles (64 x 64,
 # 128 x 128) and around its K-step (64 bf16, 32 fp32), and more experts than the tile search holds.
 @pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
 @pytest.mark.parametrize("E,C,M,H", [(4, 31, 8, 264), (3, 33, 72, 40), (5, 63, 136, 248), (4, 65, 520, 24), (2, 129, 264, 328),
