@@ -11,8 +11,9 @@ of seeded synthetic input that is already resident in HBM.  The bench line is th
              rocprofv3 counter summary of the same workload under profiles/ (null where none is recorded)
   stages     per-stage mean milliseconds and, for encode/decode, algorithmic HBM GB/s
   cpu_baseline  the CPU oracle timed on this machine's host cores on a bounded sample of the same workload
-  fused_dispatch  the same step through moe_layer_forward_fused (the first expert GEMM gathers its rows from the tokens,
-             no dispatch buffer), timed in a second loop of the same length; information only, `value` is the plain path
+  fused_dispatch  the same step through moe_layer_forward_fused (the first expert GEMM gathers its rows from the tokens on
+             every step), timed in a second loop of the same length; information only: `value` is moe_layer_forward, which
+             fuses the dispatch too except on the steps that record stage events (every stage is then a kernel of its own)
   other_workloads  the other four workloads measured the same way in the same run (not bench lines)
   hip_graph_ms_per_step  (workloads under 2 ms per step) the same step replayed from a captured HIP graph; information only
 """

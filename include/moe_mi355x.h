@@ -261,16 +261,17 @@ int moe_decode_backward(const void* d_out, const void* Y, int dtype, const int32
  *   Optional outputs (each may be NULL): idx, loc [T,k] int32; gate_w [T,k] fp32; counts [E] int32; logits [T,E] fp32.
  *   ws / ws_bytes: at least moe_layer_workspace_bytes(T,M,H,E,k,C,dtype), 256-byte aligned.
  *   stage_events: NULL, or MOE_NUM_STAGE_EVENTS hipEvent_t handles recorded on `stream` at the stage boundaries
- *   listed above (for per-stage timing; the events belong to the caller). */
+ *   listed above (for per-stage timing; the events belong to the caller).
+ * With stage_events every stage runs as kernels of its own, the dispatch buffer included.  Without them the dispatch is fused
+ * into the first expert GEMM, which reads its rows from x through the slot -> token map; the results are bit-identical. */
 int moe_layer_forward(const void* x, const void* Wg, const float* gate_bias,
                       const void* W1, const void* b1, const void* W2, const void* b2,
                       int64_t T, int64_t M, int64_t H, int64_t E, int k, double f, int normalize, int act, int dtype,
                       void* out, int32_t* idx, int32_t* loc, float* gate_w, int32_t* counts, float* logits,
                       void* ws, size_t ws_bytes, void* stream, void* const* stage_events);
 
-/* moe_layer_forward with the dispatch fused into the first expert GEMM (moe_expert_ffn_gather) where that kernel
- * supports the shape and dtype, identical to moe_layer_forward otherwise.  Same arguments, same outputs; the encode
- * stage's events [2] and [3] are then recorded back to back. */
+/* moe_layer_forward with the dispatch fused into the first expert GEMM whether or not the stages are timed.  Same arguments,
+ * same outputs; the encode stage's events [2] and [3] are recorded back to back. */
 int moe_layer_forward_fused(const void* x, const void* Wg, const float* gate_bias, const void* W1, const void* b1,
                             const void* W2, const void* b2, int64_t T, int64_t M, int64_t H, int64_t E, int k, double f,
                             int normalize, int act, int dtype, void* out, int32_t* idx, int32_t* loc, float* gate_w,
@@ -304,15 +305,14 @@ int moe_layer_forward_dynamic(const void* x, const void* Wg, const float* gate_b
 
 /* One training step of the layer (Sec. 3.2: forward, then the backward pass mirrors it).  moe_layer_forward_train
  * computes what moe_layer_forward computes (`out` is bit-identical) and keeps in `state` what the backward needs:
- * logits, routing, the dispatch buffer, the first layer's values before and after the activation, the expert outputs.
+ * logits, routing, the first layer's values before and after the activation, the expert outputs.
  * moe_layer_backward then takes d_out = dLoss/d out [T,M] and the same x, weights and shape arguments, and writes
  *   dx [T,M] (through encode and through the gate), dWg [M,E], dgate_bias [E] fp32, dW1 [E,M,H], db1 [E,H],
  *   dW2 [E,H,M], db2 [E,M]   (any of dWg ... db2 may be NULL; dx is required),
  * running moe_decode_backward, moe_expert_ffn_backward, moe_encode_backward and moe_gate_backward on the state's
  * buffers.  The choice of experts, the slot assignment and dropped choices carry no gradient.
- * Where the matrix-core kernels take the shape (bf16, M and H multiples of 256, T * M * 2 < 2^32) the step never writes
- * the dispatch buffer: the forward's first product and the backward's dW1 = Z^T dP read the rows of Z from x through the
- * slot -> token map, as moe_layer_forward_fused does; results are bit-identical to the buffered route.
+ * The step never writes the dispatch buffer: the forward's first product and the backward's dW1 = Z^T dP read the rows of Z
+ * from x through the slot -> token map, as moe_layer_forward_fused does; results are bit-identical to the buffered route.
  *   state: device memory of at least moe_layer_train_state_bytes(T, M, H, E, k, moe_capacity(T, E, k, f), dtype)
  *   bytes, 256-byte aligned, owned by the caller; its layout is private; it must not change between the two calls.
  *   One state serves one step at a time: two steps that overlap on different streams need two states. */

@@ -133,10 +133,9 @@ hipError_t launch_dynamic_capacity(const int32_t* counts, int64_t E, int64_t bou
 // C_dev (optional, device): only choices with loc < min(*C_dev, C) are kept; slot_src keeps its [E, C] layout
 hipError_t launch_slot_sources(const int32_t* idx, const int32_t* loc, int64_t T, int64_t E, int k, int64_t C,
                                int32_t* slot_src, hipStream_t s, const int64_t* C_dev = nullptr);
-// C_dev (optional, device): as for launch_slot_sources (slot_src must have been built with the same C_dev)
 hipError_t launch_encode(const void* x, int dtype, const int32_t* idx, const int32_t* loc, const int32_t* slot_src,
                          int64_t T, int64_t M, int64_t E, int k, int64_t C, void* Z, hipStream_t s,
-                         bool fill_unfilled = true, const int64_t* C_dev = nullptr);
+                         bool fill_unfilled = true);
 // C_dev (optional, device): only choices with loc < min(*C_dev, C) are kept; Y keeps its [E, C, M] layout
 hipError_t launch_decode(const void* Y, int dtype, const int32_t* idx, const int32_t* loc, const float* gate_w,
                          int64_t T, int64_t M, int64_t E, int k, int64_t C, void* out, hipStream_t s,
@@ -156,9 +155,8 @@ hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, cons
                                   int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, int64_t rows_hint = 0,
                                   const int32_t* gather = nullptr, int64_t gather_rows = 0);
 size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W);
-// bf16 shapes whose first product, or whose products in both directions, read A through `gather` on the large tile
+// shapes moe_expert_ffn_gather takes
 bool grouped_gemm_gathers_on_large_tile(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows);
-bool grouped_gemm_tn_gathers(int64_t E, int64_t C, int64_t M, int64_t H, int64_t gather_rows);
 
 size_t gate_backward_workspace_bytes(int64_t T, int64_t M, int64_t E);
 hipError_t launch_gate_backward(const void* x, const void* Wg, const float* logits, const int32_t* idx, const float* dgate_w,
@@ -176,6 +174,6 @@ hipError_t launch_expert_ffn_backward(const void* Z, const void* W1, const void*
                                       void* db2, hipStream_t s, int64_t rows_hint = 0, const int32_t* gather = nullptr,
                                       int64_t gather_rows = 0);
 // With `gather` [E, C] (slot -> token) `Z` is the token matrix [gather_rows, M] itself (fused dispatch: the slabs of
-// dispatched rows were never written); needs saved pre-activations and shapes grouped_gemm_tn_gathers takes.
+// dispatched rows were never written); needs saved pre-activations.
 
 }  // namespace moe

@@ -762,10 +762,6 @@ bool grouped_gemm_gathers_on_large_tile(int64_t E, int64_t C, int64_t K, int64_t
   return large_tile_supports(E, C, K, N, gather_rows);
 }
 
-bool grouped_gemm_tn_gathers(int64_t E, int64_t C, int64_t M, int64_t H, int64_t gather_rows) {
-  return large_tile_supports_backward(E, C, M, H) && gather_rows > 0 && gather_rows * M * 2 < ((int64_t)1 << 32);
-}
-
 static double mean_or(int64_t rows_hint, int64_t C) { return (double)(rows_hint > 0 && rows_hint < C ? rows_hint : C); }
 
 hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, int act, int dtype, const int32_t* counts,
@@ -793,15 +789,15 @@ hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, cons
 size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W) { return (size_t)E * BK * W * 2; }
 
 // out[e] (R x N) = At[e]^T * B[e] over the first min(kfill[e], C) of the C slots; At [E, C, R], B [E, C, N].  a_tail and
-// b_tail: scratch of grouped_gemm_tn_tail_bytes(E, R) and (E, N).  With `gather` (grouped_gemm_tn_gathers shapes only) At
-// is one matrix [gather_rows, R] and slot c of expert e is its row gather[e, c].
+// b_tail: scratch of grouped_gemm_tn_tail_bytes(E, R) and (E, N).  With `gather` [E, C] At is one matrix [gather_rows, R] and
+// slot c of expert e is its row gather[e, c].
 hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
                                   int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, int64_t rows_hint,
                                   const int32_t* gather, int64_t gather_rows) {
-  const bool large_ok = dtype == MOE_BF16 && large_tile_supports_backward(E, C, R, N);
-  const Tile tile = gather ? Tile::k256 : choose_tile(kTN, large_ok, E, R, mean_or(rows_hint, C), C, N);
+  const bool large_ok = dtype == MOE_BF16 && large_tile_supports_backward(E, C, R, N) && gather_rows * R * 2 < ((int64_t)1 << 32);
+  const Tile tile = choose_tile(kTN, large_ok, E, R, mean_or(rows_hint, C), C, N);
   if (tile == Tile::k256) return launch_large_tn(At, B, kfill, E, C, R, N, a_tail, b_tail, out, s, gather, gather_rows);
-  const TileArgs p = {At, B, nullptr, nullptr, nullptr, 0, R, C, (int)N, (int)E, 0, 0, out, kfill, nullptr, nullptr, -1};
+  const TileArgs p = {At, B, nullptr, nullptr, gather, gather_rows, R, C, (int)N, (int)E, 0, 0, out, kfill, nullptr, nullptr, -1};
   return launch_small<kTN>(dtype, tile, p, s);
 }
 

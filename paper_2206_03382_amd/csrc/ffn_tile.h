@@ -28,7 +28,7 @@ struct TileArgs {
   const void* B;
   const void* bias;
   const int32_t* counts;
-  const int32_t* gather;        // kNN: A's row r is row gather[e, r] of one matrix [gather_rows, K]
+  const int32_t* gather;        // slot -> row [E, slots]: A is one matrix of gather_rows rows, [., K] (kNN) or [., C] (kTN, GK)
   int64_t gather_rows;
   int64_t C;                    // rows of A (kNN, kNT) or its width (kTN)
   int64_t K;                    // length of the reduction; slots per expert (kTN)
@@ -50,7 +50,8 @@ template <int MOST, int L> __device__ __forceinline__ void wait_for_loads(int la
 
 __device__ __align__(256) uint4 g_zero_piece[16];                   // stays zero: where pieces past the reduction's end are read
 
-template <typename ET, int MODE, int BM, int BN, int WR, int WC, int NS>
+// GK (kTN): A's k rows (slots) are gathered; the row numbers of a K-step are fetched a K-step before its loads go out.
+template <typename ET, int MODE, int BM, int BN, int WR, int WC, int NS, bool GK = false>
 __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(const TileArgs p) {
   constexpr int ES = (int)sizeof(ET), EC = 16 / ES;                 // elements per 16-byte piece
   constexpr int BKE = 128 / ES;                                     // k per K-step
@@ -113,7 +114,9 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
     if (TRA) {
-      a_ptr[i] = slow_source((const char*)p.A + (int64_t)e * p.K * p.C * ES, p.C, m0, BM, i, a_k[i]);
+      const char* base = (const char*)p.A + (GK ? 0 : (int64_t)e * p.K * p.C * ES);
+      a_ptr[i] = slow_source(base, p.C, m0, BM, i, a_k[i]);
+      if (GK) a_ptr[i] -= (int64_t)a_k[i] * p.C * ES;              // row 0 of the gathered matrix
     } else {
       int64_t row = m0 + (i * NW + wave) * 8 + (lane >> 3);
       row = row < rows ? row : rows - 1;                            // rows past the fill repeat the last one
@@ -138,19 +141,33 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   const int64_t a_step = TRA ? (int64_t)BKE * p.C * ES : 128, b_step = TRB ? (int64_t)BKE * p.N * ES : 128;
   const uint32_t smem_addr = (uint32_t)(uintptr_t)LDS_PTR(char, smem);
   const char* zero = (const char*)g_zero_piece;
-  auto issue_whole = [&](int t) __attribute__((always_inline)) {    // K-step t -> stage t % NS; t ascends by one per call
+  int grow[GK ? LA : 1];                                            // rows of the next K-step to load
+  auto fetch_rows = [&](int t, int (&g)[GK ? LA : 1]) __attribute__((always_inline)) {
+    if constexpr (GK) {
+#pragma unroll
+      for (int i = 0; i < LA; ++i) {
+        const int64_t slot = (int64_t)t * BKE + a_k[i];
+        g[i] = p.gather[(int64_t)e * p.K + (slot < p.K ? slot : p.K - 1)];
+      }
+    }
+  };
+  auto a_source = [&](int i, const int (&g)[GK ? LA : 1]) __attribute__((always_inline)) -> const char* {
+    if constexpr (GK) return a_ptr[i] + (int64_t)((uint32_t)g[i] < (uint64_t)p.gather_rows ? g[i] : 0) * p.C * ES;
+    else return a_ptr[i];
+  };
+  auto issue_whole = [&](int t, const int (&g)[GK ? LA : 1]) __attribute__((always_inline)) {   // K-step t -> stage t % NS; t ascends by one per call
     const uint32_t dst = smem_addr + (uint32_t)((t % NS) * STAGE);
 #pragma unroll
-    for (int i = 0; i < LA; ++i) { global_to_lds_16(a_ptr[i], dst + (i * NW + wave) * 1024); a_ptr[i] += a_step; }
+    for (int i = 0; i < LA; ++i) { global_to_lds_16(a_source(i, g), dst + (i * NW + wave) * 1024); if (!GK) a_ptr[i] += a_step; }
 #pragma unroll
     for (int i = 0; i < LB; ++i) { global_to_lds_16(b_ptr[i], dst + A_BYTES + (i * NW + wave) * 1024); b_ptr[i] += b_step; }
   };
-  auto issue = [&](int t) __attribute__((always_inline)) {          // the same, with zeros past the end of the reduction
-    if (t < KT - 1) { issue_whole(t); return; }
+  auto issue = [&](int t, const int (&g)[GK ? LA : 1]) __attribute__((always_inline)) {   // the same, with zeros past the end of the reduction
+    if (t < KT - 1) { issue_whole(t, g); return; }
     const uint32_t dst = smem_addr + (uint32_t)((t % NS) * STAGE);
     const int left = (int)(kend - (int64_t)t * BKE);
 #pragma unroll
-    for (int i = 0; i < LA; ++i) global_to_lds_16(a_k[i] < left ? a_ptr[i] : zero, dst + (i * NW + wave) * 1024);
+    for (int i = 0; i < LA; ++i) global_to_lds_16(a_k[i] < left ? a_source(i, g) : zero, dst + (i * NW + wave) * 1024);
 #pragma unroll
     for (int i = 0; i < LB; ++i) global_to_lds_16(b_k[i] < left ? b_ptr[i] : zero, dst + A_BYTES + (i * NW + wave) * 1024);
   };
@@ -192,9 +209,13 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
         braw[j][g] = *reinterpret_cast<const Raw4*>(be + (col < p.N ? col : n0));
       }
   }
+  int first_rows[NS][GK ? LA : 1];
+#pragma unroll
+  for (int t = 0; t < NS; ++t) fetch_rows(t, first_rows[t]);
 #pragma unroll
   for (int t = 0; t < NS; ++t)
-    if (t < KT) issue(t);
+    if (t < KT) issue(t, first_rows[t]);
+  fetch_rows(NS, grow);
   f32x16 acc[TI][TJ];
 #pragma unroll
   for (int j = 0; j < TJ; ++j)
@@ -263,8 +284,9 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
         PIN();
         asm volatile("s_barrier" ::: "memory");
         PIN();
-        if (STEADY) issue_whole(kt + NS);
-        else if (kt + NS < KT) issue(kt + NS);
+        if (STEADY) issue_whole(kt + NS, grow);
+        else if (kt + NS < KT) issue(kt + NS, grow);
+        if (GK) { fetch_rows(kt + NS + 1, grow); PIN(); }
         read(0, smem + ((kt + 1) % NS) * STAGE, 0);
         PIN();
       }
@@ -360,6 +382,12 @@ static hipError_t launch_tile(TileArgs p, hipStream_t s) {
   p.NT = (int)ceil_div(p.N, BN);
   const int64_t blocks = p.E <= kMaxExperts ? tile_grid(p.E, p.MT, p.NT) : (int64_t)p.E * p.MT * p.NT;
   if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  if constexpr (MODE == kTN) {
+    if (p.gather) {
+      grouped_gemm_tile_kernel<ET, MODE, BM, BN, 2, 2, NS, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(p);
+      return hipGetLastError();
+    }
+  }
   grouped_gemm_tile_kernel<ET, MODE, BM, BN, 2, 2, NS><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(p);
   return hipGetLastError();
 }
@@ -384,7 +412,8 @@ static Tile choose_tile(int mode, bool large_ok, int64_t E, int64_t rows, double
   };
   // the weight gradients' large kernel comes with two launches that pad its last K-step
   const double c256 = large_ok ? cost(256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 1.1) : 1e30;
-  const double c128 = cost(128, 2, 1.5, 3.5, 0.3, 0.56), c64 = cost(64, 3, 3.0, 1.5, 0.3, 0.235);
+  // and 64 x 64 was the best tile for one of 278 weight gradients
+  const double c128 = cost(128, 2, 1.5, 3.5, 0.3, 0.56), c64 = mode == kTN ? 1e30 : cost(64, 3, 3.0, 1.5, 0.3, 0.235);
   return c256 <= c128 && c256 <= c64 ? Tile::k256 : (c128 <= c64 ? Tile::k128 : Tile::k64);
 }
 
@@ -393,6 +422,8 @@ static Tile choose_tile(int mode, bool large_ok, int64_t E, int64_t rows, double
 template <int MODE>
 static hipError_t launch_small(int dtype, Tile tile, const TileArgs& p, hipStream_t s) {
   if (dtype == MOE_F32) return launch_tile<float, MODE, 64, 64, 2>(p, s);
-  if (tile == Tile::k64) return launch_tile<uint16_t, MODE, 64, 64, 3>(p, s);
+  if constexpr (MODE != kTN) {
+    if (tile == Tile::k64) return launch_tile<uint16_t, MODE, 64, 64, 3>(p, s);
+  }
   return launch_tile<uint16_t, MODE, 128, 128, 2>(p, s);
 }

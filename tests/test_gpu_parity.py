@@ -595,6 +595,24 @@ def test_layer_train_step_fills_at_reduction_step_boundaries(moe, T):
 # ----------------------------------------------------------------------------------------------------------------
 # the layer call allocates nothing, clears nothing by memset and never synchronises: it can be captured in a HIP graph
 # ----------------------------------------------------------------------------------------------------------------
+# Dispatch fused into the first GEMM (and into the first layer's weight gradient) on the small tiles, and the same pass with
+# its stages kept apart for timing: bit-identical.
+@pytest.mark.parametrize("cfg", [synth.CONFIGS[0].scaled(T=700, M=264, H=328, E=5, k=2, normalize=1), synth.CONFIGS[1].scaled(T=2000, M=264, H=520, E=8),
+                                 synth.CONFIGS[1].scaled(T=67, M=776, H=136, E=16)], ids=lambda c: f"{c.name}-T{c.T}-M{c.M}-H{c.H}-E{c.E}")
+def test_layer_fused_on_small_tiles(moe, cfg):
+    test_layer_forward_backward(moe, cfg)
+    inp = synth.make_inputs(cfg, seed=6, bias_std=0.25)
+    d = cfg.dtype
+    layer = moe.MoELayer(dev(inp["Wg"], d), None, dev(inp["W1"], d), dev(inp["b1"], d), dev(inp["W2"], d), dev(inp["b2"], d), T=cfg.T, k=cfg.k,
+                         f=cfg.f, normalize=cfg.normalize, act=cfg.act)
+    events = moe.StageEvents()
+    x = dev(inp["x"], d)
+    apart = layer.forward(x, events).clone()
+    assert min(events.stage_ms()) >= 0.0
+    assert torch.equal(layer.forward(x), apart)
+    events.close()
+
+
 def test_layer_forward_in_hip_graph(moe):
     cfg = synth.CONFIGS[1].scaled(T=1500, M=256, H=512, E=8)
     inp = synth.make_inputs(cfg, seed=21, bias_std=0.25)
