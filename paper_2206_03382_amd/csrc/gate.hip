@@ -58,7 +58,7 @@ template <> struct Raw8<uint16_t> {
 template <typename XT, int NT, int KS, int TW, bool VECW>
 __global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
                                                           const float* __restrict__ bias, int64_t T, int M, int Mq, int E,
-                                                          int e_base, float* __restrict__ logits) {
+                                                          float* __restrict__ logits) {
   // The block's four waves are 4/KS token groups times KS splits of the reduction; a wave owns TW tiles of 16 tokens.
   // Split ks owns k in [ks*Mq, (ks+1)*Mq) (Mq a multiple of BKW); the partial sums are added in split order at the
   // end.  Narrow gates (few experts) have one accumulator tile per 16 tokens, a serial chain of dependent MFMAs: TW
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__
   auto wg_fetch = [&](int kl) {
 #pragma unroll
     for (int i = 0; i < WPT; ++i) {
-      const int id = (threadIdx.x + i * 256) * VEC, q = id / (BKW * EN), r = (id / EN) % BKW, e = e_base + id % EN;
+      const int id = (threadIdx.x + i * 256) * VEC, q = id / (BKW * EN), r = (id / EN) % BKW, e = id % EN;
       const int kk = q * Mq + kl + r;
       const bool live = kl + r < Mq && kk < M && e < E;
       const XT* src = Wg + (live ? (int64_t)kk * E + e : 0);
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__
   for (int w = 0; w < TW; ++w)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      const int e = e_base + nt * 16 + m;
+      const int e = nt * 16 + m;
       if (e >= E) continue;
       const double be = bias ? (double)bias[e] : 0.0;
 #pragma unroll
@@ -221,28 +221,149 @@ __global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__
     }
 }
 
+// Wide gates (more than 64 experts; the cosine router's projection): a block's 2 x 2 waves own 32 tokens x 128 experts, a wave
+// 16 x 64 as four accumulator tiles.  Both operands go through LDS as fp32, 32 k at a time (the next 32 k are fetched to
+// registers meanwhile), and are widened on the way out: per 32 k a wave issues 32 matrix instructions of 64 cycles against
+// 34 LDS reads and 40 conversions, which hide behind them, and 21 KB of LDS let seven blocks share a unit and cover each
+// other's staging.  What binds is the fp64 matrix pipe.  Blocks are small because the count of blocks per unit is what
+// divides unevenly; all expert blocks go in one launch.  Replaced four waves of 16 tokens x 128 experts on fp64 weights in LDS,
+// one launch per 128 experts: 25088 tokens, M = 768, 256 columns
+// 275 -> 211 us (47 TFLOP/s; the fp64 matrix pipe alone sustains 67). Seven blocks per unit need 72 registers: at 96 the blocks past
+// the fifth of a unit run by themselves at the end, 229 us.
+// LDS rows: 36 floats per token (16 rows x 4 groups of a ds_read_b128 spread over all banks), 130 per k of the weights (the
+// four k of an operand read lie 16 banks apart).
+constexpr int kWideTokens = 32, kWideExperts = 128, kWideK = 32, kWideLdx = 36, kWideLdw = 130;
+
+// N consecutive values of a row as floats, kept raw while in flight
+template <typename XT, int N> struct RawN {
+  uint32_t w[N * (int)sizeof(XT) / 4];
+  __device__ __forceinline__ void load_vec(const XT* p) {                        // aligned to N * sizeof(XT) = 8, 16 or 32 bytes
+    if constexpr (N * sizeof(XT) == 8) {
+      const uint2 v = *reinterpret_cast<const uint2*>(p);
+      w[0] = v.x; w[1] = v.y;
+    } else {
+#pragma unroll
+      for (int i = 0; i < N * (int)sizeof(XT) / 16; ++i) {
+        const uint4 v = reinterpret_cast<const uint4*>(p)[i];
+        w[4 * i] = v.x; w[4 * i + 1] = v.y; w[4 * i + 2] = v.z; w[4 * i + 3] = v.w;
+      }
+    }
+  }
+  __device__ __forceinline__ void keep_if(bool on) {
+#pragma unroll
+    for (int i = 0; i < N * (int)sizeof(XT) / 4; ++i) w[i] = on ? w[i] : 0u;
+  }
+  __device__ __forceinline__ float get(int i) const {
+    if constexpr (sizeof(XT) == 4) return __uint_as_float(w[i]);
+    else return __uint_as_float((i & 1) ? w[i >> 1] & 0xffff0000u : w[i >> 1] << 16);
+  }
+  __device__ __forceinline__ void set(int i, XT v) {
+    if constexpr (sizeof(XT) == 4) w[i] = __float_as_uint(v);
+    else w[i >> 1] = (i & 1) ? (w[i >> 1] & 0xffffu) | ((uint32_t)v << 16) : (uint32_t)v;
+  }
+};
+
+template <typename XT, bool VECW>
+__global__ __launch_bounds__(256, VECW && sizeof(XT) == 2 ? 7 : 4) void gate_logits_wide_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
+                                                               const float* __restrict__ bias, int64_t T, int M, int E,
+                                                               int expert_blocks, float* __restrict__ logits) {
+  __shared__ __attribute__((aligned(16))) float xs[kWideTokens * kWideLdx];
+  __shared__ __attribute__((aligned(16))) float ws[kWideK * kWideLdw];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, kq = lane >> 4, wt = wave >> 1, we = wave & 1;
+  const int64_t t0 = (int64_t)(blockIdx.x / expert_blocks) * kWideTokens;       // the blocks that share tokens run together
+  const int e0 = (int)(blockIdx.x % expert_blocks) * kWideExperts;
+
+  // staging: thread i brings 4 values of token i / 8 and 16 of k row i / 8
+  const int srow = threadIdx.x >> 3, sp = threadIdx.x & 7;
+  const int64_t st = t0 + srow < T ? t0 + srow : T - 1;
+  const XT* xsrc = x + st * (int64_t)M + sp * 4;
+  const int we0 = e0 + sp * 16;                                     // first expert of this thread's 16
+  RawN<XT, 4> xr;
+  RawN<XT, 8> wr[2];
+  auto fetch = [&](int k0) __attribute__((always_inline)) {          // M is a multiple of 8: four values are all inside or all outside
+    const bool live = k0 + sp * 4 < M;
+    xr.load_vec(live ? xsrc + k0 : xsrc - sp * 4);
+    xr.keep_if(live);
+    const bool wlive = k0 + srow < M;
+    const XT* row = Wg + (int64_t)(wlive ? k0 + srow : 0) * E;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int e = we0 + 8 * h;
+      if (VECW) {                                                   // E a multiple of 8, rows 16-byte aligned
+        const bool on = wlive && e < E;
+        wr[h].load_vec(row + (e < E ? e : 0));
+        wr[h].keep_if(on);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) wr[h].set(u, row[e + u < E ? e + u : E - 1]);
+        wr[h].keep_if(wlive);                                       // columns past E repeat the last one and are never stored
+      }
+    }
+  };
+  f64x4 acc[4];
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) acc[nt] = f64x4{0.0, 0.0, 0.0, 0.0};
+  fetch(0);
+  for (int k0 = 0; k0 < M; k0 += kWideK) {
+    __syncthreads();                                                // the previous chunk has been read
+    *reinterpret_cast<float4*>(&xs[srow * kWideLdx + sp * 4]) = make_float4(xr.get(0), xr.get(1), xr.get(2), xr.get(3));
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int u = 0; u < 8; u += 2)
+        *reinterpret_cast<float2*>(&ws[srow * kWideLdw + sp * 16 + 8 * h + u]) = make_float2(wr[h].get(u), wr[h].get(u + 1));
+    __syncthreads();
+    if (k0 + kWideK < M) fetch(k0 + kWideK);
+    const float* xa = &xs[(wt * 16 + r) * kWideLdx + kq * 8];
+    const float4 a0 = *reinterpret_cast<const float4*>(xa), a1 = *reinterpret_cast<const float4*>(xa + 4);
+    const float av[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+    const float* wb = &ws[kq * 8 * kWideLdw + we * 64 + r];
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+      for (int nt = 0; nt < 4; ++nt)
+        acc[nt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[s], (double)wb[s * kWideLdw + nt * 16], acc[nt], 0, 0, 0);
+  }
+#pragma unroll
+  for (int nt = 0; nt < 4; ++nt) {
+    const int e = e0 + we * 64 + nt * 16 + r;
+    if (e >= E) continue;
+    const double be = bias ? (double)bias[e] : 0.0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t t = t0 + wt * 16 + 4 * v + kq;
+      if (t < T) logits[t * E + e] = (float)(acc[nt][v] + be);
+    }
+  }
+}
+
 template <typename XT, int NT, int KS, int TW>
 static void launch_gate_logits_one(const XT* x, const XT* Wg, const float* bias, int64_t T, int64_t M, int64_t E,
-                                   int64_t e_base, float* logits, hipStream_t s) {
+                                   float* logits, hipStream_t s) {
   constexpr int BKW = 4096 / (KS * NT * 16);
   const int Mq = (int)(ceil_div(ceil_div(M, KS), BKW) * BKW);       // k per split, a whole number of LDS chunks
   const dim3 grid((unsigned)ceil_div(T, 16 * TW * (4 / KS))), block(256);
   constexpr int VEC = 16 / (int)sizeof(XT);
-  const bool vecw = E % VEC == 0 && e_base % VEC == 0 && ((uintptr_t)Wg & 15) == 0;
-  if (vecw) gate_logits_kernel<XT, NT, KS, TW, true><<<grid, block, 0, s>>>(x, Wg, bias, T, (int)M, Mq, (int)E, (int)e_base, logits);
-  else gate_logits_kernel<XT, NT, KS, TW, false><<<grid, block, 0, s>>>(x, Wg, bias, T, (int)M, Mq, (int)E, (int)e_base, logits);
+  const bool vecw = E % VEC == 0 && ((uintptr_t)Wg & 15) == 0;
+  if (vecw) gate_logits_kernel<XT, NT, KS, TW, true><<<grid, block, 0, s>>>(x, Wg, bias, T, (int)M, Mq, (int)E, logits);
+  else gate_logits_kernel<XT, NT, KS, TW, false><<<grid, block, 0, s>>>(x, Wg, bias, T, (int)M, Mq, (int)E, logits);
 }
 
 template <typename XT>
 static hipError_t launch_gate_logits_t(const XT* x, const XT* Wg, const float* bias, int64_t T, int64_t M, int64_t E,
                                        float* logits, hipStream_t s) {
-  for (int64_t e_base = 0; e_base < E; e_base += 128) {
-    const int64_t rem = E - e_base;
-    if (rem <= 16) launch_gate_logits_one<XT, 1, 4, kNarrowGateTilesPerWave>(x, Wg, bias, T, M, E, e_base, logits, s);
-    else if (rem <= 32) launch_gate_logits_one<XT, 2, 4, 2>(x, Wg, bias, T, M, E, e_base, logits, s);
-    else if (rem <= 64) launch_gate_logits_one<XT, 4, 2, 2>(x, Wg, bias, T, M, E, e_base, logits, s);
-    else launch_gate_logits_one<XT, 8, 1, 1>(x, Wg, bias, T, M, E, e_base, logits, s);
+  if (E > 64) {
+    const int64_t expert_blocks = ceil_div(E, kWideExperts), blocks = ceil_div(T, kWideTokens) * expert_blocks;
+    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+    if (E % 8 == 0 && ((uintptr_t)Wg & 15) == 0)
+      gate_logits_wide_kernel<XT, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, (int)expert_blocks, logits);
+    else
+      gate_logits_wide_kernel<XT, false><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, (int)expert_blocks, logits);
   }
+  else if (E <= 16) launch_gate_logits_one<XT, 1, 4, kNarrowGateTilesPerWave>(x, Wg, bias, T, M, E, logits, s);
+  else if (E <= 32) launch_gate_logits_one<XT, 2, 4, 2>(x, Wg, bias, T, M, E, logits, s);
+  else launch_gate_logits_one<XT, 4, 2, 2>(x, Wg, bias, T, M, E, logits, s);
   return hipGetLastError();
 }
 
@@ -928,29 +1049,74 @@ __global__ __launch_bounds__(256) void cosine_prepare_kernel(const float* __rest
   if (threadIdx.x == 0) norm[e] = fmax(sqrt(part[0]), 1e-12);
 }
 
-// One wave per token, one lane per expert: the token's projection is fetched 64 values at a time and broadcast lane by
-// lane; every lane accumulates its expert's dot product and the token's squared norm in fp64, in ascending d.
+// A wave owns 16 tokens and NT tiles of 16 experts on the fp64 matrix cores; a block's four waves share the experts.  The
+// projections (as fp32) and the experts' vectors pass through LDS 32 dimensions at a time, the next ones fetched to
+// registers meanwhile, so every global access is contiguous and any D works.  The squared norms come from the same operand
+// values.  Bound by the latency of D / 32 rounds; one lane per expert and a broadcast per dimension, which this replaced, was
+// a serial chain of 2 D fp64 operations with half the lanes idle at 32 experts: 25088 tokens, D = 256, 214 -> 19 us.
+template <int NT>
 __global__ __launch_bounds__(256) void cosine_logits_kernel(const float* __restrict__ proj, const double* __restrict__ MeT,
                                                             const double* __restrict__ norm, double tau, int64_t T, int D,
-                                                            int E, float* __restrict__ logits) {
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
-  const int64_t nwaves = (int64_t)gridDim.x * 4;
-  for (int64_t t = wave; t < T; t += nwaves) {
-    for (int e0 = 0; e0 < E; e0 += 64) {
-      const int e = e0 + lane;
-      const int ec = e < E ? e : E - 1;                   // lanes past the last expert repeat it and store nothing
-      double dot = 0.0, nx2 = 0.0;
-      for (int d0 = 0; d0 < D; d0 += 64) {
-        const float pv = (d0 + lane < D) ? proj[t * D + d0 + lane] : 0.f;
-        const int n = (D - d0) < 64 ? (D - d0) : 64;
-        for (int dd = 0; dd < n; ++dd) {
-          const double sd = (double)__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(pv), dd));
-          dot = fma(sd, MeT[(int64_t)(d0 + dd) * E + ec], dot);
-          nx2 = fma(sd, sd, nx2);
-        }
-      }
-      if (e < E) logits[t * E + e] = (float)((dot / (fmax(sqrt(nx2), 1e-12) * norm[e])) / tau);
+                                                            int E, int expert_blocks, float* __restrict__ logits) {
+  constexpr int EN = NT * 16, DK = 32;
+  constexpr int LDP = 36, LDM = NT == 1 ? EN : EN + 16;             // the rows of an operand read lie in different banks
+  constexpr int WPT = DK * EN / 256;
+  __shared__ float ps[64 * LDP];
+  __shared__ double ms[DK * LDM];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, kq = lane >> 4;
+  const int64_t t0 = (int64_t)(blockIdx.x / expert_blocks) * 64;
+  const int e0 = (int)(blockIdx.x % expert_blocks) * EN;
+  float pr[8];                                                      // thread i: dimension i % 32 of tokens i / 32 + 8 u
+  double mr[WPT];                                                   // and pieces i + 256 u of the [32][EN] chunk
+  auto fetch = [&](int d0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t t = t0 + (threadIdx.x >> 5) + 8 * u;
+      const int d = d0 + (threadIdx.x & 31);
+      const float v = proj[(t < T ? t : T - 1) * D + (d < D ? d : 0)];
+      pr[u] = d < D ? v : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < WPT; ++u) {
+      const int id = threadIdx.x + 256 * u, d = d0 + id / EN, e = e0 + id % EN;
+      const double v = MeT[(int64_t)(d < D ? d : 0) * E + (e < E ? e : E - 1)];
+      mr[u] = d < D ? v : 0.0;                                      // experts past the last repeat it and are never stored
+    }
+  };
+  f64x4 acc[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) acc[nt] = f64x4{0.0, 0.0, 0.0, 0.0};
+  double n2 = 0.0;                                                  // this lane's share of token r's squared norm
+  fetch(0);
+  for (int d0 = 0; d0 < D; d0 += DK) {
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 8; ++u) ps[((threadIdx.x >> 5) + 8 * u) * LDP + (threadIdx.x & 31)] = pr[u];
+#pragma unroll
+    for (int u = 0; u < WPT; ++u) ms[((threadIdx.x + 256 * u) / EN) * LDM + (threadIdx.x + 256 * u) % EN] = mr[u];
+    __syncthreads();
+    if (d0 + DK < D) fetch(d0 + DK);
+#pragma unroll
+    for (int s = 0; s < DK / 4; ++s) {
+      const double a = (double)ps[(wave * 16 + r) * LDP + 4 * s + kq];
+      n2 = fma(a, a, n2);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+        acc[nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, ms[(4 * s + kq) * LDM + nt * 16 + r], acc[nt], 0, 0, 0);
+    }
+  }
+  n2 += __shfl_xor(n2, 16, 64);
+  n2 += __shfl_xor(n2, 32, 64);                                     // now the whole norm of token r
+  const double nt_own = fmax(sqrt(n2), 1e-12);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const double nx = __shfl(nt_own, 4 * v + kq, 64);               // of the token this register belongs to
+    const int64_t t = t0 + wave * 16 + 4 * v + kq;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const int e = e0 + nt * 16 + r;
+      if (e < E && t < T) logits[t * E + e] = (float)((acc[nt][v] / (nx * norm[e])) / tau);
     }
   }
 }
@@ -963,8 +1129,14 @@ hipError_t launch_gate_logits_cosine(const void* x, const void* Wp, const float*
   cosine_prepare_kernel<<<dim3((unsigned)E), dim3(256), 0, s>>>(Me, (int)E, (int)D, MeT, norm);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  const int64_t blocks = ceil_div(T, 4);
-  cosine_logits_kernel<<<dim3((unsigned)(blocks < 16384 ? blocks : 16384)), dim3(256), 0, s>>>(proj, MeT, norm, tau, T, (int)D, (int)E, logits);
+  const int64_t token_blocks = ceil_div(T, 64);
+#define MOE_COSINE(NT)                                                                                                        \
+  do {                                                                                                                        \
+    const int64_t eb = ceil_div(E, NT * 16);                                                                                  \
+    cosine_logits_kernel<NT><<<dim3((unsigned)(token_blocks * eb)), dim3(256), 0, s>>>(proj, MeT, norm, tau, T, (int)D, (int)E, (int)eb, logits); \
+  } while (0)
+  if (E <= 16) MOE_COSINE(1); else if (E <= 32) MOE_COSINE(2); else MOE_COSINE(4);
+#undef MOE_COSINE
   return hipGetLastError();
 }
 

@@ -197,6 +197,35 @@ def test_gate_logits(moe, dtype, T, M, E, bias):
     assert (got != ref).mean() <= 1e-4
 
 
+@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
+@pytest.mark.parametrize("T,M,E", [(1, 8, 65), (31, 24, 72), (32, 32, 128), (33, 40, 129), (97, 72, 192), (64, 256, 136)])
+def test_gate_logits_wide_edges(moe, dtype, T, M, E):
+    """Gates beyond 64 experts around the block (32 tokens x 128 experts) and the chunk (32 k); Wg also at an address that
+    is aligned to one element only.  Bound: as above."""
+    cfg = synth.CONFIGS[1].scaled(T=T, M=M, H=8, E=E, dtype=dtype, cfg_id=44)
+    inp = synth.make_inputs(cfg, seed=T + E)
+    ref = O.gate_logits(inp["x"], inp["Wg"], None)
+    x, Wg = dev(inp["x"], dtype), dev(inp["Wg"], dtype)
+    shifted = torch.empty(M * E + 1, dtype=Wg.dtype, device="cuda")[1:].view(M, E)
+    shifted.copy_(Wg)
+    for w in (Wg, shifted):
+        got = moe.gate_logits(x, w, None).cpu().numpy()
+        assert (np.abs(got - ref) <= np.spacing(np.abs(ref).astype(np.float32))).all()
+        assert (got != ref).mean() <= max(1e-4, 1.5 / got.size)
+
+
+@pytest.mark.parametrize("T,D,E", [(63, 31, 16), (64, 32, 17), (65, 33, 32), (130, 64, 33), (16, 100, 65)])
+def test_cosine_router_edges(moe, T, D, E):
+    """Around the block of 64 tokens, the 32 dimensions per round and the 16, 32 or 64 experts per block."""
+    rng = np.random.default_rng(T + D + E)
+    x = rng.standard_normal((T, 16)).astype(np.float32)
+    Wp = (rng.standard_normal((16, D)) / 4).astype(np.float32)
+    Me = rng.standard_normal((E, D)).astype(np.float32)
+    ref = O.cosine_gate_logits(x, Wp, Me, 0.07)
+    g = moe.gate_logits_cosine(dev(x, synth.DT_F32), dev(Wp, synth.DT_F32), torch.from_numpy(Me).cuda(), 0.07).cpu().numpy()
+    assert (np.abs(g - ref) <= np.spacing(np.abs(ref).astype(np.float32))).all() and (g != ref).mean() <= max(1e-4, 1.5 / g.size)
+
+
 # ----------------------------------------------------------------------------------------------------------------
 # cosine router front-end (moe_gate_logits_cosine) followed by the usual top-k
 # ----------------------------------------------------------------------------------------------------------------
