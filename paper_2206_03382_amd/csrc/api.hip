@@ -42,7 +42,7 @@ size_t gate_route_workspace(int64_t T, int64_t M, int64_t E, int k, int dtype) {
 template <typename F>
 hipError_t run_gate(const void* x, const void* Wg, const float* bias, int dtype, int64_t T, int64_t M, int64_t E, int k, int64_t C,
                     int normalize, float* logits, int32_t* idx, float* gate_w, int32_t* loc, int32_t* counts, int32_t* slot_src,
-                    void* ws, hipStream_t s, F&& after_logits) {
+                    void* ws, hipStream_t s, F&& after_logits, bool mark_unfilled = true) {
   int32_t* counters = (int32_t*)ws;
   if (gate_uses_fast_logits(dtype, T, M, E)) {
     const GateFastWorkspace f = gate_fast_layout((char*)ws + align_up(moe_gate_workspace_bytes(T, E, k), 256), T, M, E);
@@ -50,12 +50,12 @@ hipError_t run_gate(const void* x, const void* Wg, const float* bias, int dtype,
     if (err != hipSuccess) return err;
     if (!after_logits()) return hipErrorUnknown;
     const GateRepair repair = {f.margin, x, f.Wt, bias, M, f.Mp};
-    return launch_gate_topk(logits, T, E, k, C, normalize, idx, gate_w, loc, counts, slot_src, counters, s, nullptr, &repair);
+    return launch_gate_topk(logits, T, E, k, C, normalize, idx, gate_w, loc, counts, slot_src, counters, s, nullptr, &repair, mark_unfilled);
   }
   hipError_t err = launch_gate_logits(x, Wg, bias, dtype, T, M, E, logits, s);
   if (err != hipSuccess) return err;
   if (!after_logits()) return hipErrorUnknown;
-  return launch_gate_topk(logits, T, E, k, C, normalize, idx, gate_w, loc, counts, slot_src, counters, s);
+  return launch_gate_topk(logits, T, E, k, C, normalize, idx, gate_w, loc, counts, slot_src, counters, s, nullptr, nullptr, mark_unfilled);
 }
 
 struct LayerWorkspace {
@@ -560,31 +560,32 @@ int moe_layer_forward_dynamic(const void* x, const void* Wg, const float* gate_b
   int32_t* d_src = (int32_t*)(base + w.slot_src);
   hipStream_t s = (hipStream_t)stream;
 
-  // arrivals do not depend on the capacity: count them first (no slot sources yet), then choose the capacity on the device.
-  // The plain linear router takes the fast logits with exact repair of near-ties; the cosine router and batch prioritized
-  // routing (whose token order is itself decided on the logits) take logits that are exactly rounded throughout.
-  int st;
+  // arrivals do not depend on the capacity: they are counted, and every choice below the caller's bound gets its slot in the
+  // layout that bound gives ([E, C_max, ...]); the capacity is then chosen on the device and only narrows which choices are
+  // kept (loc < C, read from device memory) and how many rows of a slab are filled.  Slots past a fill are never used, so
+  // they are not marked.  The plain linear router takes the fast logits with exact repair of near-ties; the cosine router
+  // and batch prioritized routing (whose token order is itself decided on the logits) take logits that are exactly rounded
+  // throughout.
   if (router == MOE_ROUTER_LINEAR && !bpr) {
-    st = run_gate(x, Wg, gate_bias, dtype, T, M, E, k, C_max, normalize, d_logits, d_idx, d_gw, d_loc, d_counts, nullptr,
-                  base + w.gate_ws, s, [] { return true; }) == hipSuccess ? MOE_OK : MOE_HIP_ERROR;
+    if (run_gate(x, Wg, gate_bias, dtype, T, M, E, k, C_max, normalize, d_logits, d_idx, d_gw, d_loc, d_counts, d_src,
+                 base + w.gate_ws, s, [] { return true; }, false) != hipSuccess)
+      return MOE_HIP_ERROR;
   } else {
-    if (router == MOE_ROUTER_COSINE)
-      st = moe_gate_logits_cosine(x, Wg, Me, tau, dtype, T, M, D, E, d_logits, base + w.cosine_ws, moe_cosine_gate_workspace_bytes(T, D, E), stream);
-    else
-      st = launch_gate_logits(x, Wg, gate_bias, dtype, T, M, E, d_logits, s) == hipSuccess ? MOE_OK : MOE_HIP_ERROR;
-    if (st != MOE_OK) return st;
-    if (bpr)
-      st = moe_gate_topk_bpr(d_logits, T, E, k, C_max, normalize, d_idx, d_gw, d_loc, d_counts, nullptr, base + w.gate_ws,
-                             moe_gate_bpr_workspace_bytes(T, E, k), stream);
-    else
-      st = launch_gate_topk(d_logits, T, E, k, C_max, normalize, d_idx, d_gw, d_loc, d_counts, nullptr, (int32_t*)(base + w.gate_ws), s) == hipSuccess
-               ? MOE_OK : MOE_HIP_ERROR;
+    if (router == MOE_ROUTER_COSINE) {
+      const int st = moe_gate_logits_cosine(x, Wg, Me, tau, dtype, T, M, D, E, d_logits, base + w.cosine_ws,
+                                            moe_cosine_gate_workspace_bytes(T, D, E), stream);
+      if (st != MOE_OK) return st;
+    } else if (launch_gate_logits(x, Wg, gate_bias, dtype, T, M, E, d_logits, s) != hipSuccess) {
+      return MOE_HIP_ERROR;
+    }
+    const int32_t* perm = nullptr;
+    if (bpr && launch_bpr_order(d_logits, T, E, base + w.gate_ws + align_up(moe_gate_workspace_bytes(T, E, k), 256), &perm, s) != hipSuccess)
+      return MOE_HIP_ERROR;
+    if (launch_gate_topk(d_logits, T, E, k, C_max, normalize, d_idx, d_gw, d_loc, d_counts, d_src, (int32_t*)(base + w.gate_ws), s,
+                         perm, nullptr, false) != hipSuccess)
+      return MOE_HIP_ERROR;
   }
-  if (st != MOE_OK) return st;
   if (launch_dynamic_capacity(d_counts, E, bound, d_C, s, fixed, d_fills) != hipSuccess) return MOE_HIP_ERROR;
-  // every buffer keeps the layout the caller's bound gives ([E, C_max, ...]); the chosen capacity only narrows which
-  // choices are kept (loc < C, read from device memory) and how many rows of a slab are filled
-  if (launch_slot_sources(d_idx, d_loc, T, E, k, C_max, d_src, s, d_C) != hipSuccess) return MOE_HIP_ERROR;
   // the first GEMM reads its rows from the tokens through slot_src
   if (launch_grouped_gemm(x, W1, b1, act, dtype, d_fills, E, C_max, M, H, base + w.hidden, s, mean_fill(T, E, k), nullptr, d_src, T) != hipSuccess)
     return MOE_HIP_ERROR;

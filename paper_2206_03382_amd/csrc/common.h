@@ -117,10 +117,11 @@ bool gate_logits_fast_supports(int dtype, int64_t T, int64_t M, int64_t E);
 hipError_t launch_gate_logits_fast(const void* x, const void* Wg, const float* bias, int64_t T, int64_t M, int64_t E,
                                    float* logits, const GateFastWorkspace& w, hipStream_t s);
 // `repair` (optional): the logits are approximate to within repair->margin[t]; near-ties are then recomputed in fp64 and
-// written back into `logits` (not combinable with `perm`)
+// written back into `logits` (not combinable with `perm`).  Without mark_unfilled the slots past an expert's fill keep whatever
+// slot_src held (callers that never use them).
 hipError_t launch_gate_topk(float* logits, int64_t T, int64_t E, int k, int64_t C, int normalize, int32_t* idx,
                             float* gate_w, int32_t* loc, int32_t* counts, int32_t* slot_src, int32_t* block_counts,
-                            hipStream_t s, const int32_t* perm = nullptr, const GateRepair* repair = nullptr);
+                            hipStream_t s, const int32_t* perm = nullptr, const GateRepair* repair = nullptr, bool mark_unfilled = true);
 size_t bpr_order_workspace_bytes(int64_t T);
 hipError_t launch_bpr_order(const float* logits, int64_t T, int64_t E, void* ws, const int32_t** perm, hipStream_t s);
 hipError_t launch_decode_backward(const void* d_out, const void* Y, int dtype, const int32_t* idx, const int32_t* loc,
@@ -130,9 +131,8 @@ hipError_t launch_decode_backward(const void* d_out, const void* Y, int dtype, c
 // fills[e] (optional) = min(counts[e], out[0])
 hipError_t launch_dynamic_capacity(const int32_t* counts, int64_t E, int64_t bound, int64_t* out, hipStream_t s,
                                    int64_t fixed = 0, int32_t* fills = nullptr);
-// C_dev (optional, device): only choices with loc < min(*C_dev, C) are kept; slot_src keeps its [E, C] layout
 hipError_t launch_slot_sources(const int32_t* idx, const int32_t* loc, int64_t T, int64_t E, int k, int64_t C,
-                               int32_t* slot_src, hipStream_t s, const int64_t* C_dev = nullptr);
+                               int32_t* slot_src, hipStream_t s);
 hipError_t launch_encode(const void* x, int dtype, const int32_t* idx, const int32_t* loc, const int32_t* slot_src,
                          int64_t T, int64_t M, int64_t E, int k, int64_t C, void* Z, hipStream_t s,
                          bool fill_unfilled = true);

@@ -902,7 +902,7 @@ __global__ __launch_bounds__(kGateTokensPerBlock) void gate_assign_kernel(const 
 
 hipError_t launch_gate_topk(float* logits, int64_t T, int64_t E, int k, int64_t C, int normalize, int32_t* idx,
                             float* gate_w, int32_t* loc, int32_t* counts, int32_t* slot_src, int32_t* block_counts,
-                            hipStream_t s, const int32_t* perm, const GateRepair* repair) {
+                            hipStream_t s, const int32_t* perm, const GateRepair* repair, bool mark_unfilled) {
   const int NB = (int)ceil_div(T, kGateTokensPerBlock);
   // lane group per token: up to 16 experts one value per lane; from there on 16 lanes with up to 8 logits each (4 tokens
   // per wave), and a whole wave beyond 128 experts
@@ -945,7 +945,7 @@ hipError_t launch_gate_topk(float* logits, int64_t T, int64_t E, int k, int64_t 
 #undef MOE_TOPK_LANE
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
-  gate_scan_kernel<<<dim3((unsigned)E), block, 0, s>>>(block_counts, k * NB, (int)E, C, counts, slot_src);
+  gate_scan_kernel<<<dim3((unsigned)E), block, 0, s>>>(block_counts, k * NB, (int)E, C, counts, mark_unfilled ? slot_src : nullptr);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
   gate_assign_kernel<<<grid, dim3(kGateTokensPerBlock), 0, s>>>(idx, block_counts, T, (int)E, k, C, NB, loc, slot_src, perm);
@@ -1002,26 +1002,22 @@ __global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* __restrict__ p, 
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = v;
 }
 
-// C_dev (optional): the capacity chosen on the device; slots then sit `stride` apart per expert (the caller's bound)
 __global__ __launch_bounds__(256) void slot_sources_kernel(const int32_t* __restrict__ idx, const int32_t* __restrict__ loc,
-                                                           int64_t pairs, int k, int E, int64_t C, int64_t stride,
-                                                           const int64_t* __restrict__ C_dev,
-                                                           int32_t* __restrict__ slot_src) {
-  if (C_dev) { const int64_t c = *C_dev; C = c < C ? c : C; }
+                                                           int64_t pairs, int k, int E, int64_t C, int32_t* __restrict__ slot_src) {
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < pairs; p += (int64_t)gridDim.x * 256) {
     const int e = idx[p], l = loc[p];
-    if (l >= 0 && l < C && (unsigned)e < (unsigned)E) slot_src[(int64_t)e * stride + l] = (int32_t)(p / k);
+    if (l >= 0 && l < C && (unsigned)e < (unsigned)E) slot_src[(int64_t)e * C + l] = (int32_t)(p / k);
   }
 }
 
 hipError_t launch_slot_sources(const int32_t* idx, const int32_t* loc, int64_t T, int64_t E, int k, int64_t C,
-                               int32_t* slot_src, hipStream_t s, const int64_t* C_dev) {
+                               int32_t* slot_src, hipStream_t s) {
   const int64_t n = E * C, fb = ceil_div(n, 256 * 4);
   fill_i32_kernel<<<dim3((unsigned)(fb < 8192 ? fb : 8192)), dim3(256), 0, s>>>(slot_src, n, -1);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   const int64_t pairs = T * k, sb = ceil_div(pairs, 256);
-  slot_sources_kernel<<<dim3((unsigned)(sb < 8192 ? sb : 8192)), dim3(256), 0, s>>>(idx, loc, pairs, k, (int)E, C, C, C_dev, slot_src);
+  slot_sources_kernel<<<dim3((unsigned)(sb < 8192 ? sb : 8192)), dim3(256), 0, s>>>(idx, loc, pairs, k, (int)E, C, slot_src);
   return hipGetLastError();
 }
 
@@ -1145,152 +1141,178 @@ hipError_t launch_gate_logits_cosine(const void* x, const void* Wp, const float*
 // of decreasing priority, priority = the token's largest routing probability 1 / sum_e exp(l_e - l_max), computed in
 // fp64 and rounded to fp32 so that the order is a decision on an exactly comparable key; ties -> lower token.
 // ---------------------------------------------------------------------------------------------------------------
-// The sort key is the complement of the fp32 priority's bit pattern (priorities are positive, so the pattern orders like
-// the value): ascending keys = descending priority.  A stable sort keeps equal priorities in token order.
-__global__ __launch_bounds__(256) void bpr_key_kernel(const float* __restrict__ logits, int64_t T, int E,
-                                                      uint32_t* __restrict__ key, int32_t* __restrict__ val) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
-  const float* row = logits + t * E;
-  float mx = row[0];
-  for (int e = 1; e < E; ++e) mx = fmaxf(mx, row[e]);
-  double se = 0.0;
-  for (int e = 0; e < E; ++e) se += exp((double)row[e] - (double)mx);
-  const float prio = (float)(1.0 / se);
-  key[t] = ~__float_as_uint(prio);
-  val[t] = (int32_t)t;
+// The sort key ascends as the fp32 priority descends.  A priority lies in [1/512, 1] (its sum has one to 512 terms, the largest
+// of them 1), so 27 bits tell all of them apart; tokens with a NaN among their logits come first (negative NaNs before
+// positive ones, as their bit patterns order).  A stable sort keeps equal priorities in token order.
+//
+// Stable least-significant-digit radix sort of (key, token) pairs, three passes of 9 bits and four launches in all:
+//   bpr_key_kernel   : keys, and the first digit's histogram of every quarter tile
+//   bpr_sort_kernel  : one pass.  A block owns a tile of consecutive pairs; it adds up the histograms of all tiles (at most
+//                      128 x 512 counters) and of those before its own by itself instead of waiting for a scan, ranks its
+//                      pairs (a pair's place = start of its (digit, tile) run + the pairs of that digit before it in the
+//                      tile), moves them and counts the next digit of every pair into the histogram of the tile it lands in.
+// Integer sums only (the atomics' order does not matter); every result is a pure function of the keys.  A chain of small
+// launches, bound by their number and latency: digits of 11, 11 and 10 bits over tiles of 2048 pairs with a histogram, a
+// one-block scan and a scatter launch each took ten launches, 25088 tokens 120 us; now 34 us.
+constexpr int kSortBits = 9, kSortBins = 1 << kSortBits, kSortSub = 1024, kSortMaxTiles = 128;
+inline int64_t sort_subs(int64_t T) { return ceil_div(T, (int64_t)kSortSub * kSortMaxTiles); }   // tiles are this many times 1024 pairs
+
+__device__ __forceinline__ uint32_t bpr_key(float prio) {
+  const uint32_t b = __float_as_uint(prio);
+  const uint32_t one = 0x3F800000u, least = 0x3B000000u;            // 1 and 1/512
+  return b >= least && b <= one ? one - b + 2u : (b >> 31 ? 0u : 1u);
 }
 
-// Stable least-significant-digit radix sort of (key, token) pairs, three passes of 11, 11 and 10 bits.  A block owns a
-// tile of 2048 consecutive pairs.  Pass: per-tile digit histograms -> one exclusive scan over (digit, tile) -> stable
-// scatter (a pair's place = start of its (digit, tile) run + the number of pairs of that digit before it in the tile).
-// Integer arithmetic only; every result is a pure function of the keys.
-constexpr int kSortTile = 2048, kSortBins = 2048;
-
-__global__ __launch_bounds__(256) void radix_hist_kernel(const uint32_t* __restrict__ key, int64_t n, int shift, int bins, int tiles,
-                                                         uint32_t* __restrict__ hist) {
+// A block owns subs x 256 consecutive tokens (a quarter of a tile).  hist0[block][digit] is written whole; hist1 and hist2
+// ([tiles][digits], `clear` counters in all) are cleared for the atomics of the passes.
+template <bool VEC4>
+__global__ __launch_bounds__(256) void bpr_key_kernel(const float* __restrict__ logits, int64_t T, int E, int subs,
+                                                      uint32_t* __restrict__ key, int32_t* __restrict__ val,
+                                                      uint32_t* __restrict__ hist0, uint32_t* __restrict__ hist12, int64_t clear) {
   __shared__ uint32_t h[kSortBins];
-  for (int i = threadIdx.x; i < bins; i += 256) h[i] = 0;
+  for (int i = threadIdx.x; i < kSortBins; i += 256) h[i] = 0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < clear; i += (int64_t)gridDim.x * 256) hist12[i] = 0;
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
-  for (int i = threadIdx.x; i < kSortTile; i += 256)
-    if (base + i < n) atomicAdd(&h[(key[base + i] >> shift) & (bins - 1)], 1u);
-  __syncthreads();
-  for (int i = threadIdx.x; i < bins; i += 256) hist[(int64_t)i * tiles + blockIdx.x] = h[i];
-}
-
-// exclusive scan of hist[0 .. m) in place, one block (the array holds bins x tiles counters: small next to the keys), 8192
-// counters per round: eight consecutive ones per thread, a shuffle scan inside each wave, the 16 wave totals through LDS
-__global__ __launch_bounds__(1024) void radix_scan_kernel(uint32_t* __restrict__ hist, int64_t m) {
-  __shared__ uint32_t wave_tot[16];
-  __shared__ uint32_t carry_s;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (threadIdx.x == 0) carry_s = 0;
-  __syncthreads();
-  for (int64_t r0 = 0; r0 < m; r0 += 8192) {
-    const int64_t start = r0 + (int64_t)threadIdx.x * 8;
-    uint32_t v[8], sum = 0;
-    if (start + 8 <= m) {                                // the array is 256-byte aligned and start a multiple of 8
-      const uint4 a = *reinterpret_cast<const uint4*>(hist + start), b = *reinterpret_cast<const uint4*>(hist + start + 4);
-      v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  for (int q = 0; q < subs; ++q) {
+    const int64_t t = ((int64_t)blockIdx.x * subs + q) * 256 + threadIdx.x;
+    if (t >= T) break;
+    const float* row = logits + t * E;
+    float mx = row[0];
+    double se = 0.0;
+    if (VEC4) {                                                     // rows are 16-byte aligned; the same sums in the same order
+#pragma unroll 4
+      for (int e = 0; e < E; e += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(row + e);
+        mx = fmaxf(fmaxf(fmaxf(fmaxf(mx, v.x), v.y), v.z), v.w);
+      }
+#pragma unroll 4
+      for (int e = 0; e < E; e += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(row + e);
+        se += exp((double)v.x - (double)mx);
+        se += exp((double)v.y - (double)mx);
+        se += exp((double)v.z - (double)mx);
+        se += exp((double)v.w - (double)mx);
+      }
     } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = start + i < m ? hist[start + i] : 0u;
+      for (int e = 1; e < E; ++e) mx = fmaxf(mx, row[e]);
+      for (int e = 0; e < E; ++e) se += exp((double)row[e] - (double)mx);
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) sum += v[i];
-    uint32_t inc = sum;                                  // inclusive scan of the sums over the wave
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t t = __shfl_up(inc, d, 64);
-      if (lane >= d) inc += t;
-    }
-    if (lane == 63) wave_tot[wave] = inc;
-    __syncthreads();
-    uint32_t run = carry_s + inc - sum;
-    for (int w = 0; w < wave; ++w) run += wave_tot[w];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (start + i < m) hist[start + i] = run;
-      run += v[i];
-    }
-    __syncthreads();
-    if (threadIdx.x == 1023) carry_s = run;               // the last thread's running sum = everything so far
-    __syncthreads();
+    const uint32_t k = bpr_key((float)(1.0 / se));
+    key[t] = k;
+    val[t] = (int32_t)t;
+    atomicAdd(&h[k & (kSortBins - 1)], 1u);
   }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kSortBins; i += 256) hist0[(int64_t)blockIdx.x * kSortBins + i] = h[i];
 }
 
-__global__ __launch_bounds__(256) void radix_scatter_kernel(const uint32_t* __restrict__ key_in, const int32_t* __restrict__ val_in,
-                                                            int64_t n, int shift, int bins, int tiles,
-                                                            const uint32_t* __restrict__ offsets, uint32_t* __restrict__ key_out,
-                                                            int32_t* __restrict__ val_out) {
-  __shared__ uint32_t before[kSortBins];                  // pairs of each digit in the tile's earlier sub-tiles
-  __shared__ uint16_t cnt[4][kSortBins];                  // pairs of each digit in each wave of the current sub-tile
+// hist: [rows][digits] of this pass, `rows_per_tile` rows to a tile.  hist_next (optional): [tiles][digits] of the next digit.
+__global__ __launch_bounds__(1024) void bpr_sort_kernel(const uint32_t* __restrict__ key_in, const int32_t* __restrict__ val_in,
+                                                        int64_t n, int subs, int shift, const uint32_t* __restrict__ hist, int rows,
+                                                        int rows_per_tile, uint32_t* __restrict__ hist_next,
+                                                        uint32_t* __restrict__ key_out, int32_t* __restrict__ val_out) {
+  constexpr int NW = 16;
+  __shared__ uint32_t start[kSortBins];                             // where this tile's run of a digit begins
+  __shared__ uint32_t half_all[kSortBins], half_before[kSortBins], wave_tot[8];
+  __shared__ uint16_t cnt[NW][kSortBins];                           // pairs of each digit in each wave, then in the waves before it
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int i = threadIdx.x; i < bins; i += 256) { before[i] = 0; cnt[0][i] = 0; cnt[1][i] = 0; cnt[2][i] = 0; cnt[3][i] = 0; }
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
-  const int nbits = bins == 2048 ? 11 : 10;
-  for (int sub = 0; sub < kSortTile / 256; ++sub) {      // sub-tiles in order; within one: wave by wave, lane by lane
-    const int64_t i = base + sub * 256 + threadIdx.x;
+  const int d_own = threadIdx.x & (kSortBins - 1), half = threadIdx.x >> kSortBits;
+  {                                                                 // totals of a digit: even rows by one half of the block, odd by the other
+    const int first = blockIdx.x * rows_per_tile;
+    uint32_t all = 0, before = 0;
+#pragma unroll 8
+    for (int r = half; r < rows; r += 2) {
+      const uint32_t c = hist[(int64_t)r * kSortBins + d_own];
+      all += c;
+      before += r < first ? c : 0u;
+    }
+    if (half == 1) { half_all[d_own] = all; half_before[d_own] = before; }
+    __syncthreads();
+    uint32_t inc = 0;
+    if (half == 0) {                                                // waves 0 .. 7: scan over the digits
+      all += half_all[d_own];
+      before += half_before[d_own];
+      inc = all;
+#pragma unroll
+      for (int s = 1; s < 64; s <<= 1) {
+        const uint32_t v = __shfl_up(inc, s, 64);
+        if (lane >= s) inc += v;
+      }
+      if (lane == 63) wave_tot[wave] = inc;
+    }
+    __syncthreads();
+    if (half == 0) {
+      uint32_t base = inc - all + before;
+      for (int w = 0; w < wave; ++w) base += wave_tot[w];
+      start[d_own] = base;
+    }
+  }
+  const int64_t tile_pairs = (int64_t)subs * kSortSub;
+  for (int q = 0; q < subs; ++q) {                                  // 1024 pairs at a time, in order
+    for (int i = threadIdx.x; i < NW * kSortBins / 2; i += 1024) reinterpret_cast<uint32_t*>(&cnt[0][0])[i] = 0;
+    __syncthreads();
+    const int64_t i = blockIdx.x * tile_pairs + (int64_t)q * kSortSub + threadIdx.x;
     const bool live = i < n;
     const uint32_t k = live ? key_in[i] : 0u;
     const int32_t v = live ? val_in[i] : 0;
-    const int d = (int)((k >> shift) & (uint32_t)(bins - 1));
+    const int d = (int)((k >> shift) & (uint32_t)(kSortBins - 1));
     // lanes of this wave with the same digit: intersect, bit by bit, the ballots that agree with this lane's bit
     unsigned long long peers = __ballot(live);
-    for (int bit = 0; bit < nbits; ++bit) {
+#pragma unroll
+    for (int bit = 0; bit < kSortBits; ++bit) {
       const unsigned long long set = __ballot((d >> bit) & 1);
       peers &= ((d >> bit) & 1) ? set : ~set;
     }
     const int rank_in_wave = __popcll(peers & ((1ull << lane) - 1ull));
     if (live && rank_in_wave == 0) cnt[wave][d] = (uint16_t)__popcll(peers);   // the group's first lane reports its size
     __syncthreads();
+    uint32_t sum = 0;
+    if (half == 0) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const uint32_t c = cnt[w][d_own];
+        cnt[w][d_own] = (uint16_t)sum;
+        sum += c;
+      }
+    }
+    __syncthreads();
     if (live) {
-      uint32_t r = before[d] + rank_in_wave;
-      for (int w = 0; w < wave; ++w) r += cnt[w][d];
-      const int64_t dst = (int64_t)offsets[(int64_t)d * tiles + blockIdx.x] + r;
+      const uint32_t dst = start[d] + cnt[wave][d] + rank_in_wave;
       key_out[dst] = k;
       val_out[dst] = v;
+      if (hist_next) atomicAdd(&hist_next[(int64_t)(dst / (uint32_t)tile_pairs) * kSortBins + ((k >> (shift + kSortBits)) & (kSortBins - 1))], 1u);
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < bins; q += 256) {
-      before[q] += (uint32_t)cnt[0][q] + cnt[1][q] + cnt[2][q] + cnt[3][q];
-      cnt[0][q] = 0; cnt[1][q] = 0; cnt[2][q] = 0; cnt[3][q] = 0;
-    }
-    __syncthreads();
+    if (half == 0) start[d_own] += sum;                             // read again only behind the next barrier
   }
 }
 
 size_t bpr_order_workspace_bytes(int64_t T) {
-  const int64_t tiles = ceil_div(T, kSortTile);
-  return 4 * align_up((size_t)T * 4, 256) + align_up((size_t)kSortBins * tiles * 4, 256);
+  const int64_t subs = sort_subs(T);
+  const size_t rows0 = (size_t)ceil_div(T, 256 * subs), tiles = (size_t)ceil_div(T, kSortSub * subs);
+  return 4 * align_up((size_t)T * 4, 256) + (rows0 + 2 * tiles) * kSortBins * 4;
 }
 
 // perm[i] = the token that arrives i-th under batch prioritized routing; returns it through *perm (a piece of ws)
 hipError_t launch_bpr_order(const float* logits, int64_t T, int64_t E, void* ws, const int32_t** perm, hipStream_t s) {
-  const int64_t tiles = ceil_div(T, kSortTile);
+  const int64_t subs = sort_subs(T);
+  const int rows0 = (int)ceil_div(T, 256 * subs), tiles = (int)ceil_div(T, kSortSub * subs);
   const size_t piece = align_up((size_t)T * 4, 256);
   char* base = (char*)ws;
   uint32_t* key[2] = {(uint32_t*)base, (uint32_t*)(base + piece)};
   int32_t* val[2] = {(int32_t*)(base + 2 * piece), (int32_t*)(base + 3 * piece)};
-  uint32_t* hist = (uint32_t*)(base + 4 * piece);
-  bpr_key_kernel<<<dim3((unsigned)ceil_div(T, 256)), dim3(256), 0, s>>>(logits, T, (int)E, key[0], val[0]);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  const int shifts[3] = {0, 11, 22}, binsv[3] = {2048, 2048, 1024};
-  int cur = 0;
-  for (int p = 0; p < 3; ++p) {
-    radix_hist_kernel<<<dim3((unsigned)tiles), dim3(256), 0, s>>>(key[cur], T, shifts[p], binsv[p], (int)tiles, hist);
-    radix_scan_kernel<<<dim3(1), dim3(1024), 0, s>>>(hist, (int64_t)binsv[p] * tiles);
-    radix_scatter_kernel<<<dim3((unsigned)tiles), dim3(256), 0, s>>>(key[cur], val[cur], T, shifts[p], binsv[p], (int)tiles, hist,
-                                                                     key[cur ^ 1], val[cur ^ 1]);
-    err = hipGetLastError();
-    if (err != hipSuccess) return err;
-    cur ^= 1;
-  }
-  *perm = val[cur];
-  return hipSuccess;
+  uint32_t* hist0 = (uint32_t*)(base + 4 * piece);
+  uint32_t* hist1 = hist0 + (int64_t)rows0 * kSortBins;
+  uint32_t* hist2 = hist1 + (int64_t)tiles * kSortBins;
+  const int64_t clear = 2 * (int64_t)tiles * kSortBins;
+  if (E % 4 == 0) bpr_key_kernel<true><<<dim3((unsigned)rows0), dim3(256), 0, s>>>(logits, T, (int)E, (int)subs, key[0], val[0], hist0, hist1, clear);
+  else bpr_key_kernel<false><<<dim3((unsigned)rows0), dim3(256), 0, s>>>(logits, T, (int)E, (int)subs, key[0], val[0], hist0, hist1, clear);
+  const dim3 grid((unsigned)tiles), block(1024);
+  bpr_sort_kernel<<<grid, block, 0, s>>>(key[0], val[0], T, (int)subs, 0, hist0, rows0, 4, hist1, key[1], val[1]);
+  bpr_sort_kernel<<<grid, block, 0, s>>>(key[1], val[1], T, (int)subs, kSortBits, hist1, tiles, 1, hist2, key[0], val[0]);
+  bpr_sort_kernel<<<grid, block, 0, s>>>(key[0], val[0], T, (int)subs, 2 * kSortBits, hist2, tiles, 1, nullptr, key[1], val[1]);
+  *perm = val[1];
+  return hipGetLastError();
 }
 
 }  // namespace moe

@@ -99,6 +99,23 @@ def test_gate_topk_batch_prioritized(moe, T, E, k, f, normalize, quantum):
     assert np.array_equal(got["slot_src"].cpu().numpy(), O.slot_source(ref["idx"], ref["loc"], E, C))
 
 
+@pytest.mark.parametrize("T,E", [(255, 8), (1023, 8), (1024, 6), (1025, 512), (131072, 4), (131073, 4)])
+def test_gate_topk_batch_prioritized_tile_edges(moe, T, E):
+    """Around a sort tile, and around the count of tokens from which a tile is walked in several parts; equal logits give the
+    lowest priority there is, one dominating logit the highest, and a NaN comes before all."""
+    logits = synth.make_logits(T, E, seed=T, quantum=0.25)
+    logits[::5] = 0.0
+    logits[3::7, 0] = 200.0
+    C = O.capacity(T, E, 1, 0.5)
+    ref = O.route(logits, 1, C, 0, bpr=True)
+    got = moe.gate_topk(torch.from_numpy(logits).cuda(), 1, C, 0, bpr=True)
+    assert_routing_equal(got, ref, C, f"BPR T={T} E={E}")
+    first = torch.from_numpy(logits).cuda()
+    first[T // 2] = float("nan")
+    got = moe.gate_topk(first, 1, C, 0, bpr=True)
+    assert int(got["loc"][T // 2, 0]) == 0
+
+
 def test_gate_topk_batch_prioritized_many_tokens(moe):
     """More tokens than one sort tile many times over (and past 2^18): the prioritized order comes from a radix sort, whose
     place computations span several tiles and all three digit passes; quantised logits give long runs of equal priorities."""
