@@ -111,6 +111,8 @@ struct GateRepair {
   const float* bias;
   int64_t M, Mp;
 };
+// exact logits: a launch of so few tiles of 16 tokens x 16 experts that a block of 16 waves takes each
+inline bool gate_logits_few_tiles(int64_t T, int64_t E) { return T <= 8192 && E <= 8192 && ((T + 15) / 16) * ((E + 15) / 16) <= 512; }
 size_t gate_fast_workspace_bytes(int64_t T, int64_t M, int64_t E);
 GateFastWorkspace gate_fast_layout(void* ws, int64_t T, int64_t M, int64_t E);
 bool gate_logits_fast_supports(int dtype, int64_t T, int64_t M, int64_t E);

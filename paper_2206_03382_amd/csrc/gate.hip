@@ -13,9 +13,15 @@
 
 namespace moe {
 
-// token tiles (of 16) per wave for gates of at most 16 experts: 4 measured best on MI355X (2: +5 %, 1: +10 % time)
-constexpr int kNarrowGateTilesPerWave = 4;
 typedef __attribute__((ext_vector_type(4))) double f64x4;
+// gate_slots_kernel's limits: counters that every block adds up (16 per thread; at 12.5 k it took 18 us where scan and
+// assignment take 10 in two launches), and (expert, rank) pairs in LDS
+constexpr int kSlotsMaxCounters = 4096, kSlotsMaxPairs = 1024;
+// Blocks of 64 tokens from which wide gates decide with one lane per token.  Below, a token's lane group spreads a block's work
+// over more of the chip: 6000 tokens, 64 experts, top-4: 19 us against 23 (51 against 73 with near-tie repairs); 65536
+// tokens, top-2: 30 against 25.
+constexpr int kLaneTopkMinBlocks = 512;
+
 
 // ---------------------------------------------------------------------------------------------------------------
 // logits[t,e] = sum_m x[t,m] Wg[m,e] + bias[e], fp64 accumulate (v_mfma_f64_16x16x4_f64), one rounding to fp32.
@@ -24,216 +30,6 @@ typedef __attribute__((ext_vector_type(4))) double f64x4;
 // A lane keeps 8 consecutive x values (k = kq*8 .. kq*8+7 of a 32-wide chunk); MFMA step s uses k = kq*8+s for
 // both operands, so the chunk's 32 k-values are covered exactly once.
 // ---------------------------------------------------------------------------------------------------------------
-// Eight consecutive x values of one lane, kept raw while in flight and widened when used.
-template <typename XT> struct Raw8;
-template <> struct Raw8<float> {
-  float4 a, b;
-  __device__ __forceinline__ void load(const float* p) { a = *reinterpret_cast<const float4*>(p); b = *reinterpret_cast<const float4*>(p + 4); }
-  __device__ __forceinline__ void zero() { a = make_float4(0.f, 0.f, 0.f, 0.f); b = a; }
-  __device__ __forceinline__ void keep_if(uint32_t m) {            // m = all ones keeps the values, 0 makes them +0
-    a.x = __uint_as_float(__float_as_uint(a.x) & m); a.y = __uint_as_float(__float_as_uint(a.y) & m);
-    a.z = __uint_as_float(__float_as_uint(a.z) & m); a.w = __uint_as_float(__float_as_uint(a.w) & m);
-    b.x = __uint_as_float(__float_as_uint(b.x) & m); b.y = __uint_as_float(__float_as_uint(b.y) & m);
-    b.z = __uint_as_float(__float_as_uint(b.z) & m); b.w = __uint_as_float(__float_as_uint(b.w) & m);
-  }
-  __device__ __forceinline__ void widen(float (&v)[8]) const {
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-  }
-};
-template <> struct Raw8<uint16_t> {
-  uint4 a;
-  __device__ __forceinline__ void load(const uint16_t* p) { a = *reinterpret_cast<const uint4*>(p); }
-  __device__ __forceinline__ void zero() { a = make_uint4(0, 0, 0, 0); }
-  __device__ __forceinline__ void keep_if(uint32_t m) { a.x &= m; a.y &= m; a.z &= m; a.w &= m; }
-  __device__ __forceinline__ void widen(float (&v)[8]) const {
-    const uint32_t w[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      v[2 * i] = __uint_as_float(w[i] << 16);
-      v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-};
-
-template <typename XT, int NT, int KS, int TW, bool VECW>
-__global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
-                                                          const float* __restrict__ bias, int64_t T, int M, int Mq, int E,
-                                                          float* __restrict__ logits) {
-  // The block's four waves are 4/KS token groups times KS splits of the reduction; a wave owns TW tiles of 16 tokens.
-  // Split ks owns k in [ks*Mq, (ks+1)*Mq) (Mq a multiple of BKW); the partial sums are added in split order at the
-  // end.  Narrow gates (few experts) have one accumulator tile per 16 tokens, a serial chain of dependent MFMAs: TW
-  // token tiles per wave and several waves per SIMD give the matrix pipe independent chains to interleave, and the
-  // TW tiles share every Wg operand read.
-  // Wg is staged through LDS as fp64, BKW rows per split at a time (32 KB in all whatever NT is).  x goes straight
-  // from global memory to registers through a ring of PF passes (PF * 32 k) per lane and token tile.
-  constexpr int EN = NT * 16, ENP = EN + 1, BKW = 4096 / (KS * EN), PF = 8 / TW, TG = 4 / KS;
-  static_assert(BKW % 32 == 0 && ((PF * 32) % BKW == 0 || BKW % (PF * 32) == 0), "LDS chunks must hold whole passes");
-  // rows are padded by one double: the 64-byte pieces that the staging threads write and the 4 rows x 16 columns that
-  // an MFMA operand read gathers then both spread evenly over the LDS banks
-  __shared__ double wlds[KS * BKW * ENP];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int ks = wave % KS, tg = wave / KS;
-  const int m = lane & 15, kq = lane >> 4;
-  const int64_t t0 = ((int64_t)blockIdx.x * TG + tg) * (16 * TW);
-  const int kfirst = ks * Mq;                                       // first k of this wave's split
-  const XT* xrow[TW];
-#pragma unroll
-  for (int w = 0; w < TW; ++w) {
-    const int64_t t = t0 + w * 16 + m;
-    xrow[w] = x + (t < T ? t : T - 1) * (int64_t)M + kfirst + kq * 8;
-  }
-  f64x4 acc[TW][NT];
-#pragma unroll
-  for (int w = 0; w < TW; ++w)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[w][nt] = f64x4{0.0, 0.0, 0.0, 0.0};
-
-  // this thread's part of a Wg chunk (rows kl .. kl+BKW-1 of every split), fetched one chunk ahead so that its latency
-  // hides behind the MFMAs.  VECW (E a multiple of the 16-byte vector, Wg 16-byte aligned): 16-byte pieces of a row;
-  // otherwise single elements.
-  constexpr int VEC = VECW ? 16 / (int)sizeof(XT) : 1;
-  constexpr int WPT = KS * BKW * EN / (256 * VEC);
-  constexpr int WORDS = VECW ? 4 : 1;                  // raw 32-bit words of one piece
-  static_assert(WPT >= 1, "every thread stages at least one piece");
-  uint32_t wraw[WPT][WORDS];
-  // branch-free (dead pieces re-read the start of Wg and are masked to zero): a load inside a divergent branch would be
-  // waited for on the spot, together with every x load in flight
-  auto wg_fetch = [&](int kl) {
-#pragma unroll
-    for (int i = 0; i < WPT; ++i) {
-      const int id = (threadIdx.x + i * 256) * VEC, q = id / (BKW * EN), r = (id / EN) % BKW, e = id % EN;
-      const int kk = q * Mq + kl + r;
-      const bool live = kl + r < Mq && kk < M && e < E;
-      const XT* src = Wg + (live ? (int64_t)kk * E + e : 0);
-      const uint32_t keep = live ? 0xffffffffu : 0u;
-      if (VECW) {
-        const uint4 v = *reinterpret_cast<const uint4*>(src);
-        wraw[i][0] = v.x & keep; wraw[i][WORDS > 1 ? 1 : 0] = v.y & keep; wraw[i][WORDS > 2 ? 2 : 0] = v.z & keep;
-        wraw[i][WORDS > 3 ? 3 : 0] = v.w & keep;
-      } else if (sizeof(XT) == 2) {
-        wraw[i][0] = (uint32_t)*reinterpret_cast<const uint16_t*>(src) & keep;
-      } else {
-        wraw[i][0] = *reinterpret_cast<const uint32_t*>(src) & keep;
-      }
-    }
-  };
-  auto wg_stage = [&]() {
-#pragma unroll
-    for (int i = 0; i < WPT; ++i) {
-      const int id = (threadIdx.x + i * 256) * VEC;
-      double* dst = wlds + (id / EN) * ENP + id % EN;
-      if (sizeof(XT) == 2) {                           // bf16: even element in the low half of a word
-        if (VECW) {
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            dst[2 * u] = (double)__uint_as_float(wraw[i][u % WORDS] << 16);
-            dst[2 * u + 1] = (double)__uint_as_float(wraw[i][u % WORDS] & 0xffff0000u);
-          }
-        } else dst[0] = (double)__uint_as_float(wraw[i][0] << 16);
-      } else {
-#pragma unroll
-        for (int u = 0; u < VEC; ++u) dst[u] = (double)__uint_as_float(wraw[i][u % WORDS]);
-      }
-    }
-  };
-  wg_fetch(0);
-
-  Raw8<XT> ring[TW][PF];
-#pragma unroll
-  for (int j = 0; j < PF; ++j)
-#pragma unroll
-    for (int w = 0; w < TW; ++w) {
-      const bool live = j * 32 + kq * 8 < Mq && kfirst + j * 32 + kq * 8 < M;
-      ring[w][j].load(xrow[w] + (live ? j * 32 : -(kfirst + kq * 8)));       // dead lanes re-read the row's start
-      ring[w][j].keep_if(live ? 0xffffffffu : 0u);
-    }
-
-  const double* wmine = wlds + ks * BKW * ENP;
-  for (int kbase = 0; kbase < Mq; kbase += PF * 32) {
-#pragma unroll
-    for (int j = 0; j < PF; ++j) {
-      const int kl = kbase + j * 32;                   // this pass covers kl .. kl+31 of the split (uniform across the block)
-      if (kl >= Mq) break;
-      if (kl % BKW == 0) {                             // refill the LDS chunk of Wg that starts here
-        __syncthreads();
-        wg_stage();
-        __syncthreads();
-        wg_fetch(kl + BKW);
-      }
-      float xv[TW][8];
-      const int kn = kl + PF * 32 + kq * 8;            // refill the ring slot with the pass PF ahead
-#pragma unroll
-      for (int w = 0; w < TW; ++w) {
-        ring[w][j].widen(xv[w]);
-        // branch-free (dead lanes re-read the row's start), so that the compiler can count the loads in flight and
-        // the wait for the next Wg chunk does not drain this prefetch
-        const bool live = kn < Mq && kfirst + kn < M;
-        ring[w][j].load(xrow[w] + (live ? kl + PF * 32 : -(kfirst + kq * 8)));
-        ring[w][j].keep_if(live ? 0xffffffffu : 0u);
-      }
-      const int r0 = kl % BKW + kq * 8;
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          const double b = wmine[(r0 + s) * ENP + nt * 16 + m];
-#pragma unroll
-          for (int w = 0; w < TW; ++w) acc[w][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xv[w][s], b, acc[w][nt], 0, 0, 0);
-        }
-      }
-    }
-  }
-  if (KS > 1) {                                        // partial sums of splits 1 .. KS-1 go through LDS to split 0
-    double* red = wlds;                                // [KS-1][TG][TW][NT][64 lanes][4]
-    static_assert((KS - 1) * TG * TW * NT * 256 <= KS * BKW * ENP, "the partial sums must fit into the staging buffer");
-    __syncthreads();
-    if (ks > 0) {
-#pragma unroll
-      for (int w = 0; w < TW; ++w)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) red[(((((ks - 1) * TG + tg) * TW + w) * NT + nt) * 64 + lane) * 4 + v] = acc[w][nt][v];
-    }
-    __syncthreads();
-    if (ks > 0) return;
-#pragma unroll
-    for (int q = 1; q < KS; ++q)
-#pragma unroll
-      for (int w = 0; w < TW; ++w)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) acc[w][nt][v] += red[(((((q - 1) * TG + tg) * TW + w) * NT + nt) * 64 + lane) * 4 + v];
-  }
-#pragma unroll
-  for (int w = 0; w < TW; ++w)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      const int e = nt * 16 + m;
-      if (e >= E) continue;
-      const double be = bias ? (double)bias[e] : 0.0;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int64_t t = t0 + w * 16 + 4 * v + kq;
-        if (t < T) logits[t * E + e] = (float)(acc[w][nt][v] + be);
-      }
-    }
-}
-
-// Wide gates (more than 64 experts; the cosine router's projection): a block's 2 x 2 waves own 32 tokens x 128 experts, a wave
-// 16 x 64 as four accumulator tiles.  Both operands go through LDS as fp32, 32 k at a time (the next 32 k are fetched to
-// registers meanwhile), and are widened on the way out: per 32 k a wave issues 32 matrix instructions of 64 cycles against
-// 34 LDS reads and 40 conversions, which hide behind them, and 21 KB of LDS let seven blocks share a unit and cover each
-// other's staging.  What binds is the fp64 matrix pipe.  Blocks are small because the count of blocks per unit is what
-// divides unevenly; all expert blocks go in one launch.  Replaced four waves of 16 tokens x 128 experts on fp64 weights in LDS,
-// one launch per 128 experts: 25088 tokens, M = 768, 256 columns
-// 275 -> 211 us (47 TFLOP/s; the fp64 matrix pipe alone sustains 67). Seven blocks per unit need 72 registers: at 96 the blocks past
-// the fifth of a unit run by themselves at the end, 229 us.
-// LDS rows: 36 floats per token (16 rows x 4 groups of a ds_read_b128 spread over all banks), 130 per k of the weights (the
-// four k of an operand read lie 16 banks apart).
-constexpr int kWideTokens = 32, kWideExperts = 128, kWideK = 32, kWideLdx = 36, kWideLdw = 130;
-
 // N consecutive values of a row as floats, kept raw while in flight
 template <typename XT, int N> struct RawN {
   uint32_t w[N * (int)sizeof(XT) / 4];
@@ -262,6 +58,122 @@ template <typename XT, int N> struct RawN {
     else w[i >> 1] = (i & 1) ? (w[i >> 1] & 0xffffu) | ((uint32_t)v << 16) : (uint32_t)v;
   }
 };
+
+// Gates of up to 64 experts, and few tokens whatever the gate: a wave owns TW tiles of 16 tokens x NT tiles of 16 experts over
+// one of KS parts of the reduction, a block the KS parts of its tiles, whose sums are added in part order through LDS.  Both
+// operands come straight from global memory, two passes of 32 k ahead in registers: x once in 16-byte pieces, Wg (which every
+// wave reads, so from the caches) element by element in the layout the instruction wants.  No barrier and no LDS in the
+// loop, so waves drift apart and cover each other's loads.  Binds: the fp64 matrix pipe (16 columns are computed whatever E
+// is) and beside it the element loads of Wg; for few tokens the chain of M / (32 KS) passes, hence KS = 16 there.
+// Measured against four waves on fp64 weights staged through LDS, in a captured graph with its launch: 512 tokens, M = 1024,
+// 64 experts, fp32 53 -> 17 us; 64 tokens, M = 4096, 64 experts 180 -> 20; 16384 tokens, M = 2048, 8 experts 41 -> 35.
+template <typename XT, int NT, int KS, int TW>
+__global__ __launch_bounds__(64 * KS) void gate_logits_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
+                                                              const float* __restrict__ bias, int64_t T, int M, int E,
+                                                              float* __restrict__ logits) {
+  constexpr int PF = 2;
+  __shared__ double red[KS - 1][TW * NT][4][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, kq = lane >> 4;
+  const int64_t t0 = (int64_t)blockIdx.x * (16 * TW);
+  const int e0 = blockIdx.y * (16 * NT);
+  const int passes = (M + 31) / 32, per = (passes + KS - 1) / KS;
+  const int p0 = wave * per, p1 = p0 + per < passes ? p0 + per : passes;   // this wave's passes (possibly none)
+  const XT* xrow[TW];
+#pragma unroll
+  for (int w = 0; w < TW; ++w) {
+    const int64_t t = t0 + w * 16 + r;
+    xrow[w] = x + (t < T ? t : T - 1) * (int64_t)M;
+  }
+  int ecol[NT];                                                     // columns past the last repeat it and are never stored
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) ecol[nt] = e0 + nt * 16 + r < E ? e0 + nt * 16 + r : E - 1;
+  RawN<XT, 8> xr[PF][TW];
+  XT wr[PF][NT][8];
+  auto fetch = [&](int slot, int p) __attribute__((always_inline)) { // k past the row's end: the row's start is read and zeroed
+    const int k = p * 32 + kq * 8;
+    const bool live = k < M;
+#pragma unroll
+    for (int w = 0; w < TW; ++w) {
+      xr[slot][w].load_vec(xrow[w] + (live ? k : 0));
+      xr[slot][w].keep_if(live);
+    }
+    const XT* wp = Wg + (int64_t)(live ? k : 0) * E;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const XT v = wp[(int64_t)u * E + ecol[nt]];
+        wr[slot][nt][u] = live ? v : (XT)0;
+      }
+  };
+  f64x4 acc[TW][NT];
+#pragma unroll
+  for (int w = 0; w < TW; ++w)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[w][nt] = f64x4{0.0, 0.0, 0.0, 0.0};
+  auto compute = [&](int slot) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const double b = (double)load_as_f32<XT>(&wr[slot][nt][u]);
+#pragma unroll
+        for (int w = 0; w < TW; ++w) acc[w][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xr[slot][w].get(u), b, acc[w][nt], 0, 0, 0);
+      }
+  };
+#pragma unroll
+  for (int q = 0; q < PF; ++q)
+    if (p0 + q < p1) fetch(q, p0 + q);
+  for (int p = p0; p < p1; p += PF) {
+#pragma unroll
+    for (int q = 0; q < PF; ++q) {
+      if (p + q >= p1) break;
+      compute(q);
+      if (p + q + PF < p1) fetch(q, p + q + PF);
+    }
+  }
+  if (wave > 0) {
+#pragma unroll
+    for (int w = 0; w < TW; ++w)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[wave - 1][w * NT + nt][v][lane] = acc[w][nt][v];
+  }
+  __syncthreads();
+  if (wave > 0) return;
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const int e = e0 + nt * 16 + r;
+    const double be = bias && e < E ? (double)bias[e] : 0.0;
+#pragma unroll
+    for (int w = 0; w < TW; ++w) {
+#pragma unroll
+      for (int q = 1; q < KS; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[w][nt][v] += red[q - 1][w * NT + nt][v][lane];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int64_t t = t0 + w * 16 + 4 * v + kq;
+        if (t < T && e < E) logits[t * E + e] = (float)(acc[w][nt][v] + be);
+      }
+    }
+  }
+}
+
+// Wide gates (more than 64 experts; the cosine router's projection): a block's 2 x 2 waves own 32 tokens x 128 experts, a wave
+// 16 x 64 as four accumulator tiles.  Both operands go through LDS as fp32, 32 k at a time (the next 32 k are fetched to
+// registers meanwhile), and are widened on the way out: per 32 k a wave issues 32 matrix instructions of 64 cycles against
+// 34 LDS reads and 40 conversions, which hide behind them, and 21 KB of LDS let seven blocks share a unit and cover each
+// other's staging.  What binds is the fp64 matrix pipe.  Blocks are small because the count of blocks per unit is what
+// divides unevenly; all expert blocks go in one launch.  Replaced four waves of 16 tokens x 128 experts on fp64 weights in LDS,
+// one launch per 128 experts: 25088 tokens, M = 768, 256 columns
+// 275 -> 211 us (47 TFLOP/s; the fp64 matrix pipe alone sustains 67). Seven blocks per unit need 72 registers: at 96 the blocks past
+// the fifth of a unit run by themselves at the end, 229 us.
+// LDS rows: 36 floats per token (16 rows x 4 groups of a ds_read_b128 spread over all banks), 130 per k of the weights (the
+// four k of an operand read lie 16 banks apart).
+constexpr int kWideTokens = 32, kWideExperts = 128, kWideK = 32, kWideLdx = 36, kWideLdw = 130;
 
 template <typename XT, bool VECW>
 __global__ __launch_bounds__(256, VECW && sizeof(XT) == 2 ? 7 : 4) void gate_logits_wide_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
@@ -341,29 +253,37 @@ __global__ __launch_bounds__(256, VECW && sizeof(XT) == 2 ? 7 : 4) void gate_log
 template <typename XT, int NT, int KS, int TW>
 static void launch_gate_logits_one(const XT* x, const XT* Wg, const float* bias, int64_t T, int64_t M, int64_t E,
                                    float* logits, hipStream_t s) {
-  constexpr int BKW = 4096 / (KS * NT * 16);
-  const int Mq = (int)(ceil_div(ceil_div(M, KS), BKW) * BKW);       // k per split, a whole number of LDS chunks
-  const dim3 grid((unsigned)ceil_div(T, 16 * TW * (4 / KS))), block(256);
-  constexpr int VEC = 16 / (int)sizeof(XT);
-  const bool vecw = E % VEC == 0 && ((uintptr_t)Wg & 15) == 0;
-  if (vecw) gate_logits_kernel<XT, NT, KS, TW, true><<<grid, block, 0, s>>>(x, Wg, bias, T, (int)M, Mq, (int)E, logits);
-  else gate_logits_kernel<XT, NT, KS, TW, false><<<grid, block, 0, s>>>(x, Wg, bias, T, (int)M, Mq, (int)E, logits);
+  const dim3 grid((unsigned)ceil_div(T, 16 * TW), (unsigned)ceil_div(E, 16 * NT));
+  gate_logits_kernel<XT, NT, KS, TW><<<grid, dim3(64 * KS), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, logits);
 }
 
 template <typename XT>
 static hipError_t launch_gate_logits_t(const XT* x, const XT* Wg, const float* bias, int64_t T, int64_t M, int64_t E,
                                        float* logits, hipStream_t s) {
-  if (E > 64) {
+  // few tiles of 16 tokens x 16 experts: one to a block of 16 waves, whatever E is.  At 512 tiles as fast as four waves with
+  // all of a gate's experts, below up to three times as fast (64 tokens, M = 4096, 64 experts: 20 us against 67).
+  if (gate_logits_few_tiles(T, E)) {
+    launch_gate_logits_one<XT, 1, 16, 1>(x, Wg, bias, T, M, E, logits, s);
+  } else if (E > 64) {
     const int64_t expert_blocks = ceil_div(E, kWideExperts), blocks = ceil_div(T, kWideTokens) * expert_blocks;
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
     if (E % 8 == 0 && ((uintptr_t)Wg & 15) == 0)
       gate_logits_wide_kernel<XT, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, (int)expert_blocks, logits);
     else
       gate_logits_wide_kernel<XT, false><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, (int)expert_blocks, logits);
+  } else {
+    // two token tiles per wave halve the reads of Wg, for many tokens (65536 tokens, M = 2048, 8 experts: 100 -> 94 us; 16384: no gain)
+    const bool many = T >= 32768;
+    if (E <= 16) {
+      if (many) launch_gate_logits_one<XT, 1, 4, 2>(x, Wg, bias, T, M, E, logits, s);
+      else launch_gate_logits_one<XT, 1, 4, 1>(x, Wg, bias, T, M, E, logits, s);
+    } else if (E <= 32) {
+      launch_gate_logits_one<XT, 2, 4, 1>(x, Wg, bias, T, M, E, logits, s);
+    } else {
+      if (many) launch_gate_logits_one<XT, 4, 4, 2>(x, Wg, bias, T, M, E, logits, s);
+      else launch_gate_logits_one<XT, 4, 4, 1>(x, Wg, bias, T, M, E, logits, s);
+    }
   }
-  else if (E <= 16) launch_gate_logits_one<XT, 1, 4, kNarrowGateTilesPerWave>(x, Wg, bias, T, M, E, logits, s);
-  else if (E <= 32) launch_gate_logits_one<XT, 2, 4, 2>(x, Wg, bias, T, M, E, logits, s);
-  else launch_gate_logits_one<XT, 4, 2, 2>(x, Wg, bias, T, M, E, logits, s);
   return hipGetLastError();
 }
 
@@ -867,11 +787,23 @@ __global__ __launch_bounds__(256) void gate_scan_kernel(int32_t* __restrict__ bl
   }
 }
 
-// One wave per block of 64 tokens, one lane per token: position among the block's earlier tokens with the same
-// (rank, expert), found by grouping the lanes by expert with ballots (one round per distinct expert in the wave).
+// Number of lanes below this one whose token goes to the same expert: intersects, bit by bit of the expert's number, the
+// ballots that agree with this lane's bit.
+__device__ __forceinline__ int rank_among_lanes(int e, bool valid, int bits, int lane) {
+  unsigned long long peers = __ballot(valid);
+  for (int b = 0; b < bits; ++b) {
+    const bool mine = (e >> b) & 1;
+    const unsigned long long set = __ballot(mine);
+    peers &= mine ? set : ~set;
+  }
+  return __popcll(peers & ((1ull << lane) - 1ull));
+}
+
+// One wave per block of 64 tokens, one lane per token: scanned offset plus the position among the block's earlier tokens
+// with the same (rank, expert).
 __global__ __launch_bounds__(kGateTokensPerBlock) void gate_assign_kernel(const int32_t* __restrict__ idx,
                                                                           const int32_t* __restrict__ block_off, int64_t T,
-                                                                          int E, int k, int64_t C, int NB,
+                                                                          int E, int bits, int k, int64_t C, int NB,
                                                                           int32_t* __restrict__ loc,
                                                                           int32_t* __restrict__ slot_src,
                                                                           const int32_t* __restrict__ perm) {
@@ -880,20 +812,61 @@ __global__ __launch_bounds__(kGateTokensPerBlock) void gate_assign_kernel(const 
   const bool valid = tv < T;
   int64_t t = tv;
   if (valid && perm) { const int32_t p = perm[tv]; t = ((uint32_t)p < (uint64_t)T) ? p : tv; }
-  const unsigned long long below = (1ull << lane) - 1ull;
   for (int j = 0; j < k; ++j) {
-    const int e = valid ? idx[t * k + j] : -1;
-    unsigned long long remaining = __ballot(valid);
-    int r = 0;
-    while (remaining) {
-      const int leader = __ffsll((long long)remaining) - 1;
-      const int e0 = __shfl(e, leader);
-      const unsigned long long same = __ballot(valid && e == e0);
-      if (e == e0) r = __popcll(same & below);
-      remaining &= ~same;
-    }
+    const int e = valid ? idx[t * k + j] : 0;
+    const int r = rank_among_lanes(e, valid, bits, lane);
     if (valid) {
       const int l = block_off[((int64_t)e * k + j) * NB + blockIdx.x] + r;
+      loc[t * k + j] = l;
+      if (slot_src && l < C) slot_src[(int64_t)e * C + l] = (int32_t)t;
+    }
+  }
+}
+
+// Scan and assignment in one launch, for counters few enough that every block adds them up by itself: `before` of an (expert,
+// rank) = all arrivals at lower ranks + those of this rank in earlier blocks.  Saves a launch and its wait where those are
+// what the stage costs: 2 to 4 us of a small gate's 15.
+__global__ __launch_bounds__(256) void gate_slots_kernel(const int32_t* __restrict__ idx, const int32_t* __restrict__ block_counts,
+                                                         int64_t T, int E, int bits, int k, int64_t C, int NB,
+                                                         int32_t* __restrict__ counts, int32_t* __restrict__ loc,
+                                                         int32_t* __restrict__ slot_src, int mark_unfilled,
+                                                         const int32_t* __restrict__ perm) {
+  __shared__ int all[kSlotsMaxPairs], before[kSlotsMaxPairs];
+  const int lane = threadIdx.x & 63, pairs = E * k;
+  for (int q = threadIdx.x; q < pairs; q += 256) { all[q] = 0; before[q] = 0; }
+  __syncthreads();
+#pragma unroll 4
+  for (int i = threadIdx.x; i < pairs * NB; i += 256) {             // integer sums: their order does not matter
+    const int c = block_counts[i], q = i / NB, b = i - q * NB;
+    if (c) {
+      atomicAdd(&all[q], c);
+      if (b < (int)blockIdx.x) atomicAdd(&before[q], c);
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < E; e += 256) {                      // ranks in order: exclusive sums over the lower ones
+    int run = 0;
+    for (int j = 0; j < k; ++j) { before[e * k + j] += run; run += all[e * k + j]; }
+    all[e * k] = run;                                               // the expert's arrivals
+    if (blockIdx.x == 0) counts[e] = run;
+  }
+  __syncthreads();
+  if (mark_unfilled && slot_src) {
+    for (int e = blockIdx.x; e < E; e += gridDim.x) {
+      const int64_t total = all[e * k], first = total < C ? total : C;
+      for (int64_t c = first + threadIdx.x; c < C; c += 256) slot_src[(int64_t)e * C + c] = -1;
+    }
+  }
+  if (threadIdx.x >= kGateTokensPerBlock) return;
+  const int64_t tv = (int64_t)blockIdx.x * kGateTokensPerBlock + lane;
+  const bool valid = tv < T;
+  int64_t t = tv;
+  if (valid && perm) { const int32_t p = perm[tv]; t = ((uint32_t)p < (uint64_t)T) ? p : tv; }
+  for (int j = 0; j < k; ++j) {
+    const int e = valid ? idx[t * k + j] : 0;
+    const int r = rank_among_lanes(e, valid, bits, lane);
+    if (valid) {
+      const int l = before[e * k + j] + r;
       loc[t * k + j] = l;
       if (slot_src && l < C) slot_src[(int64_t)e * C + l] = (int32_t)t;
     }
@@ -930,7 +903,7 @@ hipError_t launch_gate_topk(float* logits, int64_t T, int64_t E, int k, int64_t 
   } while (0)
   // wide gates with few choices: one lane per token (its LDS footprint, 4 waves x (8.25 KB + k E bytes), must fit 64 KB);
   // tokens in a caller-given order (perm) keep the lane-group kernel
-  const bool lane_kernel = !perm && E > 16 && k <= 32 && (size_t)k * E <= 7936;
+  const bool lane_kernel = !perm && NB >= kLaneTopkMinBlocks && E > 16 && k <= 32 && (size_t)k * E <= 7936;
   if (lane_kernel) {
     if (k <= 1) MOE_TOPK_LANE(1); else if (k <= 2) MOE_TOPK_LANE(2); else if (k <= 4) MOE_TOPK_LANE(4);
     else if (k <= 8) MOE_TOPK_LANE(8); else if (k <= 16) MOE_TOPK_LANE(16); else MOE_TOPK_LANE(32);
@@ -945,10 +918,16 @@ hipError_t launch_gate_topk(float* logits, int64_t T, int64_t E, int k, int64_t 
 #undef MOE_TOPK_LANE
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
+  int bits = 0;
+  while ((1 << bits) < E) ++bits;
+  if (E * k <= kSlotsMaxPairs && E * k * NB <= kSlotsMaxCounters) {
+    gate_slots_kernel<<<grid, block, 0, s>>>(idx, block_counts, T, (int)E, bits, k, C, NB, counts, loc, slot_src, mark_unfilled, perm);
+    return hipGetLastError();
+  }
   gate_scan_kernel<<<dim3((unsigned)E), block, 0, s>>>(block_counts, k * NB, (int)E, C, counts, mark_unfilled ? slot_src : nullptr);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  gate_assign_kernel<<<grid, dim3(kGateTokensPerBlock), 0, s>>>(idx, block_counts, T, (int)E, k, C, NB, loc, slot_src, perm);
+  gate_assign_kernel<<<grid, dim3(kGateTokensPerBlock), 0, s>>>(idx, block_counts, T, (int)E, bits, k, C, NB, loc, slot_src, perm);
   return hipGetLastError();
 }
 

@@ -128,6 +128,37 @@ def test_gate_topk_batch_prioritized_many_tokens(moe):
     assert not np.array_equal(ref["kept"], O.route(logits, k, C, 1)["kept"])       # the order matters at this capacity
 
 
+@pytest.mark.parametrize("T,E,k", [(1024, 64, 4), (1025, 64, 4), (1024, 64, 5), (64, 512, 2), (65, 100, 11), (4096, 64, 1), (32704, 17, 2),
+                                   (32705, 17, 2), (32769, 24, 3)])
+def test_gate_topk_kernel_switches(moe, T, E, k):
+    """Around the count of arrival counters from which scan and assignment are two launches, and the count of 64-token blocks
+    from which wide gates decide with one lane per token."""
+    logits = synth.make_logits(T, E, seed=T + k, quantum=0.25)
+    logits[:, 1] += 0.75
+    C = O.capacity(T, E, k, 1.0)
+    ref = O.route(logits, k, C, 1)
+    got = moe.gate_topk(torch.from_numpy(logits).cuda(), k, C, 1)
+    assert_routing_equal(got, ref, C, f"T={T} E={E} k={k}")
+    assert np.array_equal(got["slot_src"].cpu().numpy(), O.slot_source(ref["idx"], ref["loc"], E, C))
+
+
+@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
+@pytest.mark.parametrize("T,M,E", [(8192, 40, 16), (8193, 40, 16), (256, 2056, 512), (257, 72, 512), (2048, 520, 49), (32768, 48, 16),
+                                   (32769, 24, 40), (15, 1032, 17)])
+def test_gate_route_few_tiles(moe, dtype, T, M, E):
+    """Around 512 tiles of 16 tokens x 16 experts (beyond, and beyond 2^20 tiles x M for bf16, other kernels take the logits)
+    and around the two token tiles per wave of large batches; the reduction ends inside a part and inside a pass."""
+    k = 2
+    cfg = synth.CONFIGS[1].scaled(T=T, M=M, H=8, E=E, k=k, dtype=dtype, cfg_id=63 + dtype)
+    inp = synth.make_inputs(cfg, seed=T + M)
+    logits = O.gate_logits(inp["x"], inp["Wg"], None)
+    C = O.capacity(T, E, k, 1.0)
+    ref = O.route(logits, k, C, 1)
+    got = moe.gate_route(dev(inp["x"], dtype), dev(inp["Wg"], dtype), None, k, C, 1)
+    check_routed_logits(got["logits"].cpu().numpy(), logits)
+    assert_routing_equal(got, ref, C, f"gate_route T={T} M={M} E={E}")
+
+
 def test_gate_topk_is_deterministic(moe):
     logits = torch.from_numpy(synth.make_logits(5000, 64, seed=3, quantum=0.25)).cuda()
     a = moe.gate_topk(logits, 4, 300, 1)
