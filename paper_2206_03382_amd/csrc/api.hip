@@ -662,11 +662,12 @@ int moe_layer_backward(const void* x, const void* Wg, const void* W1, const void
   if (launch_expert_ffn_backward(x, W1, b1, W2, base + w.pre, base + w.hidden, base + w.dY, act, dtype, counts, E, C, M, H,
                                  base + w.ffn_ws, base + w.dZ, dW1, db1, dW2, db2, s, mean_fill(T, E, k), src, T) != hipSuccess)
     return MOE_HIP_ERROR;
-  // encode: dx = sum of a token's kept slot rows of dZ (decode with unit weights)
-  if (launch_decode(base + w.dZ, dtype, idx, loc, nullptr, T, M, E, k, C, dx, s) != hipSuccess) return MOE_HIP_ERROR;
+  // encode: dx = sum of a token's kept slot rows of dZ (decode with unit weights, or inside the gate's dx);
   // gate: dx += dlogits Wg^T, dWg, dbias
-  if (launch_gate_backward(x, Wg, logits, idx, dgw, normalize, dtype, T, M, E, k, base + w.gate_bwd_ws, dx, 1, dWg, dgate_bias,
-                           nullptr, s) != hipSuccess)
+  const bool fused = gate_backward_takes_slabs(dtype, Wg, T, M, E, k);
+  if (!fused && launch_decode(base + w.dZ, dtype, idx, loc, nullptr, T, M, E, k, C, dx, s) != hipSuccess) return MOE_HIP_ERROR;
+  if (launch_gate_backward(x, Wg, logits, idx, dgw, normalize, dtype, T, M, E, k, base + w.gate_bwd_ws, dx, fused ? 0 : 1, dWg, dgate_bias,
+                           nullptr, s, fused ? base + w.dZ : nullptr, loc, C) != hipSuccess)
     return MOE_HIP_ERROR;
   return MOE_OK;
 }

@@ -156,6 +156,13 @@ hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, cons
 hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
                                   int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, int64_t rows_hint = 0,
                                   const int32_t* gather = nullptr, int64_t gather_rows = 0);
+// out[s] (R x N, fp32) = At^T * B over k = s length .. min(K, (s + 1) length) - 1, s < count; At [K, R], B [K, N], R and N
+// multiples of 8.  The sum over s is the caller's.
+struct GemmSlices {
+  int64_t length, count;
+};
+GemmSlices gemm_slices(int dtype, int64_t K, int64_t R, int64_t N);
+hipError_t launch_gemm_tn_slices(const void* At, const void* B, int dtype, int64_t K, int64_t R, int64_t N, float* out, hipStream_t s);
 size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W);
 // shapes moe_expert_ffn_gather takes
 bool grouped_gemm_gathers_on_large_tile(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows);
@@ -163,7 +170,10 @@ bool grouped_gemm_gathers_on_large_tile(int64_t E, int64_t C, int64_t K, int64_t
 size_t gate_backward_workspace_bytes(int64_t T, int64_t M, int64_t E);
 hipError_t launch_gate_backward(const void* x, const void* Wg, const float* logits, const int32_t* idx, const float* dgate_w,
                                 int normalize, int dtype, int64_t T, int64_t M, int64_t E, int k, void* ws, void* dx,
-                                int accumulate_dx, void* dWg, float* dbias, float* dlogits, hipStream_t s);
+                                int accumulate_dx, void* dWg, float* dbias, float* dlogits, hipStream_t s,
+                                const void* slabs = nullptr, const int32_t* loc = nullptr, int64_t C = 0);
+// With `slabs` [E,C,M] (where gate_backward_takes_slabs) dx = the sum of a token's kept slot rows + the gate's share.
+bool gate_backward_takes_slabs(int dtype, const void* Wg, int64_t T, int64_t M, int64_t E, int k);
 
 // Backward of the expert feed-forward layer (ffn_backward.hip): byte offsets of its workspace pieces
 struct FfnBackwardWorkspace {

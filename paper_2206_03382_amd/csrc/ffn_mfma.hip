@@ -771,7 +771,7 @@ hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, i
   const bool large_ok = dtype == MOE_BF16 && large_tile_supports(E, C, K, N, gather ? gather_rows : 0);
   const Tile tile = choose_tile(kNN, large_ok, E, C, mean_or(rows_hint, C), K, N);
   if (tile == Tile::k256) return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, gather, gather_rows, pre_out);
-  const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, out, nullptr, nullptr, pre_out, act};
+  const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, out, nullptr, nullptr, pre_out, act, 0};
   return launch_small<kNN>(dtype, tile, p, s);
 }
 
@@ -782,7 +782,7 @@ hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, cons
   const bool large_ok = dtype == MOE_BF16 && large_tile_supports(E, C, K, N, 0) && N * K * 2 < ((int64_t)1 << 32);
   const Tile tile = choose_tile(kNT, large_ok, E, C, mean_or(rows_hint, C), K, N);
   if (tile == Tile::k256) return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s);
-  const TileArgs p = {A, Bt, nullptr, counts, nullptr, 0, C, K, (int)N, (int)E, 0, 0, out, nullptr, pre, nullptr, pre ? act : -1};
+  const TileArgs p = {A, Bt, nullptr, counts, nullptr, 0, C, K, (int)N, (int)E, 0, 0, out, nullptr, pre, nullptr, pre ? act : -1, 0};
   return launch_small<kNT>(dtype, tile, p, s);
 }
 
@@ -797,8 +797,45 @@ hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, cons
   const bool large_ok = dtype == MOE_BF16 && large_tile_supports_backward(E, C, R, N) && gather_rows * R * 2 < ((int64_t)1 << 32);
   const Tile tile = choose_tile(kTN, large_ok, E, R, mean_or(rows_hint, C), C, N);
   if (tile == Tile::k256) return launch_large_tn(At, B, kfill, E, C, R, N, a_tail, b_tail, out, s, gather, gather_rows);
-  const TileArgs p = {At, B, nullptr, nullptr, gather, gather_rows, R, C, (int)N, (int)E, 0, 0, out, kfill, nullptr, nullptr, -1};
+  const TileArgs p = {At, B, nullptr, nullptr, gather, gather_rows, R, C, (int)N, (int)E, 0, 0, out, kfill, nullptr, nullptr, -1, 0};
   return launch_small<kTN>(dtype, tile, p, s);
+}
+
+// The reduction of a kTN product with one small result, cut into slices whose sums leave as fp32: see common.h.
+template <typename ET, int BM, int BN, int WR, int WC>
+static hipError_t launch_slices(TileArgs p, hipStream_t s) {
+  p.MT = (int)ceil_div(p.C, BM);
+  p.NT = (int)ceil_div(p.N, BN);
+  const int64_t blocks = tile_grid(p.E, p.MT, p.NT);
+  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  grouped_gemm_tile_kernel<ET, kTN, BM, BN, WR, WC, 2, false, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(p);
+  return hipGetLastError();
+}
+
+static int slices_width(int dtype, int64_t N) { return dtype == MOE_F32 ? 64 : (N <= 32 ? 32 : (N <= 64 ? 64 : 128)); }
+
+// Enough slices for about four blocks per compute unit, but no more than 64 (their sums are written and read again) and none
+// shorter than 256 k; a slice is a whole number of K-steps.
+GemmSlices gemm_slices(int dtype, int64_t K, int64_t R, int64_t N) {
+  const int64_t bm = dtype == MOE_F32 ? 64 : 128, tiles = ceil_div(R, bm) * ceil_div(N, slices_width(dtype, N));
+  int64_t n = ceil_div(1024, tiles);
+  n = n < 64 ? n : 64;
+  n = n < ceil_div(K, 256) ? n : ceil_div(K, 256);
+  GemmSlices g;
+  g.length = ceil_div(ceil_div(K, n), 64) * 64;
+  g.count = ceil_div(K, g.length);
+  return g;
+}
+
+hipError_t launch_gemm_tn_slices(const void* At, const void* B, int dtype, int64_t K, int64_t R, int64_t N, float* out, hipStream_t s) {
+  const GemmSlices g = gemm_slices(dtype, K, R, N);
+  TileArgs p = {At, B, nullptr, nullptr, nullptr, 0, R, g.length, (int)N, (int)g.count, 0, 0, out, nullptr, nullptr, nullptr, -1, K};
+  if (dtype == MOE_F32) return launch_slices<float, 64, 64, 2, 2>(p, s);
+  switch (slices_width(dtype, N)) {
+    case 32: return launch_slices<uint16_t, 128, 32, 4, 1>(p, s);
+    case 64: return launch_slices<uint16_t, 128, 64, 2, 2>(p, s);
+    default: return launch_slices<uint16_t, 128, 128, 2, 2>(p, s);
+  }
 }
 
 }  // namespace moe

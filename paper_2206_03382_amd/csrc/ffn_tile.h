@@ -38,6 +38,7 @@ struct TileArgs {
   const void* pre;              // kNT: multiply by act'(pre) (act >= 0) or add pre (act < 0)
   void* pre_out;                // kNN: the values before the activation go here as well
   int act;
+  int64_t ktotal;               // PART: length of the whole reduction, of which every "expert" is K consecutive k
 };
 
 // Waits until at most min(later, MOST) K-steps' loads, L of them each, are outstanding.
@@ -51,7 +52,8 @@ template <int MOST, int L> __device__ __forceinline__ void wait_for_loads(int la
 __device__ __align__(256) uint4 g_zero_piece[16];                   // stays zero: where pieces past the reduction's end are read
 
 // GK (kTN): A's k rows (slots) are gathered; the row numbers of a K-step are fetched a K-step before its loads go out.
-template <typename ET, int MODE, int BM, int BN, int WR, int WC, int NS, bool GK = false>
+// PART (kTN): one long product cut along its reduction: "expert" e reduces k = e K .. e K + K - 1, and the sums leave as fp32.
+template <typename ET, int MODE, int BM, int BN, int WR, int WC, int NS, bool GK = false, bool PART = false>
 __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(const TileArgs p) {
   constexpr int ES = (int)sizeof(ET), EC = 16 / ES;                 // elements per 16-byte piece
   constexpr int BKE = 128 / ES;                                     // k per K-step
@@ -62,7 +64,9 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
   constexpr int LA = A_BYTES / (NW * 1024), LB = BN * 128 / (NW * 1024);   // direct loads per wave and K-step
   static_assert(LA >= 1 && LB >= 1 && TI >= 1 && TJ >= 1, "every wave loads and owns something");
-  static_assert(NW * WTM * WTN * ES <= NS * STAGE, "the epilogue's transpose fits into the stages");
+  constexpr bool BF16O = BF16 && !PART;                             // type of the results
+  constexpr int OS = BF16O ? 2 : 4, OC = 16 / OS;
+  static_assert(NW * WTM * WTN * OS <= NS * STAGE, "the epilogue's transpose fits into the stages");
   __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
 
   const int lane = threadIdx.x & 63;
@@ -87,6 +91,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   const int64_t n0 = (int64_t)nt * BN;
   int64_t kend = p.K;                                               // k that exist
   if (MODE == kTN && p.kfill) { const int64_t c = p.kfill[e]; kend = c < p.K ? (c > 0 ? c : 0) : p.K; }
+  if (PART) { const int64_t left = p.ktotal - (int64_t)e * p.K; kend = left < p.K ? (left > 0 ? left : 0) : p.K; }
   const int KT = kend > 0 ? (int)((kend + BKE - 1) / BKE) : 1;
 
   // ---- this lane's direct loads: address at K-step 0, and k of its piece (to tell what lies past the end) ---------------
@@ -311,11 +316,12 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   // ---- epilogue: the wave's tile goes through its own piece of LDS, so that stores are 16 bytes per lane and whole row
   // pieces; piece c of row r sits at position c ^ (r % pieces per row).
   __syncthreads();                                                  // the stages are done with
-  constexpr int CPR = WTN * ES / 16, RPI = 64 / CPR;                // pieces per row, rows per store
-  char* wtile = smem + wave * (WTM * WTN * ES);
+  constexpr int CPR = WTN * OS / 16, RPI = 64 / CPR;                // pieces per row, rows per store
+  char* wtile = smem + wave * (WTM * WTN * OS);
   const int64_t nw = n0 + wn * WTN;
   const int64_t out_at = ((int64_t)e * p.C + m0 + wm * WTM) * p.N + nw;
-  auto write_tile = [&](auto act_tag, ET* dst, const ET* pre) __attribute__((always_inline)) {
+  using OT = std::conditional_t<BF16O, uint16_t, float>;
+  auto write_tile = [&](auto act_tag, OT* dst, const OT* pre) __attribute__((always_inline)) {
     constexpr int ACT = decltype(act_tag)::value;
 #pragma unroll
     for (int i = 0; i < TI; ++i) {
@@ -328,9 +334,9 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             v[u] = acc[i][j][4 * g + u];
-            if (ACT >= 0 && !pre) v[u] = BF16 ? epilogue_act<ACT>(v[u]) : apply_act(v[u], ACT);
+            if (ACT >= 0 && !pre) v[u] = BF16O ? epilogue_act<ACT>(v[u]) : apply_act(v[u], ACT);
           }
-          if constexpr (BF16) {
+          if constexpr (BF16O) {
             u32x2 pk;
             pk.x = pack_bf16x2(v[0], v[1]);
             pk.y = pack_bf16x2(v[2], v[3]);
@@ -347,24 +353,24 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
       const int r = it * RPI + lane / CPR;
       const int ch = (lane % CPR) ^ (r % CPR);
       u32x4 q = *LDS_PTR(u32x4, wtile + r * (CPR * 16) + ((lane % CPR) << 4));
-      if (r < live && nw + ch * EC < p.N) {
-        const int64_t at = out_at + (int64_t)r * p.N + ch * EC;
+      if (r < live && nw + ch * OC < p.N) {
+        const int64_t at = out_at + (int64_t)r * p.N + ch * OC;
         if (pre) {                                                  // times act'(pre), both factors as stored; or plus `pre`
-          float g[EC], pv[EC];
-          Vec16<ET>::unpack(__builtin_bit_cast(uint4, q), g);
-          Vec16<ET>::unpack(*reinterpret_cast<const uint4*>(pre + at), pv);
+          float g[OC], pv[OC];
+          Vec16<OT>::unpack(__builtin_bit_cast(uint4, q), g);
+          Vec16<OT>::unpack(*reinterpret_cast<const uint4*>(pre + at), pv);
 #pragma unroll
-          for (int u = 0; u < EC; ++u) g[u] = ACT < 0 ? g[u] + pv[u] : g[u] * (BF16 ? epilogue_act_grad<ACT>(pv[u]) : apply_act_grad(pv[u], ACT));
-          q = __builtin_bit_cast(u32x4, Vec16<ET>::pack(g));
+          for (int u = 0; u < OC; ++u) g[u] = ACT < 0 ? g[u] + pv[u] : g[u] * (BF16O ? epilogue_act_grad<ACT>(pv[u]) : apply_act_grad(pv[u], ACT));
+          q = __builtin_bit_cast(u32x4, Vec16<OT>::pack(g));
         }
         *reinterpret_cast<u32x4*>(dst + at) = q;
       }
     }
     __builtin_amdgcn_wave_barrier();
   };
-  ET* out = (ET*)p.out;
-  const ET* pre = MODE == kNT ? (const ET*)p.pre : nullptr;
-  if (MODE == kNN && p.pre_out) write_tile(std::integral_constant<int, -1>{}, (ET*)p.pre_out, nullptr);
+  OT* out = (OT*)p.out;
+  const OT* pre = MODE == kNT ? (const OT*)p.pre : nullptr;
+  if (MODE == kNN && p.pre_out) write_tile(std::integral_constant<int, -1>{}, (OT*)p.pre_out, nullptr);
   if (MODE == kTN) write_tile(std::integral_constant<int, -1>{}, out, nullptr);
   else switch (p.act) {
     case MOE_ACT_RELU: write_tile(std::integral_constant<int, MOE_ACT_RELU>{}, out, pre); break;

@@ -454,6 +454,47 @@ def test_expert_ffn_gelu_epilogue_range(moe):
 # ----------------------------------------------------------------------------------------------------------------
 # moe_gate_backward
 # ----------------------------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("T,M,E", [(63, 136, 8), (64, 128, 10), (65, 120, 11), (255, 64, 16), (257, 72, 21), (1025, 264, 22), (16385, 8, 33)])
+@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
+def test_gate_backward_slices(moe, dtype, T, M, E):
+    """dWg against fp64 from the same dlogits, with column counts and token counts around the tiles, the blocks and the slices of
+    the reduction.  Bound: the sum of T products in fp32, about sqrt(T) roundings of 2^-24 of the terms' 2-norm, and one rounding
+    of the result to its type; factor 8 for the tails."""
+    k = min(E, 3)
+    rng = np.random.default_rng(T + E)
+    x = torch.from_numpy(rng.standard_normal((T, M)).astype(np.float32)).cuda()
+    Wg = torch.from_numpy((rng.standard_normal((M, E)) / 8).astype(np.float32)).cuda()
+    if dtype == synth.DT_BF16:
+        x, Wg = x.bfloat16(), Wg.bfloat16()
+    logits = torch.from_numpy(rng.standard_normal((T, E)).astype(np.float32)).cuda()
+    idx = torch.argsort(logits, dim=1, descending=True)[:, :k].to(torch.int32).contiguous()
+    dgw = torch.from_numpy(rng.standard_normal((T, k)).astype(np.float32)).cuda()
+    g = moe.gate_backward(x, Wg, logits, idx, dgw, 1)
+    dl, xd = g["dlogits"].double().cpu(), x.double().cpu()
+    ref, norm = xd.T @ dl, ((xd ** 2).T @ (dl ** 2)).sqrt()
+    half = 2.0 ** -8 if dtype == synth.DT_BF16 else 2.0 ** -24                      # unit roundoff: 8 and 24 significant bits
+    assert ((g["dWg"].double().cpu() - ref).abs() <= half * ref.abs() + 8 * 2.0 ** -24 * T ** 0.5 * norm + 1e-30).all()
+    assert ((g["dbias"].double().cpu() - dl.sum(0)).abs() <= 8 * 2.0 ** -24 * T ** 0.5 * (dl ** 2).sum(0).sqrt() + 1e-30).all()
+    refx = dl @ Wg.double().cpu().T
+    normx = (dl ** 2 @ (Wg.double().cpu() ** 2).T).sqrt()
+    assert ((g["dx"].double().cpu() - refx).abs() <= half * refx.abs() + 8 * 2.0 ** -24 * E ** 0.5 * normx + 1e-30).all()
+
+
+def test_gate_backward_infinite_token(moe):
+    """A token entry that is infinite makes its row of dWg infinite with the sign of the token's dlogits, and no other."""
+    T, M, E, k = 300, 64, 8, 2
+    rng = np.random.default_rng(5)
+    x = torch.from_numpy(rng.standard_normal((T, M)).astype(np.float32)).cuda().bfloat16()
+    x[7, 3] = float("inf")
+    Wg = torch.zeros((M, E), device="cuda", dtype=torch.bfloat16)
+    logits = torch.from_numpy(rng.standard_normal((T, E)).astype(np.float32)).cuda()
+    idx = torch.argsort(logits, dim=1, descending=True)[:, :k].to(torch.int32).contiguous()
+    g = moe.gate_backward(x, Wg, logits, idx, torch.ones((T, k), device="cuda").mul_(torch.arange(1, k + 1, device="cuda")), 0)
+    dW, dl = g["dWg"].float(), g["dlogits"]
+    assert torch.equal(dW[3], torch.sign(dl[7]) * float("inf"))
+    assert torch.isfinite(dW[torch.arange(M) != 3]).all() and torch.isfinite(g["dx"].float()).all()
+
+
 @pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
 @pytest.mark.parametrize("T,M,E,k,normalize", [(1, 8, 1, 1, 1), (70, 40, 4, 2, 1), (1000, 256, 8, 2, 1), (333, 776, 17, 5, 0),
                                                (2500, 128, 128, 8, 1), (1025, 64, 300, 3, 1), (20000, 256, 64, 2, 1),
