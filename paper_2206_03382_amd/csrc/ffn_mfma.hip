@@ -68,9 +68,10 @@ constexpr int kNN = 0, kNT = 1, kTN = 2;    // operand layouts, see the head of 
 __device__ __forceinline__ void global_to_lds_16(const char* base, uint32_t voff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
 }
-// The same from an address of the lane's own.
-__device__ __forceinline__ void global_to_lds_16(const char* addr, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(addr), "s"(lds_addr) : "memory", "m0");
+// The same from an address of the lane's own; STREAM: with the nontemporal hint, for data that is read once.
+template <bool STREAM = false> __device__ __forceinline__ void global_to_lds_16(const char* addr, uint32_t lds_addr) {
+  if constexpr (STREAM) asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(addr), "s"(lds_addr) : "memory", "m0");
+  else asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(addr), "s"(lds_addr) : "memory", "m0");
 }
 
 // Branch-free activations for the bf16 epilogue.  gelu(v) = v Phi(v) with Phi(-y) = erfc(y / sqrt 2) / 2 for y = |v|:

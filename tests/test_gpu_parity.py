@@ -406,6 +406,22 @@ def test_expert_ffn(moe, dtype, E, C, M, H, act, bias, use_counts):
         assert np.isnan(got[~mask]).all(), "rows past counts[e] must be left untouched"
 
 
+@pytest.mark.parametrize("E,C,M,H", [(8, 48, 2056, 2048), (8, 49, 2056, 2048), (64, 33, 768, 1032), (70, 3, 1032, 776), (8, 96, 2048, 2056)])
+def test_expert_ffn_streamed_weights(moe, E, C, M, H):
+    """Experts of a few rows: around the row count up to which weights are streamed, with widths that leave the last column tile
+    ragged, on both tile widths; the last shape takes the 64 x 128 tile without streaming."""
+    dtype, act = synth.DT_BF16, O.ACT_SILU
+    cfg = synth.CONFIGS[1].scaled(T=E * C, M=M, H=H, E=E, dtype=dtype, cfg_id=46)
+    inp = synth.make_inputs(cfg, seed=C, bias_std=0.5)
+    Z = inp["x"].reshape(E, C, M)
+    counts = np.array([(7 * e + C) % (C + 2) for e in range(E)], dtype=np.int32)
+    ref = O.expert_ffn(Z, inp["W1"], inp["b1"], inp["W2"], inp["b2"], act, rows=counts)
+    got = host(moe.expert_ffn(dev(Z, dtype), dev(inp["W1"], dtype), dev(inp["b1"], dtype), dev(inp["W2"], dtype), dev(inp["b2"], dtype),
+                              act, torch.from_numpy(counts).cuda()))
+    mask = np.arange(C)[None, :] < np.minimum(counts, C)[:, None]
+    assert_close(got[mask], ref[mask], dtype, "streamed weights")
+
+
 # The grouped GEMM deals its live tiles to the XCDs in groups of 32, 16 or 8, chosen on the device from the number of
 # live tiles (below 512: 8; below 1024: 16): fills that put the first product exactly at, just below and between the
 # thresholds, with ragged last row tiles and an empty expert.  H = 1024 gives the first product
