@@ -11,7 +11,7 @@
 // swizzles are the same for both types:
 //   k-contiguous operand: [rows][8 pieces of 16 bytes], piece g of row r at position g ^ ((r / 2) % 8)  (ds_read_b128)
 //   k-slow operand:       [k rows][width], bf16 pieces swizzled for ds_read_b64_tr_b16, fp32 read as single words
-// Several blocks share a compute unit (64 KB of LDS or less each), so that one block's matrix instructions cover another's
+// Several blocks share a compute unit (72 KB of LDS or less each), so that one block's matrix instructions cover another's
 // barrier, load latency, tile search and epilogue; what is left binds by LDS reads (128 x 128: about three quarters of
 // the LDS rate at the matrix cores' peak) and, for few tiles, by how evenly they divide among the units.
 //

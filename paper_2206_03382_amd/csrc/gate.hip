@@ -1,11 +1,13 @@
 // Gating function and capacity-limited slot assignment (arXiv 2206.03382 Sec. 2.1, Eq. 1; Appendix B names the
 // location scan).  Four kernels:
 //   gate_logits_kernel : logits = x * Wg + bias on the fp64 matrix cores (order-independent after rounding to fp32)
+//                        (gate_logits_wide_kernel: more than 64 experts and many tokens)
 //   gate_topk_kernel   : per token softmax + k rounds of (value, index) argmax in a sub-wave group; per-block,
 //                        per-rank, per-expert arrival counters
 //   gate_scan_kernel   : per expert, exclusive scan of the counters in arrival order (rank, block); totals;
 //                        marks unfilled slots of slot_src with -1
 //   gate_assign_kernel : per token and rank, position inside its block + scanned offset -> loc, slot_src
+//                        (gate_slots_kernel: scan and assignment at once where the counters are few)
 // No order-dependent atomics: every integer output is a pure function of the logits.
 // Further down: the dynamic capacity factor and slot sources for a capacity chosen after routing (Sec. 4.1), the cosine
 // router (Appendix), and the token order of batch prioritized routing (Sec. 3.2 / Appendix ablation).
