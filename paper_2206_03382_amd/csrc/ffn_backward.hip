@@ -19,15 +19,26 @@ __device__ __forceinline__ int64_t live_rows(const int32_t* limit, int e, int64_
 
 // out[e, c] = sum over the live rows r of src[e, r, c], fp32, in a fixed order: 32 interleaved row classes, each summed
 // in ascending row order by one thread (16-byte pieces, 8 pieces = 64 or 32 columns per block), then added in class
-// order.   src [E,C,W] as rows of cpr pieces, out [E,W].
+// order.   src [E,C,W] as rows of cpr pieces, out [E,W].  Both bias gradients of the layer go in one launch (blocks below
+// first.blocks sum the first matrix): for layers of few tokens the launches are what they cost
+// (training step of 3001 tokens 334 -> 329 us, fp32 step of 4096 607 -> 601).
+template <typename ET> struct ColsumJob {
+  const uint4* src;
+  ET* out;
+  int cpr, blocks;
+};
 template <typename ET>
-__global__ __launch_bounds__(256) void colsum_kernel(const uint4* __restrict__ src, const int32_t* __restrict__ limit,
-                                                     int64_t C, int cpr, ET* __restrict__ out) {
+__global__ __launch_bounds__(256) void colsum_kernel(const ColsumJob<ET> first, const ColsumJob<ET> second,
+                                                     const int32_t* __restrict__ limit, int64_t C) {
+  const bool other = (int)blockIdx.x >= first.blocks;
+  const uint4* __restrict__ src = other ? second.src : first.src;
+  ET* __restrict__ out = other ? second.out : first.out;
+  const int cpr = other ? second.cpr : first.cpr, block = other ? blockIdx.x - first.blocks : blockIdx.x;
   constexpr int N = Vec16<ET>::N;
   __shared__ float part[32][8 * N + 1];
   const int e = blockIdx.y;
   const int rc = threadIdx.x >> 3, pc = threadIdx.x & 7;
-  const int64_t piece = (int64_t)blockIdx.x * 8 + pc;
+  const int64_t piece = (int64_t)block * 8 + pc;
   const int64_t rows = live_rows(limit, e, C);
   float s[N];
 #pragma unroll
@@ -45,7 +56,7 @@ __global__ __launch_bounds__(256) void colsum_kernel(const uint4* __restrict__ s
   for (int u = 0; u < N; ++u) part[rc][pc * N + u] = s[u];
   __syncthreads();
   if (threadIdx.x < 8 * N) {
-    const int64_t col = (int64_t)blockIdx.x * 8 * N + threadIdx.x;
+    const int64_t col = (int64_t)block * 8 * N + threadIdx.x;
     if (col < (int64_t)cpr * N) {
       float t = 0.f;
 #pragma unroll
@@ -89,14 +100,11 @@ static hipError_t ffn_backward_t(const void* Z, const void* W1, const void* b1, 
     MOE_TRY(launch_grouped_gemm(Z, W1, b1, -1, dtype, counts, E, C, M, H, ws + w.pre, s, rows_hint));
   }
   auto colsums = [&]() -> hipError_t {
-    if (db1) {
-      const int cprH = (int)(H * es / 16);
-      colsum_kernel<ET><<<dim3((unsigned)ceil_div(cprH, 8), (unsigned)E), dim3(256), 0, s>>>((const uint4*)dP, counts, C, cprH, (ET*)db1);
-    }
-    if (db2) {
-      const int cprM = (int)(M * es / 16);
-      colsum_kernel<ET><<<dim3((unsigned)ceil_div(cprM, 8), (unsigned)E), dim3(256), 0, s>>>((const uint4*)dY, counts, C, cprM, (ET*)db2);
-    }
+    const int cprH = (int)(H * es / 16), cprM = (int)(M * es / 16);
+    const ColsumJob<ET> j1 = {(const uint4*)dP, (ET*)db1, cprH, db1 ? (int)ceil_div(cprH, 8) : 0};
+    const ColsumJob<ET> j2 = {(const uint4*)dY, (ET*)db2, cprM, db2 ? (int)ceil_div(cprM, 8) : 0};
+    if (j1.blocks + j2.blocks == 0) return hipSuccess;
+    colsum_kernel<ET><<<dim3((unsigned)(j1.blocks + j2.blocks), (unsigned)E), dim3(256), 0, s>>>(j1, j2, counts, C);
     return hipGetLastError();
   };
   // dP = (dY W2^T) * act'(pre);  dZ = dP W1^T;  dW2 = hidden^T dY;  dW1 = Z^T dP

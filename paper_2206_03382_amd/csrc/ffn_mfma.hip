@@ -649,10 +649,20 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
 }
 
 // dst[e, j, :] = src[e, 64 (KT_e - 1) + j, :] if that slot is below the expert's fill, else 0, for j < 64: the last
-// K-step of a kTN product.   src [E, C, W], dst [E, 64, W]; 16-byte pieces, one block per (expert, 4 slots).
-__global__ __launch_bounds__(256) void tail_rows_kernel(const uint4* __restrict__ src, const int32_t* __restrict__ kfill,
-                                                        int64_t C, int cpr, uint4* __restrict__ dst,
-                                                        const int32_t* __restrict__ gather, int64_t gather_rows) {
+// K-step of a kTN product.   src [E, C, W], dst [E, 64, W]; 16-byte pieces, one block per (expert, 4 slots, operand).
+struct TailRows {
+  const uint4* src;
+  uint4* dst;
+  const int32_t* gather;        // slot -> row, src is then one matrix
+  int64_t gather_rows;
+  int cpr;
+};
+__global__ __launch_bounds__(256) void tail_rows_kernel(const TailRows a, const TailRows b, const int32_t* __restrict__ kfill, int64_t C) {
+  const uint4* __restrict__ src = blockIdx.z ? b.src : a.src;
+  uint4* __restrict__ dst = blockIdx.z ? b.dst : a.dst;
+  const int32_t* __restrict__ gather = blockIdx.z ? b.gather : a.gather;
+  const int64_t gather_rows = blockIdx.z ? b.gather_rows : a.gather_rows;
+  const int cpr = blockIdx.z ? b.cpr : a.cpr;
   const int e = blockIdx.y;
   int64_t fill = C;
   if (kfill) { const int64_t c = kfill[e]; fill = c < C ? (c > 0 ? c : 0) : C; }
@@ -733,9 +743,8 @@ static hipError_t launch_large_nt(const void* A, const void* Bt, const int32_t* 
 static hipError_t launch_large_tn(const void* At, const void* B, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
                                   int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, const int32_t* gather,
                                   int64_t gather_rows) {
-  const int cprR = (int)(R / 8), cprN = (int)(N / 8);
-  tail_rows_kernel<<<dim3(BK / 4, (unsigned)E), dim3(256), 0, s>>>((const uint4*)At, kfill, C, cprR, (uint4*)a_tail, gather, gather_rows);
-  tail_rows_kernel<<<dim3(BK / 4, (unsigned)E), dim3(256), 0, s>>>((const uint4*)B, kfill, C, cprN, (uint4*)b_tail, nullptr, 0);
+  const TailRows ta = {(const uint4*)At, (uint4*)a_tail, gather, gather_rows, (int)(R / 8)}, tb = {(const uint4*)B, (uint4*)b_tail, nullptr, 0, (int)(N / 8)};
+  tail_rows_kernel<<<dim3(BK / 4, (unsigned)E, 2), dim3(256), 0, s>>>(ta, tb, kfill, C);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   const int MT = (int)(R / BM), NT = (int)(N / BN);

@@ -428,7 +428,7 @@ static Tile choose_tile(int mode, bool large_ok, int64_t E, int64_t rows, double
   Tile best = Tile::k128;
   double least = cost(128, 128, 2, 1.5, 3.5, 0.3, 0.56);
   auto consider = [&](Tile t, double c) { if (c < least) { least = c; best = t; } };
-  // the weight gradients' large kernel comes with two launches that pad its last K-step
+  // the weight gradients' large kernel comes with a launch that pads its last K-step
   if (large_ok) consider(Tile::k256, cost(256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 1.1));
   if (mode != kTN) {                                                // 64 x 64 was the best tile for one of 278 weight gradients
     consider(Tile::k64x128, cost(64, 128, 2, 2.5, 2.5, 0.3, 0.44));
