@@ -781,6 +781,7 @@ hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, i
   const bool large_ok = dtype == MOE_BF16 && large_tile_supports(E, C, K, N, gather ? gather_rows : 0);
   const Tile tile = choose_tile(kNN, large_ok, E, C, mean_or(rows_hint, C), K, N);
   if (tile == Tile::k256) return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, gather, gather_rows, pre_out);
+  if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports(E, C, K, N, 0)) act += kFullAct;
   const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, out, nullptr, nullptr, pre_out, act, 0};
   return launch_small<kNN>(dtype, tile, p, s);
 }
@@ -792,6 +793,7 @@ hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, cons
   const bool large_ok = dtype == MOE_BF16 && large_tile_supports(E, C, K, N, 0) && N * K * 2 < ((int64_t)1 << 32);
   const Tile tile = choose_tile(kNT, large_ok, E, C, mean_or(rows_hint, C), K, N);
   if (tile == Tile::k256) return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s);
+  if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports_backward(E, C, K, N)) act += kFullAct;
   const TileArgs p = {A, Bt, nullptr, counts, nullptr, 0, C, K, (int)N, (int)E, 0, 0, out, nullptr, pre, nullptr, pre ? act : -1, 0};
   return launch_small<kNT>(dtype, tile, p, s);
 }

@@ -37,9 +37,22 @@ struct TileArgs {
   const int32_t* kfill;         // kTN: live slots per expert
   const void* pre;              // kNT: multiply by act'(pre) (act >= 0) or add pre (act < 0)
   void* pre_out;                // kNN: the values before the activation go here as well
-  int act;
+  int act;                      // MOE_ACT_*, + kFullAct (bf16 results) for the form with erf and true divisions; < 0: none
   int64_t ktotal;               // PART: length of the whole reduction, of which every "expert" is K consecutive k
 };
+
+// The activations of bf16 results.  The fit behind epilogue_act is good to 6e-7, which is below a bf16 rounding except where GeLU
+// itself is small: at -4 it is off by 0.4 %, twice that rounding, and the erf form by 0.02 %.  Widths the large tile does not
+// take have always had the erf form (and true divisions) and keep it, whichever tile they run on; widths it takes keep the fit.
+constexpr int kFullAct = 4;
+template <int ACT> __device__ __forceinline__ float tile_act(float v) {
+  if constexpr (ACT >= kFullAct) return apply_act(v, ACT - kFullAct);
+  else return epilogue_act<ACT>(v);
+}
+template <int ACT> __device__ __forceinline__ float tile_act_grad(float p) {
+  if constexpr (ACT >= kFullAct) return apply_act_grad(p, ACT - kFullAct);
+  else return epilogue_act_grad<ACT>(p);
+}
 
 // Waits until at most min(later, MOST) K-steps' loads, L of them each, are outstanding.
 template <int MOST, int L> __device__ __forceinline__ void wait_for_loads(int later) {
@@ -335,7 +348,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             v[u] = acc[i][j][4 * g + u];
-            if (ACT >= 0 && !pre) v[u] = BF16O ? epilogue_act<ACT>(v[u]) : apply_act(v[u], ACT);
+            if (ACT >= 0 && !pre) v[u] = BF16O ? tile_act<ACT>(v[u]) : apply_act(v[u], ACT);
           }
           if constexpr (BF16O) {
             u32x2 pk;
@@ -361,7 +374,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
           Vec16<OT>::unpack(__builtin_bit_cast(uint4, q), g);
           Vec16<OT>::unpack(*reinterpret_cast<const uint4*>(pre + at), pv);
 #pragma unroll
-          for (int u = 0; u < OC; ++u) g[u] = ACT < 0 ? g[u] + pv[u] : g[u] * (BF16O ? epilogue_act_grad<ACT>(pv[u]) : apply_act_grad(pv[u], ACT));
+          for (int u = 0; u < OC; ++u) g[u] = ACT < 0 ? g[u] + pv[u] : g[u] * (BF16O ? tile_act_grad<ACT>(pv[u]) : apply_act_grad(pv[u], ACT));
           q = __builtin_bit_cast(u32x4, Vec16<OT>::pack(g));
         }
         *reinterpret_cast<u32x4*>(dst + at) = q;
@@ -377,6 +390,8 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
     case MOE_ACT_RELU: write_tile(std::integral_constant<int, MOE_ACT_RELU>{}, out, pre); break;
     case MOE_ACT_GELU: write_tile(std::integral_constant<int, MOE_ACT_GELU>{}, out, pre); break;
     case MOE_ACT_SILU: write_tile(std::integral_constant<int, MOE_ACT_SILU>{}, out, pre); break;
+    case MOE_ACT_GELU + kFullAct: if (BF16O) write_tile(std::integral_constant<int, MOE_ACT_GELU + kFullAct>{}, out, pre); break;
+    case MOE_ACT_SILU + kFullAct: if (BF16O) write_tile(std::integral_constant<int, MOE_ACT_SILU + kFullAct>{}, out, pre); break;
     default: write_tile(std::integral_constant<int, -1>{}, out, pre); break;
   }
 }

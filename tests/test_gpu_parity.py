@@ -467,6 +467,37 @@ def test_expert_ffn_gelu_epilogue_range(moe):
     assert (np.abs(Y - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-6).all()
 
 
+def test_expert_ffn_gelu_off_the_large_tiles_grid(moe):
+    """Widths that are no multiple of 256 take GeLU and its derivative in the erf form: element by element through identity
+    weights.  Bound: half a bf16 unit of the result; one unit of erf near 1 (2^-24) in Phi; a few roundings of 2^-24 of the
+    terms.  The fit that the 256 x 256 tile uses is off by up to 6e-7 and misses it on both sides."""
+    C, M, d = 512, 264, synth.DT_BF16
+    eye, eye6 = np.eye(M, dtype=np.float32)[None], (6.0 * np.eye(M, dtype=np.float32))[None]
+
+    def half_ulp(r):
+        return 2.0 ** (np.floor(np.log2(np.maximum(np.abs(r), 2.0 ** -126))) - 8)
+
+    def phi_terms(v):
+        t = torch.from_numpy(v)
+        return (0.5 * torch.erfc(-t / np.sqrt(2.0))).numpy(), v * np.exp(-0.5 * v * v) / np.sqrt(2 * np.pi)
+
+    z = synth.round_to_bf16(np.linspace(-1.0, 1.0, C * M, dtype=np.float32).reshape(1, C, M))
+    v = 6.0 * z.astype(np.float64)
+    ref = v * phi_terms(v)[0]
+    Y = host(moe.expert_ffn(dev(z, d), dev(eye6, d), None, dev(eye, d), None, O.ACT_GELU)).astype(np.float64)
+    assert float((np.abs(Y - ref) - half_ulp(ref) - 2.0 ** -24 * np.abs(v) - 2.0 ** -22 * np.abs(ref)).max()) <= 0
+    # dP = act'(pre) for dY = 1 through W2 = 1, dZ = dP; every bf16 value up to 8 in size is among the pre-activations
+    bits = np.arange(0x3000, 0x4100, dtype=np.uint32)
+    vals = (bits << 16).view(np.float32)
+    pre = np.resize(np.concatenate([vals, -vals]), (1, C, M))
+    v = pre.astype(np.float64)
+    Phi, v_phi = phi_terms(v)
+    ones = dev(np.ones((1, C, M), dtype=np.float32), d)
+    g = moe.expert_ffn_backward(ones, dev(eye, d), None, dev(eye, d), ones, ones, O.ACT_GELU, pre=dev(pre, d))
+    err = np.abs(host(g["dZ"]).astype(np.float64) - (Phi + v_phi))
+    assert float((err - half_ulp(Phi + v_phi) - 2.0 ** -24 - 2.0 ** -22 * (Phi + np.abs(v_phi))).max()) <= 0
+
+
 # ----------------------------------------------------------------------------------------------------------------
 # moe_gate_backward
 # ----------------------------------------------------------------------------------------------------------------
