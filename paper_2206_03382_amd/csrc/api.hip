@@ -534,7 +534,8 @@ int moe_layer_forward_dynamic(const void* x, const void* Wg, const float* gate_b
   if (!x || !Wg || !W1 || !W2 || !out || !ws || !act_ok(act) || capacity_setting != capacity_setting) return MOE_INVALID_ARG;
   if (int st = dynamic_shape_status(T, M, H, E, k, C_max, dtype, router, D, bpr)) return st;
   if (router == MOE_ROUTER_COSINE && (!Me || gate_bias || !(tau > 0.0))) return MOE_INVALID_ARG;
-  if (!aligned(x, 16) || !aligned(W1, 16) || !aligned(W2, 16) || !aligned(out, 16) || !aligned(ws, 256) || (C_out && !aligned(C_out, 8)))
+  if (!aligned(x, 16) || !aligned(W1, 16) || !aligned(W2, 16) || !aligned(out, 16) || !aligned(ws, 256) || (C_out && !aligned(C_out, 8)) ||
+      (bpr && logits && !aligned(logits, 16)))                       // batch prioritized routing reads their rows in 16-byte pieces
     return MOE_UNSUPPORTED;
   // what the host knows of the capacity: a fixed one (positive setting) or an upper bound (the caller's C_max and, for a
   // negative setting, what Eq. 1 gives for the factor -setting)
