@@ -259,9 +259,21 @@ static void launch_gate_logits_one(const XT* x, const XT* Wg, const float* bias,
   gate_logits_kernel<XT, NT, KS, TW><<<grid, dim3(64 * KS), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, logits);
 }
 
+// Tokens to a launch: a grid dimension holds fewer than 2^32 threads, 256 to every 16 tokens or, for wide gates, to every 32
+// tokens and 128 experts.
+static int64_t gate_logits_tokens_per_launch(int64_t E) {
+  const int64_t n = ((int64_t)1 << 27) / (E > 64 ? ceil_div(E, kWideExperts) : 1) / kWideTokens * kWideTokens;
+  return n > kWideTokens ? n : kWideTokens;
+}
+
 template <typename XT>
 static hipError_t launch_gate_logits_t(const XT* x, const XT* Wg, const float* bias, int64_t T, int64_t M, int64_t E,
                                        float* logits, hipStream_t s) {
+  const int64_t most = gate_logits_tokens_per_launch(E);
+  for (; T > most; T -= most, x += most * M, logits += most * E) {
+    const hipError_t err = launch_gate_logits_t<XT>(x, Wg, bias, most, M, E, logits, s);
+    if (err != hipSuccess) return err;
+  }
   // few tiles of 16 tokens x 16 experts: one to a block of 16 waves, whatever E is.  At 512 tiles as fast as four waves with
   // all of a gate's experts, below up to three times as fast (64 tokens, M = 4096, 64 experts: 20 us against 67).
   if (gate_logits_few_tiles(T, E)) {
@@ -1106,11 +1118,14 @@ hipError_t launch_gate_logits_cosine(const void* x, const void* Wp, const float*
   cosine_prepare_kernel<<<dim3((unsigned)E), dim3(256), 0, s>>>(Me, (int)E, (int)D, MeT, norm);
   err = hipGetLastError();
   if (err != hipSuccess) return err;
-  const int64_t token_blocks = ceil_div(T, 64);
+  constexpr int64_t most = (int64_t)1 << 26;                         // tokens to a launch: at most 2^20 blocks x 8 x 256 threads
 #define MOE_COSINE(NT)                                                                                                        \
   do {                                                                                                                        \
     const int64_t eb = ceil_div(E, NT * 16);                                                                                  \
-    cosine_logits_kernel<NT><<<dim3((unsigned)(token_blocks * eb)), dim3(256), 0, s>>>(proj, MeT, norm, tau, T, (int)D, (int)E, (int)eb, logits); \
+    for (int64_t t = 0; t < T; t += most) {                                                                                   \
+      const int64_t n = T - t < most ? T - t : most;                                                                          \
+      cosine_logits_kernel<NT><<<dim3((unsigned)(ceil_div(n, 64) * eb)), dim3(256), 0, s>>>(proj + t * D, MeT, norm, tau, n, (int)D, (int)E, (int)eb, logits + t * E); \
+    }                                                                                                                         \
   } while (0)
   if (E <= 16) MOE_COSINE(1); else if (E <= 32) MOE_COSINE(2); else MOE_COSINE(4);
 #undef MOE_COSINE

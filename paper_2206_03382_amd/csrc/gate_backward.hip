@@ -23,9 +23,10 @@ namespace {
 // false, [T, Ep] fp32 (optional); dl16 [T, E64] bf16, zero-padded (optional).  All blocks
 // together write wgp [M, Ep], Wg with zero-padded rows (optional).
 // Bound by its loads' latency, so few tokens take one round per block (3001 tokens, 17 experts 12.7 us with four, 5.3 with one);
-// many take four, which keeps the rows of pbias few.  One thread per token, which this replaced, was a serial chain of 3 E
+// many take four, which keeps the rows of pbias few (and eight beyond 2^29, where 2^24 blocks would be more threads than a grid
+// dimension holds).  One thread per token, which this replaced, was a serial chain of 3 E
 // exponentials: 32768 tokens x 128 experts 87 us, now 40.
-inline int gate_backward_rounds(int64_t T) { return T < 8192 ? 1 : 4; }
+inline int gate_backward_rounds(int64_t T) { return T < 8192 ? 1 : (T <= ((int64_t)1 << 29) ? 4 : 8); }
 
 struct GateBackwardArgs {
   const float* logits;

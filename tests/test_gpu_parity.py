@@ -262,6 +262,19 @@ def test_gate_logits_wide_edges(moe, dtype, T, M, E):
         assert (got != ref).mean() <= max(1e-4, 1.5 / got.size)
 
 
+def test_gate_logits_many_tokens(moe):
+    """More tokens than one launch's grid can hold (2^28 in blocks of 256 threads to 16 tokens), with tokens around the places
+    where the launches meet checked.  Values are small integers: the logits are exact."""
+    T, M, E = 2 ** 28 + 5, 8, 17
+    x = torch.randint(-8, 9, (T, M), device="cuda", dtype=torch.int8).to(torch.bfloat16)
+    Wg = torch.randint(-8, 9, (M, E), device="cuda").to(torch.bfloat16)
+    got = moe.gate_logits(x, Wg, None)
+    for t0 in (0, 2 ** 27 - 40, 2 ** 28 - 40, T - 50):
+        assert torch.equal(got[t0:t0 + 50], x[t0:t0 + 50].float() @ Wg.float()), t0
+    picked = torch.randint(0, T, (1 << 20,), device="cuda")
+    assert torch.equal(got[picked], x[picked].float() @ Wg.float())
+
+
 @pytest.mark.parametrize("T,D,E", [(63, 31, 16), (64, 32, 17), (65, 33, 32), (130, 64, 33), (16, 100, 65)])
 def test_cosine_router_edges(moe, T, D, E):
     """Around the block of 64 tokens, the 32 dimensions per round and the 16, 32 or 64 experts per block."""
