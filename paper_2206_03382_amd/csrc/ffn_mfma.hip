@@ -57,6 +57,7 @@ constexpr int kStageBytes = 65536;          // A tile 32 KB + B tile 32 KB
 constexpr int kATileBytes = 32768;
 constexpr int kLoadsPerWave = 16;           // 64 KB per K-step / (4 waves x 1 KB per wave-load)
 constexpr int kMaxExperts = 512;            // the tile search keeps one register per 64 experts
+constexpr int64_t kMaxBlocks = (int64_t)1 << 24;   // of 256 threads, in a grid dimension
 constexpr int kNN = 0, kNT = 1, kTN = 2;    // operand layouts, see the head of this file
 
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
@@ -782,7 +783,7 @@ hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, i
   const Tile tile = choose_tile(kNN, large_ok, E, C, mean_or(rows_hint, C), K, N);
   if (tile == Tile::k256) return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, gather, gather_rows, pre_out);
   if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports(E, C, K, N, 0)) act += kFullAct;
-  const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, out, nullptr, nullptr, pre_out, act, 0};
+  const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, 0, out, nullptr, nullptr, pre_out, act, 0};
   return launch_small<kNN>(dtype, tile, p, s);
 }
 
@@ -794,7 +795,7 @@ hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, cons
   const Tile tile = choose_tile(kNT, large_ok, E, C, mean_or(rows_hint, C), K, N);
   if (tile == Tile::k256) return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s);
   if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports_backward(E, C, K, N)) act += kFullAct;
-  const TileArgs p = {A, Bt, nullptr, counts, nullptr, 0, C, K, (int)N, (int)E, 0, 0, out, nullptr, pre, nullptr, pre ? act : -1, 0};
+  const TileArgs p = {A, Bt, nullptr, counts, nullptr, 0, C, K, (int)N, (int)E, 0, 0, 0, out, nullptr, pre, nullptr, pre ? act : -1, 0};
   return launch_small<kNT>(dtype, tile, p, s);
 }
 
@@ -809,7 +810,7 @@ hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, cons
   const bool large_ok = dtype == MOE_BF16 && large_tile_supports_backward(E, C, R, N) && gather_rows * R * 2 < ((int64_t)1 << 32);
   const Tile tile = choose_tile(kTN, large_ok, E, R, mean_or(rows_hint, C), C, N);
   if (tile == Tile::k256) return launch_large_tn(At, B, kfill, E, C, R, N, a_tail, b_tail, out, s, gather, gather_rows);
-  const TileArgs p = {At, B, nullptr, nullptr, gather, gather_rows, R, C, (int)N, (int)E, 0, 0, out, kfill, nullptr, nullptr, -1, 0};
+  const TileArgs p = {At, B, nullptr, nullptr, gather, gather_rows, R, C, (int)N, (int)E, 0, 0, 0, out, kfill, nullptr, nullptr, -1, 0};
   return launch_small<kTN>(dtype, tile, p, s);
 }
 
@@ -819,7 +820,7 @@ static hipError_t launch_slices(TileArgs p, hipStream_t s) {
   p.MT = (int)ceil_div(p.C, BM);
   p.NT = (int)ceil_div(p.N, BN);
   const int64_t blocks = tile_grid(p.E, p.MT, p.NT);
-  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   grouped_gemm_tile_kernel<ET, kTN, BM, BN, WR, WC, 2, false, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(p);
   return hipGetLastError();
 }
@@ -841,7 +842,7 @@ GemmSlices gemm_slices(int dtype, int64_t K, int64_t R, int64_t N) {
 
 hipError_t launch_gemm_tn_slices(const void* At, const void* B, int dtype, int64_t K, int64_t R, int64_t N, float* out, hipStream_t s) {
   const GemmSlices g = gemm_slices(dtype, K, R, N);
-  TileArgs p = {At, B, nullptr, nullptr, nullptr, 0, R, g.length, (int)N, (int)g.count, 0, 0, out, nullptr, nullptr, nullptr, -1, K};
+  TileArgs p = {At, B, nullptr, nullptr, nullptr, 0, R, g.length, (int)N, (int)g.count, 0, 0, 0, out, nullptr, nullptr, nullptr, -1, K};
   if (dtype == MOE_F32) return launch_slices<float, 64, 64, 2, 2>(p, s);
   switch (slices_width(dtype, N)) {
     case 32: return launch_slices<uint16_t, 128, 32, 4, 1>(p, s);

@@ -33,6 +33,7 @@ struct TileArgs {
   int64_t C;                    // rows of A (kNN, kNT) or its width (kTN)
   int64_t K;                    // length of the reduction; slots per expert (kTN)
   int N, E, MT, NT;
+  int plain;                    // block y, x = expert, tile of it; else the numbering of find_tile in x
   void* out;
   const int32_t* kfill;         // kTN: live slots per expert
   const void* pre;              // kNT: multiply by act'(pre) (act >= 0) or add pre (act < 0)
@@ -91,14 +92,13 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WC, wn = wave % WC, kg = lane >> 5;
 
-  // ---- which tile: the search of the large kernel, or plain numbering for more experts than it takes ----------------
+  // ---- which tile: the search of the large kernel, or plain numbering where that does not do ---------------------
   int e, mt, nt, rows;
-  if (p.E <= kMaxExperts) {
+  if (!p.plain) {
     if (find_tile<BM>(blockIdx.x, lane, p.E, p.C, p.counts, p.NT, e, mt, nt, rows) != kTileLive) return;
   } else {
-    const int per = p.MT * p.NT;
-    e = blockIdx.x / per;
-    mt = (blockIdx.x % per) / p.NT;
+    e = blockIdx.y;
+    mt = blockIdx.x / p.NT;
     nt = blockIdx.x % p.NT;
     int64_t r = p.C;
     if (p.counts) { const int64_t c = p.counts[e]; r = c < p.C ? (c > 0 ? c : 0) : p.C; }
@@ -436,15 +436,19 @@ template <typename ET, int MODE, int BM, int BN, int NS, bool STREAM = false>
 static hipError_t launch_tile(TileArgs p, hipStream_t s) {
   p.MT = (int)ceil_div(p.C, BM);
   p.NT = (int)ceil_div(p.N, BN);
-  const int64_t blocks = p.E <= kMaxExperts ? tile_grid(p.E, p.MT, p.NT) : (int64_t)p.E * p.MT * p.NT;
-  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
+  // more experts than the search takes, or more blocks than a grid dimension holds (2^32 threads: launches beyond run cut short)
+  int64_t blocks = tile_grid(p.E, p.MT, p.NT);
+  p.plain = p.E > kMaxExperts || blocks >= kMaxBlocks;
+  if (p.plain) blocks = (int64_t)p.MT * p.NT;
+  if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks, p.plain ? (unsigned)p.E : 1);
   if constexpr (MODE == kTN) {
     if (p.gather) {
-      grouped_gemm_tile_kernel<ET, MODE, BM, BN, 2, 2, NS, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(p);
+      grouped_gemm_tile_kernel<ET, MODE, BM, BN, 2, 2, NS, true><<<grid, dim3(256), 0, s>>>(p);
       return hipGetLastError();
     }
   }
-  grouped_gemm_tile_kernel<ET, MODE, BM, BN, 2, 2, NS, false, false, STREAM><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(p);
+  grouped_gemm_tile_kernel<ET, MODE, BM, BN, 2, 2, NS, false, false, STREAM><<<grid, dim3(256), 0, s>>>(p);
   return hipGetLastError();
 }
 

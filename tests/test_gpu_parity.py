@@ -435,6 +435,21 @@ def test_expert_ffn_streamed_weights(moe, E, C, M, H):
     assert_close(got[mask], ref[mask], dtype, "streamed weights")
 
 
+def test_expert_ffn_many_blocks(moe):
+    """More tiles than a grid dimension can hold in blocks of 256 threads (2^24), with more experts than the tile search takes.
+    Values are small integers and the second layer's weights zero except in one row, so that the results are exact."""
+    E, M, H = 65535, 8, 32776
+    Z = torch.randint(-4, 5, (E, 1, M), device="cuda").to(torch.bfloat16)
+    W1 = torch.randint(-4, 5, (E, M, H), device="cuda", dtype=torch.int8).to(torch.bfloat16)
+    W2 = torch.zeros((E, H, M), device="cuda", dtype=torch.bfloat16)
+    h = torch.randint(0, H, (E,), device="cuda")
+    experts = torch.arange(E, device="cuda")
+    W2[experts, h] = 1.0
+    Y = moe.expert_ffn(Z, W1, None, W2, None, O.ACT_RELU)
+    want = (Z[:, 0].float() * W1[experts, :, h].float()).sum(1).clamp(min=0)
+    assert torch.equal(Y[:, 0].float(), want[:, None].expand(E, M))
+
+
 # The grouped GEMM deals its live tiles to the XCDs in groups of 32, 16 or 8, chosen on the device from the number of
 # live tiles (below 512: 8; below 1024: 16): fills that put the first product exactly at, just below and between the
 # thresholds, with ragged last row tiles and an empty expert.  H = 1024 gives the first product
