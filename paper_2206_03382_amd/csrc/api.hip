@@ -19,7 +19,8 @@ inline int gate_shape_status(int64_t T, int64_t E, int k) {
   return MOE_OK;
 }
 
-// rows an expert holds on average if the choices spread evenly (a hint for the GEMM's tile)
+// rows an expert holds on average: every choice is one row, so the experts hold no more than E times this in all, wherever the
+// choices go
 inline int64_t mean_fill(int64_t T, int64_t E, int k) { return ceil_div(T * k, E); }
 
 inline int row_shape_status(int64_t M) {

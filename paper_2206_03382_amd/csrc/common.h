@@ -146,7 +146,8 @@ hipError_t launch_decode(const void* Y, int dtype, const int32_t* idx, const int
 // out[e] = epilogue(A[e] (rows_e x K) * B[e] (K x N) + bias[e]); A [E,C,K], B [E,K,N], out [E,C,N].
 // act < 0 means no activation.  With `pre_out` [E,C,N] the values before the activation are written there as well.
 // With `gather` [E, C] row c of A[e] is row gather[e, c] of one matrix [gather_rows, K].
-// rows_hint: rows an expert holds on average as far as the caller knows (0: C); it only steers the choice of the tile.
+// rows_hint: rows an expert holds on average (0: unknown, up to C).  It steers the choice of the tile, and with `counts` it is a
+// promise: the experts hold no more than E * rows_hint rows among them, which is what the grid is sized for.
 hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, int act, int dtype, const int32_t* counts,
                                int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, int64_t rows_hint = 0,
                                void* pre_out = nullptr, const int32_t* gather = nullptr, int64_t gather_rows = 0);

@@ -39,6 +39,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "ffn_rules.h"
 
 namespace moe {
 
@@ -51,15 +52,11 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 namespace {
 
-constexpr int BM = 256, BN = 256, BK = 64;
+constexpr int BM = kLargeTile, BN = kLargeTile, BK = kLargeK;
 constexpr int kThreads = 256;
 constexpr int kStageBytes = 65536;          // A tile 32 KB + B tile 32 KB
 constexpr int kATileBytes = 32768;
 constexpr int kLoadsPerWave = 16;           // 64 KB per K-step / (4 waves x 1 KB per wave-load)
-constexpr int kMaxExperts = 512;            // the tile search keeps one register per 64 experts
-constexpr int64_t kMaxBlocks = (int64_t)1 << 24;   // of 256 threads, in a grid dimension
-constexpr int kNN = 0, kNT = 1, kTN = 2;    // operand layouts, see the head of this file
-
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 #define PIN() __builtin_amdgcn_sched_barrier(0)
 
@@ -139,25 +136,6 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
 }
 
 }  // namespace
-
-// A weight-gradient product (kTN) reduces over an expert's slots: K-steps of 64 slots, the last one (whole or not) read
-// from the side buffers, which also covers an expert without any slot (one K-step of zeros).
-__host__ __device__ inline int slot_ksteps(int64_t fill) { return fill > 0 ? (int)((fill + BK - 1) / BK) : 1; }
-
-// Tiles per group of the block numbering (log2): 32 when the launch has several rounds of tiles for every compute unit;
-// fewer when it has not, so that the groups, which are dealt whole to the XCDs, still spread evenly over them.
-__host__ __device__ inline int group_size_log2(int64_t live_tiles) { return live_tiles >= 1024 ? 5 : (live_tiles >= 512 ? 4 : 3); }
-
-// Blocks to launch so that every tile is reached whatever the fills turn out to be and whichever group size they select.
-static inline int64_t tile_grid(int64_t E, int64_t MT, int64_t NT) {
-  int64_t blocks = 0;
-  for (int gs = 3; gs <= 5; ++gs) {
-    const int64_t G = (int64_t)1 << gs, groups = E * ceil_div(MT * NT, G);      // upper bound: every expert full
-    const int64_t b = ceil_div(groups, 8) * 8 * G;                              // G blocks per group, groups dealt to 8 XCDs
-    blocks = b > blocks ? b : blocks;
-  }
-  return blocks;
-}
 
 // Which tile block number b works on (see the numbering described in the kernel below).  Returns kTileNone past the last
 // live group, kTileIdle for an idle slot of a short group, kTileLive otherwise with the expert, its row and column tile and
@@ -679,20 +657,13 @@ __global__ __launch_bounds__(256) void tail_rows_kernel(const TailRows a, const 
     dst[((int64_t)e * BK + j) * cpr + ch] = slot < fill ? src[row * cpr + ch] : make_uint4(0, 0, 0, 0);
 }
 
-static bool large_tile_supports(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows) {
-  if (K % BK != 0 || N % BN != 0 || E > kMaxExperts) return false;
-  const int64_t tiles = E * ceil_div(C, BM) * (N / BN);
-  // 32-bit byte offsets inside one expert's A slab (or the whole token matrix when gathering) and B matrix
-  const int64_t a_rows = gather_rows > 0 ? gather_rows : C;
-  return tiles < ((int64_t)1 << 30) && a_rows * K * 2 < ((int64_t)1 << 32) && K * N * 2 < ((int64_t)1 << 32) &&
-         gather_rows < ((int64_t)1 << 31);
-}
-
 static hipError_t launch_large_nn(const void* A, const void* B, const void* bias, int act, const int32_t* counts,
-                                  int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s,
+                                  int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, int64_t total,
                                   const int32_t* gather, int64_t gather_rows, void* pre_out) {
   const int MT = (int)ceil_div(C, BM), NT = (int)(N / BN);
-  const dim3 grid((unsigned)tile_grid(E, MT, NT)), block(kThreads);
+  const int64_t blocks = tile_grid(E, MT, NT, live_row_tiles(E, C, total, BM));
+  if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), block(kThreads);
 #define MOE_LAUNCH_GEMM(ACT, DUAL)                                                                                    \
   grouped_gemm_mfma_kernel<ACT, kNN, false, DUAL><<<grid, block, 0, s>>>(                                             \
       (const uint16_t*)A, (const uint16_t*)B, (const uint16_t*)bias, counts, gather, (int)gather_rows, (int)E, C,     \
@@ -719,9 +690,11 @@ static hipError_t launch_large_nn(const void* A, const void* B, const void* bias
 // out[e] = A[e] (rows_e x K) * Bt[e]^T, Bt [E, N, K]; with `pre` [E, C, N] the result is multiplied by act'(pre), or,
 // with act < 0, has `pre` added (pre == out accumulates in place).
 static hipError_t launch_large_nt(const void* A, const void* Bt, const int32_t* counts, int64_t E, int64_t C,
-                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s) {
+                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s, int64_t total) {
   const int MT = (int)ceil_div(C, BM), NT = (int)(N / BN);
-  const dim3 grid((unsigned)tile_grid(E, MT, NT)), block(kThreads);
+  const int64_t blocks = tile_grid(E, MT, NT, live_row_tiles(E, C, total, BM));
+  if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), block(kThreads);
 #define MOE_LAUNCH_GEMM(ACT, GRAD)                                                                                    \
   grouped_gemm_mfma_kernel<ACT, kNT, GRAD><<<grid, block, 0, s>>>(                                                    \
       (const uint16_t*)A, (const uint16_t*)Bt, nullptr, counts, nullptr, 0, (int)E, C, (int)K, (int)N, MT, NT,        \
@@ -749,7 +722,9 @@ static hipError_t launch_large_tn(const void* At, const void* B, const int32_t* 
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   const int MT = (int)(R / BM), NT = (int)(N / BN);
-  const dim3 grid((unsigned)tile_grid(E, MT, NT)), block(kThreads);
+  const int64_t blocks = tile_grid(E, MT, NT, E * MT);
+  if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), block(kThreads);
   if (gather)
     grouped_gemm_mfma_kernel<-1, kTN, false, false, true><<<grid, block, 0, s>>>(
         (const uint16_t*)At, (const uint16_t*)B, nullptr, nullptr, gather, (int)gather_rows, (int)E, R, (int)C, (int)N, MT, NT,
@@ -761,42 +736,37 @@ static hipError_t launch_large_tn(const void* At, const void* B, const int32_t* 
   return hipGetLastError();
 }
 
-// Shapes for which the three layouts of an expert layer's backward run on the large tile.
-static bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M, int64_t H) {
-  const int64_t W = M > H ? M : H;
-  const int64_t tiles = E * ceil_div(C > W ? C : W, BM) * (W / BN);
-  return M % BN == 0 && H % BN == 0 && E <= kMaxExperts && tiles < ((int64_t)1 << 30) &&
-         C * W * 2 < ((int64_t)1 << 32) && M * H * 2 < ((int64_t)1 << 32);
-}
-
 bool grouped_gemm_gathers_on_large_tile(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows) {
   return large_tile_supports(E, C, K, N, gather_rows);
 }
 
-static double mean_or(int64_t rows_hint, int64_t C) { return (double)(rows_hint > 0 && rows_hint < C ? rows_hint : C); }
+// Rows that exist in all, at most.  Only a caller that counts has a hint that is also a promise.
+static int64_t total_rows(const int32_t* counts, int64_t E, int64_t C, int64_t rows_hint) {
+  return E * (counts && rows_hint > 0 && rows_hint < C ? rows_hint : C);
+}
 
 hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, int act, int dtype, const int32_t* counts,
                                int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, int64_t rows_hint,
                                void* pre_out, const int32_t* gather, int64_t gather_rows) {
   if (act < 0) pre_out = nullptr;                                   // nothing to tell apart
-  const bool large_ok = dtype == MOE_BF16 && large_tile_supports(E, C, K, N, gather ? gather_rows : 0);
-  const Tile tile = choose_tile(kNN, large_ok, E, C, mean_or(rows_hint, C), K, N);
-  if (tile == Tile::k256) return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, gather, gather_rows, pre_out);
+  const Tile tile = dtype == MOE_BF16 ? tile_of(kNN, E, C, K, N, rows_hint, gather ? gather_rows : 0) : Tile::k64;
+  const int64_t total = total_rows(counts, E, C, rows_hint);
+  if (tile == Tile::k256) return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, total, gather, gather_rows, pre_out);
   if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports(E, C, K, N, 0)) act += kFullAct;
   const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, 0, out, nullptr, nullptr, pre_out, act, 0};
-  return launch_small<kNN>(dtype, tile, p, s);
+  return launch_small<kNN>(dtype, tile, p, total, s);
 }
 
 // out[e] = A[e] (rows_e x K) * Bt[e]^T, Bt [E, N, K]; with `pre` [E, C, N] the result is multiplied by act'(pre), or,
 // with act < 0, has `pre` added (pre == out accumulates in place).
 hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, const int32_t* counts, int64_t E, int64_t C,
                                   int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s, int64_t rows_hint) {
-  const bool large_ok = dtype == MOE_BF16 && large_tile_supports(E, C, K, N, 0) && N * K * 2 < ((int64_t)1 << 32);
-  const Tile tile = choose_tile(kNT, large_ok, E, C, mean_or(rows_hint, C), K, N);
-  if (tile == Tile::k256) return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s);
+  const Tile tile = dtype == MOE_BF16 ? tile_of(kNT, E, C, K, N, rows_hint, 0) : Tile::k64;
+  const int64_t total = total_rows(counts, E, C, rows_hint);
+  if (tile == Tile::k256) return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s, total);
   if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports_backward(E, C, K, N)) act += kFullAct;
   const TileArgs p = {A, Bt, nullptr, counts, nullptr, 0, C, K, (int)N, (int)E, 0, 0, 0, out, nullptr, pre, nullptr, pre ? act : -1, 0};
-  return launch_small<kNT>(dtype, tile, p, s);
+  return launch_small<kNT>(dtype, tile, p, total, s);
 }
 
 size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W) { return (size_t)E * BK * W * 2; }
@@ -807,11 +777,10 @@ size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W) { return (size_t)E * BK 
 hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
                                   int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, int64_t rows_hint,
                                   const int32_t* gather, int64_t gather_rows) {
-  const bool large_ok = dtype == MOE_BF16 && large_tile_supports_backward(E, C, R, N) && gather_rows * R * 2 < ((int64_t)1 << 32);
-  const Tile tile = choose_tile(kTN, large_ok, E, R, mean_or(rows_hint, C), C, N);
+  const Tile tile = dtype == MOE_BF16 ? tile_of(kTN, E, R, C, N, rows_hint, gather_rows) : Tile::k64;
   if (tile == Tile::k256) return launch_large_tn(At, B, kfill, E, C, R, N, a_tail, b_tail, out, s, gather, gather_rows);
   const TileArgs p = {At, B, nullptr, nullptr, gather, gather_rows, R, C, (int)N, (int)E, 0, 0, 0, out, kfill, nullptr, nullptr, -1, 0};
-  return launch_small<kTN>(dtype, tile, p, s);
+  return launch_small<kTN>(dtype, tile, p, E * R, s);
 }
 
 // The reduction of a kTN product with one small result, cut into slices whose sums leave as fp32: see common.h.
@@ -819,7 +788,7 @@ template <typename ET, int BM, int BN, int WR, int WC>
 static hipError_t launch_slices(TileArgs p, hipStream_t s) {
   p.MT = (int)ceil_div(p.C, BM);
   p.NT = (int)ceil_div(p.N, BN);
-  const int64_t blocks = tile_grid(p.E, p.MT, p.NT);
+  const int64_t blocks = tile_grid(p.E, p.MT, p.NT, (int64_t)p.E * p.MT);
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   grouped_gemm_tile_kernel<ET, kTN, BM, BN, WR, WC, 2, false, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(p);
   return hipGetLastError();

@@ -1,0 +1,127 @@
+// Which kernel and which grid a product of the grouped GEMM (ffn_mfma.hip) takes: plain host arithmetic on sizes, kept apart
+// from the kernels so that a test can ask it without a GPU.
+#pragma once
+#include <math.h>
+#include <stdint.h>
+
+#ifdef __HIPCC__
+#define MOE_HOST_DEVICE __host__ __device__
+#else
+#define MOE_HOST_DEVICE
+#endif
+
+namespace moe {
+
+constexpr int kNN = 0, kNT = 1, kTN = 2;    // operand layouts, see the head of ffn_mfma.hip
+constexpr int kLargeTile = 256, kLargeK = 64;   // rows and columns of the large tile, its K-step
+constexpr int kMaxExperts = 512;            // the tile search keeps one register per 64 experts
+constexpr int64_t kMaxBlocks = (int64_t)1 << 24;   // of 256 threads, in a grid dimension: launches beyond 2^32 threads run cut short
+
+static inline int64_t tiles_in(int64_t n, int64_t tile) { return (n + tile - 1) / tile; }
+
+// A weight-gradient product (kTN) reduces over an expert's slots: K-steps of 64 slots, the last one (whole or not) read
+// from the side buffers, which also covers an expert without any slot (one K-step of zeros).
+MOE_HOST_DEVICE inline int slot_ksteps(int64_t fill) { return fill > 0 ? (int)((fill + kLargeK - 1) / kLargeK) : 1; }
+
+// Tiles per group of the block numbering (log2): 32 when the launch has several rounds of tiles for every compute unit;
+// fewer when it has not, so that the groups, which are dealt whole to the XCDs, still spread evenly over them.
+constexpr int64_t kTilesForGroups16 = 512, kTilesForGroups32 = 1024;
+MOE_HOST_DEVICE inline int group_size_log2(int64_t live_tiles) {
+  return live_tiles >= kTilesForGroups32 ? 5 : (live_tiles >= kTilesForGroups16 ? 4 : 3);
+}
+
+// Row tiles that hold rows, at most, when the experts hold `total` rows among them, each at most C.
+static inline int64_t live_row_tiles(int64_t E, int64_t C, int64_t total, int64_t tile_rows) {
+  const int64_t full = E * tiles_in(C, tile_rows), n = total / tile_rows + (E < total ? E : total);
+  return n < full ? n : full;
+}
+
+// Blocks to launch so that every tile is reached whatever the fills turn out to be and whichever group size they select: E experts
+// of at most MT x NT tiles, of which at most `row_tiles` row tiles are live in all.  A group has G blocks, groups are dealt to
+// 8 XCDs, and an expert ends in one short group at most.
+// The layer knows its total (every choice is one row).  Without it the grid has to hold C rows of every expert, and where the
+// capacity is far above the mean fill nearly all blocks find nothing to do, each after a tile search and holding its LDS: dynamic
+// capacity, buffers for all 2048 tokens, 128 experts, M = 4096, H = 1024: layer 746 us, 487 with the bound.
+static inline int64_t tile_grid(int64_t E, int64_t MT, int64_t NT, int64_t row_tiles) {
+  const int64_t most = row_tiles * NT;                              // live tiles
+  int64_t blocks = 0;
+  for (int gs = 3; gs <= 5; ++gs) {
+    if (gs > group_size_log2(most)) break;                          // too few tiles for this group size
+    const int64_t limit = gs == 3 ? kTilesForGroups16 - 1 : (gs == 4 ? kTilesForGroups32 - 1 : most);
+    const int64_t live = most < limit ? most : limit, G = (int64_t)1 << gs;
+    const int64_t full = E * tiles_in(MT * NT, G), n = live / G + (E < live ? E : live), groups = n < full ? n : full;
+    const int64_t b = tiles_in(groups, 8) * 8 * G;
+    blocks = b > blocks ? b : blocks;
+  }
+  return blocks;
+}
+
+// Shapes the 256 x 256 tile takes in the forward layout; gather_rows > 0: A's rows are gathered from that many.
+static inline bool large_tile_supports(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows) {
+  if (K % kLargeK != 0 || N % kLargeTile != 0 || E > kMaxExperts) return false;
+  const int64_t tiles = E * tiles_in(C, kLargeTile) * (N / kLargeTile);
+  // 32-bit byte offsets inside one expert's A slab (or the whole token matrix when gathering) and B matrix
+  const int64_t a_rows = gather_rows > 0 ? gather_rows : C;
+  return tiles < ((int64_t)1 << 30) && a_rows * K * 2 < ((int64_t)1 << 32) && K * N * 2 < ((int64_t)1 << 32) &&
+         gather_rows < ((int64_t)1 << 31);
+}
+
+// Shapes for which the three layouts of an expert layer's backward run on it.
+static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M, int64_t H) {
+  const int64_t W = M > H ? M : H;
+  const int64_t tiles = E * tiles_in(C > W ? C : W, kLargeTile) * (W / kLargeTile);
+  return M % kLargeTile == 0 && H % kLargeTile == 0 && E <= kMaxExperts && tiles < ((int64_t)1 << 30) &&
+         C * W * 2 < ((int64_t)1 << 32) && M * H * 2 < ((int64_t)1 << 32);
+}
+
+// Which tile a bf16 launch takes.  The shapes differ in how much of the chip a launch of few tiles uses, how finely its work
+// divides among the 256 compute units, and how fast a full unit runs: 256 x 256 (one block per unit) is 1.2-1.3 times
+// as fast as 128 x 128 (two) and 1.7-1.9 times as fast as 64 x 64 (three) once every unit has several tiles, and the
+// slowest by up to 3 times where it leaves most units idle.  Estimated time of a launch in microseconds:
+//   base + fix * rounds + ksteps * max(lat * rounds, thr * tiles per unit),    rounds = tiles per unit / blocks per unit
+// with constants fitted to 694 measured launches (4-128 experts, 8-4096 rows each, K and N 768-4096, with and without a
+// transposed A).  Over those the choice is 2.8 % (2.3 % for weight gradients) off the best of the three on average, against
+// 21 % (24 %) for always taking the largest tile.  64 x 128 (two blocks) came later, for the launches between: two products of
+// 8 experts x 96 rows, K = N = 2048: 68 (128 x 128) and 61 us (64 x 64) -> 53.
+//
+// Experts of so few rows that one tile holds them read their weights once, and that is all their launch does: 64 x 128 with the
+// nontemporal hint on the weights, 64 experts x 16 rows, 1024 x 4096, two products 221 -> 189 us (5.2 -> 6.1 TB/s over both; the
+// hint alone 202).  Where that leaves units without a block, 64 x 64 one stage deeper (8 experts x 16 rows, 2048 x 2048: 40 -> 33 us).
+// Weights below 48 MB keep the plain loads: they may stay in the caches from one call to the next (17 experts, 776 x 1544,
+// 32 rows: 39 us plain, 41 streamed).
+enum class Tile { k256, k128, k64x128, k64, k64x128_stream, k64_stream };
+static inline Tile choose_tile(int mode, bool large_ok, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
+  if (mode != kTN && mean_rows <= 48.0 && (double)E * K * N * 2 >= 48e6) return E * tiles_in(N, 128) >= 256 ? Tile::k64x128_stream : Tile::k64_stream;
+  const double ksteps = (mode == kTN ? mean_rows : (double)K) / 64 + 0.5;
+  auto cost = [&](int bm, int bn, int per_unit, double base, double fix, double lat, double thr) {
+    const double row_tiles = mode == kTN ? (double)tiles_in(rows, bm) : (mean_rows / bm + 0.5 > 1.0 ? mean_rows / bm + 0.5 : 1.0);
+    double q = (double)E * row_tiles * (double)tiles_in(N, bn) / 256.0;             // tiles per compute unit
+    q = q <= 4.0 * per_unit ? ceil(q - 0.02) : q + 0.5;
+    const double rounds = q > per_unit ? q / per_unit : 1.0;
+    return base + fix * rounds + ksteps * (lat * rounds > thr * q ? lat * rounds : thr * q);
+  };
+  Tile best = Tile::k128;
+  double least = cost(128, 128, 2, 1.5, 3.5, 0.3, 0.56);
+  auto consider = [&](Tile t, double c) { if (c < least) { least = c; best = t; } };
+  // the weight gradients' large kernel comes with a launch that pads its last K-step
+  if (large_ok) consider(Tile::k256, cost(256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 1.1));
+  if (mode != kTN) {                                                // 64 x 64 was the best tile for one of 278 weight gradients
+    consider(Tile::k64x128, cost(64, 128, 2, 2.5, 2.5, 0.3, 0.44));
+    consider(Tile::k64, cost(64, 64, 3, 3.0, 1.5, 0.3, 0.235));
+  }
+  return best;
+}
+
+// Rows an expert holds on average: the caller's hint, or all of them.
+static inline double mean_or(int64_t rows_hint, int64_t C) { return (double)(rows_hint > 0 && rows_hint < C ? rows_hint : C); }
+
+// The tile of a bf16 product: out[e] (C x N) over K, with A gathered from gather_rows rows where that is > 0 (kNN); over the slots K
+// of an expert, of which rows_hint are filled on average, for an output of C x N (kTN).
+static inline Tile tile_of(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
+  if (mode == kTN)
+    return choose_tile(kTN, large_tile_supports_backward(E, K, C, N) && gather_rows * C * 2 < ((int64_t)1 << 32), E, C, mean_or(rows_hint, K), K, N);
+  const bool large_ok = large_tile_supports(E, C, K, N, mode == kNN ? gather_rows : 0);
+  return choose_tile(mode, large_ok, E, C, mean_or(rows_hint, C), K, N);
+}
+
+}  // namespace moe

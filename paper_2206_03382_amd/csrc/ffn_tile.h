@@ -433,11 +433,11 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
 }  // namespace
 
 template <typename ET, int MODE, int BM, int BN, int NS, bool STREAM = false>
-static hipError_t launch_tile(TileArgs p, hipStream_t s) {
+static hipError_t launch_tile(TileArgs p, int64_t total, hipStream_t s) {
   p.MT = (int)ceil_div(p.C, BM);
   p.NT = (int)ceil_div(p.N, BN);
   // more experts than the search takes, or more blocks than a grid dimension holds (2^32 threads: launches beyond run cut short)
-  int64_t blocks = tile_grid(p.E, p.MT, p.NT);
+  int64_t blocks = tile_grid(p.E, p.MT, p.NT, live_row_tiles(p.E, p.C, total, BM));
   p.plain = p.E > kMaxExperts || blocks >= kMaxBlocks;
   if (p.plain) blocks = (int64_t)p.MT * p.NT;
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
@@ -452,57 +452,19 @@ static hipError_t launch_tile(TileArgs p, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Which tile a bf16 launch takes.  The shapes differ in how much of the chip a launch of few tiles uses, how finely its work
-// divides among the 256 compute units, and how fast a full unit runs: 256 x 256 (one block per unit) is 1.2-1.3 times
-// as fast as 128 x 128 (two) and 1.7-1.9 times as fast as 64 x 64 (three) once every unit has several tiles, and the
-// slowest by up to 3 times where it leaves most units idle.  Estimated time of a launch in microseconds:
-//   base + fix * rounds + ksteps * max(lat * rounds, thr * tiles per unit),    rounds = tiles per unit / blocks per unit
-// with constants fitted to 694 measured launches (4-128 experts, 8-4096 rows each, K and N 768-4096, with and without a
-// transposed A).  Over those the choice is 2.8 % (2.3 % for weight gradients) off the best of the three on average, against
-// 21 % (24 %) for always taking the largest tile.  64 x 128 (two blocks) came later, for the launches between: two products of
-// 8 experts x 96 rows, K = N = 2048: 68 (128 x 128) and 61 us (64 x 64) -> 53.
-//
-// Experts of so few rows that one tile holds them read their weights once, and that is all their launch does: 64 x 128 with the
-// nontemporal hint on the weights, 64 experts x 16 rows, 1024 x 4096, two products 221 -> 189 us (5.2 -> 6.1 TB/s over both; the
-// hint alone 202).  Where that leaves units without a block, 64 x 64 one stage deeper (8 experts x 16 rows, 2048 x 2048: 40 -> 33 us).
-// Weights below 48 MB keep the plain loads: they may stay in the caches from one call to the next (17 experts, 776 x 1544,
-// 32 rows: 39 us plain, 41 streamed).
-enum class Tile { k256, k128, k64x128, k64, k64x128_stream, k64_stream };
-static Tile choose_tile(int mode, bool large_ok, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
-  if (mode != kTN && mean_rows <= 48.0 && (double)E * K * N * 2 >= 48e6) return E * ceil_div(N, 128) >= 256 ? Tile::k64x128_stream : Tile::k64_stream;
-  const double ksteps = (mode == kTN ? mean_rows : (double)K) / 64 + 0.5;
-  auto cost = [&](int bm, int bn, int per_unit, double base, double fix, double lat, double thr) {
-    const double row_tiles = mode == kTN ? (double)ceil_div(rows, bm) : (mean_rows / bm + 0.5 > 1.0 ? mean_rows / bm + 0.5 : 1.0);
-    double q = (double)E * row_tiles * (double)ceil_div(N, bn) / 256.0;             // tiles per compute unit
-    q = q <= 4.0 * per_unit ? ceil(q - 0.02) : q + 0.5;
-    const double rounds = q > per_unit ? q / per_unit : 1.0;
-    return base + fix * rounds + ksteps * (lat * rounds > thr * q ? lat * rounds : thr * q);
-  };
-  Tile best = Tile::k128;
-  double least = cost(128, 128, 2, 1.5, 3.5, 0.3, 0.56);
-  auto consider = [&](Tile t, double c) { if (c < least) { least = c; best = t; } };
-  // the weight gradients' large kernel comes with a launch that pads its last K-step
-  if (large_ok) consider(Tile::k256, cost(256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 1.1));
-  if (mode != kTN) {                                                // 64 x 64 was the best tile for one of 278 weight gradients
-    consider(Tile::k64x128, cost(64, 128, 2, 2.5, 2.5, 0.3, 0.44));
-    consider(Tile::k64, cost(64, 64, 3, 3.0, 1.5, 0.3, 0.235));
-  }
-  return best;
-}
-
-// The launches below the large tile.  fp32: the matrix instruction is 16 times slower, loads hardly matter, and the finest
+// The launches below the large tile (`total`: rows of all experts that exist, at most).  fp32: the matrix instruction is 16 times slower, loads hardly matter, and the finest
 // tile divides best (64 x 64, five blocks per unit: within 2-4 % of the best of four shapes over 442 launches).
 template <int MODE>
-static hipError_t launch_small(int dtype, Tile tile, const TileArgs& p, hipStream_t s) {
-  if (dtype == MOE_F32) return launch_tile<float, MODE, 64, 64, 2>(p, s);
+static hipError_t launch_small(int dtype, Tile tile, const TileArgs& p, int64_t total, hipStream_t s) {
+  if (dtype == MOE_F32) return launch_tile<float, MODE, 64, 64, 2>(p, total, s);
   if constexpr (MODE != kTN) {
     switch (tile) {
-      case Tile::k64: return launch_tile<uint16_t, MODE, 64, 64, 3>(p, s);
-      case Tile::k64x128: return launch_tile<uint16_t, MODE, 64, 128, 3>(p, s);
-      case Tile::k64_stream: return launch_tile<uint16_t, MODE, 64, 64, 4, true>(p, s);
-      case Tile::k64x128_stream: return launch_tile<uint16_t, MODE, 64, 128, 3, true>(p, s);
+      case Tile::k64: return launch_tile<uint16_t, MODE, 64, 64, 3>(p, total, s);
+      case Tile::k64x128: return launch_tile<uint16_t, MODE, 64, 128, 3>(p, total, s);
+      case Tile::k64_stream: return launch_tile<uint16_t, MODE, 64, 64, 4, true>(p, total, s);
+      case Tile::k64x128_stream: return launch_tile<uint16_t, MODE, 64, 128, 3, true>(p, total, s);
       default: break;
     }
   }
-  return launch_tile<uint16_t, MODE, 128, 128, 2>(p, s);
+  return launch_tile<uint16_t, MODE, 128, 128, 2>(p, total, s);
 }

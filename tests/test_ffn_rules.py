@@ -1,0 +1,46 @@
+"""The grouped GEMM's host rules (csrc/ffn_rules.h), compiled on their own: no GPU needed."""
+import numpy as np
+import pytest
+
+
+def blocks_needed(tiles, NT):
+    """Blocks the kernels' tile search can ask for when expert e has tiles[e] live row tiles of NT tiles each: whole groups first,
+    a short one per expert with a remainder, dealt to 8 XCDs."""
+    live = int(tiles.sum()) * NT
+    G = 32 if live >= 1024 else (16 if live >= 512 else 8)
+    per = tiles * NT
+    groups = int((per // G).sum() + (per % G > 0).sum())
+    return -(-groups // 8) * 8 * G
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_grid_reaches_every_tile(ffn_rules, seed):
+    """Whatever the fills are, as long as they keep to the total the caller promises, in all and expert by expert."""
+    rng = np.random.default_rng(seed)
+    for _ in range(3000):
+        E, tile = int(rng.integers(1, 513)), int(rng.choice([64, 128, 256]))
+        C, NT = int(2 ** rng.uniform(0, 14)), int(2 ** rng.uniform(0, 7))
+        total = int(rng.integers(1, E * C + 1)) if rng.random() < 0.5 else E * int(rng.integers(1, C + 1))
+        kind = rng.integers(4)
+        if kind == 0:                                  # as many experts with one row over a whole tile as the total allows
+            fills = np.full(E, min(C, int(rng.integers(0, C // tile + 1)) * tile + 1))
+        elif kind == 1:                                # one row each, the rest to a few
+            fills = np.ones(E, dtype=np.int64)
+            fills[:max(1, E // 16)] = C
+        elif kind == 2:
+            fills = np.minimum(rng.multinomial(total, rng.dirichlet(np.full(E, 0.2))), C)
+        else:
+            fills = rng.integers(0, C + 1, size=E)
+        fills = np.minimum(fills, np.maximum(total - (np.cumsum(fills) - fills), 0))      # within the total
+        assert fills.sum() <= total
+        grid = ffn_rules.grid(E, C, tile, NT, total)
+        assert grid >= blocks_needed(-(-fills // tile), NT), (E, C, tile, NT, total)
+
+
+def test_grid_is_bounded_by_the_rows_that_exist(ffn_rules):
+    """Buffers sized for every token, 128 experts: the grid follows the 4096 rows that exist, not 128 x 2048."""
+    E, T, k = 128, 2048, 2
+    for tile, NT in ((64, 8), (64, 32), (128, 16), (256, 4)):
+        live = (T * k // tile + E) * NT
+        assert ffn_rules.grid(E, T, tile, NT, T * k) <= live + 32 * (E + 8)
+        assert ffn_rules.grid(E, T, tile, NT, E * T) >= E * T // tile * NT
