@@ -94,7 +94,10 @@ static inline Tile choose_tile(int mode, bool large_ok, int64_t E, int64_t rows,
   if (mode != kTN && mean_rows <= 48.0 && (double)E * K * N * 2 >= 48e6) return E * tiles_in(N, 128) >= 256 ? Tile::k64x128_stream : Tile::k64_stream;
   const double ksteps = (mode == kTN ? mean_rows : (double)K) / 64 + 0.5;
   auto cost = [&](int bm, int bn, int per_unit, double base, double fix, double lat, double thr) {
-    const double row_tiles = mode == kTN ? (double)tiles_in(rows, bm) : (mean_rows / bm + 0.5 > 1.0 ? mean_rows / bm + 0.5 : 1.0);
+    // an average fill ends in half a tile, but no expert has more row tiles than its slab (without this bound 24 experts x 256
+    // rows, 2048 x 2048, counted as 1.5 tiles each: two products 180 us on smaller tiles, 137 on the large one)
+    const double full = (double)tiles_in(rows, bm), some = mean_rows / bm + 0.5;
+    const double row_tiles = mode == kTN || some > full ? full : (some > 1.0 ? some : 1.0);
     double q = (double)E * row_tiles * (double)tiles_in(N, bn) / 256.0;             // tiles per compute unit
     q = q <= 4.0 * per_unit ? ceil(q - 0.02) : q + 0.5;
     const double rounds = q > per_unit ? q / per_unit : 1.0;

@@ -44,3 +44,14 @@ def test_grid_is_bounded_by_the_rows_that_exist(ffn_rules):
         live = (T * k // tile + E) * NT
         assert ffn_rules.grid(E, T, tile, NT, T * k) <= live + 32 * (E + 8)
         assert ffn_rules.grid(E, T, tile, NT, E * T) >= E * T // tile * NT
+
+
+K256, K128, K64X128, K64, K64X128_STREAM, K64_STREAM = range(6)
+
+
+def test_tile_of_exact_row_counts(ffn_rules):
+    """Slabs whose rows fill whole row tiles of 256, or stay short of one: the large tile, which measured 13 to 32 % faster there
+    than what a row count taken for an average one chose (32 experts x 160 rows, 2048 x 2048: 146 against 176 us)."""
+    for E, C, M, H in ((24, 224, 2048, 2048), (24, 256, 2048, 2048), (32, 160, 2048, 2048), (32, 192, 2048, 2048), (16, 448, 2048, 2048),
+                       (64, 192, 1024, 4096), (32, 448, 4096, 1024), (32, 448, 1024, 4096)):
+        assert ffn_rules.tile(0, E, C, M, H, 0, 0) == K256 and ffn_rules.tile(0, E, C, H, M, 0, 0) == K256, (E, C, M, H)
