@@ -12,13 +12,11 @@
 // Further down: the dynamic capacity factor and slot sources for a capacity chosen after routing (Sec. 4.1), the cosine
 // router (Appendix), and the token order of batch prioritized routing (Sec. 3.2 / Appendix ablation).
 #include "common.h"
+#include "gate_rules.h"
 
 namespace moe {
 
 typedef __attribute__((ext_vector_type(4))) double f64x4;
-// gate_slots_kernel's limits: counters that every block adds up (16 per thread; at 12.5 k it took 18 us where scan and
-// assignment take 10 in two launches), and (expert, rank) pairs in LDS
-constexpr int kSlotsMaxCounters = 4096, kSlotsMaxPairs = 1024;
 // Blocks of 64 tokens from which wide gates decide with one lane per token.  Below, a token's lane group spreads a block's work
 // over more of the chip: 6000 tokens, 64 experts, top-4: 19 us against 23 (51 against 73 with near-tie repairs); 65536
 // tokens, top-2: 30 against 25.
@@ -839,7 +837,7 @@ __global__ __launch_bounds__(kGateTokensPerBlock) void gate_assign_kernel(const 
 
 // Scan and assignment in one launch, for counters few enough that every block adds them up by itself: `before` of an (expert,
 // rank) = all arrivals at lower ranks + those of this rank in earlier blocks.  Saves a launch and its wait where those are
-// what the stage costs: 2 to 4 us of a small gate's 15.
+// what the stage costs: 1 to 2 us of a small gate's 6 to 10.
 __global__ __launch_bounds__(256) void gate_slots_kernel(const int32_t* __restrict__ idx, const int32_t* __restrict__ block_counts,
                                                          int64_t T, int E, int bits, int k, int64_t C, int NB,
                                                          int32_t* __restrict__ counts, int32_t* __restrict__ loc,
@@ -934,7 +932,7 @@ hipError_t launch_gate_topk(float* logits, int64_t T, int64_t E, int k, int64_t 
   if (err != hipSuccess) return err;
   int bits = 0;
   while ((1 << bits) < E) ++bits;
-  if (E * k <= kSlotsMaxPairs && E * k * NB <= kSlotsMaxCounters) {
+  if (slots_in_one_launch(NB, E, k)) {
     gate_slots_kernel<<<grid, block, 0, s>>>(idx, block_counts, T, (int)E, bits, k, C, NB, counts, loc, slot_src, mark_unfilled, perm);
     return hipGetLastError();
   }

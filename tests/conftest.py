@@ -21,6 +21,7 @@ def golden_dir():
 
 RULES_SOURCE = r"""
 #include "paper_2206_03382_amd/csrc/ffn_rules.h"
+#include "paper_2206_03382_amd/csrc/gate_rules.h"
 extern "C" {
 int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total) {
   return moe::tile_grid(E, moe::tiles_in(C, tile), NT, moe::live_row_tiles(E, C, total, tile));
@@ -28,19 +29,22 @@ int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total) {
 int tile(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
   return (int)moe::tile_of(mode, E, C, K, N, rows_hint, gather_rows);
 }
+int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T + 63) / 64, E, k); }
 }
 """
 
 
 @pytest.fixture(scope="session")
 def ffn_rules(tmp_path_factory):
-    """The grouped GEMM's host rules: grid(), and tile(), whose results are numbered as the enum in csrc/ffn_rules.h is."""
+    """The host rules of the grouped GEMM: grid(), and tile(), whose results are numbered as the enum in csrc/ffn_rules.h is;
+    and of the gate: one_launch()."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
     lib = ctypes.CDLL(str(d / "rules.so"))
     lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
+    lib.one_launch.restype, lib.one_launch.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     return lib
 
 

@@ -1,4 +1,4 @@
-"""The grouped GEMM's host rules (csrc/ffn_rules.h), compiled on their own: no GPU needed."""
+"""The host rules of the grouped GEMM and of the gate (csrc/ffn_rules.h, csrc/gate_rules.h), compiled on their own: no GPU needed."""
 import numpy as np
 import pytest
 
@@ -55,3 +55,12 @@ def test_tile_of_exact_row_counts(ffn_rules):
     for E, C, M, H in ((24, 224, 2048, 2048), (24, 256, 2048, 2048), (32, 160, 2048, 2048), (32, 192, 2048, 2048), (16, 448, 2048, 2048),
                        (64, 192, 1024, 4096), (32, 448, 4096, 1024), (32, 448, 1024, 4096)):
         assert ffn_rules.tile(0, E, C, M, H, 0, 0) == K256 and ffn_rules.tile(0, E, C, H, M, 0, 0) == K256, (E, C, M, H)
+
+
+def test_slots_in_one_launch_where_it_is_the_faster(ffn_rules):
+    """Scan and assignment in one launch only where that measured faster than two (both sides beside the rule)."""
+    for T, E, k in ((64, 8, 2), (2048, 8, 2), (8192, 8, 1), (4096, 8, 2), (1024, 32, 2), (512, 64, 2), (64, 16, 4)):
+        assert ffn_rules.one_launch(T, E, k), (T, E, k)
+    for T, E, k in ((16384, 8, 1), (32768, 8, 1), (16384, 8, 2), (8192, 8, 4), (4096, 16, 2), (8192, 32, 1), (64, 32, 1), (64, 64, 2),
+                    (256, 64, 4), (256, 128, 1)):
+        assert not ffn_rules.one_launch(T, E, k), (T, E, k)

@@ -142,6 +142,12 @@ def test_gate_topk_kernel_switches(moe, T, E, k):
     assert np.array_equal(got["slot_src"].cpu().numpy(), O.slot_source(ref["idx"], ref["loc"], E, C))
 
 
+@pytest.mark.parametrize("T,E,k", [(4096, 8, 2), (4097, 8, 2), (8193, 8, 1), (512, 64, 2), (500, 65, 2), (64, 16, 8), (64, 17, 2), (1000, 43, 3)])
+def test_gate_topk_slots_in_one_launch(moe, T, E, k):
+    """Around the counts of counters, pairs and experts up to which scan and assignment are one launch."""
+    test_gate_topk_kernel_switches(moe, T, E, k)
+
+
 @pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
 @pytest.mark.parametrize("T,M,E", [(8192, 40, 16), (8193, 40, 16), (256, 2056, 512), (257, 72, 512), (2048, 520, 49), (32768, 48, 16),
                                    (32769, 24, 40), (15, 1032, 17)])
