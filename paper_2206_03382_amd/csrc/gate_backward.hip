@@ -12,6 +12,7 @@
 // padded to 8) that share every read of x.  Infinities: the second and third pieces of a value that is not finite are 0, and a
 // sum over first pieces that is not finite stands for the whole, so an infinite token entry gives what the plain product gives.
 #include "common.h"
+#include "gate_rules.h"
 
 namespace moe {
 
@@ -394,7 +395,7 @@ static hipError_t gate_backward_t(const void* x, const void* Wg, const float* lo
     const ET* wg = pad_wg ? (const ET*)a.wgp : (const ET*)Wg;
     const int ldw = pad_wg ? (int)w.Ep : (int)E;
 #define MOE_GATE_DX(TT) gate_dx_kernel<ET, TT><<<dim3((unsigned)ceil_div(T, TT), ny), dim3(threads), 0, s>>>(a.dl, wg, ldw, T, cpr, (int)E, accumulate_dx, (const uint4*)slabs, idx, loc, k, C, (uint4*)dx)
-    if (T * ny >= 16 * 1024) MOE_GATE_DX(16); else MOE_GATE_DX(4);
+    if (gate_dx_tokens(T, M * (int64_t)sizeof(ET)) == 16) MOE_GATE_DX(16); else MOE_GATE_DX(4);
 #undef MOE_GATE_DX
     err = hipGetLastError();
   }

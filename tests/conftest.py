@@ -29,6 +29,7 @@ int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total) {
 int tile(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
   return (int)moe::tile_of(mode, E, C, K, N, rows_hint, gather_rows);
 }
+int dx_tokens(int64_t T, int64_t row_bytes) { return moe::gate_dx_tokens(T, row_bytes); }
 int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T + 63) / 64, E, k); }
 }
 """
@@ -37,7 +38,7 @@ int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T
 @pytest.fixture(scope="session")
 def ffn_rules(tmp_path_factory):
     """The host rules of the grouped GEMM: grid(), and tile(), whose results are numbered as the enum in csrc/ffn_rules.h is;
-    and of the gate: one_launch()."""
+    and of the gate: one_launch(), dx_tokens()."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
@@ -45,6 +46,7 @@ def ffn_rules(tmp_path_factory):
     lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
     lib.one_launch.restype, lib.one_launch.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
+    lib.dx_tokens.restype, lib.dx_tokens.argtypes = ctypes.c_int, [ctypes.c_int64] * 2
     return lib
 
 

@@ -64,3 +64,11 @@ def test_slots_in_one_launch_where_it_is_the_faster(ffn_rules):
     for T, E, k in ((16384, 8, 1), (32768, 8, 1), (16384, 8, 2), (8192, 8, 4), (4096, 16, 2), (8192, 32, 1), (64, 32, 1), (64, 64, 2),
                     (256, 64, 4), (256, 128, 1)):
         assert not ffn_rules.one_launch(T, E, k), (T, E, k)
+
+
+def test_gate_dx_tokens_per_block(ffn_rules):
+    """Sixteen tokens to a block wherever four had measured slower than before (fp32 rows of M x 4 bytes, bf16 of M x 2)."""
+    for T, row_bytes in ((1024, 8192), (2048, 8192), (4096, 8192), (1024, 16384), (2048, 16384), (4096, 3104), (8192, 1024), (8192, 4096)):
+        assert ffn_rules.dx_tokens(T, row_bytes) == 16, (T, row_bytes)
+    for T, row_bytes in ((64, 1024), (1024, 1024), (4096, 1024), (1024, 3104), (256, 8192), (256, 16384), (3001, 1552), (1024, 4096)):
+        assert ffn_rules.dx_tokens(T, row_bytes) == 4, (T, row_bytes)
