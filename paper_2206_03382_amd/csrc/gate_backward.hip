@@ -18,17 +18,13 @@ namespace moe {
 
 namespace {
 
-// G lanes per token (16, or 64 for gates of more than 128 experts), lane gl holds experts gl + G i.  p = softmax(logits);
+// G lanes per token (8, 16, or 64 for gates of more than 128 experts), lane gl holds experts gl + G i.  p = softmax(logits);
 // g_j = p[idx_j]; gate_w = g / sum g (normalize) or g.  A block walks `rounds` rounds of 256 / G tokens; with `pbias` it adds up
 // their dlogits per expert, in token order, through LDS.  dl [T,E] fp32 (optional); dcols: [T, 3 Ep] bf16 pieces or, SPLIT
 // false, [T, Ep] fp32 (optional); dl16 [T, E64] bf16, zero-padded (optional).  All blocks
 // together write wgp [M, Ep], Wg with zero-padded rows (optional).
-// Bound by its loads' latency, so few tokens take one round per block (3001 tokens, 17 experts 12.7 us with four, 5.3 with one);
-// many take four, which keeps the rows of pbias few (and eight beyond 2^29, where 2^24 blocks would be more threads than a grid
-// dimension holds).  One thread per token, which this replaced, was a serial chain of 3 E
-// exponentials: 32768 tokens x 128 experts 87 us, now 40.
-inline int gate_backward_rounds(int64_t T) { return T < 8192 ? 1 : (T <= ((int64_t)1 << 29) ? 4 : 8); }
-
+// Bound by its loads' latency.  One thread per token, which this replaced, was a serial chain of 3 E exponentials: 65536 tokens,
+// 128 experts 62 us, now 27; 8 experts 8.5, now 6.2.
 struct GateBackwardArgs {
   const float* logits;
   const int32_t* idx;
@@ -296,7 +292,6 @@ __global__ __launch_bounds__(256) void gate_dw_reduce_kernel(const float* __rest
 struct GateBackwardLayout {
   size_t dl, pbias, part, dcols, wgp, dl16, total;
   int64_t Ep, E64;
-  int token_block;
 };
 
 GateBackwardLayout gate_backward_layout(int64_t T, int64_t M, int64_t E) {
@@ -305,11 +300,10 @@ GateBackwardLayout gate_backward_layout(int64_t T, int64_t M, int64_t E) {
   auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes, 256); return at; };
   w.Ep = align_up(E, 8);
   w.E64 = align_up(E, 64);
-  w.token_block = (E <= 128 ? 16 : 4) * gate_backward_rounds(T);
   auto part_bytes = [&](int dtype, int64_t N) { return (size_t)(gemm_slices(dtype, T, M, N).count * M * N * 4); };
   const size_t bf16 = part_bytes(MOE_BF16, 3 * w.Ep), fp32 = part_bytes(MOE_F32, w.Ep);
   w.dl = take((size_t)T * E * 4);
-  w.pbias = take((size_t)ceil_div(T, w.token_block) * E * 4);
+  w.pbias = take((size_t)ceil_div(T, gate_backward_token_block(T, E, true)) * E * 4);
   w.part = take(bf16 > fp32 ? bf16 : fp32);
   w.dcols = take((size_t)T * 3 * w.Ep * 2);                 // 6 bytes per padded entry, or 4 as fp32
   w.wgp = take((size_t)M * w.Ep * 2);
@@ -363,17 +357,18 @@ static hipError_t gate_backward_t(const void* x, const void* Wg, const float* lo
   // experts (other counts get zero-padded operands); the accumulate form adds dx in the epilogue
   const bool dx_wide = dx && wide_dx(dtype, Wg, T, M, E);
   const bool pad_wg = BF16 && dx && !dx_wide && E % 8 != 0;
-  GateBackwardArgs a = {logits, idx, dgate_w, T, (int)E, k, normalize, (int)w.Ep, (int)w.E64, gate_backward_rounds(T), dlogits_out, nullptr, nullptr, nullptr,
+  const int64_t token_block = gate_backward_token_block(T, E, dbias != nullptr);
+  GateBackwardArgs a = {logits, idx, dgate_w, T, (int)E, k, normalize, (int)w.Ep, (int)w.E64, (int)(token_block * gate_backward_lanes(E) / 256), dlogits_out, nullptr, nullptr, nullptr,
                         (const uint16_t*)Wg, nullptr, M};
   if (dx && !dx_wide && !a.dl) a.dl = (float*)(ws + w.dl);
   if (dWg) a.dcols = ws + w.dcols;
   if (dx_wide) a.dl16 = (uint16_t*)(ws + w.dl16);
   if (pad_wg) a.wgp = (uint16_t*)(ws + w.wgp);
   if (dbias) a.pbias = (float*)(ws + w.pbias);
-  const int nb = (int)ceil_div(T, w.token_block);
-  const size_t shmem = dbias ? (size_t)w.token_block * (E + 1) * sizeof(float) : 0;       // at most 33 KB
+  const int nb = (int)ceil_div(T, token_block);
+  const size_t shmem = dbias ? (size_t)token_block * (E + 1) * sizeof(float) : 0;         // at most 33 KB where memory holds the tokens
 #define MOE_GATE_BACKWARD(G, V) gate_backward_kernel<G, V, BF16><<<dim3((unsigned)nb), dim3(256), shmem, s>>>(a)
-  if (E <= 16) MOE_GATE_BACKWARD(16, 1); else if (E <= 32) MOE_GATE_BACKWARD(16, 2); else if (E <= 64) MOE_GATE_BACKWARD(16, 4);
+  if (E <= 8) MOE_GATE_BACKWARD(8, 1); else if (E <= 16) MOE_GATE_BACKWARD(16, 1); else if (E <= 32) MOE_GATE_BACKWARD(16, 2); else if (E <= 64) MOE_GATE_BACKWARD(16, 4);
   else if (E <= 128) MOE_GATE_BACKWARD(16, 8); else if (E <= 256) MOE_GATE_BACKWARD(64, 4); else MOE_GATE_BACKWARD(64, 8);
 #undef MOE_GATE_BACKWARD
   hipError_t err = hipGetLastError();

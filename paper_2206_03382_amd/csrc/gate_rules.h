@@ -16,6 +16,18 @@ inline bool slots_in_one_launch(int64_t token_blocks, int64_t E, int k) {
   return E * k <= kSlotsMaxPairs && E * k * token_blocks <= kSlotsMaxCounters && E <= 16 * token_blocks;
 }
 
+// Lanes to a token and tokens to a block of gate_backward_kernel, whose blocks walk rounds of 256 / lanes tokens, one behind the
+// other.  Few tokens take one round; with dbias, whose rows of one per block are added up in another launch, many take more.
+// Measured with 1, 2 and 4 rounds: without dbias 8192 tokens, 8 experts 4.4, 5.2 and 7.2 us, 65536 6.1, 6.2 and 7.7, 131072, 64 experts
+// 27.7, 27.5 and 29.6; with it 8192, 8 8.0, 8.6 and 11.1, 32768, 32 20.2, 15.1 and 15.6, 65536, 32 35.1, 24.8 and 20.5.
+inline int gate_backward_lanes(int64_t E) { return E <= 8 ? 8 : (E <= 128 ? 16 : 64); }
+inline int64_t gate_backward_token_block(int64_t T, int64_t E, bool bias) {
+  const int64_t tokens = 256 / gate_backward_lanes(E);
+  int64_t rounds = T < 8192 ? 1 : (T < 65536 ? (bias ? 2 : 1) : (bias ? 4 : 2));
+  while ((T + tokens * rounds - 1) / (tokens * rounds) >= ((int64_t)1 << 24)) rounds *= 2;   // a grid dimension holds fewer than 2^32 threads
+  return tokens * rounds;
+}
+
 // Tokens to a block of gate_dx_kernel.  Every block reads the whole of Wg: few tokens to a block spread a small launch over the
 // chip, many keep those reads down.  Measured with 4 and with 16, fp32, dx alone: 1024 tokens, M = 2048, 17 experts 31.3 and
 // 20.5 us, 4096, 2048, 300 1658 and 457; 256, 2048, 17 15.4 and 17.8; 2048, 776, 24 15.5 and 16.4; 4096, 776, 24 24.0 and 17.9;

@@ -30,6 +30,7 @@ int tile(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint
   return (int)moe::tile_of(mode, E, C, K, N, rows_hint, gather_rows);
 }
 int dx_tokens(int64_t T, int64_t row_bytes) { return moe::gate_dx_tokens(T, row_bytes); }
+int64_t backward_tokens(int64_t T, int64_t E, int bias) { return moe::gate_backward_token_block(T, E, bias); }
 int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T + 63) / 64, E, k); }
 }
 """
@@ -38,7 +39,7 @@ int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T
 @pytest.fixture(scope="session")
 def ffn_rules(tmp_path_factory):
     """The host rules of the grouped GEMM: grid(), and tile(), whose results are numbered as the enum in csrc/ffn_rules.h is;
-    and of the gate: one_launch(), dx_tokens()."""
+    and of the gate: one_launch(), dx_tokens(), backward_tokens()."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
@@ -47,6 +48,7 @@ def ffn_rules(tmp_path_factory):
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
     lib.one_launch.restype, lib.one_launch.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     lib.dx_tokens.restype, lib.dx_tokens.argtypes = ctypes.c_int, [ctypes.c_int64] * 2
+    lib.backward_tokens.restype, lib.backward_tokens.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     return lib
 
 

@@ -72,3 +72,14 @@ def test_gate_dx_tokens_per_block(ffn_rules):
         assert ffn_rules.dx_tokens(T, row_bytes) == 16, (T, row_bytes)
     for T, row_bytes in ((64, 1024), (1024, 1024), (4096, 1024), (1024, 3104), (256, 8192), (256, 16384), (3001, 1552), (1024, 4096)):
         assert ffn_rules.dx_tokens(T, row_bytes) == 4, (T, row_bytes)
+
+
+def test_gate_backward_tokens_per_block(ffn_rules):
+    """One round per block wherever its rounds had measured slower than before; never 2^24 blocks of 256 threads."""
+    for T, E in ((8192, 4), (16384, 4), (32768, 8), (16384, 16), (65535, 8)):
+        assert ffn_rules.backward_tokens(T, E, 0) == (32 if E <= 8 else 16), (T, E)
+    assert ffn_rules.backward_tokens(65536, 4, 0) == 64 and ffn_rules.backward_tokens(16384, 8, 1) == 64
+    for T in (2 ** 28, 2 ** 29, 2 ** 30 - 63, 2 ** 30):
+        for E in (1, 8, 9, 128, 129, 512):
+            for bias in (0, 1):
+                assert -(-T // ffn_rules.backward_tokens(T, E, bias)) < 2 ** 24
