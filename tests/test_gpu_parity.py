@@ -623,6 +623,12 @@ def test_gate_backward(moe, dtype, T, M, E, k, normalize):
     assert np.abs(g["dbias"].cpu().numpy() - ref["dbias"]).max() <= 1e-5 * max(np.abs(ref_dl).sum(axis=0).max(), 1e-30)
 
 
+@pytest.mark.parametrize("T,M,E", [(1, 1032, 5), (40, 4096, 4), (33, 776, 130)])
+def test_gate_backward_few_tokens(moe, T, M, E):
+    """Fewer blocks of tokens than the padding of Wg's rows takes."""
+    test_gate_backward(moe, synth.DT_BF16, T, M, E, 3, 1)
+
+
 # ----------------------------------------------------------------------------------------------------------------
 # moe_expert_ffn_backward
 # ----------------------------------------------------------------------------------------------------------------
