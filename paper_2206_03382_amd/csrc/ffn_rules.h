@@ -60,11 +60,13 @@ static inline int64_t tile_grid(int64_t E, int64_t MT, int64_t NT, int64_t row_t
 static inline bool large_tile_supports(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows) {
   if (K % kLargeK != 0 || N % kLargeTile != 0 || E > kMaxExperts) return false;
   const int64_t tiles = E * tiles_in(C, kLargeTile) * (N / kLargeTile);
-  // 32-bit byte offsets inside one expert's A slab (or the whole token matrix when gathering) and B matrix
-  const int64_t a_rows = gather_rows > 0 ? gather_rows : C;
-  return tiles < ((int64_t)1 << 30) && a_rows * K * 2 < ((int64_t)1 << 32) && K * N * 2 < ((int64_t)1 << 32) &&
-         gather_rows < ((int64_t)1 << 31);
+  // 32-bit byte offsets inside one expert's A slab and B matrix; in a gathered matrix offsets may count 16-byte pieces
+  const int64_t a_rows = gather_rows > 0 ? gather_rows : C, a_bytes = (int64_t)1 << (gather_rows > 0 ? 36 : 32);
+  return tiles < ((int64_t)1 << 30) && a_rows * K * 2 < a_bytes && K * N * 2 < ((int64_t)1 << 32) && gather_rows < ((int64_t)1 << 31);
 }
+
+// Whether byte offsets into a gathered matrix of rows of K bf16 values need more than 32 bits.
+static inline bool far_rows(int64_t gather_rows, int64_t K) { return gather_rows * K * 2 >= ((int64_t)1 << 32); }
 
 // Shapes for which the three layouts of an expert layer's backward run on it.
 static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M, int64_t H) {
@@ -122,7 +124,7 @@ static inline double mean_or(int64_t rows_hint, int64_t C) { return (double)(row
 // of an expert, of which rows_hint are filled on average, for an output of C x N (kTN).
 static inline Tile tile_of(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
   if (mode == kTN)
-    return choose_tile(kTN, large_tile_supports_backward(E, K, C, N) && gather_rows * C * 2 < ((int64_t)1 << 32), E, C, mean_or(rows_hint, K), K, N);
+    return choose_tile(kTN, large_tile_supports_backward(E, K, C, N) && gather_rows * C * 2 < ((int64_t)1 << 36), E, C, mean_or(rows_hint, K), K, N);
   const bool large_ok = large_tile_supports(E, C, K, N, mode == kNN ? gather_rows : 0);
   return choose_tile(mode, large_ok, E, C, mean_or(rows_hint, C), K, N);
 }

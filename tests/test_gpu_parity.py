@@ -834,6 +834,31 @@ def test_layer_fused_on_small_tiles(moe, cfg):
     events.close()
 
 
+def test_layer_of_tokens_beyond_4_gib(moe, ffn_rules):
+    """A token matrix of more than 4 GiB: the rows that the first product and the first weight gradient of the large tile gather
+    through 64-bit addresses are those of the dispatch buffer, bit for bit."""
+    T, M, H, E, k = 2 ** 19 + 1000, 4096, 256, 8, 1
+    assert T * M * 2 > 2 ** 32 and ffn_rules.tile(0, E, T // E, M, H, T // E, T) == 0 and ffn_rules.tile(2, E, M, T // E, H, T // E, T) == 0
+    gen = torch.Generator(device="cuda").manual_seed(3)
+
+    def rand(*shape, std=1.0):
+        return torch.randn(shape, generator=gen, device="cuda", dtype=torch.bfloat16).mul_(std)
+
+    x, Wg, W1, W2, d_out = rand(T, M), rand(M, E, std=1 / 64), rand(E, M, H, std=1 / 64), rand(E, H, M, std=1 / 16), rand(T, M)
+    layer = moe.MoELayer(Wg, None, W1, None, W2, None, T=T, k=k, f=1.0, normalize=0, act=O.ACT_SILU)
+    events = moe.StageEvents()
+    apart = layer.forward(x, events).clone()                                  # with its stages apart: through the dispatch buffer
+    events.close()
+    assert torch.equal(layer.forward(x), apart)
+    del layer
+    want = moe.layer_forward_backward(x, Wg, None, W1, None, W2, None, k, 1.0, 0, O.ACT_SILU, d_out)
+    tl = moe.TrainLayer(Wg, None, W1, None, W2, None, T=T, k=k, f=1.0, normalize=0, act=O.ACT_SILU)
+    assert torch.equal(tl.forward(x), apart)
+    got = tl.backward(x, d_out)
+    for name in ("dx", "dW1", "dW2", "db1", "db2"):
+        assert torch.equal(got[name], want[name]), name
+
+
 def test_layer_forward_in_hip_graph(moe):
     cfg = synth.CONFIGS[1].scaled(T=1500, M=256, H=512, E=8)
     inp = synth.make_inputs(cfg, seed=21, bias_std=0.25)
