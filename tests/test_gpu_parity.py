@@ -391,7 +391,7 @@ FFN_CASES = [
     (synth.DT_F32, 3, 70, 40, 72, O.ACT_GELU, True, True),
     (synth.DT_F32, 4, 256, 256, 512, O.ACT_RELU, False, False),
     (synth.DT_F32, 2, 130, 264, 136, O.ACT_SILU, True, True),
-    (synth.DT_BF16, 2, 100, 72, 40, O.ACT_GELU, True, True),            # generic (non-MFMA) bf16 shapes
+    (synth.DT_BF16, 2, 100, 72, 40, O.ACT_GELU, True, True),            # widths off the large tile's grid
     (synth.DT_BF16, 3, 300, 256, 256, O.ACT_RELU, False, False),        # MFMA path, ragged last row tile
     (synth.DT_BF16, 2, 513, 512, 768, O.ACT_GELU, True, True),
     (synth.DT_BF16, 5, 1000, 768, 1024, O.ACT_SILU, True, True),
@@ -454,6 +454,26 @@ def test_expert_ffn_many_blocks(moe):
     Y = moe.expert_ffn(Z, W1, None, W2, None, O.ACT_RELU)
     want = (Z[:, 0].float() * W1[experts, :, h].float()).sum(1).clamp(min=0)
     assert torch.equal(Y[:, 0].float(), want[:, None].expand(E, M))
+
+
+STREAMED = [(8, 48, 2056, 2048), (64, 33, 768, 1032), (70, 3, 1032, 776), (8, 96, 2048, 2056)]
+
+
+@pytest.mark.parametrize("E,C,M,H", STREAMED)
+def test_expert_ffn_streamed_weights_backward(moe, ffn_rules, E, C, M, H):
+    """The products with the weights transposed, streamed on both tile widths, and the 64 x 128 tile without streaming."""
+    dh, dz = ffn_rules.tile(1, E, C, M, H, 0, 0), ffn_rules.tile(1, E, C, H, M, 0, 0)
+    assert (dh, dz) == {8: (5, 5) if C <= 48 else (1, 2), 64: (4, 4), 70: (4, 4)}[E]   # numbers of the enum Tile
+    test_expert_ffn_backward(moe, synth.DT_BF16, E, C, M, H, O.ACT_SILU, True, True)
+
+
+@pytest.mark.parametrize("M", [2048, 2056])
+def test_layer_streamed_weights(moe, ffn_rules, M):
+    """A decode step and a training step of a handful of tokens: streamed weights with rows gathered from the tokens."""
+    cfg = synth.CONFIGS[1].scaled(T=16, M=M, H=2048, E=8, k=2, f=2.0)
+    assert ffn_rules.tile(0, 8, 8, M, 2048, 4, 16) == 5 and ffn_rules.tile(1, 8, 8, M, 2048, 4, 0) == 5
+    test_layer_small(moe, cfg, True)
+    test_layer_forward_backward(moe, cfg)
 
 
 # The grouped GEMM deals its live tiles to the XCDs in groups of 32, 16 or 8, chosen on the device from the number of
@@ -637,7 +657,7 @@ FFN_BWD_CASES = [
     (synth.DT_F32, 1, 1, 8, 8, O.ACT_RELU, False, False),
     (synth.DT_F32, 3, 70, 40, 72, O.ACT_GELU, True, True),
     (synth.DT_F32, 2, 130, 264, 136, O.ACT_SILU, True, True),
-    (synth.DT_BF16, 2, 100, 72, 40, O.ACT_GELU, True, True),            # generic (non-MFMA) bf16 shapes
+    (synth.DT_BF16, 2, 100, 72, 40, O.ACT_GELU, True, True),            # widths off the large tile's grid
     (synth.DT_BF16, 3, 300, 256, 256, O.ACT_RELU, False, False),        # MFMA GEMMs, capacity not a multiple of 64
     (synth.DT_BF16, 2, 513, 512, 768, O.ACT_GELU, True, True),
     (synth.DT_BF16, 5, 1000, 768, 1024, O.ACT_SILU, True, True),
@@ -710,6 +730,15 @@ def run_layer(moe, cfg, inp):
     return layer, out
 
 
+def forward_through_slabs(moe, layer, x):
+    """The layer's pass with its stages apart, which writes the dispatch buffer and has the first expert product read it."""
+    events = moe.StageEvents()
+    out = layer.forward(x, events)
+    torch.cuda.synchronize()
+    events.close()
+    return out
+
+
 def check_logits(got, ref, floor=0.0):
     """Exactly rounded logits (fp64 sums on both sides): equal up to the last bit, in all but a few entries."""
     ulp = np.spacing(np.abs(ref).astype(np.float32))
@@ -726,7 +755,7 @@ SMALL_LAYERS = [
     synth.CONFIGS[0].scaled(T=300, M=40, H=72, E=3),
     synth.CONFIGS[0],
     synth.CONFIGS[1].scaled(T=1500, M=256, H=512, E=8),
-    synth.CONFIGS[1].scaled(T=2000, M=264, H=520, E=8),                   # shapes that take the generic bf16 GEMM
+    synth.CONFIGS[1].scaled(T=2000, M=264, H=520, E=8),                   # widths off the large tile's grid
     synth.CONFIGS[2].scaled(T=1960, M=768, H=1024, E=32),
     synth.CONFIGS[3].scaled(T=4096, M=256, H=512, E=64),
     synth.CONFIGS[4].scaled(T=4096, M=512, H=256, E=128),
@@ -813,6 +842,51 @@ def test_layer_train_step_fills_at_reduction_step_boundaries(moe, T):
         assert (host(g["dW1"])[e].view(np.uint32) << 1 == 0).all() and (host(g["dW2"])[e].view(np.uint32) << 1 == 0).all()
 
 
+def test_layer_train_step_on_the_large_tile(moe, ffn_rules):
+    """The same corner cases on the 256 x 256 tile in all three layouts, which the choice by the mean fill gives experts of any
+    fill: reductions of 0 to 5 steps, whole and not, gathered and from the dispatch buffer, and row tiles of 0 to 8 live
+    32-row pieces with the activation's derivative in the epilogue.  A token's expert is written into its first entries."""
+    cfg = synth.CONFIGS[1].scaled(T=15360, M=768, H=768, E=24, k=1, f=5.0)
+    T, M, H, E = cfg.T, cfg.M, cfg.H, cfg.E
+    C = O.capacity(T, E, 1, cfg.f)
+    for hint, rows in ((T // E, T), (0, 0)):                                  # the layer; the stage entry points
+        for mode, a, b in ((0, M, H), (0, H, M), (1, M, H), (1, H, M)):
+            assert ffn_rules.tile(mode, E, C, a, b, hint, rows if a == M and mode == 0 else 0) == 0
+        assert ffn_rules.tile(2, E, H, C, M, hint, 0) == 0 and ffn_rules.tile(2, E, M, C, H, hint, rows) == 0
+    fills = [0, 1, 63, 64, 65, 128, 129, 192, 193, 31, 33, 95, 97, 127, 160, 224, 255, 256, 257, 321]
+    fills += [(T - sum(fills)) // 4 + i for i in (-3, -1, 1, 3)]
+    fills[-1] += T - sum(fills)
+    assert max(fills) <= C
+    inp = synth.make_inputs(cfg, seed=33, bias_std=0.25)
+    expert = np.random.default_rng(7).permutation(np.repeat(np.arange(E), fills))
+    inp["x"][:, :E] = 0.0
+    inp["x"][np.arange(T), expert] = 8.0
+    inp["Wg"] = np.zeros_like(inp["Wg"])
+    inp["Wg"][:E] = np.eye(E)
+    d_out = synth.make_inputs(cfg.scaled(cfg_id=54), seed=34)["x"]
+    ref = O.moe_layer_backward(inp["x"], inp["Wg"], None, inp["W1"], inp["b1"], inp["W2"], inp["b2"], cfg.k, cfg.f, cfg.normalize, cfg.act, d_out)
+    assert ref["forward"]["counts"].tolist() == fills
+    d = cfg.dtype
+    Wg, W1, b1, W2, b2 = (dev(inp[n], d) for n in ("Wg", "W1", "b1", "W2", "b2"))
+    tl = moe.TrainLayer(Wg, None, W1, b1, W2, b2, T=T, k=cfg.k, f=cfg.f, normalize=cfg.normalize, act=cfg.act)
+    xd, dod = dev(inp["x"], d), dev(d_out, d)
+    out = tl.forward(xd)
+    g = tl.backward(xd, dod)
+    apart = moe.layer_forward_backward(xd, Wg, None, W1, b1, W2, b2, cfg.k, cfg.f, cfg.normalize, cfg.act, dod)
+    torch.cuda.synchronize()
+    assert_close(host(out), ref["forward"]["out"], d, "out")
+    assert torch.equal(out, apart["out"])
+    for name in ("dx", "dW1", "db1", "dW2", "db2"):
+        assert_close(host(g[name]), ref[name], d, name)
+        assert torch.equal(g[name], apart[name]), name
+    for e, n in enumerate(fills):                                             # every expert against its own scale, too
+        if n:
+            for name in ("dW1", "dW2"):
+                assert_close(host(g[name][e]), ref[name][e], d, f"{name} of an expert of {n} slots")
+        else:
+            assert not host(g["dW1"])[e].any() and not host(g["dW2"])[e].any()
+
+
 # ----------------------------------------------------------------------------------------------------------------
 # the layer call allocates nothing, clears nothing by memset and never synchronises: it can be captured in a HIP graph
 # ----------------------------------------------------------------------------------------------------------------
@@ -891,8 +965,14 @@ FUSED_LAYERS = [
     synth.CONFIGS[2].scaled(T=1960, M=768, H=1024, E=32),
     synth.CONFIGS[3].scaled(T=4096, M=256, H=512, E=64),
     synth.CONFIGS[4].scaled(T=4096, M=512, H=256, E=128),
-    synth.CONFIGS[1].scaled(T=2000, M=264, H=520, E=8),                   # unsupported by the fused kernel: falls back
+    synth.CONFIGS[1].scaled(T=2000, M=264, H=520, E=8),                   # widths off the large tile's grid
+    synth.CONFIGS[1].scaled(T=6144, M=1024, H=1024, E=16),                # the large tile
 ]
+
+
+def test_fused_layers_cover_the_large_tile(ffn_rules):
+    tiles = [ffn_rules.tile(0, c.E, O.capacity(c.T, c.E, c.k, c.f), c.M, c.H, -(-c.T * c.k // c.E), c.T) for c in FUSED_LAYERS]
+    assert tiles[-1] == 0 and any(t != 0 for t in tiles)                      # 0: the large tile
 
 
 @pytest.mark.parametrize("cfg", FUSED_LAYERS, ids=lambda c: f"{c.name}-T{c.T}-M{c.M}-H{c.H}-E{c.E}")
@@ -905,8 +985,9 @@ def test_layer_fused_dispatch(moe, cfg):
                          dev(inp["W1"], d), dev(inp["b1"], d), dev(inp["W2"], d), dev(inp["b2"], d),
                          T=cfg.T, k=cfg.k, f=cfg.f, normalize=cfg.normalize, act=cfg.act, keep_routing=True)
     xd = dev(inp["x"], d)
-    plain = host(layer.forward(xd)).copy()
+    plain = host(forward_through_slabs(moe, layer, xd)).copy()
     fused = host(layer.forward(xd, fuse_dispatch=True)).copy()
+    assert torch.equal(layer.forward(xd).cpu().view(torch.uint8), layer.forward(xd, fuse_dispatch=True).cpu().view(torch.uint8))
     torch.cuda.synchronize()
     assert_routing_equal(layer.routing, ref, ref["C"], cfg.name)
     assert_close(fused, ref["out"], cfg.dtype, f"fused-dispatch layer output ({cfg.name})")
@@ -1084,8 +1165,10 @@ def test_layer_full_size(moe, cfg):
     assert_routing_equal(layer.routing, ref, ref["C"], cfg.name)
     plain = host(out).copy()
     assert_close(plain, ref["out"], cfg.dtype, f"layer output ({cfg.name})")
+    apart = host(forward_through_slabs(moe, layer, dev(inp["x"], cfg.dtype)))
+    assert np.array_equal(apart.view(np.uint32), plain.view(np.uint32)), "fused dispatch must reproduce the buffered path bit for bit"
     fused = host(layer.forward(dev(inp["x"], cfg.dtype), fuse_dispatch=True))
-    assert np.array_equal(fused.view(np.uint32), plain.view(np.uint32)), "fused dispatch must reproduce the plain path bit for bit"
+    assert np.array_equal(fused.view(np.uint32), plain.view(np.uint32))
 
 
 def test_layer_backward_full_size(moe):
@@ -1142,9 +1225,10 @@ def test_layer_full_size_finegrained(moe, progress):
     layer = moe.MoELayer(dev(inp["Wg"], d), None, W1d, None, W2d, None, T=cfg.T, k=cfg.k, f=cfg.f,
                          normalize=cfg.normalize, act=cfg.act, keep_routing=True)
     out = layer.forward(xd).clone()
+    assert torch.equal(forward_through_slabs(moe, layer, xd), out), "fused dispatch must reproduce the buffered path bit for bit"
     fused = layer.forward(xd, fuse_dispatch=True)
     torch.cuda.synchronize()
-    assert torch.equal(fused, out), "fused dispatch must reproduce the plain path bit for bit"
+    assert torch.equal(fused, out)
     check_routed_logits(layer.routing["logits"].cpu().numpy(), logits)
     assert_routing_equal(layer.routing, ref, C, cfg.name)
     g = layer.routing
