@@ -1,7 +1,7 @@
 // Gating function and capacity-limited slot assignment (arXiv 2206.03382 Sec. 2.1, Eq. 1; Appendix B names the
-// location scan).  Four kernels:
+// location scan).  The kernels of the gate:
 //   gate_logits_kernel : logits = x * Wg + bias on the fp64 matrix cores (order-independent after rounding to fp32)
-//                        (gate_logits_wide_kernel: more than 64 experts and many tokens)
+//                        (gate_logits_wide_kernel: wide gates and many tokens)
 //   gate_topk_kernel   : per token softmax + k rounds of (value, index) argmax in a sub-wave group; per-block,
 //                        per-rank, per-expert arrival counters
 //   gate_scan_kernel   : per expert, exclusive scan of the counters in arrival order (rank, block); totals;
@@ -59,7 +59,7 @@ template <typename XT, int N> struct RawN {
   }
 };
 
-// Gates of up to 64 experts, and few tokens whatever the gate: a wave owns TW tiles of 16 tokens x NT tiles of 16 experts over
+// Gates of up to 64 experts, few tokens, and what wide gates leave over: a wave owns TW tiles of 16 tokens x NT tiles of 16 experts over
 // one of KS parts of the reduction, a block the KS parts of its tiles, whose sums are added in part order through LDS.  Both
 // operands come straight from global memory, two passes of 32 k ahead in registers: x once in 16-byte pieces, Wg (which every
 // wave reads, so from the caches) element by element in the layout the instruction wants.  No barrier and no LDS in the
@@ -70,13 +70,13 @@ template <typename XT, int N> struct RawN {
 template <typename XT, int NT, int KS, int TW>
 __global__ __launch_bounds__(64 * KS) void gate_logits_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
                                                               const float* __restrict__ bias, int64_t T, int M, int E,
-                                                              float* __restrict__ logits) {
+                                                              int e_base, float* __restrict__ logits) {
   constexpr int PF = 2;
   __shared__ double red[KS - 1][TW * NT][4][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, kq = lane >> 4;
   const int64_t t0 = (int64_t)blockIdx.x * (16 * TW);
-  const int e0 = blockIdx.y * (16 * NT);
+  const int e0 = e_base + blockIdx.y * (16 * NT);
   const int passes = (M + 31) / 32, per = (passes + KS - 1) / KS;
   const int p0 = wave * per, p1 = p0 + per < passes ? p0 + per : passes;   // this wave's passes (possibly none)
   const XT* xrow[TW];
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(64 * KS) void gate_logits_kernel(const XT* __restri
   }
 }
 
-// Wide gates (more than 64 experts; the cosine router's projection): a block's 2 x 2 waves own 32 tokens x 128 experts, a wave
+// Wide gates of many tokens (the cosine router's projection; the rule: gate_rules.h): a block's 2 x 2 waves own 32 tokens x 128 experts, a wave
 // 16 x 64 as four accumulator tiles.  Both operands go through LDS as fp32, 32 k at a time (the next 32 k are fetched to
 // registers meanwhile), and are widened on the way out: per 32 k a wave issues 32 matrix instructions of 64 cycles against
 // 34 LDS reads and 40 conversions, which hide behind them, and 21 KB of LDS let seven blocks share a unit and cover each
@@ -175,8 +175,9 @@ __global__ __launch_bounds__(64 * KS) void gate_logits_kernel(const XT* __restri
 // four k of an operand read lie 16 banks apart).
 constexpr int kWideTokens = 32, kWideExperts = 128, kWideK = 32, kWideLdx = 36, kWideLdw = 130;
 
-template <typename XT, bool VECW>
-__global__ __launch_bounds__(256, VECW && sizeof(XT) == 2 ? 7 : 4) void gate_logits_wide_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
+// E a multiple of 8 and Wg 16-byte aligned.
+template <typename XT>
+__global__ __launch_bounds__(256, sizeof(XT) == 2 ? 7 : 4) void gate_logits_wide_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
                                                                const float* __restrict__ bias, int64_t T, int M, int E,
                                                                int expert_blocks, float* __restrict__ logits) {
   __shared__ __attribute__((aligned(16))) float xs[kWideTokens * kWideLdx];
@@ -202,15 +203,8 @@ __global__ __launch_bounds__(256, VECW && sizeof(XT) == 2 ? 7 : 4) void gate_log
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int e = we0 + 8 * h;
-      if (VECW) {                                                   // E a multiple of 8, rows 16-byte aligned
-        const bool on = wlive && e < E;
-        wr[h].load_vec(row + (e < E ? e : 0));
-        wr[h].keep_if(on);
-      } else {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) wr[h].set(u, row[e + u < E ? e + u : E - 1]);
-        wr[h].keep_if(wlive);                                       // columns past E repeat the last one and are never stored
-      }
+      wr[h].load_vec(row + (e < E ? e : 0));
+      wr[h].keep_if(wlive && e < E);
     }
   };
   f64x4 acc[4];
@@ -250,11 +244,12 @@ __global__ __launch_bounds__(256, VECW && sizeof(XT) == 2 ? 7 : 4) void gate_log
   }
 }
 
+// Experts e_base .. end - 1 (end: E, or a whole number of tiles on)
 template <typename XT, int NT, int KS, int TW>
-static void launch_gate_logits_one(const XT* x, const XT* Wg, const float* bias, int64_t T, int64_t M, int64_t E,
-                                   float* logits, hipStream_t s) {
-  const dim3 grid((unsigned)ceil_div(T, 16 * TW), (unsigned)ceil_div(E, 16 * NT));
-  gate_logits_kernel<XT, NT, KS, TW><<<grid, dim3(64 * KS), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, logits);
+static void launch_gate_logits_one(const XT* x, const XT* Wg, const float* bias, int64_t T, int64_t M, int64_t E, int64_t e_base,
+                                   int64_t end, float* logits, hipStream_t s) {
+  const dim3 grid((unsigned)ceil_div(T, 16 * TW), (unsigned)ceil_div(end - e_base, 16 * NT));
+  gate_logits_kernel<XT, NT, KS, TW><<<grid, dim3(64 * KS), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, (int)e_base, logits);
 }
 
 // Tokens to a launch: a grid dimension holds fewer than 2^32 threads, 256 to every 16 tokens or, for wide gates, to every 32
@@ -275,26 +270,35 @@ static hipError_t launch_gate_logits_t(const XT* x, const XT* Wg, const float* b
   // few tiles of 16 tokens x 16 experts: one to a block of 16 waves, whatever E is.  At 512 tiles as fast as four waves with
   // all of a gate's experts, below up to three times as fast (64 tokens, M = 4096, 64 experts: 20 us against 67).
   if (gate_logits_few_tiles(T, E)) {
-    launch_gate_logits_one<XT, 1, 16, 1>(x, Wg, bias, T, M, E, logits, s);
-  } else if (E > 64) {
-    const int64_t expert_blocks = ceil_div(E, kWideExperts), blocks = ceil_div(T, kWideTokens) * expert_blocks;
-    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
-    if (E % 8 == 0 && ((uintptr_t)Wg & 15) == 0)
-      gate_logits_wide_kernel<XT, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, (int)expert_blocks, logits);
-    else
-      gate_logits_wide_kernel<XT, false><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, (int)expert_blocks, logits);
-  } else {
-    // two token tiles per wave halve the reads of Wg, for many tokens (65536 tokens, M = 2048, 8 experts: 100 -> 94 us; 16384: no gain)
-    const bool many = T >= 32768;
-    if (E <= 16) {
-      if (many) launch_gate_logits_one<XT, 1, 4, 2>(x, Wg, bias, T, M, E, logits, s);
-      else launch_gate_logits_one<XT, 1, 4, 1>(x, Wg, bias, T, M, E, logits, s);
-    } else if (E <= 32) {
-      launch_gate_logits_one<XT, 2, 4, 1>(x, Wg, bias, T, M, E, logits, s);
-    } else {
-      if (many) launch_gate_logits_one<XT, 4, 4, 2>(x, Wg, bias, T, M, E, logits, s);
-      else launch_gate_logits_one<XT, 4, 4, 1>(x, Wg, bias, T, M, E, logits, s);
-    }
+    launch_gate_logits_one<XT, 1, 16, 1>(x, Wg, bias, T, M, E, 0, E, logits, s);
+    return hipGetLastError();
+  }
+  // Experts below `wide` go to the wide kernel, the others to the narrow one, 64 at a time and then what is left.
+  const bool vecw = E % 8 == 0 && ((uintptr_t)Wg & 15) == 0;
+  const int64_t wide = gate_logits_wide_experts(T, E, vecw);
+  if (wide > 0) {
+    const int64_t expert_blocks = ceil_div(wide, kWideExperts), blocks = ceil_div(T, kWideTokens) * expert_blocks;
+    gate_logits_wide_kernel<XT><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(x, Wg, bias, T, (int)M, (int)E, (int)expert_blocks, logits);
+  }
+  // The narrow kernel's waves: two token tiles halve the reads of Wg and eight parts of the reduction shorten its chain, each where
+  // enough blocks are left (bf16, M = 4096: 12000 tokens, 32 experts, eight parts and four 74 and 79 us; 16384 with two token
+  // tiles 86, with one 95; 16384, 64 experts, two and one 165 and 183; 8200 157 and 135).
+  int64_t e = wide;
+  if (E - e > 32) {
+    const int64_t end = E - e <= 64 ? E : E - (E - e) % 64;
+    if (T >= 16384) launch_gate_logits_one<XT, 4, 4, 2>(x, Wg, bias, T, M, E, e, end, logits, s);
+    else launch_gate_logits_one<XT, 4, 4, 1>(x, Wg, bias, T, M, E, e, end, logits, s);
+    e = end;
+  }
+  if (E - e > 32) {
+    if (T >= 16384) launch_gate_logits_one<XT, 4, 4, 2>(x, Wg, bias, T, M, E, e, E, logits, s);
+    else launch_gate_logits_one<XT, 4, 4, 1>(x, Wg, bias, T, M, E, e, E, logits, s);
+  } else if (E - e > 16) {
+    if (T >= 16384) launch_gate_logits_one<XT, 2, 8, 2>(x, Wg, bias, T, M, E, e, E, logits, s);
+    else launch_gate_logits_one<XT, 2, 8, 1>(x, Wg, bias, T, M, E, e, E, logits, s);
+  } else if (E > e) {
+    if (T >= 32768) launch_gate_logits_one<XT, 1, 4, 2>(x, Wg, bias, T, M, E, e, E, logits, s);
+    else launch_gate_logits_one<XT, 1, 8, 1>(x, Wg, bias, T, M, E, e, E, logits, s);
   }
   return hipGetLastError();
 }

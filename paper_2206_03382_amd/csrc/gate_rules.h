@@ -16,6 +16,16 @@ inline bool slots_in_one_launch(int64_t token_blocks, int64_t E, int k) {
   return E * k <= kSlotsMaxPairs && E * k * token_blocks <= kSlotsMaxCounters && E <= 16 * token_blocks;
 }
 
+// Experts whose exact logits the wide kernel takes, in blocks of 128 (vecw: its 16-byte pieces of Wg's rows are whole); the narrow
+// kernel takes the others, 64 at a time.  Blocks of 128 fill badly with few tokens or with a remainder: fp32, M = 2048, narrow and
+// wide 4096 tokens, 128 experts 56 and 132 us, 16384 168 and 189, 65536 661 and 630; 12000, 512 502 and 484; 65536, 96 520 and 628;
+// 136 (128 + 8 against 256) 766 and 1210; 120 697 and 629.
+inline int64_t gate_logits_wide_experts(int64_t T, int64_t E, bool vecw) {
+  if (E <= 64 || !vecw || T * E < ((int64_t)1 << 22)) return 0;
+  const int64_t left = E % 128;
+  return left <= 96 ? E - left : E;
+}
+
 // Lanes to a token and tokens to a block of gate_backward_kernel, whose blocks walk rounds of 256 / lanes tokens, one behind the
 // other.  Few tokens take one round; with dbias, whose rows of one per block are added up in another launch, many take more.
 // Measured with 1, 2 and 4 rounds: without dbias 8192 tokens, 8 experts 4.4, 5.2 and 7.2 us, 65536 6.1, 6.2 and 7.7, 131072, 64 experts

@@ -268,6 +268,15 @@ def test_gate_logits_wide_edges(moe, dtype, T, M, E):
         assert (got != ref).mean() <= max(1e-4, 1.5 / got.size)
 
 
+@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
+@pytest.mark.parametrize("T,M,E", [(8200, 40, 65), (8200, 72, 100), (32768, 24, 128), (32767, 24, 128), (30850, 32, 136), (32776, 40, 232), (16400, 24, 40),
+                                   (16384, 40, 24), (9000, 1032, 130)])
+def test_gate_logits_wide_and_narrow(moe, dtype, T, M, E):
+    """Around the counts of tokens and experts that send blocks of 128 experts to the wide kernel and the rest to the narrow one,
+    in its forms of one and two token tiles.  Bound: as above."""
+    test_gate_logits(moe, dtype, T, M, E, True)
+
+
 def test_gate_logits_many_tokens(moe):
     """More tokens than one launch's grid can hold (2^28 in blocks of 256 threads to 16 tokens), with tokens around the places
     where the launches meet checked.  Values are small integers: the logits are exact."""
