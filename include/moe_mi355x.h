@@ -102,8 +102,9 @@ size_t moe_gate_route_workspace_bytes(int64_t T, int64_t M, int64_t E, int k, in
 
 /* The gating function from the tokens (Sec. 2.1): moe_gate_logits followed by moe_gate_topk, at memory speed.
  *   Inputs as moe_gate_logits, outputs as moe_gate_topk (logits [T,E] fp32 is an output here, required).
- * fp32 gates run exactly those two steps.  bf16 gates compute the logits on the bf16 matrix cores (exact products, fp32
- * sums of 32 terms, fp64 sums of those) with a rigorous per-token error bound B_t = 32 * 2^-23 * |x_t| * max_e |w_e|; a
+ * fp32 gates, bf16 gates of few tokens (at most 512 tiles of 16 tokens x 16 experts) and gates of more than 512 experts run
+ * exactly those two steps.  Other bf16 gates compute the logits on the bf16 matrix cores (exact products, blocked fp32 sums)
+ * with a rigorous per-token error bound B_t, a small multiple of 32 * 2^-23 * (|x_t| * max_e |w_e| + max_e |b_e|); a
  * token whose k+1 largest logits are not separated by more than 2 B_t has the logits of every expert that can still
  * reach its top k recomputed in fp64 and rounded once, and is decided on those.  So idx, loc, counts and slot_src are
  * the ones exactly rounded logits give (what moe_gate_logits + moe_gate_topk return), while `logits` holds exactly
@@ -171,7 +172,8 @@ int moe_encode(const void* x, int dtype, const int32_t* idx, const int32_t* loc,
  *   bf16 once after the activation and Y once at the end.  fp32: fp32 products and sums on the matrix cores.
  *   counts [E] int32 or NULL: if given, only the first min(counts[e], C) rows of each expert are computed and the
  *   remaining rows of Y and hidden are left untouched (decode never reads them); if NULL all C rows are computed.
- *   act: ReLU, GeLU (the erf form v * Phi(v); the bf16 matrix-core path evaluates Phi to within 6e-7) or SiLU. */
+ *   act: ReLU, GeLU (the erf form v * Phi(v)) or SiLU.  bf16 layers with M % 64 == 0 and H % 256 == 0 evaluate Phi to within
+ *   6e-7 and SiLU with the hardware's reciprocal; layers of other widths, and fp32 ones, with erf and a division. */
 int moe_expert_ffn(const void* Z, const void* W1, const void* b1, const void* W2, const void* b2,
                    int act, int dtype, const int32_t* counts,
                    int64_t E, int64_t C, int64_t M, int64_t H, void* hidden, void* Y, void* stream);
@@ -182,7 +184,8 @@ int moe_expert_ffn(const void* Z, const void* W1, const void* b1, const void* W2
  *   x [T,M]; slot_src [E,C] from moe_gate_topk or moe_slot_sources; everything else as moe_expert_ffn.
  *   Rows of Y and hidden past min(counts[e], C) (or, with counts = NULL, rows of unfilled slots) hold unspecified
  *   values; decode never reads them.
- * bf16 only, M % 64 == 0 and H % 256 == 0 and T*M*2 < 2^32, else MOE_UNSUPPORTED (use the two calls instead). */
+ * bf16 only, M % 64 == 0 and H % 256 == 0 and T*M*2 < 2^32, else MOE_UNSUPPORTED (use the two calls instead; the layer entries
+ * read their rows from x whatever the sizes). */
 int moe_expert_ffn_gather(const void* x, const int32_t* slot_src, int64_t T, const void* W1, const void* b1, const void* W2,
                           const void* b2, int act, int dtype, const int32_t* counts, int64_t E, int64_t C, int64_t M,
                           int64_t H, void* hidden, void* Y, void* stream);
@@ -193,8 +196,8 @@ int moe_expert_ffn_gather(const void* x, const int32_t* slot_src, int64_t T, con
 int moe_decode(const void* Y, int dtype, const int32_t* idx, const int32_t* loc, const float* gate_w,
                int64_t T, int64_t M, int64_t E, int k, int64_t C, void* out, void* stream);
 
-/* Bytes of workspace moe_gate_backward needs (dlogits [T,E] fp32 and the per-slice partial sums of dWg and of dbias;
- * a slice is 64 tokens, or more so that there are at most 256 slices).  0 on invalid arguments. */
+/* Bytes of workspace moe_gate_backward needs (dlogits [T,E] fp32 and in the form dWg's product reads, the partial sums of
+ * dWg for at most 64 slices of the tokens and those of dbias for blocks of them).  0 on invalid arguments. */
 size_t moe_gate_backward_workspace_bytes(int64_t T, int64_t M, int64_t E, int k);
 
 /* Backward of the gating function (Sec. 2.1 gate; Sec. 3.2: the backward pass mirrors the forward).  With
@@ -204,7 +207,9 @@ size_t moe_gate_backward_workspace_bytes(int64_t T, int64_t M, int64_t E, int k)
  *   dWg      = x^T dlogits;   dbias = column sums of dlogits.
  * x, dx [T,M] and Wg, dWg [M,E] in `dtype`; logits [T,E] fp32 and idx [T,k] as the forward produced them; dbias [E] and
  * dlogits [T,E] fp32.  Any of dx, dWg, dbias, dlogits may be NULL.  The choice of experts and the slot assignment carry
- * no gradient.  fp32 arithmetic, fixed summation orders (within a token slice ascending, then slice by slice); for bf16
+ * no gradient.  fp32 arithmetic in summation orders that the sizes alone fix: dWg adds up at most 64 slices of the tokens, each
+ * a product on the matrix cores with fp32 sums (bf16 gates: dlogits enters as three bf16 pieces that hold its 24 bits; fp32 gates:
+ * sums of 64 tokens, added up in turn), dbias blocks of tokens.  For bf16
  * gates with 32 or more experts and M % 256 == 0, dx is a matrix-core product of dlogits rounded to bf16 (fp32 sums).
  * ws: moe_gate_backward_workspace_bytes, 256-byte aligned; x and dx 16-byte aligned. */
 int moe_gate_backward(const void* x, const void* Wg, const float* logits, const int32_t* idx, const float* dgate_w, int normalize,

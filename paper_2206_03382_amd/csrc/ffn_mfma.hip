@@ -812,8 +812,8 @@ static hipError_t launch_slices(TileArgs p, hipStream_t s) {
 static int slices_width(int dtype, int64_t N) { return N <= 32 ? 32 : (N <= 64 || dtype == MOE_F32 ? 64 : 128); }
 static int slices_height(int dtype, int64_t N) { return dtype == MOE_F32 && N > 32 ? 64 : 128; }
 
-// Enough slices for about four blocks per compute unit, but no more than 64 (their sums are written and read again) and none
-// shorter than 256 k; a slice is a whole number of K-steps.
+// Enough slices for about four blocks per compute unit, but no more than 64 (their sums are written and read again) and no more
+// than one to 256 k; a slice is a whole number of K-steps.
 GemmSlices gemm_slices(int dtype, int64_t K, int64_t R, int64_t N) {
   const int64_t tiles = ceil_div(R, slices_height(dtype, N)) * ceil_div(N, slices_width(dtype, N));
   int64_t n = ceil_div(1024, tiles);

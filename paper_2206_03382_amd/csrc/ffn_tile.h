@@ -17,9 +17,9 @@
 //
 // What it replaced was an fp32 FMA kernel on operands transposed and padded in memory, at 12 TFLOP/s in either type.
 // Measured, training step of 17 experts x 353 rows, M = 776, H = 1544, bf16: the six products 645-700 us -> 35-57 us each,
-// step 5060 -> 417 us.  8 experts x 1024 rows, M = 512, H = 1024, fp32: products 166-228 us -> 72-95 us (117 TFLOP/s in
-// the weight gradients; fp32 matrix peak 157), step 1585 -> 630 us.  8 experts x 4 rows, M = H = 2048, bf16: 29 us on the
-// large tile -> 13 us (67 MB of weights: 5.1 TB/s), layer 121 -> 72 us.
+// step 5060 -> 337 us with all its other kernels.  8 experts x 1024 rows, M = 512, H = 1024, fp32: products 166-228 us -> 72-95 us
+// (117 TFLOP/s in the weight gradients; fp32 matrix peak 157), step 1585 -> 603 us.  8 experts x 4 rows, M = H = 2048, bf16: 29 us
+// on the large tile -> 13 us (67 MB of weights: 5.1 TB/s), layer 121 -> 51 us.
 
 namespace {
 

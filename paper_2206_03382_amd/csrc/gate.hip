@@ -19,7 +19,9 @@ namespace moe {
 typedef __attribute__((ext_vector_type(4))) double f64x4;
 // Blocks of 64 tokens from which wide gates decide with one lane per token.  Below, a token's lane group spreads a block's work
 // over more of the chip: 6000 tokens, 64 experts, top-4: 19 us against 23 (51 against 73 with near-tie repairs); 65536
-// tokens, top-2: 30 against 25.
+// tokens, top-2: 27 against 21.  At the line itself (32768 tokens) the two are alike for few choices (top-1 of 32 12.4 and 11.0 us,
+// top-4 of 64 24.1 and 23.3) and the lane form still loses for many (top-8 of 128 46 and 55, whole gate of M = 4096 with its
+// repairs 167 and 266); from 65536 tokens on it wins there too (79 and 68; 131072 tokens 147 and 103).
 constexpr int kLaneTopkMinBlocks = 512;
 
 

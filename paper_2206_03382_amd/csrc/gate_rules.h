@@ -41,7 +41,8 @@ inline int64_t gate_backward_token_block(int64_t T, int64_t E, bool bias) {
 // Tokens to a block of gate_dx_kernel.  Every block reads the whole of Wg: few tokens to a block spread a small launch over the
 // chip, many keep those reads down.  Measured with 4 and with 16, fp32, dx alone: 1024 tokens, M = 2048, 17 experts 31.3 and
 // 20.5 us, 4096, 2048, 300 1658 and 457; 256, 2048, 17 15.4 and 17.8; 2048, 776, 24 15.5 and 16.4; 4096, 776, 24 24.0 and 17.9;
-// bf16 4096, 2048, 17 30.1 and 23.5, 1024, 2048, 17 12.3 and 16.0.  The two meet near 8 MB of tokens whatever the width and the type.
+// bf16 4096, 2048, 17 30.1 and 23.5, 1024, 2048, 17 12.3 and 16.0.  The two meet near 8 MB of tokens whatever the width and the type:
+// 8.4 MB, fp32, 4096, 512, 8 10.3 and 10.8, 4096, 512, 64 32.4 and 27.1; 16.8 MB, 8192, 512, 8 14.4 and 12.7.
 inline int gate_dx_tokens(int64_t T, int64_t row_bytes) { return T * row_bytes >= 8000000 ? 16 : 4; }
 
 }  // namespace moe
