@@ -53,7 +53,8 @@ int64_t moe_capacity(int64_t T, int64_t E, int k, double f);
 size_t moe_gate_workspace_bytes(int64_t T, int64_t E, int k);
 
 /* Bytes of workspace moe_layer_forward needs: gate intermediates, the dispatch buffer [E,C,M], the hidden
- * activations [E,C,H] and the expert output [E,C,M].  0 on invalid arguments. */
+ * activations [E,C,H] and the expert output [E,C,M].  Only a call that times its stages writes the dispatch buffer, but the
+ * workspace holds it for every call.  0 on invalid arguments. */
 size_t moe_layer_workspace_bytes(int64_t T, int64_t M, int64_t H, int64_t E, int k, int64_t C, int dtype);
 
 /* Gating function, linear part (Sec. 2.1):  logits[t,e] = sum_m x[t,m] * Wg[m,e] + gate_bias[e].
