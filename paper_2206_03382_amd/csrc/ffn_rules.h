@@ -83,7 +83,11 @@ static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M,
 //   base + fix * rounds + ksteps * max(lat * rounds, thr * tiles per unit),    rounds = tiles per unit / blocks per unit
 // with constants fitted to 694 measured launches (4-128 experts, 8-4096 rows each, K and N 768-4096, with and without a
 // transposed A).  Over those the choice is 2.8 % (2.3 % for weight gradients) off the best of the three on average, against
-// 21 % (24 %) for always taking the largest tile.  64 x 128 (two blocks) came later, for the launches between: two products of
+// 21 % (24 %) for always taking the largest tile.  They are launches by themselves, without an activation: products that follow each
+// other run at the board's power limit, and take 1.2-1.7 times the estimate on the 256 tile (ViT layer 200 us where 134 are
+// estimated, 16384 tokens on 8 experts 316 and 208; 128 x 128, 17 experts x 353 rows, 48 and 28).  The choice holds there all the
+// same: without the 256 tile whole forward passes take 451 us (ViT), 740 (mid), 477 (Zipf gate) and 23650 (131072 tokens, top-8)
+// against 434, 667, 392 and 18900, training steps 2404 and 20750 against 2035 and 16020.  64 x 128 (two blocks) came later, for the launches between: two products of
 // 8 experts x 96 rows, K = N = 2048: 68 (128 x 128) and 61 us (64 x 64) -> 53.
 //
 // Experts of so few rows that one tile holds them read their weights once, and that is all their launch does: 64 x 128 with the
