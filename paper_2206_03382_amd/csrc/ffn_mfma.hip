@@ -5,18 +5,22 @@
 //   fp32 accumulation, rows_e = min(counts[e], C) (or C).  Requires K % 64 == 0 and N % 256 == 0.
 //
 // Tiling: one 256-thread block (4 waves, one per SIMD) owns a 256 x 256 output tile; waves form a 2 x 2 grid, each
-// owning 128 x 128 as 4 x 4 tiles of v_mfma_f32_32x32x16_bf16 (256 accumulator registers per lane).  Large wave tiles
+// owning 128 x 128 as 8 x 8 tiles of v_mfma_f32_16x16x32_bf16 (256 accumulator registers per lane).  Large wave tiles
 // keep LDS->register traffic, the scarce resource on this chip, at 2 x 128 x 2 bytes per k per wave.  K advances in
 // steps of 64 through a two-stage LDS ring (2 x 64 KB) filled by direct global->LDS loads (16 bytes per lane, no
-// staging registers).  Within a wave every MFMA is followed by at most one LDS read or one direct load, so the
+// staging registers).  Within a wave every MFMA is followed by at most one LDS read and one direct load, so the
 // data movement of the next sub-step hides in the shadow of the current sub-step's MFMAs; one workgroup barrier per
-// K-step hands the LDS stages over.
+// K-step hands the LDS stages over.  With 4 x 4 tiles of v_mfma_f32_32x32x16_bf16, which takes more power for the same
+// product, the same schedule ran at 1.63 GHz where this one runs at 1.95: 8192^3 (two products) 1528 -> 1448 us, 8 experts x
+// 4096 rows, 2048 x 2048 483 -> 467 us, 32 experts x 8192 rows, 4096 x 1024 3994 -> 3857 us.  What is left is the way from L2
+// into LDS: without the direct loads the same products take 0.79 of the time.
 //
 // LDS layouts (both written by the direct loads, which place lane l's 16 bytes at base + 16 l):
 //   A tile  [256 rows][8 chunks of 8 k]:   chunk g of row r is stored at chunk position g ^ ((r / 2) % 8), so the 16 lanes
 //           that share an LDS cycle of a ds_read_b128 (16 consecutive rows, same g) cover all 64 banks once.
-//   B tile  [64 k][32 chunks of 8 n]:      chunk c of row k is stored at position c ^ (4 (k % 4)); the two 16-lane
-//           blocks of a ds_read_b64_tr_b16 that share a cycle (4 k rows x 32 bytes each) then cover all banks once.
+//   B tile  [64 k][32 chunks of 8 n]:      chunk c of row k is stored at position c ^ (4 (k % 4)) ^ (2 (k / 8 % 2)); the two
+//           16-lane blocks of a ds_read_b64_tr_b16 that share a cycle (4 k rows x 32 bytes each, 8 k apart) then cover all
+//           banks once.
 // B is K x N with N contiguous, but the matrix cores want k-contiguous operands: ds_read_b64_tr_b16 transposes
 // 4 k x 16 n sub-blocks on the way out of LDS (source lane s of a 16-lane block supplies row k0 + s/4,
 // columns n0 + 4 (s%4) .. +3; result lane l holds column n0 + l, rows k0 .. k0+3).
@@ -33,7 +37,7 @@
 //        past the fill.
 //
 // The two MFMA operands are passed swapped (B fragment first), so that a lane's accumulator registers hold four
-// consecutive output columns of one row: D'[n][m] with m = lane % 32, n = 8 (v/4) + 4 (lane/32) + v % 4.  The
+// consecutive output columns of one row: D'[n][m] with m = lane % 16, n = 4 (lane/16) + v.  The
 // epilogue packs them to 8 bytes, transposes the wave's 128 x 128 tile through LDS and stores whole 256-byte row pieces.
 #include <cmath>
 #include <type_traits>
@@ -47,6 +51,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short short4v;
 typedef __attribute__((ext_vector_type(8))) short short8v;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
@@ -57,6 +62,11 @@ constexpr int kThreads = 256;
 constexpr int kStageBytes = 65536;          // A tile 32 KB + B tile 32 KB
 constexpr int kATileBytes = 32768;
 constexpr int kLoadsPerWave = 16;           // 64 KB per K-step / (4 waves x 1 KB per wave-load)
+// Schedule of a K-step's 128 products per wave: the LDS reads of the next sub-step spread over a sub-step's first 48 products,
+// the barrier behind the 57th of the first sub-step, a direct load of the K-step after next behind every fourth product from
+// there on.  One load behind every second product: 5 % slower (the four waves' loads queue up); reads over 32 or 40 products,
+// a load behind every third or fifth, the barrier 8 to 16 products earlier: up to 2 % slower.
+constexpr int kReadSpan = 48, kBarrierAt = 56, kLoadEvery = 4;
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 #define PIN() __builtin_amdgcn_sched_barrier(0)
 
@@ -120,7 +130,7 @@ template <int ACT> __device__ __forceinline__ float epilogue_act(float v) {
 }
 
 struct Frags {
-  bf16x8 a[4], b[4];
+  bf16x8 a[8], b[8];
 };
 
 // Inclusive prefix sum over the 64 lanes with data-parallel primitives (shifts inside rows of 16 lanes, then the rows'
@@ -206,18 +216,18 @@ __device__ __forceinline__ int find_tile(int b, int lane, int E, int64_t C, cons
 
 
 // ---- main loop -------------------------------------------------------------------------------------------------
-// K-step kt (64 wide) is four sub-steps of 16 MFMAs.  While sub-step s computes from one fragment buffer, the 12 LDS
-// reads of sub-step s+1 fill the other.  The direct loads of K-step kt+2 go into the stage K-step kt is read from, so
-// they may start only after the barrier that follows the last read of that stage (issued during sub-step 2): 8 of a
-// wave's 16 loads are issued in sub-step 3 of K-step kt, the other 8 in sub-step 0 of K-step kt+1, and they are
-// waited for before the barrier of K-step kt+1, two sub-steps later.
+// K-step kt (64 wide) is two sub-steps of 64 MFMAs.  While sub-step s computes from one fragment buffer, the LDS reads of
+// sub-step s+1 (24, or 16 / 32 with no / two transposed operands) fill the other.  The direct loads of K-step kt+2 go into the
+// stage K-step kt is read from, so they may start only after the barrier that follows the last read of that stage, at the
+// end of sub-step 0; a wave's 16 loads are issued from there to the end of sub-step 1 and waited for before the barrier of
+// K-step kt+1, most of a sub-step after the last of them.
 // GK (kTN only): the k-rows of A are gathered.  K-step t's row 2 (4 q + wave) + kg is row gk.rows[64 t + ...] of the
 // matrix at a_base (row length gk.row_bytes); a_voff[0] then holds the lane's offset into the side buffer for q = 0.
 struct GatherK {
   const int32_t* rows;          // this expert's slot -> row map (uniform)
   uint32_t row_bytes;           // bytes per row of the gathered matrix
   uint32_t nrows;               // rows of the gathered matrix (indices outside read row 0)
-  uint32_t col;                 // per lane: byte offset of its 16-byte piece inside a row
+  uint32_t col;                 // per lane: byte offset of its 16-byte piece inside a row, for even q (odd q: the swizzle's 2 (k / 8 % 2), 32 bytes)
   uint32_t tail_step;           // bytes between the side buffer's k-rows of consecutive q
 };
 // FAR: A's rows lie up to 64 GiB apart (gathered from a token matrix beyond 4 GiB): offsets count 16-byte pieces, and a load takes
@@ -227,45 +237,43 @@ template <int NI, int MODE, bool GK = false, bool FAR = false>
 __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, const char* b_base, const char* a_last,
                                                const char* b_last, const uint32_t (&a_voff)[8],
                                                const uint32_t (&b_voff)[8], int64_t a_step, int64_t b_step,
-                                               const int (&a_off)[4], const int (&b_off)[4], int a_swz, int kg,
+                                               const int (&a_off)[8], const int (&b_off)[8], int kg, int kq,
                                                int a_mask, int wave, int KT, const uint16_t* bias_w,
-                                               f32x16 (&acc)[4][4], const GatherK& gk = GatherK{}) {
+                                               f32x4 (&acc)[8][8], const GatherK& gk = GatherK{}) {
   constexpr bool FULL = NI == 4;
   constexpr bool TRA = MODE == kTN;          // A through transposing reads (two per fragment)
   constexpr bool TRB = MODE != kNT;          // B through transposing reads
-  constexpr int NRA = TRA ? 8 : 4, NRB = TRB ? 8 : 4, NR = NRA + NRB;   // LDS reads per sub-step
+  constexpr int NRA = TRA ? 16 : 8, NRB = TRB ? 16 : 8, NR = NRA + NRB;   // LDS reads per sub-step
+  constexpr int PA = TRA ? 2 : 1;
   Frags f[2];
   const uint32_t smem_addr = (uint32_t)(uintptr_t)LDS_PTR(char, smem);
 
-  // read number r (0 .. NR-1) of sub-step s from `stage` into fragment buffer `d`: first A's, then B's.  A direct read
-  // fetches a lane's 8 k of one row (ds_read_b128); a transposed fragment takes two reads of 4 k each.
-  auto read_direct = [&](const char* stage, int off, int s) -> bf16x8 {
-    return *LDS_PTR(bf16x8, stage + off + (((2 * s + kg) ^ a_swz) << 4));
+  // read number r (0 .. NR-1) of sub-step s (32 k) from `stage` into fragment buffer `d`: the first of A, then B's, then the
+  // rest of A's, the order in which the products want them.  A direct read fetches a lane's 8 k of one row (ds_read_b128; off[s]
+  // is the lane's address of sub-tile 0); a transposed fragment takes two reads of 4 k each (off[t] is sub-tile t's address).
+  auto read_direct = [&](const char* stage, const int (&off)[8], int t, int s) -> bf16x8 {
+    return *LDS_PTR(bf16x8, stage + off[s] + t * 2048);
   };
-  auto read_tr = [&](const char* stage, int off, int s, int half) -> short4v {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(short4v, stage + off + (16 * s + 4 * half) * 512));
+  auto read_tr = [&](const char* stage, const int (&off)[8], int t, int s, int half) -> short4v {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(LDS_PTR(short4v, stage + off[t] + (32 * s + 4 * half) * 512));
   };
   auto join = [](short4v lo, short4v hi) -> bf16x8 {
     return __builtin_bit_cast(bf16x8, (short8v)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  auto read = [&](const char* stage, int s, int r, Frags& d, short4v (&lo)[8]) {
-    if (r < NRA) {
-      if (!TRA) {
-        if (r < NI) d.a[r] = read_direct(stage, a_off[r], s);
-      } else {
-        const int i = r >> 1;
-        if ((r & 1) == 0) lo[i] = read_tr(stage, a_off[i], s, 0);
-        else d.a[i] = join(lo[i], read_tr(stage, a_off[i], s, 1));
+  auto read = [&](const char* stage, int s, int r, Frags& d, short4v& lo) {
+    const bool is_b = r >= PA && r < PA + NRB;
+    if (is_b) {
+      const int rb = r - PA;
+      if (NI > 0) {
+        if (!TRB) d.b[rb] = read_direct(stage, b_off, rb, s);
+        else if ((rb & 1) == 0) lo = read_tr(stage, b_off, rb >> 1, s, 0);
+        else d.b[rb >> 1] = join(lo, read_tr(stage, b_off, rb >> 1, s, 1));
       }
-    } else if (NI > 0) {
-      const int rb = r - NRA;
-      if (!TRB) {
-        d.b[rb] = read_direct(stage, b_off[rb], s);
-      } else {
-        const int j = rb >> 1;
-        if ((rb & 1) == 0) lo[4 + j] = read_tr(stage, b_off[j], s, 0);
-        else d.b[j] = join(lo[4 + j], read_tr(stage, b_off[j], s, 1));
-      }
+    } else {
+      const int ra = r < PA ? r : r - NRB;
+      if (!TRA) { if (ra < 2 * NI) d.a[ra] = read_direct(stage, a_off, ra, s); }
+      else if ((ra & 1) == 0) lo = read_tr(stage, a_off, ra >> 1, s, 0);
+      else d.a[ra >> 1] = join(lo, read_tr(stage, a_off, ra >> 1, s, 1));
     }
   };
   // direct load number idx (0..15: A0..A7, B0..B7) of K-step `tile` (the caller guarantees tile < KT).  With a
@@ -282,10 +290,10 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       if (tail) {
-        g[q] = (a_voff[0] + q * gk.tail_step) >> (FAR ? 4 : 0);
+        g[q] = ((a_voff[0] ^ (32 * (q & 1))) + q * gk.tail_step) >> (FAR ? 4 : 0);
       } else {
         const uint32_t r = g[q] < gk.nrows ? g[q] : 0u;
-        g[q] = r * (gk.row_bytes >> (FAR ? 4 : 0)) + (gk.col >> (FAR ? 4 : 0));
+        g[q] = r * (gk.row_bytes >> (FAR ? 4 : 0)) + ((gk.col ^ (32 * (q & 1))) >> (FAR ? 4 : 0));
       }
     }
   };
@@ -311,44 +319,46 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
     }
   };
   auto mfma = [&](int m, const Frags& c) {
-    const int i = m >> 2, j = m & 3;
-    if (i < NI) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(c.b[j], c.a[i], acc[i][j], 0, 0, 0);
+    const int i = m >> 3, j = m & 7;
+    if (i < 2 * NI) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c.b[j], c.a[i], acc[i][j], 0, 0, 0);
   };
-  // one sub-step: 16 MFMAs from `c`, interleaved with the NR reads of (stage, s_next) into `n` (if READS) and with the
-  // direct loads dma_first .. dma_first+7 of K-step dma_tile (if DMA); both switches are compile-time so that the
-  // steady-state loop body is branch-free
-  auto substep = [&](auto reads_tag, auto dma_tag, const Frags& c, Frags& n, const char* stage, int s_next, int dma_first,
-                     int dma_tile) {
-    constexpr bool READS = decltype(reads_tag)::value, DMA = decltype(dma_tag)::value;
-    short4v lo[8];
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      mfma(m, c);
-      PIN();
-      if (READS && m < NR) read(stage, s_next, m, n, lo);
-      if (DMA && (m & 1) == 1) dma(dma_first + (m >> 1), dma_tile);
-      PIN();
-    }
-  };
-  using T_ = std::true_type;
-  using F_ = std::false_type;
-  // one K-step; DMA0: second half of the loads of K-step kt+1 (sub-step 0), DMA3: first half of K-step kt+2
-  // (sub-step 3), NEXT: a K-step kt+1 exists
-  // TAIL (gathered A only): K-step kt+2 is the last one
-  auto kstep = [&](auto dma0_tag, auto dma3_tag, auto next_tag, int kt, auto tail_tag) {
-    constexpr bool TAIL = decltype(tail_tag)::value;
+  // One K-step; DMA: a K-step kt+2 exists; NEXT: a K-step kt+1 exists, or the reads ahead find a stage that holds nothing new and
+  // are not used.  Every body more makes the compiler move accumulators around between them (with two transposed operands every
+  // one less makes it spill).
+  auto kstep = [&](auto dma_tag, auto next_tag, int kt, auto tail_tag) __attribute__((always_inline)) {
+    constexpr bool DMA = decltype(dma_tag)::value, NEXT = decltype(next_tag)::value;
     const char* cur = smem + (kt & 1) * kStageBytes;
     const char* nxt = smem + ((kt + 1) & 1) * kStageBytes;
-    if (GK && decltype(dma3_tag)::value && !TAIL) { gather_fetch(kt + 2, gv); PIN(); }
-    substep(T_{}, dma0_tag, f[0], f[1], cur, 1, 8, kt + 1);
-    substep(T_{}, F_{}, f[1], f[0], cur, 2, 0, 0);
-    substep(T_{}, F_{}, f[0], f[1], cur, 3, 0, 0);
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");      // K-step kt+1 has landed; reads of `cur` are done
-    PIN();
-    asm volatile("s_barrier" ::: "memory");
-    PIN();
-    if (GK && decltype(dma3_tag)::value) { gather_offsets(TAIL, gv); PIN(); }   // nothing else is in flight here
-    substep(next_tag, dma3_tag, f[1], f[0], nxt, 0, 0, kt + 2);
+    constexpr bool tail = decltype(tail_tag)::value;                // gathered A: K-step kt+2 is the last one
+    if (GK && DMA && !tail) { gather_fetch(kt + 2, gv); PIN(); }
+    short4v lo;
+    auto read_at = [&](int m) { const int r = (m * NR + kReadSpan - 1) / kReadSpan; return r < ((m + 1) * NR + kReadSpan - 1) / kReadSpan ? r : NR; };
+    auto loads = [&](int p) {                                       // p: products since the barrier
+      if (DMA && p % kLoadEvery == 1 && p / kLoadEvery < kLoadsPerWave) dma(p / kLoadEvery, kt + 2);
+    };
+#pragma unroll
+    for (int m = 0; m < 64; ++m) {
+      mfma(m, f[0]);
+      PIN();
+      if (const int r = read_at(m); r < NR) read(cur, 1, r, f[1], lo);
+      if (m == kBarrierAt) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // K-step kt+1 has landed; reads of `cur` are done
+        PIN();
+        asm volatile("s_barrier" ::: "memory");
+        PIN();
+        if (GK && DMA) { gather_offsets(tail, gv); PIN(); }          // nothing else is in flight here
+      }
+      if (m > kBarrierAt) loads(m - kBarrierAt);
+      PIN();
+    }
+#pragma unroll
+    for (int m = 0; m < 64; ++m) {
+      mfma(m, f[1]);
+      PIN();
+      if (const int r = read_at(m); NEXT && r < NR) read(nxt, 0, r, f[0], lo);
+      loads(m + 64 - kBarrierAt);
+      PIN();
+    }
   };
 
   uint32_t gv1[8];
@@ -368,23 +378,17 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
 #pragma unroll
     for (int idx = 0; idx < kLoadsPerWave; ++idx) dma(idx, 1);
   }
-  // while the first stages are in flight: the accumulators start from the bias (register 4 g + u of tile (i, j) is
-  // column 32 j + 8 g + 4 kg + u of the wave's 128), or from zero
+  // while the first stages are in flight: the accumulators start from the bias (register u of tile (i, j) is column
+  // 16 j + 4 kq + u of the wave's 128), or from zero
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      float b0 = 0.f, b1 = 0.f, b2 = 0.f, b3 = 0.f;
-      if (bias_w) {
-        const u32x2 bb = *reinterpret_cast<const u32x2*>(bias_w + j * 32 + 8 * g + 4 * kg);
-        b0 = __uint_as_float(bb.x << 16); b1 = __uint_as_float(bb.x & 0xffff0000u);
-        b2 = __uint_as_float(bb.y << 16); b3 = __uint_as_float(bb.y & 0xffff0000u);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (i < NI) { acc[i][j][4 * g] = b0; acc[i][j][4 * g + 1] = b1; acc[i][j][4 * g + 2] = b2; acc[i][j][4 * g + 3] = b3; }
-      }
+  for (int j = 0; j < 8; ++j) {
+    f32x4 b = {0.f, 0.f, 0.f, 0.f};
+    if (bias_w) {
+      const u32x2 bb = *reinterpret_cast<const u32x2*>(bias_w + j * 16 + 4 * kq);
+      b = f32x4{__uint_as_float(bb.x << 16), __uint_as_float(bb.x & 0xffff0000u), __uint_as_float(bb.y << 16), __uint_as_float(bb.y & 0xffff0000u)};
     }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) if (i < 2 * NI) acc[i][j] = b;
   }
   PIN();
   if (KT > 1) {
@@ -397,29 +401,25 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
   asm volatile("s_barrier" ::: "memory");
   PIN();
   {
-    short4v lo[8];
+    short4v lo;
 #pragma unroll
     for (int r = 0; r < NR; ++r) read(smem, 0, r, f[0], lo);
   }
   PIN();
 
-  if (KT >= 3) {
-    if (GK) {                                                        // the K-step that loads the last one is peeled as well
-      if (KT == 3) kstep(F_{}, T_{}, T_{}, 0, T_{});
-      else kstep(F_{}, T_{}, T_{}, 0, F_{});
-      for (int kt = 1; kt < KT - 3; ++kt) kstep(T_{}, T_{}, T_{}, kt, F_{});
-      if (KT > 3) kstep(T_{}, T_{}, T_{}, KT - 3, T_{});
-    } else {
-      kstep(F_{}, T_{}, T_{}, 0, F_{});                              // K-step 1 was loaded whole in the prologue
-      for (int kt = 1; kt < KT - 2; ++kt) kstep(T_{}, T_{}, T_{}, kt, F_{});
-    }
-    kstep(T_{}, F_{}, T_{}, KT - 2, F_{});                           // no K-step KT to load
-    kstep(F_{}, F_{}, F_{}, KT - 1, F_{});
-  } else if (KT == 2) {
-    kstep(F_{}, F_{}, T_{}, 0, F_{});
-    kstep(F_{}, F_{}, F_{}, 1, F_{});
+  using T_ = std::true_type;
+  using F_ = std::false_type;
+  int kt = 0;
+  for (; kt < KT - (GK ? 3 : 2); ++kt) kstep(T_{}, T_{}, kt, F_{});
+  if constexpr (GK) {
+    if (kt < KT - 2) kstep(T_{}, T_{}, kt++, T_{});
+  }
+  if constexpr (MODE == kTN) {
+    if (kt < KT - 1) kstep(F_{}, T_{}, kt++, F_{});
+    kstep(F_{}, F_{}, kt, F_{});
   } else {
-    kstep(F_{}, F_{}, F_{}, 0, F_{});
+#pragma unroll 1
+    for (; kt < KT; ++kt) kstep(F_{}, T_{}, kt, F_{});
   }
 }
 
@@ -499,7 +499,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
     const int r = (q * 4 + wave) * 8 + (lane >> 3);                 // row of a k-contiguous tile
     const int g = (lane & 7) ^ ((r >> 1) & 7);                      // global chunk that lands at position lane % 8
     const int kr = (q * 4 + wave) * 2 + (lane >> 5);                // k-row of a k-slow tile
-    const int c = (lane & 31) ^ (4 * (kr & 3));
+    const int c = (lane & 31) ^ (4 * (kr & 3)) ^ (2 * ((kr >> 3) & 1));
     if (MODE == kTN) {
       a_mask |= 1 << q;
       a_voff[q] = (uint32_t)(((int64_t)kr * C + m0 + c * 8) * 2);
@@ -520,32 +520,31 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
   const int64_t b_step = MODE == kNT ? (int64_t)BK * 2 : (int64_t)BK * N * 2;
 
   // ---- LDS read offsets of this lane's MFMA fragments ------------------------------------------------------------
-  // direct (k-contiguous tile): row * 128, + ((2 s + kg) ^ a_swz) * 16 per sub-step s
-  // transposed (k-slow tile):   k-row * 512 + swizzled 16-byte chunk + 8-byte half, + (16 s + 4 half) * 512
-  const int kg = lane >> 5;
-  const int a_swz = ((lane & 31) >> 1) & 7;                         // ((row >> 1) & 7): tile-row offsets are multiples of 32
-  auto direct_off = [&](int w, int t) { return (w * 128 + t * 32 + (lane & 31)) * 128; };
+  // direct (k-contiguous tile): row * 128 + ((4 s + kq) ^ (row / 2 % 8)) * 16, one per sub-step s (sub-tile 0; 2048 bytes apart)
+  // transposed (k-slow tile):   k-row * 512 + swizzled 16-byte chunk + 8-byte half, one per sub-tile, + (32 s + 4 half) * 512
+  const int kg = lane >> 5, kq = lane >> 4;
+  auto direct_off = [&](int w, int s) { return (w * 128 + (lane & 15)) * 128 + (((4 * s + kq) ^ ((lane & 15) >> 1)) << 4); };
   auto tr_off = [&](int w, int t) {
-    const int c = w * 16 + t * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
-    const int swz = 4 * ((lane >> 2) & 3);                          // 4 (k & 3), k & 3 = (lane % 16) / 4
-    return (kg * 8 + ((lane & 15) >> 2)) * 512 + ((c ^ swz) << 4) + ((lane & 1) << 3);
+    const int kr = (lane & 15) >> 2;                                // k % 4 of the row this lane supplies; k / 8 % 2 = kq % 2
+    const int c = w * 16 + t * 2 + ((lane & 3) >> 1);
+    return (kq * 8 + kr) * 512 + ((c ^ (4 * kr) ^ (2 * (kq & 1))) << 4) + ((lane & 1) << 3);
   };
-  int a_off[4], b_off[4];
+  int a_off[8], b_off[8];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    a_off[i] = MODE == kTN ? tr_off(wm, i) : direct_off(wm, i);
-    b_off[i] = kATileBytes + (MODE == kNT ? direct_off(wn, i) : tr_off(wn, i));
+  for (int i = 0; i < 8; ++i) {
+    a_off[i] = MODE == kTN ? tr_off(wm, i) : direct_off(wm, i & 1);
+    b_off[i] = kATileBytes + (MODE == kNT ? direct_off(wn, i & 1) : tr_off(wn, i));
   }
   // 32-row sub-tiles of this wave that hold real rows (the last row tile of an expert is usually ragged)
   const int64_t wave_rows = rows - m0 - wm * 128;
   const int ni = wave_rows >= 128 ? 4 : (wave_rows <= 0 ? 0 : (int)((wave_rows + 31) >> 5));
 
-  f32x16 acc[4][4];
+  f32x4 acc[8][8];
   const uint16_t* bias_w = bias ? bias + (int64_t)e * N + n0 + wn * 128 : nullptr;
 
   // the number of live sub-tiles is a template argument, so that the loop body of a ragged tile is as branch-free as a
   // full one's (a wave with no rows still loads its share of B and joins the barriers)
-#define MOE_TILE_LOOP(NI) tile_main_loop<NI, MODE, false, FAR && MODE == kNN>(smem, a_base, b_base, a_last, b_last, a_voff, b_voff, a_step, b_step, a_off, b_off, a_swz, kg, a_mask, wave, KT, bias_w, acc)
+#define MOE_TILE_LOOP(NI) tile_main_loop<NI, MODE, false, FAR && MODE == kNN>(smem, a_base, b_base, a_last, b_last, a_voff, b_voff, a_step, b_step, a_off, b_off, kg, kq, a_mask, wave, KT, bias_w, acc)
   if (MODE == kTN && GK) {
     GatherK gk;
     gk.rows = gather + (int64_t)e * K;
@@ -553,7 +552,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
     gk.nrows = (uint32_t)gather_rows;
     gk.col = a_voff[0] - (uint32_t)((wave * 2 + kg) * C * 2);       // (m0 + 8 c) * 2: the k-row term taken out again
     gk.tail_step = (uint32_t)(8 * C * 2);
-    tile_main_loop<4, MODE, true, FAR>(smem, a_base, b_base, a_last, b_last, a_voff, b_voff, a_step, b_step, a_off, b_off, a_swz, kg,
+    tile_main_loop<4, MODE, true, FAR>(smem, a_base, b_base, a_last, b_last, a_voff, b_voff, a_step, b_step, a_off, b_off, kg, kq,
                                   a_mask, wave, KT, bias_w, acc, gk);
   } else if (MODE == kTN) {                                         // output rows are a weight dimension: never ragged
     MOE_TILE_LOOP(4);
@@ -581,23 +580,18 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
   auto write_tile = [&](auto raw_tag, uint16_t* dst) {
     constexpr bool RAW = decltype(raw_tag)::value;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (i >= ni) break;
-      const int r = i * 32 + (lane & 31);
+    for (int i = 0; i < 8; ++i) {
+      if (i >= 2 * ni) break;
+      const int r = i * 16 + (lane & 15);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < 8; ++j) {
+        float v[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float v[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = acc[i][j][4 * g + u];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) v[u] = epilogue_act<(GRAD || RAW) ? -1 : ACT>(v[u]);
-          u32x2 pk;
-          pk.x = pack_bf16x2(v[0], v[1]);
-          pk.y = pack_bf16x2(v[2], v[3]);
-          *LDS_PTR(u32x2, wtile + r * 256 + (((4 * j + g) ^ (r & 15)) << 4) + 8 * kg) = pk;
-        }
+        for (int u = 0; u < 4; ++u) v[u] = epilogue_act<(GRAD || RAW) ? -1 : ACT>(acc[i][j][u]);
+        u32x2 pk;
+        pk.x = pack_bf16x2(v[0], v[1]);
+        pk.y = pack_bf16x2(v[2], v[3]);
+        *LDS_PTR(u32x2, wtile + r * 256 + (((2 * j + (kq >> 1)) ^ (r & 15)) << 4) + 8 * (kq & 1)) = pk;
       }
     }
     uint16_t* oute = dst + out_at;
