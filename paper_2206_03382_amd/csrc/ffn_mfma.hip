@@ -151,7 +151,7 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
 // live group, kTileIdle for an idle slot of a short group, kTileLive otherwise with the expert, its row and column tile and
 // the expert's number of real rows.
 constexpr int kTileLive = 0, kTileIdle = 1, kTileNone = 2;
-template <int TILE_ROWS>
+template <int TILE_ROWS, int GROUP_SHIFT = 0>
 __device__ __forceinline__ int find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
                                          int& e_out, int& mt_out, int& nt_out, int& rows_out) {
   auto live_rows = [&](int el) -> int {                             // rows of expert el that exist (its fill, at most C)
@@ -172,7 +172,7 @@ __device__ __forceinline__ int find_tile(int b, int lane, int E, int64_t C, cons
     if (c * 64 >= E) break;
     live_tiles += __builtin_amdgcn_readlane(wave_inclusive_scan(mtv[c] * NT), 63);
   }
-  const int gs = group_size_log2(live_tiles), G = 1 << gs;          // tiles per group
+  const int gs = group_size_log2(live_tiles >> GROUP_SHIFT) + GROUP_SHIFT, G = 1 << gs;   // tiles per group
   const int group = ((b / 8) >> gs) * 8 + b % 8, slot = (b / 8) & (G - 1);
   int total_full = 0;                                               // full groups of all experts
 #pragma unroll
@@ -213,6 +213,7 @@ __device__ __forceinline__ int find_tile(int b, int lane, int E, int64_t C, cons
 }
 
 #include "ffn_tile.h"
+#include "ffn_half.h"
 
 
 // ---- main loop -------------------------------------------------------------------------------------------------
@@ -659,11 +660,14 @@ __global__ __launch_bounds__(256) void tail_rows_kernel(const TailRows a, const 
     dst[((int64_t)e * BK + j) * cpr + ch] = slot < fill ? src[row * cpr + ch] : make_uint4(0, 0, 0, 0);
 }
 
+// `mean`: rows an expert holds on average (for half_tile); `total`: rows of all experts that exist, at most.
 static hipError_t launch_large_nn(const void* A, const void* B, const void* bias, int act, const int32_t* counts,
-                                  int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, int64_t total,
+                                  int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, double mean, int64_t total,
                                   const int32_t* gather, int64_t gather_rows, void* pre_out) {
-  const int MT = (int)ceil_div(C, BM), NT = (int)(N / BN);
-  const int64_t blocks = tile_grid(E, MT, NT, live_row_tiles(E, C, total, BM));
+  const bool half = half_tile(E, C, mean, K, N) && !far_rows(gather_rows, K) && !pre_out;
+  const int64_t bm = half ? BM / 2 : BM;
+  const int MT = (int)ceil_div(C, bm), NT = (int)(N / BN);
+  const int64_t blocks = tile_grid(E, MT, NT, live_row_tiles(E, C, total, bm), half ? kHalfGroupShift : 0);
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
 #define MOE_LAUNCH_GEMM_AT(ACT, DUAL, FAR)                                                                            \
@@ -671,7 +675,14 @@ static hipError_t launch_large_nn(const void* A, const void* B, const void* bias
       (const uint16_t*)A, (const uint16_t*)B, (const uint16_t*)bias, counts, gather, (int)gather_rows, (int)E, C,     \
       (int)K, (int)N, MT, NT, (uint16_t*)out, nullptr, nullptr, nullptr, nullptr,                                       \
       (uint16_t*)pre_out)
-#define MOE_LAUNCH_GEMM(ACT, DUAL) do { if (far_rows(gather_rows, K)) MOE_LAUNCH_GEMM_AT(ACT, DUAL, true); else MOE_LAUNCH_GEMM_AT(ACT, DUAL, false); } while (0)
+#define MOE_LAUNCH_GEMM(ACT, DUAL)                                                                                    \
+  do {                                                                                                                \
+    if (half)                                                                                                         \
+      grouped_gemm_half_kernel<ACT><<<grid, block, 0, s>>>((const uint16_t*)A, (const uint16_t*)B, (const uint16_t*)bias, \
+                                                           counts, gather, (int)gather_rows, (int)E, C, (int)K, (int)N, MT, NT, (uint16_t*)out); \
+    else if (far_rows(gather_rows, K)) MOE_LAUNCH_GEMM_AT(ACT, DUAL, true);                                            \
+    else MOE_LAUNCH_GEMM_AT(ACT, DUAL, false);                                                                        \
+  } while (0)
   if (pre_out && act >= 0) {
     switch (act) {
       case MOE_ACT_RELU: MOE_LAUNCH_GEMM(MOE_ACT_RELU, true); break;
@@ -758,7 +769,7 @@ hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, i
   if (act < 0) pre_out = nullptr;                                   // nothing to tell apart
   const Tile tile = dtype == MOE_BF16 ? tile_of(kNN, E, C, K, N, rows_hint, gather ? gather_rows : 0) : Tile::k64;
   const int64_t total = total_rows(counts, E, C, rows_hint);
-  if (tile == Tile::k256) return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, total, gather, gather_rows, pre_out);
+  if (tile == Tile::k256) return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, mean_or(rows_hint, C), total, gather, gather_rows, pre_out);
   if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports(E, C, K, N, 0)) act += kFullAct;
   const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, 0, out, nullptr, nullptr, pre_out, act, 0};
   return launch_small<kNN>(dtype, tile, p, total, s);

@@ -36,19 +36,22 @@ static inline int64_t live_row_tiles(int64_t E, int64_t C, int64_t total, int64_
   return n < full ? n : full;
 }
 
+// The half tile (128 x 256) has two blocks on a unit: groups of twice as many tiles cover the same rows and columns.
+constexpr int kHalfGroupShift = 1;
+
 // Blocks to launch so that every tile is reached whatever the fills turn out to be and whichever group size they select: E experts
 // of at most MT x NT tiles, of which at most `row_tiles` row tiles are live in all.  A group has G blocks, groups are dealt to
 // 8 XCDs, and an expert ends in one short group at most.
 // The layer knows its total (every choice is one row).  Without it the grid has to hold C rows of every expert, and where the
 // capacity is far above the mean fill nearly all blocks find nothing to do, each after a tile search and holding its LDS: dynamic
 // capacity, buffers for all 2048 tokens, 128 experts, M = 4096, H = 1024: layer 746 us, 487 with the bound.
-static inline int64_t tile_grid(int64_t E, int64_t MT, int64_t NT, int64_t row_tiles) {
+static inline int64_t tile_grid(int64_t E, int64_t MT, int64_t NT, int64_t row_tiles, int shift = 0) {
   const int64_t most = row_tiles * NT;                              // live tiles
   int64_t blocks = 0;
   for (int gs = 3; gs <= 5; ++gs) {
-    if (gs > group_size_log2(most)) break;                          // too few tiles for this group size
-    const int64_t limit = gs == 3 ? kTilesForGroups16 - 1 : (gs == 4 ? kTilesForGroups32 - 1 : most);
-    const int64_t live = most < limit ? most : limit, G = (int64_t)1 << gs;
+    if (gs > group_size_log2(most >> shift)) break;                 // too few tiles for this group size
+    const int64_t limit = gs == 3 ? (kTilesForGroups16 << shift) - 1 : (gs == 4 ? (kTilesForGroups32 << shift) - 1 : most);
+    const int64_t live = most < limit ? most : limit, G = (int64_t)1 << (gs + shift);
     const int64_t full = E * tiles_in(MT * NT, G), n = live / G + (E < live ? E : live), groups = n < full ? n : full;
     const int64_t b = tiles_in(groups, 8) * 8 * G;
     blocks = b > blocks ? b : blocks;
@@ -95,25 +98,48 @@ static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M,
 // hint alone 202).  Where that leaves units without a block, 64 x 64 one stage deeper (8 experts x 16 rows, 2048 x 2048: 40 -> 33 us).
 // Weights below 48 MB keep the plain loads: they may stay in the caches from one call to the next (17 experts, 776 x 1544,
 // 32 rows: 39 us plain, 41 streamed).
+// The large tile has a half, 128 x 256 with two blocks to a unit (ffn_half.h), which costs more per product and less per tile: Tile::k256
+// stands for either, and half_tile says which.  Its constants were fitted with the others' held to 143 pairs of products (4-64 experts, 150-4130
+// rows each, 512-4096 wide), over which the choice among the three is 0.9 % off the best, against 3.5 % without it: 32 experts x
+// 784 rows, 768 x 3072: 331 -> 285 us; 8 x 1100, 2048 x 2048: 176 -> 166; but 8 x 2048, 2048 x 2048: 245 on the large one, 269 here.
+// Forward products only: with a transposed B (64-byte pieces of k, where the large tile loads 128) it is the slower at nearly every size
+// (backward of 32 x 784 rows: 251 and 198 us against 226 and 171), and a training step's first product, which writes twice, gains nothing (216 against 212).
 enum class Tile { k256, k128, k64x128, k64, k64x128_stream, k64_stream };
+
+static inline double launch_cost(int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N, int bm, int bn, int per_unit, double base,
+                                 double fix, double lat, double thr) {
+  const double ksteps = (mode == kTN ? mean_rows : (double)K) / 64 + 0.5;
+  // an average fill ends in half a tile, but no expert has more row tiles than its slab (without this bound 24 experts x 256
+  // rows, 2048 x 2048, counted as 1.5 tiles each: two products 180 us on smaller tiles, 137 on the large one)
+  const double full = (double)tiles_in(rows, bm), some = mean_rows / bm + 0.5;
+  const double row_tiles = mode == kTN || some > full ? full : (some > 1.0 ? some : 1.0);
+  double q = (double)E * row_tiles * (double)tiles_in(N, bn) / 256.0;               // tiles per compute unit
+  q = q <= 4.0 * per_unit ? ceil(q - 0.02) : q + 0.5;
+  const double rounds = q > per_unit ? q / per_unit : 1.0;
+  return base + fix * rounds + ksteps * (lat * rounds > thr * q ? lat * rounds : thr * q);
+}
+static inline double whole_cost(int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
+  return launch_cost(mode, E, rows, mean_rows, K, N, 256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 1.1);   // kTN: with the launch that pads its last K-step
+}
+static inline double half_cost(int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
+  return launch_cost(mode, E, rows, mean_rows, K, N, 128, 256, 2, 2.0, 4.0, 0.33, 0.72);
+}
+static inline bool half_tile(int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
+  return half_cost(kNN, E, rows, mean_rows, K, N) < whole_cost(kNN, E, rows, mean_rows, K, N);
+}
+
 static inline Tile choose_tile(int mode, bool large_ok, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
   if (mode != kTN && mean_rows <= 48.0 && (double)E * K * N * 2 >= 48e6) return E * tiles_in(N, 128) >= 256 ? Tile::k64x128_stream : Tile::k64_stream;
-  const double ksteps = (mode == kTN ? mean_rows : (double)K) / 64 + 0.5;
   auto cost = [&](int bm, int bn, int per_unit, double base, double fix, double lat, double thr) {
-    // an average fill ends in half a tile, but no expert has more row tiles than its slab (without this bound 24 experts x 256
-    // rows, 2048 x 2048, counted as 1.5 tiles each: two products 180 us on smaller tiles, 137 on the large one)
-    const double full = (double)tiles_in(rows, bm), some = mean_rows / bm + 0.5;
-    const double row_tiles = mode == kTN || some > full ? full : (some > 1.0 ? some : 1.0);
-    double q = (double)E * row_tiles * (double)tiles_in(N, bn) / 256.0;             // tiles per compute unit
-    q = q <= 4.0 * per_unit ? ceil(q - 0.02) : q + 0.5;
-    const double rounds = q > per_unit ? q / per_unit : 1.0;
-    return base + fix * rounds + ksteps * (lat * rounds > thr * q ? lat * rounds : thr * q);
+    return launch_cost(mode, E, rows, mean_rows, K, N, bm, bn, per_unit, base, fix, lat, thr);
   };
   Tile best = Tile::k128;
   double least = cost(128, 128, 2, 1.5, 3.5, 0.3, 0.56);
   auto consider = [&](Tile t, double c) { if (c < least) { least = c; best = t; } };
-  // the weight gradients' large kernel comes with a launch that pads its last K-step
-  if (large_ok) consider(Tile::k256, cost(256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 1.1));
+  if (large_ok) {
+    consider(Tile::k256, whole_cost(mode, E, rows, mean_rows, K, N));
+    if (mode == kNN) consider(Tile::k256, half_cost(mode, E, rows, mean_rows, K, N));
+  }
   if (mode != kTN) {                                                // 64 x 64 was the best tile for one of 278 weight gradients
     consider(Tile::k64x128, cost(64, 128, 2, 2.5, 2.5, 0.3, 0.44));
     consider(Tile::k64, cost(64, 64, 3, 3.0, 1.5, 0.3, 0.235));

@@ -969,6 +969,8 @@ def test_layer_forward_in_hip_graph(moe):
 # ----------------------------------------------------------------------------------------------------------------
 # dispatch fused into the first expert GEMM: same results as encode + FFN on the rows that exist
 # ----------------------------------------------------------------------------------------------------------------
+K256 = 0                                                                      # Tile of csrc/ffn_rules.h
+
 FUSED_LAYERS = [
     synth.CONFIGS[1].scaled(T=1500, M=256, H=512, E=8),
     synth.CONFIGS[2].scaled(T=1960, M=768, H=1024, E=32),
@@ -1001,6 +1003,34 @@ def test_layer_fused_dispatch(moe, cfg):
     assert_routing_equal(layer.routing, ref, ref["C"], cfg.name)
     assert_close(fused, ref["out"], cfg.dtype, f"fused-dispatch layer output ({cfg.name})")
     assert np.array_equal(fused.view(np.uint32), plain.view(np.uint32))       # same arithmetic on the same rows
+
+
+@pytest.mark.parametrize("E,C,M,H", [(64, 1500, 64, 256), (64, 520, 256, 256), (40, 385, 1024, 256), (32, 784, 768, 3072)])
+def test_expert_ffn_half_tile(moe, ffn_rules, E, C, M, H):
+    """The 128 x 256 tile: reductions of 2 to 96 K-steps (fewer than its ring, and more), row tiles of 1 to 8 live 16-row pieces and
+    none, from the dispatch buffer and gathered, against the oracle."""
+    dtype, act = synth.DT_BF16, O.ACT_GELU
+    assert ffn_rules.tile(0, E, C, M, H, 0, 0) == K256 and ffn_rules.half(E, C, M, H, 0)
+    edges = [0, 1, 15, 16, 17, 32, 33, 64, 95, 97, 112, 113, 127, 128, 129, 255, 256, 257, C - 1, C, C + 5]
+    counts = np.array([edges[e % len(edges)] for e in range(E)], dtype=np.int32)
+    cfg = synth.CONFIGS[1].scaled(T=E * C, M=M, H=H, E=E, dtype=dtype, cfg_id=47)
+    inp = synth.make_inputs(cfg, seed=M, bias_std=0.5)
+    Z = inp["x"].reshape(E, C, M)
+    some = np.arange(len(edges))                                              # every edge once: the oracle's share
+    ref = O.expert_ffn(Z[some], inp["W1"][some], inp["b1"][some], inp["W2"][some], inp["b2"][some], act, rows=counts[some])
+    x, W1, b1, W2, b2 = (dev(inp[n], dtype) for n in ("x", "W1", "b1", "W2", "b2"))
+    c = torch.from_numpy(counts).cuda()
+    Yd = torch.full((E, C, M), float("nan"), device="cuda").to(torch.bfloat16)
+    moe.expert_ffn(x.view(E, C, M), W1, b1, W2, b2, act, c, Y=Yd)
+    got = host(Yd)
+    mask = np.arange(C)[None, :] < np.minimum(counts, C)[:, None]
+    assert_close(got[some][mask[some]], ref[mask[some]], dtype, "half tile")
+    assert np.isnan(got[~mask]).all(), "rows past counts[e] must be left untouched"
+    perm = torch.from_numpy(np.random.default_rng(E).permutation(E * C)).cuda()
+    shuffled = torch.empty_like(x)
+    shuffled[perm] = x
+    gathered = host(moe.expert_ffn_gather(shuffled, perm.view(E, C).int(), W1, b1, W2, b2, act, counts=c))
+    assert np.array_equal(gathered[mask].view(np.uint32), got[mask].view(np.uint32))
 
 
 def test_expert_ffn_gather_matches_two_calls(moe):
