@@ -7,13 +7,16 @@
 // Tiling: one 256-thread block (4 waves, one per SIMD) owns a 256 x 256 output tile; waves form a 2 x 2 grid, each
 // owning 128 x 128 as 8 x 8 tiles of v_mfma_f32_16x16x32_bf16 (256 accumulator registers per lane).  Large wave tiles
 // keep LDS->register traffic, the scarce resource on this chip, at 2 x 128 x 2 bytes per k per wave.  K advances in
-// steps of 64 through a two-stage LDS ring (2 x 64 KB) filled by direct global->LDS loads (16 bytes per lane, no
-// staging registers).  Within a wave every MFMA is followed by at most one LDS read and one direct load, so the
+// steps of 64 through LDS rings of two stages for A and three for B (5 x 32 KB, all of a unit's LDS) filled by direct global->LDS
+// loads (16 bytes per lane, no staging registers).  Within a wave every MFMA is followed by at most one LDS read and one direct load, so the
 // data movement of the next sub-step hides in the shadow of the current sub-step's MFMAs; one workgroup barrier per
 // K-step hands the LDS stages over.  With 4 x 4 tiles of v_mfma_f32_32x32x16_bf16, which takes more power for the same
 // product, the same schedule ran at 1.63 GHz where this one runs at 1.95: 8192^3 (two products) 1528 -> 1448 us, 8 experts x
-// 4096 rows, 2048 x 2048 483 -> 467 us, 32 experts x 8192 rows, 4096 x 1024 3994 -> 3857 us.  What is left is the way from L2
-// into LDS: without the direct loads the same products take 0.79 of the time.
+// 4096 rows, 2048 x 2048 483 -> 467 us, 32 experts x 8192 rows, 4096 x 1024 3994 -> 3857 us.  What bounded it then was the way from L2
+// into LDS (without the direct loads the same products took 0.79 of the time): with two stages of each operand all sixteen loads of
+// a K-step crowd into the half of a K-step between the barrier that frees their stage and its end.  The third stage of B lets its loads go
+// out before the barrier and A's after it, one in 6 to 8 products throughout: the same shapes 1496 -> 1467 us, 475 -> 446, 3865 ->
+// 3604 (1.5, 1.23 and 1.22 PFLOP/s; a tile of 16 to 64 K-steps spends 8 to 10 us outside the loop).
 //
 // LDS layouts (both written by the direct loads, which place lane l's 16 bytes at base + 16 l):
 //   A tile  [256 rows][8 chunks of 8 k]:   chunk g of row r is stored at chunk position g ^ ((r / 2) % 8), so the 16 lanes
@@ -59,14 +62,16 @@ namespace {
 
 constexpr int BM = kLargeTile, BN = kLargeTile, BK = kLargeK;
 constexpr int kThreads = 256;
-constexpr int kStageBytes = 65536;          // A tile 32 KB + B tile 32 KB
-constexpr int kATileBytes = 32768;
-constexpr int kLoadsPerWave = 16;           // 64 KB per K-step / (4 waves x 1 KB per wave-load)
+constexpr int kTileBytes = 32768;           // one K-step of A, or of B
+constexpr int kBRing = 2 * kTileBytes;      // LDS: two stages of A, then three of B
+constexpr int kRingBytes = 5 * kTileBytes;
 // Schedule of a K-step's 128 products per wave: the LDS reads of the next sub-step spread over a sub-step's first 48 products,
-// the barrier behind the 57th of the first sub-step, a direct load of the K-step after next behind every fourth product from
-// there on.  One load behind every second product: 5 % slower (the four waves' loads queue up); reads over 32 or 40 products,
-// a load behind every third or fifth, the barrier 8 to 16 products earlier: up to 2 % slower.
-constexpr int kReadSpan = 48, kBarrierAt = 56, kLoadEvery = 4;
+// B's eight direct loads of the K-step after next behind every sixth product up to the barrier, which is behind the 57th, and A's
+// behind every eighth from there on.  All sixteen behind the barrier, every fourth product: 2-5 % slower, with or without the third stage
+// of B loaded a K-step further ahead; A's behind every fourth or sixth product: up to 1 %; reads over 40 or 56 products and the barrier
+// moved with them: 1-2 %.  With gathered rows of a transposed A both operands' loads stay behind the barrier, because the wait for
+// the row indices ahead of it would wait for B's as well.
+constexpr int kReadSpan = 48, kBarrierAt = 56, kLoadEveryA = 8, kLoadEveryB = 6, kLoadEveryGathered = 4;
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 #define PIN() __builtin_amdgcn_sched_barrier(0)
 
@@ -218,10 +223,10 @@ __device__ __forceinline__ int find_tile(int b, int lane, int E, int64_t C, cons
 
 // ---- main loop -------------------------------------------------------------------------------------------------
 // K-step kt (64 wide) is two sub-steps of 64 MFMAs.  While sub-step s computes from one fragment buffer, the LDS reads of
-// sub-step s+1 (24, or 16 / 32 with no / two transposed operands) fill the other.  The direct loads of K-step kt+2 go into the
-// stage K-step kt is read from, so they may start only after the barrier that follows the last read of that stage, at the
-// end of sub-step 0; a wave's 16 loads are issued from there to the end of sub-step 1 and waited for before the barrier of
-// K-step kt+1, most of a sub-step after the last of them.
+// sub-step s+1 (24, or 16 / 32 with no / two transposed operands) fill the other.  The direct loads of K-step kt+2 fill stages that
+// an earlier K-step was read from: B's that of kt-1, so they go out from the start of K-step kt; A's that of kt itself, so they
+// start only behind the barrier that follows the last read of that stage, near the end of sub-step 0.  The barrier of K-step kt+1
+// waits for both, but not for the eight of B's kt+3 that are behind them by then.
 // GK (kTN only): the k-rows of A are gathered.  K-step t's row 2 (4 q + wave) + kg is row gk.rows[64 t + ...] of the
 // matrix at a_base (row length gk.row_bytes); a_voff[0] then holds the lane's offset into the side buffer for q = 0.
 struct GatherK {
@@ -261,20 +266,20 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
   auto join = [](short4v lo, short4v hi) -> bf16x8 {
     return __builtin_bit_cast(bf16x8, (short8v)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  auto read = [&](const char* stage, int s, int r, Frags& d, short4v& lo) {
+  auto read = [&](const char* a_stage, const char* b_stage, int s, int r, Frags& d, short4v& lo) {
     const bool is_b = r >= PA && r < PA + NRB;
     if (is_b) {
       const int rb = r - PA;
       if (NI > 0) {
-        if (!TRB) d.b[rb] = read_direct(stage, b_off, rb, s);
-        else if ((rb & 1) == 0) lo = read_tr(stage, b_off, rb >> 1, s, 0);
-        else d.b[rb >> 1] = join(lo, read_tr(stage, b_off, rb >> 1, s, 1));
+        if (!TRB) d.b[rb] = read_direct(b_stage, b_off, rb, s);
+        else if ((rb & 1) == 0) lo = read_tr(b_stage, b_off, rb >> 1, s, 0);
+        else d.b[rb >> 1] = join(lo, read_tr(b_stage, b_off, rb >> 1, s, 1));
       }
     } else {
       const int ra = r < PA ? r : r - NRB;
-      if (!TRA) { if (ra < 2 * NI) d.a[ra] = read_direct(stage, a_off, ra, s); }
-      else if ((ra & 1) == 0) lo = read_tr(stage, a_off, ra >> 1, s, 0);
-      else d.a[ra >> 1] = join(lo, read_tr(stage, a_off, ra >> 1, s, 1));
+      if (!TRA) { if (ra < 2 * NI) d.a[ra] = read_direct(a_stage, a_off, ra, s); }
+      else if ((ra & 1) == 0) lo = read_tr(a_stage, a_off, ra >> 1, s, 0);
+      else d.a[ra >> 1] = join(lo, read_tr(a_stage, a_off, ra >> 1, s, 1));
     }
   };
   // direct load number idx (0..15: A0..A7, B0..B7) of K-step `tile` (the caller guarantees tile < KT).  With a
@@ -303,21 +308,24 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
     else global_to_lds_16(base, off, dst);
   };
   uint32_t gv[8];
-  auto dma = [&](int idx, int tile) {
-    const int q = idx & 7;
-    const uint32_t dst = smem_addr + (tile & 1) * kStageBytes + (q * 4 + wave) * 1024;
+  auto dma_a = [&](int q, int tile) {
+    const uint32_t dst = smem_addr + (tile & 1) * kTileBytes + (q * 4 + wave) * 1024;
     const bool last = MODE == kTN && tile == KT - 1;
-    if (idx < 8) {
-      if (GK) {
-        load_a(last ? a_last : a_base, gv[q], dst);
-      } else {
-        const char* src = last ? a_last : a_base + tile * a_step;
-        if (FULL || ((a_mask >> q) & 1)) load_a(src, a_voff[q], dst);   // skip rows past the slab's fill
-      }
+    if (GK) {
+      load_a(last ? a_last : a_base, gv[q], dst);
     } else {
-      const char* src = last ? b_last : b_base + tile * b_step;
-      global_to_lds_16(src, b_voff[q], dst + kATileBytes);
+      const char* src = last ? a_last : a_base + tile * a_step;
+      if (FULL || ((a_mask >> q) & 1)) load_a(src, a_voff[q], dst);     // skip rows past the slab's fill
     }
+  };
+  // b_src is the K-step of B that the next loads take
+  const char* b_src = MODE == kTN && KT == 1 ? b_last : b_base;
+  auto dma_b = [&](int q, int stage) {                              // stage: byte offset in B's ring
+    global_to_lds_16(b_src, b_voff[q], smem_addr + kBRing + stage + (q * 4 + wave) * 1024);
+  };
+  auto b_advance = [&](int tile) {
+    if (MODE == kTN) b_src = tile < KT - 1 ? b_src + b_step : b_last;
+    else b_src += b_step;
   };
   auto mfma = [&](int m, const Frags& c) {
     const int i = m >> 3, j = m & 7;
@@ -326,40 +334,53 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
   // One K-step; DMA: a K-step kt+2 exists; NEXT: a K-step kt+1 exists, or the reads ahead find a stage that holds nothing new and
   // are not used.  Every body more makes the compiler move accumulators around between them (with two transposed operands every
   // one less makes it spill).
+  int b_stage = 0;                                                  // byte offset of K-step kt's stage in B's ring
   auto kstep = [&](auto dma_tag, auto next_tag, int kt, auto tail_tag) __attribute__((always_inline)) {
     constexpr bool DMA = decltype(dma_tag)::value, NEXT = decltype(next_tag)::value;
-    const char* cur = smem + (kt & 1) * kStageBytes;
-    const char* nxt = smem + ((kt + 1) & 1) * kStageBytes;
+    const char* a_cur = smem + (kt & 1) * kTileBytes;
+    const char* a_nxt = smem + (~kt & 1) * kTileBytes;
+    const int b_fill = b_stage == 0 ? 2 * kTileBytes : b_stage - kTileBytes;   // of K-step kt-1 before, of kt+2 now
+    const char* b_cur = smem + b_stage;
+    b_stage = b_stage == 2 * kTileBytes ? 0 : b_stage + kTileBytes;
+    const char* b_nxt = smem + b_stage;
     constexpr bool tail = decltype(tail_tag)::value;                // gathered A: K-step kt+2 is the last one
     if (GK && DMA && !tail) { gather_fetch(kt + 2, gv); PIN(); }
     short4v lo;
     auto read_at = [&](int m) { const int r = (m * NR + kReadSpan - 1) / kReadSpan; return r < ((m + 1) * NR + kReadSpan - 1) / kReadSpan ? r : NR; };
-    auto loads = [&](int p) {                                       // p: products since the barrier
-      if (DMA && p % kLoadEvery == 1 && p / kLoadEvery < kLoadsPerWave) dma(p / kLoadEvery, kt + 2);
+    auto loads = [&](int m) {                                       // m: products of this K-step so far
+      if (!DMA) return;
+      const int p = GK ? m - kBarrierAt - 32 : m;
+      constexpr int every = GK ? kLoadEveryGathered : kLoadEveryB;
+      if (p >= 0 && p % every == 1 && p / every < 8) dma_b(p / every, b_fill);
+      const int pa = m - kBarrierAt;
+      if (pa >= 0 && pa % kLoadEveryA == 1 && pa / kLoadEveryA < 8) dma_a(pa / kLoadEveryA, kt + 2);
     };
 #pragma unroll
     for (int m = 0; m < 64; ++m) {
       mfma(m, f[0]);
       PIN();
-      if (const int r = read_at(m); r < NR) read(cur, 1, r, f[1], lo);
+      if (const int r = read_at(m); r < NR) read(a_cur, b_cur, 1, r, f[1], lo);
       if (m == kBarrierAt) {
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // K-step kt+1 has landed; reads of `cur` are done
+        // K-step kt+1 has landed, though not B's eight loads of kt+2 behind it; reads of this K-step are done
+        if (DMA && !GK) asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         PIN();
         asm volatile("s_barrier" ::: "memory");
         PIN();
         if (GK && DMA) { gather_offsets(tail, gv); PIN(); }          // nothing else is in flight here
       }
-      if (m > kBarrierAt) loads(m - kBarrierAt);
+      loads(m);
       PIN();
     }
 #pragma unroll
     for (int m = 0; m < 64; ++m) {
       mfma(m, f[1]);
       PIN();
-      if (const int r = read_at(m); NEXT && r < NR) read(nxt, 0, r, f[0], lo);
-      loads(m + 64 - kBarrierAt);
+      if (const int r = read_at(m); NEXT && r < NR) read(a_nxt, b_nxt, 0, r, f[0], lo);
+      loads(m + 64);
       PIN();
     }
+    if (DMA) b_advance(kt + 3);
   };
 
   uint32_t gv1[8];
@@ -369,7 +390,10 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
     gather_offsets(KT == 1, gv);
   }
 #pragma unroll
-  for (int idx = 0; idx < kLoadsPerWave; ++idx) dma(idx, 0);
+  for (int q = 0; q < 8; ++q) dma_a(q, 0);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) dma_b(q, 0);
+  b_advance(1);
   if (KT > 1) {
     if (GK) {
       gather_offsets(KT == 2, gv1);
@@ -377,7 +401,10 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
       for (int q = 0; q < 8; ++q) gv[q] = gv1[q];
     }
 #pragma unroll
-    for (int idx = 0; idx < kLoadsPerWave; ++idx) dma(idx, 1);
+    for (int q = 0; q < 8; ++q) dma_a(q, 1);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) dma_b(q, kTileBytes);
+    b_advance(2);
   }
   // while the first stages are in flight: the accumulators start from the bias (register u of tile (i, j) is column
   // 16 j + 4 kq + u of the wave's 128), or from zero
@@ -394,7 +421,7 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
   PIN();
   if (KT > 1) {
     if (FULL) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");     // loads return in order: K-step 0 has landed
-    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // ragged tiles issue fewer loads: wait for all
+    else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");           // ragged tiles issue fewer loads of A: wait for both K-steps'
   } else {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
@@ -404,7 +431,7 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
   {
     short4v lo;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) read(smem, 0, r, f[0], lo);
+    for (int r = 0; r < NR; ++r) read(smem, smem, 0, r, f[0], lo);
   }
   PIN();
 
@@ -445,7 +472,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
                                                                      const uint16_t* __restrict__ b_tail,
                                                                      const uint16_t* pre,
                                                                      uint16_t* __restrict__ pre_out) {
-  __shared__ __attribute__((aligned(1024))) char smem[2 * kStageBytes];
+  __shared__ __attribute__((aligned(1024))) char smem[kRingBytes];
 
   // ---- which tile -------------------------------------------------------------------------------------------------
   // An expert's live tiles (row tiles below its fill x all column tiles) are numbered by blocks of 8 tile columns and,
@@ -534,7 +561,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     a_off[i] = MODE == kTN ? tr_off(wm, i) : direct_off(wm, i & 1);
-    b_off[i] = kATileBytes + (MODE == kNT ? direct_off(wn, i & 1) : tr_off(wn, i));
+    b_off[i] = kBRing + (MODE == kNT ? direct_off(wn, i & 1) : tr_off(wn, i));
   }
   // 32-row sub-tiles of this wave that hold real rows (the last row tile of an expert is usually ragged)
   const int64_t wave_rows = rows - m0 - wm * 128;

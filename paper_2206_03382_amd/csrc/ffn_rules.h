@@ -100,8 +100,10 @@ static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M,
 // 32 rows: 39 us plain, 41 streamed).
 // The large tile has a half, 128 x 256 with two blocks to a unit (ffn_half.h), which costs more per product and less per tile: Tile::k256
 // stands for either, and half_tile says which.  Its constants were fitted with the others' held to 143 pairs of products (4-64 experts, 150-4130
-// rows each, 512-4096 wide), over which the choice among the three is 0.9 % off the best, against 3.5 % without it: 32 experts x
+// rows each, 512-4096 wide), over which the choice among the three was 0.9 % off the best, against 3.5 % without it: 32 experts x
 // 784 rows, 768 x 3072: 331 -> 285 us; 8 x 1100, 2048 x 2048: 176 -> 166; but 8 x 2048, 2048 x 2048: 245 on the large one, 269 here.
+// The large tile's thr was 1.1 until its loads were spread over the K-step; with 0.98 the choice between the two is 0.5 % off the
+// better over 38 pairs of the same ranges (1.1: 1.1 %; 128 experts x 2048 rows, 1024 x 4096 went to the half: the pair 3915 us, 3667 now).
 // Forward products only: with a transposed B (64-byte pieces of k, where the large tile loads 128) it is the slower at nearly every size
 // (backward of 32 x 784 rows: 251 and 198 us against 226 and 171), and a training step's first product, which writes twice, gains nothing (216 against 212).
 enum class Tile { k256, k128, k64x128, k64, k64x128_stream, k64_stream };
@@ -119,7 +121,7 @@ static inline double launch_cost(int mode, int64_t E, int64_t rows, double mean_
   return base + fix * rounds + ksteps * (lat * rounds > thr * q ? lat * rounds : thr * q);
 }
 static inline double whole_cost(int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
-  return launch_cost(mode, E, rows, mean_rows, K, N, 256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 1.1);   // kTN: with the launch that pads its last K-step
+  return launch_cost(mode, E, rows, mean_rows, K, N, 256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 0.98);  // kTN: with the launch that pads its last K-step
 }
 static inline double half_cost(int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
   return launch_cost(mode, E, rows, mean_rows, K, N, 128, 256, 2, 2.0, 4.0, 0.33, 0.72);
