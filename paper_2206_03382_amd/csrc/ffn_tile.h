@@ -72,8 +72,12 @@ __device__ __align__(256) uint4 g_zero_piece[16];                   // stays zer
 // 1.4e-7 so; 131072 tokens 6.8e-7 and 1.7e-7.  Results rounded to bf16 show no difference (at most 7e-4 of dWg rounds the other
 // way either way).
 // STREAM: B is loaded as data that is read once.
-template <typename ET, int MODE, int BM, int BN, int WR, int WC, int NS, bool GK = false, bool PART = false, bool STREAM = false>
-__global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(const TileArgs p) {
+// KS: waves that share a tile of one wave along its reduction, wave w taking K-steps w, w + KS and so on through stages of its own
+// (no barrier until their sums meet, which the first wave adds up in order).  For fp32 launches of few tiles, whose time is one chain
+// of matrix instructions per wave on a part of the units: see fp32_split.  Two stages (64 KB, two blocks to a unit): three or four
+// leave room for one block, 4 experts x 256 rows, 256 x 512, two products: 15.4 us against 19.4 and 19.7.
+template <typename ET, int MODE, int BM, int BN, int WR, int WC, int NS, bool GK = false, bool PART = false, bool STREAM = false, int KS = 1>
+__global__ __launch_bounds__(WR * WC * KS * 64, 2) void grouped_gemm_tile_kernel(const TileArgs p) {
   constexpr int ES = (int)sizeof(ET), EC = 16 / ES;                 // elements per 16-byte piece
   constexpr int BKE = 128 / ES;                                     // k per K-step
   constexpr bool BF16 = ES == 2;
@@ -86,10 +90,13 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   constexpr bool BF16O = BF16 && !PART;                             // type of the results
   constexpr int OS = BF16O ? 2 : 4, OC = 16 / OS;
   static_assert(NW * WTM * WTN * OS <= NS * STAGE, "the epilogue's transpose fits into the stages");
-  __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
+  static_assert(KS == 1 || (NW == 1 && TI == 1 && TJ == 1 && !GK && !PART && KS * WTM * WTN * 4 <= KS * NS * STAGE), "split: one 32 x 32 tile");
+  __shared__ __attribute__((aligned(1024))) char smem_all[KS * NS * STAGE];
 
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave = KS > 1 ? 0 : wave_id, part = KS > 1 ? wave_id : 0;   // wave of the tile; its share of the reduction
+  char* const smem = smem_all + part * (NS * STAGE);
   const int wm = wave / WC, wn = wave % WC, kg = lane >> 5;
 
   // ---- which tile: the search of the large kernel, or plain numbering where that does not do ---------------------
@@ -110,7 +117,8 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   int64_t kend = p.K;                                               // k that exist
   if (MODE == kTN && p.kfill) { const int64_t c = p.kfill[e]; kend = c < p.K ? (c > 0 ? c : 0) : p.K; }
   if (PART) { const int64_t left = p.ktotal - (int64_t)e * p.K; kend = left < p.K ? (left > 0 ? left : 0) : p.K; }
-  const int KT = kend > 0 ? (int)((kend + BKE - 1) / BKE) : 1;
+  const int KT_all = kend > 0 ? (int)((kend + BKE - 1) / BKE) : 1;
+  const int KT = KS > 1 ? (KT_all - part + KS - 1) / KS : KT_all;   // K-steps of this wave (none where there are fewer than waves)
 
   // ---- this lane's direct loads: address at K-step 0, and k of its piece (to tell what lies past the end) ---------------
   const char* a_ptr[LA];
@@ -161,7 +169,14 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
       b_ptr[i] = fast_source(base, p.K, row < p.N ? row : p.N - 1, i, b_k[i]);
     }
   }
-  const int64_t a_step = TRA ? (int64_t)BKE * p.C * ES : 128, b_step = TRB ? (int64_t)BKE * p.N * ES : 128;
+  const int64_t a_one = TRA ? (int64_t)BKE * p.C * ES : 128, b_one = TRB ? (int64_t)BKE * p.N * ES : 128;
+  const int64_t a_step = a_one * KS, b_step = b_one * KS;
+  if (KS > 1) {
+#pragma unroll
+    for (int i = 0; i < LA; ++i) a_ptr[i] += a_one * part;
+#pragma unroll
+    for (int i = 0; i < LB; ++i) b_ptr[i] += b_one * part;
+  }
   const uint32_t smem_addr = (uint32_t)(uintptr_t)LDS_PTR(char, smem);
   const char* zero = (const char*)g_zero_piece;
   int grow[GK ? LA : 1];                                            // rows of the next K-step to load
@@ -186,9 +201,9 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
     for (int i = 0; i < LB; ++i) { global_to_lds_16<STREAM>(b_ptr[i], dst + A_BYTES + (i * NW + wave) * 1024); b_ptr[i] += b_step; }
   };
   auto issue = [&](int t, const int (&g)[GK ? LA : 1]) __attribute__((always_inline)) {   // the same, with zeros past the end of the reduction
-    if (t < KT - 1) { issue_whole(t, g); return; }
+    if (t * KS + part < KT_all - 1) { issue_whole(t, g); return; }
     const uint32_t dst = smem_addr + (uint32_t)((t % NS) * STAGE);
-    const int left = (int)(kend - (int64_t)t * BKE);
+    const int left = (int)(kend - (int64_t)(t * KS + part) * BKE);
 #pragma unroll
     for (int i = 0; i < LA; ++i) global_to_lds_16(a_k[i] < left ? a_source(i, g) : zero, dst + (i * NW + wave) * 1024);
 #pragma unroll
@@ -220,7 +235,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   // loads go out ahead of the first K-steps' and are used behind them
   using Raw4 = std::conditional_t<BF16, u32x2, u32x4>;
   Raw4 braw[TJ][4];
-  const bool has_bias = MODE == kNN && p.bias != nullptr;
+  const bool has_bias = MODE == kNN && p.bias != nullptr && part == 0;
   const int64_t bcol = n0 + wn * WTN + 4 * kg;
   if (has_bias) {
     const ET* be = (const ET*)p.bias + (int64_t)e * p.N;
@@ -329,7 +344,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
         else wait_for_loads<NS - 2, LA + LB>(KT - 2 - kt);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // this wave's reads of K-step kt are done
         PIN();
-        asm volatile("s_barrier" ::: "memory");
+        if (KS == 1) asm volatile("s_barrier" ::: "memory");
         PIN();
         if (STEADY) issue_whole(kt + NS, grow);
         else if (kt + NS < KT) issue(kt + NS, grow);
@@ -342,7 +357,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
     };
     wait_for_loads<NS - 1, LA + LB>(KT - 1);
     PIN();
-    asm volatile("s_barrier" ::: "memory");
+    if (KS == 1) asm volatile("s_barrier" ::: "memory");
     PIN();
     read(0, smem, 0);
     PIN();
@@ -364,6 +379,25 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
   // ---- epilogue: the wave's tile goes through its own piece of LDS, so that stores are 16 bytes per lane and whole row
   // pieces; piece c of row r sits at position c ^ (r % pieces per row).
   __syncthreads();                                                  // the stages are done with
+  if constexpr (KS > 1) {                                           // the parts' sums, 4 KB each, behind the first wave's tile
+    char* sums = smem_all + lane * 16;
+    if (part > 0) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *LDS_PTR(u32x4, sums + part * 4096 + g * 1024) = u32x4{__float_as_uint(acc[0][0][4 * g]), __float_as_uint(acc[0][0][4 * g + 1]),
+                                                               __float_as_uint(acc[0][0][4 * g + 2]), __float_as_uint(acc[0][0][4 * g + 3])};
+    }
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int w = 1; w < KS; ++w)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const u32x4 q = *LDS_PTR(u32x4, sums + w * 4096 + g * 1024);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[0][0][4 * g + u] += __uint_as_float(q[u]);
+      }
+  }
   constexpr int CPR = WTN * OS / 16, RPI = 64 / CPR;                // pieces per row, rows per store
   char* wtile = smem + wave * (WTM * WTN * OS);
   const int64_t nw = n0 + wn * WTN;
@@ -432,7 +466,7 @@ __global__ __launch_bounds__(WR * WC * 64, 2) void grouped_gemm_tile_kernel(cons
 
 }  // namespace
 
-template <typename ET, int MODE, int BM, int BN, int NS, bool STREAM = false>
+template <typename ET, int MODE, int BM, int BN, int NS, bool STREAM = false, int KS = 1>
 static hipError_t launch_tile(TileArgs p, int64_t total, hipStream_t s) {
   p.MT = (int)ceil_div(p.C, BM);
   p.NT = (int)ceil_div(p.N, BN);
@@ -448,14 +482,19 @@ static hipError_t launch_tile(TileArgs p, int64_t total, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  grouped_gemm_tile_kernel<ET, MODE, BM, BN, 2, 2, NS, false, false, STREAM><<<grid, dim3(256), 0, s>>>(p);
+  constexpr int W = KS > 1 ? 1 : 2;
+  grouped_gemm_tile_kernel<ET, MODE, BM, BN, W, W, NS, false, false, STREAM, KS><<<grid, dim3(256), 0, s>>>(p);
   return hipGetLastError();
 }
 
 // The launches below the large tile (`total`: rows of all experts that exist, at most).  fp32: the matrix instruction is 16 times slower, loads hardly matter, and the finest
-// tile divides best (64 x 64, five blocks per unit: within 2-4 % of the best of four shapes over 442 launches).
+// tile divides best (64 x 64, five blocks per unit: within 2-4 % of the best of four shapes over 442 launches), but for launches too
+// small to fill the chip with it (fp32_split).
 template <int MODE>
 static hipError_t launch_small(int dtype, Tile tile, const TileArgs& p, int64_t total, hipStream_t s) {
+  if constexpr (MODE != kTN) {
+    if (dtype == MOE_F32 && fp32_split(p.E, p.C, p.N)) return launch_tile<float, MODE, kSplitTile, kSplitTile, 2, false, kSplitParts>(p, total, s);
+  }
   if (dtype == MOE_F32) return launch_tile<float, MODE, 64, 64, 2>(p, total, s);
   if constexpr (MODE != kTN) {
     switch (tile) {

@@ -30,6 +30,7 @@ int tile(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint
   return (int)moe::tile_of(mode, E, C, K, N, rows_hint, gather_rows);
 }
 int half(int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint) { return moe::half_tile(E, C, moe::mean_or(rows_hint, C), K, N); }
+int split(int64_t E, int64_t C, int64_t N) { return moe::fp32_split(E, C, N); }
 int dx_tokens(int64_t T, int64_t row_bytes) { return moe::gate_dx_tokens(T, row_bytes); }
 int64_t backward_tokens(int64_t T, int64_t E, int bias) { return moe::gate_backward_token_block(T, E, bias); }
 int64_t wide_logits(int64_t T, int64_t E, int vecw) { return moe::gate_logits_wide_experts(T, E, vecw); }
@@ -40,7 +41,7 @@ int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T
 
 @pytest.fixture(scope="session")
 def ffn_rules(tmp_path_factory):
-    """The host rules of the grouped GEMM: grid(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, and half();
+    """The host rules of the grouped GEMM: grid(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, half() and split();
     and of the gate: one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text(RULES_SOURCE)
@@ -48,6 +49,7 @@ def ffn_rules(tmp_path_factory):
     lib = ctypes.CDLL(str(d / "rules.so"))
     lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
+    lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 3
     lib.half.restype, lib.half.argtypes = ctypes.c_int, [ctypes.c_int64] * 5
     lib.one_launch.restype, lib.one_launch.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     lib.dx_tokens.restype, lib.dx_tokens.argtypes = ctypes.c_int, [ctypes.c_int64] * 2

@@ -1005,6 +1005,16 @@ def test_layer_fused_dispatch(moe, cfg):
     assert np.array_equal(fused.view(np.uint32), plain.view(np.uint32))       # same arithmetic on the same rows
 
 
+# (M, H): reductions of fewer K-steps (32) than the four waves, of a ragged last one, and of many; ragged column tiles
+@pytest.mark.parametrize("E,C,M,H", [(4, 256, 256, 512), (2, 2, 8, 8), (3, 33, 40, 104), (5, 31, 96, 136), (2, 64, 1032, 2056), (16, 32, 32, 1024)])
+@pytest.mark.parametrize("use_counts", [False, True])
+def test_expert_ffn_fp32_split(moe, ffn_rules, E, C, M, H, use_counts):
+    """fp32 products on 32 x 32 tiles with the reduction split over four waves, forward and with B transposed, against the oracle."""
+    assert ffn_rules.split(E, C, M) and ffn_rules.split(E, C, H) and not ffn_rules.split(E, C, 512 * 32 + 1)
+    test_expert_ffn(moe, synth.DT_F32, E, C, M, H, O.ACT_GELU, True, use_counts)
+    test_expert_ffn_backward(moe, synth.DT_F32, E, C, M, H, O.ACT_SILU, True, use_counts)
+
+
 @pytest.mark.parametrize("E,C,M,H", [(64, 1500, 64, 256), (64, 520, 256, 256), (40, 385, 1024, 256), (32, 784, 768, 3072)])
 def test_expert_ffn_half_tile(moe, ffn_rules, E, C, M, H):
     """The 128 x 256 tile: reductions of 2 to 96 K-steps (fewer than its ring, and more), row tiles of 1 to 8 live 16-row pieces and
