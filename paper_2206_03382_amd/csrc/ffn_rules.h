@@ -140,7 +140,11 @@ static inline Tile choose_tile(int mode, bool large_ok, int64_t E, int64_t rows,
   auto consider = [&](Tile t, double c) { if (c < least) { least = c; best = t; } };
   if (large_ok) {
     consider(Tile::k256, whole_cost(mode, E, rows, mean_rows, K, N));
-    if (mode == kNN) consider(Tile::k256, half_cost(mode, E, rows, mean_rows, K, N));
+    // against the smaller tiles the half has to be clearly ahead.  By its estimate alone it took 34 pairs of short products (K from 256
+    // on, 20-180 us a pair) from them of which 15 got slower, by up to 18 % (48 experts x 196 rows, 384 x 512: 27.5 -> 32.5 us;
+    // 8 x 730, 256 x 1280: 26.3 -> 28.4); so it keeps those it gains on (8 x 21056, 512 x 256: 179 -> 145) and loses 2 % at most.  Rows that a 64-row tile
+    // holds stay there: their launch reads weights, and half of this tile would be padding (32 x 52, 3328 x 1792: 167 us there, 178-192 here)
+    if (mode == kNN && mean_rows > 64.0) consider(Tile::k256, 1.1 * half_cost(mode, E, rows, mean_rows, K, N) + 3.0);
   }
   if (mode != kTN) {                                                // 64 x 64 was the best tile for one of 278 weight gradients
     consider(Tile::k64x128, cost(64, 128, 2, 2.5, 2.5, 0.3, 0.44));
