@@ -687,11 +687,10 @@ __global__ __launch_bounds__(256) void tail_rows_kernel(const TailRows a, const 
     dst[((int64_t)e * BK + j) * cpr + ch] = slot < fill ? src[row * cpr + ch] : make_uint4(0, 0, 0, 0);
 }
 
-// `mean`: rows an expert holds on average (for half_tile); `total`: rows of all experts that exist, at most.
+// `half`: on the half tile; `total`: rows of all experts that exist, at most.
 static hipError_t launch_large_nn(const void* A, const void* B, const void* bias, int act, const int32_t* counts,
-                                  int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, double mean, int64_t total,
+                                  int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, bool half, int64_t total,
                                   const int32_t* gather, int64_t gather_rows, void* pre_out) {
-  const bool half = half_tile(E, C, mean, K, N) && !far_rows(gather_rows, K) && !pre_out;
   const int64_t bm = half ? BM / 2 : BM;
   const int MT = (int)ceil_div(C, bm), NT = (int)(N / BN);
   const int64_t blocks = tile_grid(E, MT, NT, live_row_tiles(E, C, total, bm), half ? kHalfGroupShift : 0);
@@ -794,9 +793,10 @@ hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, i
                                int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, int64_t rows_hint,
                                void* pre_out, const int32_t* gather, int64_t gather_rows) {
   if (act < 0) pre_out = nullptr;                                   // nothing to tell apart
-  const Tile tile = dtype == MOE_BF16 ? tile_of(kNN, E, C, K, N, rows_hint, gather ? gather_rows : 0) : Tile::k64;
+  const Tile tile = dtype == MOE_BF16 ? tile_of(kNN, E, C, K, N, rows_hint, gather ? gather_rows : 0, pre_out != nullptr) : Tile::k64;
   const int64_t total = total_rows(counts, E, C, rows_hint);
-  if (tile == Tile::k256) return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, mean_or(rows_hint, C), total, gather, gather_rows, pre_out);
+  if (tile == Tile::k256 || tile == Tile::kHalf)
+    return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, tile == Tile::kHalf, total, gather, gather_rows, pre_out);
   if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports(E, C, K, N, 0)) act += kFullAct;
   const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, 0, out, nullptr, nullptr, pre_out, act, 0};
   return launch_small<kNN>(dtype, tile, p, total, s);
@@ -806,7 +806,7 @@ hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, i
 // with act < 0, has `pre` added (pre == out accumulates in place).
 hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, const int32_t* counts, int64_t E, int64_t C,
                                   int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s, int64_t rows_hint) {
-  const Tile tile = dtype == MOE_BF16 ? tile_of(kNT, E, C, K, N, rows_hint, 0) : Tile::k64;
+  const Tile tile = dtype == MOE_BF16 ? tile_of(kNT, E, C, K, N, rows_hint, 0, false) : Tile::k64;
   const int64_t total = total_rows(counts, E, C, rows_hint);
   if (tile == Tile::k256) return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s, total);
   if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports_backward(E, C, K, N)) act += kFullAct;
@@ -822,7 +822,7 @@ size_t grouped_gemm_tn_tail_bytes(int64_t E, int64_t W) { return (size_t)E * BK 
 hipError_t launch_grouped_gemm_tn(const void* At, const void* B, int dtype, const int32_t* kfill, int64_t E, int64_t C, int64_t R,
                                   int64_t N, void* a_tail, void* b_tail, void* out, hipStream_t s, int64_t rows_hint,
                                   const int32_t* gather, int64_t gather_rows) {
-  const Tile tile = dtype == MOE_BF16 ? tile_of(kTN, E, R, C, N, rows_hint, gather_rows) : Tile::k64;
+  const Tile tile = dtype == MOE_BF16 ? tile_of(kTN, E, R, C, N, rows_hint, gather_rows, false) : Tile::k64;
   if (tile == Tile::k256) return launch_large_tn(At, B, kfill, E, C, R, N, a_tail, b_tail, out, s, gather, gather_rows);
   const TileArgs p = {At, B, nullptr, nullptr, gather, gather_rows, R, C, (int)N, (int)E, 0, 0, 0, out, kfill, nullptr, nullptr, -1, 0};
   return launch_small<kTN>(dtype, tile, p, E * R, s);

@@ -98,57 +98,56 @@ static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M,
 // hint alone 202).  Where that leaves units without a block, 64 x 64 one stage deeper (8 experts x 16 rows, 2048 x 2048: 40 -> 33 us).
 // Weights below 48 MB keep the plain loads: they may stay in the caches from one call to the next (17 experts, 776 x 1544,
 // 32 rows: 39 us plain, 41 streamed).
-// The large tile has a half, 128 x 256 with two blocks to a unit (ffn_half.h), which costs more per product and less per tile: Tile::k256
-// stands for either, and half_tile says which.  Its constants were fitted with the others' held to 143 pairs of products (4-64 experts, 150-4130
+// The large tile has a half, 128 x 256 with two blocks to a unit (ffn_half.h), which costs more per product and less per tile.  Its constants were fitted with the others' held to 143 pairs of products (4-64 experts, 150-4130
 // rows each, 512-4096 wide), over which the choice among the three was 0.9 % off the best, against 3.5 % without it: 32 experts x
 // 784 rows, 768 x 3072: 331 -> 285 us; 8 x 1100, 2048 x 2048: 176 -> 166; but 8 x 2048, 2048 x 2048: 245 on the large one, 269 here.
 // The large tile's thr was 1.1 until its loads were spread over the K-step; with 0.98 the choice between the two is 0.5 % off the
 // better over 38 pairs of the same ranges (1.1: 1.1 %; 128 experts x 2048 rows, 1024 x 4096 went to the half: the pair 3915 us, 3667 now).
 // Forward products only: with a transposed B (64-byte pieces of k, where the large tile loads 128) it is the slower at nearly every size
 // (backward of 32 x 784 rows: 251 and 198 us against 226 and 171), and a training step's first product, which writes twice, gains nothing (216 against 212).
-enum class Tile { k256, k128, k64x128, k64, k64x128_stream, k64_stream };
+enum class Tile { k256, k128, k64x128, k64, k64x128_stream, k64_stream, kHalf };
 
-static inline double launch_cost(int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N, int bm, int bn, int per_unit, double base,
-                                 double fix, double lat, double thr) {
+static inline double tile_cost(Tile tile, int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
   const double ksteps = (mode == kTN ? mean_rows : (double)K) / 64 + 0.5;
-  // an average fill ends in half a tile, but no expert has more row tiles than its slab (without this bound 24 experts x 256
-  // rows, 2048 x 2048, counted as 1.5 tiles each: two products 180 us on smaller tiles, 137 on the large one)
-  const double full = (double)tiles_in(rows, bm), some = mean_rows / bm + 0.5;
-  const double row_tiles = mode == kTN || some > full ? full : (some > 1.0 ? some : 1.0);
-  double q = (double)E * row_tiles * (double)tiles_in(N, bn) / 256.0;               // tiles per compute unit
-  q = q <= 4.0 * per_unit ? ceil(q - 0.02) : q + 0.5;
-  const double rounds = q > per_unit ? q / per_unit : 1.0;
-  return base + fix * rounds + ksteps * (lat * rounds > thr * q ? lat * rounds : thr * q);
-}
-static inline double whole_cost(int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
-  return launch_cost(mode, E, rows, mean_rows, K, N, 256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 0.98);  // kTN: with the launch that pads its last K-step
-}
-static inline double half_cost(int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
-  return launch_cost(mode, E, rows, mean_rows, K, N, 128, 256, 2, 2.0, 4.0, 0.33, 0.72);
-}
-static inline bool half_tile(int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
-  return half_cost(kNN, E, rows, mean_rows, K, N) < whole_cost(kNN, E, rows, mean_rows, K, N);
+  auto cost = [&](int bm, int bn, int per_unit, double base, double fix, double lat, double thr) {
+    // an average fill ends in half a tile, but no expert has more row tiles than its slab (without this bound 24 experts x 256
+    // rows, 2048 x 2048, counted as 1.5 tiles each: two products 180 us on smaller tiles, 137 on the large one)
+    const double full = (double)tiles_in(rows, bm), some = mean_rows / bm + 0.5;
+    const double row_tiles = mode == kTN || some > full ? full : (some > 1.0 ? some : 1.0);
+    double q = (double)E * row_tiles * (double)tiles_in(N, bn) / 256.0;             // tiles per compute unit
+    q = q <= 4.0 * per_unit ? ceil(q - 0.02) : q + 0.5;
+    const double rounds = q > per_unit ? q / per_unit : 1.0;
+    return base + fix * rounds + ksteps * (lat * rounds > thr * q ? lat * rounds : thr * q);
+  };
+  switch (tile) {
+    case Tile::k256: return cost(256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 0.98);   // kTN: with the launch that pads its last K-step
+    case Tile::kHalf: return cost(128, 256, 2, 2.0, 4.0, 0.33, 0.72);
+    case Tile::k64x128: return cost(64, 128, 2, 2.5, 2.5, 0.3, 0.44);
+    case Tile::k64: return cost(64, 64, 3, 3.0, 1.5, 0.3, 0.235);
+    default: return cost(128, 128, 2, 1.5, 3.5, 0.3, 0.56);
+  }
 }
 
-static inline Tile choose_tile(int mode, bool large_ok, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
+// large_ok, half_ok: whether the launch may run on the large tile, and on its half.
+static inline Tile choose_tile(int mode, bool large_ok, bool half_ok, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
   if (mode != kTN && mean_rows <= 48.0 && (double)E * K * N * 2 >= 48e6) return E * tiles_in(N, 128) >= 256 ? Tile::k64x128_stream : Tile::k64_stream;
-  auto cost = [&](int bm, int bn, int per_unit, double base, double fix, double lat, double thr) {
-    return launch_cost(mode, E, rows, mean_rows, K, N, bm, bn, per_unit, base, fix, lat, thr);
-  };
+  auto estimate = [&](Tile t) { return tile_cost(t, mode, E, rows, mean_rows, K, N); };
   Tile best = Tile::k128;
-  double least = cost(128, 128, 2, 1.5, 3.5, 0.3, 0.56);
+  double least = estimate(best);
   auto consider = [&](Tile t, double c) { if (c < least) { least = c; best = t; } };
   if (large_ok) {
-    consider(Tile::k256, whole_cost(mode, E, rows, mean_rows, K, N));
+    const double whole = estimate(Tile::k256), half = half_ok ? estimate(Tile::kHalf) : whole;
     // against the smaller tiles the half has to be clearly ahead.  By its estimate alone it took 34 pairs of short products (K from 256
     // on, 20-180 us a pair) from them of which 15 got slower, by up to 18 % (48 experts x 196 rows, 384 x 512: 27.5 -> 32.5 us;
     // 8 x 730, 256 x 1280: 26.3 -> 28.4); so it keeps those it gains on (8 x 21056, 512 x 256: 179 -> 145) and loses 2 % at most.  Rows that a 64-row tile
     // holds stay there: their launch reads weights, and half of this tile would be padding (32 x 52, 3328 x 1792: 167 us there, 178-192 here)
-    if (mode == kNN && mean_rows > 64.0) consider(Tile::k256, 1.1 * half_cost(mode, E, rows, mean_rows, K, N) + 3.0);
+    const double ahead = 1.1 * half + 3.0;
+    if (half < whole) consider(Tile::kHalf, mean_rows > 64.0 && ahead < whole ? ahead : whole);
+    else consider(Tile::k256, whole);
   }
   if (mode != kTN) {                                                // 64 x 64 was the best tile for one of 278 weight gradients
-    consider(Tile::k64x128, cost(64, 128, 2, 2.5, 2.5, 0.3, 0.44));
-    consider(Tile::k64, cost(64, 64, 3, 3.0, 1.5, 0.3, 0.235));
+    consider(Tile::k64x128, estimate(Tile::k64x128));
+    consider(Tile::k64, estimate(Tile::k64));
   }
   return best;
 }
@@ -165,12 +164,14 @@ static inline bool fp32_split(int64_t E, int64_t C, int64_t N) { return E * tile
 static inline double mean_or(int64_t rows_hint, int64_t C) { return (double)(rows_hint > 0 && rows_hint < C ? rows_hint : C); }
 
 // The tile of a bf16 product: out[e] (C x N) over K, with A gathered from gather_rows rows where that is > 0 (kNN); over the slots K
-// of an expert, of which rows_hint are filled on average, for an output of C x N (kTN).
-static inline Tile tile_of(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
+// of an expert, of which rows_hint are filled on average, for an output of C x N (kTN).  keeps_pre (kNN): the values before the
+// activation are written as well.  The half tile writes one result and takes 32-bit offsets only.
+static inline Tile tile_of(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows, bool keeps_pre) {
   if (mode == kTN)
-    return choose_tile(kTN, large_tile_supports_backward(E, K, C, N) && gather_rows * C * 2 < ((int64_t)1 << 36), E, C, mean_or(rows_hint, K), K, N);
+    return choose_tile(kTN, large_tile_supports_backward(E, K, C, N) && gather_rows * C * 2 < ((int64_t)1 << 36), false, E, C, mean_or(rows_hint, K), K, N);
   const bool large_ok = large_tile_supports(E, C, K, N, mode == kNN ? gather_rows : 0);
-  return choose_tile(mode, large_ok, E, C, mean_or(rows_hint, C), K, N);
+  const bool half_ok = mode == kNN && !keeps_pre && !far_rows(gather_rows, K);
+  return choose_tile(mode, large_ok, half_ok, E, C, mean_or(rows_hint, C), K, N);
 }
 
 }  // namespace moe

@@ -27,9 +27,14 @@ int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total) {
   return moe::tile_grid(E, moe::tiles_in(C, tile), NT, moe::live_row_tiles(E, C, total, tile));
 }
 int tile(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
-  return (int)moe::tile_of(mode, E, C, K, N, rows_hint, gather_rows);
+  return (int)moe::tile_of(mode, E, C, K, N, rows_hint, gather_rows, false);
 }
-int half(int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint) { return moe::half_tile(E, C, moe::mean_or(rows_hint, C), K, N); }
+int tile_keeping_pre(int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
+  return (int)moe::tile_of(moe::kNN, E, C, K, N, rows_hint, gather_rows, true);
+}
+double tile_cost(int tile, int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint) {
+  return moe::tile_cost((moe::Tile)tile, mode, E, C, moe::mean_or(rows_hint, mode == moe::kTN ? K : C), K, N);
+}
 int split(int64_t E, int64_t C, int64_t N) { return moe::fp32_split(E, C, N); }
 int dx_tokens(int64_t T, int64_t row_bytes) { return moe::gate_dx_tokens(T, row_bytes); }
 int64_t backward_tokens(int64_t T, int64_t E, int bias) { return moe::gate_backward_token_block(T, E, bias); }
@@ -41,8 +46,8 @@ int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T
 
 @pytest.fixture(scope="session")
 def ffn_rules(tmp_path_factory):
-    """The host rules of the grouped GEMM: grid(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, half() and split();
-    and of the gate: one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
+    """The host rules of the grouped GEMM: grid(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, the same for a
+    product that keeps its pre-activations, tile_cost() and split(); and of the gate: one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
@@ -50,7 +55,8 @@ def ffn_rules(tmp_path_factory):
     lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
     lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 3
-    lib.half.restype, lib.half.argtypes = ctypes.c_int, [ctypes.c_int64] * 5
+    lib.tile_keeping_pre.restype, lib.tile_keeping_pre.argtypes = ctypes.c_int, [ctypes.c_int64] * 6
+    lib.tile_cost.restype, lib.tile_cost.argtypes = ctypes.c_double, [ctypes.c_int] * 2 + [ctypes.c_int64] * 5
     lib.one_launch.restype, lib.one_launch.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     lib.dx_tokens.restype, lib.dx_tokens.argtypes = ctypes.c_int, [ctypes.c_int64] * 2
     lib.backward_tokens.restype, lib.backward_tokens.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]

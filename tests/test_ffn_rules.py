@@ -46,15 +46,37 @@ def test_grid_is_bounded_by_the_rows_that_exist(ffn_rules):
         assert ffn_rules.grid(E, T, tile, NT, E * T) >= E * T // tile * NT
 
 
-K256, K128, K64X128, K64, K64X128_STREAM, K64_STREAM = range(6)
+K256, K128, K64X128, K64, K64X128_STREAM, K64_STREAM, KHALF = range(7)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_half_tile_only_where_it_may_run(ffn_rules, seed):
+    """A product that keeps its pre-activations, or gathers from 4 GiB and more, runs on the whole large tile or on a smaller one: the
+    estimate of the half must not speak for the whole (48 experts x 96 rows, 256 x 3072: 41 us estimated, 23 on the 128 x 128 tile)."""
+    rng = np.random.default_rng(seed)
+    products = [(48, 96, 256, 3072, 0), (48, 320, 256, 1024, 256), (17, 96, 2048, 4096, 0), (128, 128, 4096, 768, 0)]
+    for _ in range(3000):
+        E, C = int(2 ** rng.uniform(2, 7)), int(2 ** rng.uniform(6, 13))
+        products.append((E, C, 64 * int(rng.integers(4, 65)), 256 * int(rng.integers(1, 17)), int(rng.integers(C // 4, C + 1))))
+    other = 0
+    for E, C, K, N, hint in products:
+        far = 2 ** 32 // (2 * K) + 1
+        if ffn_rules.tile(0, E, C, K, N, hint, 0) == KHALF:
+            other += 1
+        for tile in (ffn_rules.tile_keeping_pre(E, C, K, N, hint, 0), ffn_rules.tile(0, E, C, K, N, hint, far)):
+            assert tile != KHALF
+            if tile not in (K64X128_STREAM, K64_STREAM):
+                cost = [ffn_rules.tile_cost(t, 0, E, C, K, N, hint) for t in (K256, K128, K64X128, K64)]
+                assert cost[tile] == min(cost), (E, C, K, N, hint)
+    assert other > 100                                 # products that do run on the half without either
 
 
 def test_tile_of_exact_row_counts(ffn_rules):
-    """Slabs whose rows fill whole row tiles of 256, or stay short of one: the large tile, which measured 13 to 32 % faster there
+    """Slabs whose rows fill whole row tiles of 256, or stay short of one: the large tile or its half, which measured 13 to 32 % faster there
     than what a row count taken for an average one chose (32 experts x 160 rows, 2048 x 2048: 146 against 176 us)."""
     for E, C, M, H in ((24, 224, 2048, 2048), (24, 256, 2048, 2048), (32, 160, 2048, 2048), (32, 192, 2048, 2048), (16, 448, 2048, 2048),
                        (64, 192, 1024, 4096), (32, 448, 4096, 1024), (32, 448, 1024, 4096)):
-        assert ffn_rules.tile(0, E, C, M, H, 0, 0) == K256 and ffn_rules.tile(0, E, C, H, M, 0, 0) == K256, (E, C, M, H)
+        assert ffn_rules.tile(0, E, C, M, H, 0, 0) in (K256, KHALF) and ffn_rules.tile(0, E, C, H, M, 0, 0) in (K256, KHALF), (E, C, M, H)
 
 
 def test_tile_of_tokens_beyond_4_gib(ffn_rules):
