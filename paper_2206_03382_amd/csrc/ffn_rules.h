@@ -103,11 +103,15 @@ static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M,
 // 784 rows, 768 x 3072: 331 -> 285 us; 8 x 1100, 2048 x 2048: 176 -> 166; but 8 x 2048, 2048 x 2048: 245 on the large one, 269 here.
 // The large tile's thr was 1.1 until its loads were spread over the K-step; with 0.98 the choice between the two is 0.5 % off the
 // better over 38 pairs of the same ranges (1.1: 1.1 %; 128 experts x 2048 rows, 1024 x 4096 went to the half: the pair 3915 us, 3667 now).
+// With an operand transposed 1.1 stays: with 0.98 the large tile took, of the products between the two, 100 with B transposed (4-128
+// experts, 50-4200 rows, 256-4096 wide) at 1.07 times the time of the smaller tile (median, up to 1.6), and 350 weight gradients of
+// dispatched slabs at 1.21 times (17 experts x 292 rows, 2560 x 1024: 55.7 and 41.4 us).  A gathered weight gradient is another matter:
+// of the same 350 the large tile is the faster of nearly all (0.91 times; 52.4 and 56.7 us), and 0.98 chooses 0.8 % off the better, 1.1 11.6 %.
 // Forward products only: with a transposed B (64-byte pieces of k, where the large tile loads 128) it is the slower at nearly every size
 // (backward of 32 x 784 rows: 251 and 198 us against 226 and 171), and a training step's first product, which writes twice, gains nothing (216 against 212).
 enum class Tile { k256, k128, k64x128, k64, k64x128_stream, k64_stream, kHalf };
 
-static inline double tile_cost(Tile tile, int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
+static inline double tile_cost(Tile tile, int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N, bool gathered) {
   const double ksteps = (mode == kTN ? mean_rows : (double)K) / 64 + 0.5;
   auto cost = [&](int bm, int bn, int per_unit, double base, double fix, double lat, double thr) {
     // an average fill ends in half a tile, but no expert has more row tiles than its slab (without this bound 24 experts x 256
@@ -120,7 +124,9 @@ static inline double tile_cost(Tile tile, int mode, int64_t E, int64_t rows, dou
     return base + fix * rounds + ksteps * (lat * rounds > thr * q ? lat * rounds : thr * q);
   };
   switch (tile) {
-    case Tile::k256: return cost(256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, 0.98);   // kTN: with the launch that pads its last K-step
+    // kTN: with the launch that pads its last K-step, and, where its rows are gathered, less against the 128 x 128 tile, whose K-step
+    // fetches row numbers in front of every load
+    case Tile::k256: return cost(256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, mode == kNN || (mode == kTN && gathered) ? 0.98 : 1.1);
     case Tile::kHalf: return cost(128, 256, 2, 2.0, 4.0, 0.33, 0.72);
     case Tile::k64x128: return cost(64, 128, 2, 2.5, 2.5, 0.3, 0.44);
     case Tile::k64: return cost(64, 64, 3, 3.0, 1.5, 0.3, 0.235);
@@ -129,9 +135,9 @@ static inline double tile_cost(Tile tile, int mode, int64_t E, int64_t rows, dou
 }
 
 // large_ok, half_ok: whether the launch may run on the large tile, and on its half.
-static inline Tile choose_tile(int mode, bool large_ok, bool half_ok, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N) {
+static inline Tile choose_tile(int mode, bool large_ok, bool half_ok, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N, bool gathered) {
   if (mode != kTN && mean_rows <= 48.0 && (double)E * K * N * 2 >= 48e6) return E * tiles_in(N, 128) >= 256 ? Tile::k64x128_stream : Tile::k64_stream;
-  auto estimate = [&](Tile t) { return tile_cost(t, mode, E, rows, mean_rows, K, N); };
+  auto estimate = [&](Tile t) { return tile_cost(t, mode, E, rows, mean_rows, K, N, gathered); };
   Tile best = Tile::k128;
   double least = estimate(best);
   auto consider = [&](Tile t, double c) { if (c < least) { least = c; best = t; } };
@@ -168,10 +174,11 @@ static inline double mean_or(int64_t rows_hint, int64_t C) { return (double)(row
 // activation are written as well.  The half tile writes one result and takes 32-bit offsets only.
 static inline Tile tile_of(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows, bool keeps_pre) {
   if (mode == kTN)
-    return choose_tile(kTN, large_tile_supports_backward(E, K, C, N) && gather_rows * C * 2 < ((int64_t)1 << 36), false, E, C, mean_or(rows_hint, K), K, N);
+    return choose_tile(kTN, large_tile_supports_backward(E, K, C, N) && gather_rows * C * 2 < ((int64_t)1 << 36), false, E, C, mean_or(rows_hint, K), K, N,
+                       gather_rows > 0);
   const bool large_ok = large_tile_supports(E, C, K, N, mode == kNN ? gather_rows : 0);
   const bool half_ok = mode == kNN && !keeps_pre && !far_rows(gather_rows, K);
-  return choose_tile(mode, large_ok, half_ok, E, C, mean_or(rows_hint, C), K, N);
+  return choose_tile(mode, large_ok, half_ok, E, C, mean_or(rows_hint, C), K, N, gather_rows > 0);
 }
 
 }  // namespace moe

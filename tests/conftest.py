@@ -32,8 +32,8 @@ int tile(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint
 int tile_keeping_pre(int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
   return (int)moe::tile_of(moe::kNN, E, C, K, N, rows_hint, gather_rows, true);
 }
-double tile_cost(int tile, int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint) {
-  return moe::tile_cost((moe::Tile)tile, mode, E, C, moe::mean_or(rows_hint, mode == moe::kTN ? K : C), K, N);
+double tile_cost(int tile, int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
+  return moe::tile_cost((moe::Tile)tile, mode, E, C, moe::mean_or(rows_hint, mode == moe::kTN ? K : C), K, N, gather_rows > 0);
 }
 int split(int64_t E, int64_t C, int64_t N) { return moe::fp32_split(E, C, N); }
 int dx_tokens(int64_t T, int64_t row_bytes) { return moe::gate_dx_tokens(T, row_bytes); }
@@ -56,7 +56,7 @@ def ffn_rules(tmp_path_factory):
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
     lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 3
     lib.tile_keeping_pre.restype, lib.tile_keeping_pre.argtypes = ctypes.c_int, [ctypes.c_int64] * 6
-    lib.tile_cost.restype, lib.tile_cost.argtypes = ctypes.c_double, [ctypes.c_int] * 2 + [ctypes.c_int64] * 5
+    lib.tile_cost.restype, lib.tile_cost.argtypes = ctypes.c_double, [ctypes.c_int] * 2 + [ctypes.c_int64] * 6
     lib.one_launch.restype, lib.one_launch.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     lib.dx_tokens.restype, lib.dx_tokens.argtypes = ctypes.c_int, [ctypes.c_int64] * 2
     lib.backward_tokens.restype, lib.backward_tokens.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]

@@ -66,9 +66,23 @@ def test_half_tile_only_where_it_may_run(ffn_rules, seed):
         for tile in (ffn_rules.tile_keeping_pre(E, C, K, N, hint, 0), ffn_rules.tile(0, E, C, K, N, hint, far)):
             assert tile != KHALF
             if tile not in (K64X128_STREAM, K64_STREAM):
-                cost = [ffn_rules.tile_cost(t, 0, E, C, K, N, hint) for t in (K256, K128, K64X128, K64)]
+                cost = [ffn_rules.tile_cost(t, 0, E, C, K, N, hint, 0) for t in (K256, K128, K64X128, K64)]
                 assert cost[tile] == min(cost), (E, C, K, N, hint)
     assert other > 100                                 # products that do run on the half without either
+
+
+def test_tile_of_transposed_operands(ffn_rules):
+    """Products with B transposed, and weight gradients of dispatched slabs, that a smaller tile runs faster (second figure) than the
+    large one (first); the same weight gradients with gathered rows, which are the faster on the large one."""
+    for E, C, mean, K, N in ((20, 5348, 1337, 3072, 256),        # 70.0, 61.2 us
+                             (6, 868, 217, 4096, 4096),          # 85.8, 72.9
+                             (24, 105, 105, 2560, 1536)):        # 54.7, 44.4
+        assert ffn_rules.tile(1, E, C, K, N, mean, 0) != K256, (E, C, K, N)
+    for E, C, mean, R, N in ((17, 292, 292, 2560, 1024),         # 55.7, 41.4; gathered 52.4, 56.7
+                             (24, 3106, 1553, 1536, 512),        # 87.0, 74.5; 91.8, 107.4
+                             (8, 1008, 806, 1024, 3072)):        # 58.0, 47.6; 59.0, 62.8
+        assert ffn_rules.tile(2, E, R, C, N, mean, 0) == K128, (E, C, R, N)
+        assert ffn_rules.tile(2, E, R, C, N, mean, E * mean) == K256, (E, C, R, N)
 
 
 def test_tile_of_exact_row_counts(ffn_rules):
