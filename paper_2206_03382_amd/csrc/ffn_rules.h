@@ -79,36 +79,40 @@ static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M,
          C * W * 2 < ((int64_t)1 << 32) && M * H * 2 < ((int64_t)1 << 32);
 }
 
-// Which tile a bf16 launch takes.  The shapes differ in how much of the chip a launch of few tiles uses, how finely its work
-// divides among the 256 compute units, and how fast a full unit runs: 256 x 256 (one block per unit) is 1.2-1.3 times
-// as fast as 128 x 128 (two) and 1.7-1.9 times as fast as 64 x 64 (three) once every unit has several tiles, and the
-// slowest by up to 3 times where it leaves most units idle.  Estimated time of a launch in microseconds:
+// Which tile a bf16 launch takes: the one with the least estimated time among those it may run on (tile_of), in microseconds
 //   base + fix * rounds + ksteps * max(lat * rounds, thr * tiles per unit),    rounds = tiles per unit / blocks per unit
-// with constants fitted to 694 measured launches (4-128 experts, 8-4096 rows each, K and N 768-4096, with and without a
-// transposed A).  Over those the choice is 2.8 % (2.3 % for weight gradients) off the best of the three on average, against
-// 21 % (24 %) for always taking the largest tile.  They are launches by themselves, without an activation: products that follow each
-// other run at the board's power limit, and take 1.2-1.7 times the estimate on the 256 tile (ViT layer 200 us where 134 are
-// estimated, 16384 tokens on 8 experts 316 and 208; 128 x 128, 17 experts x 353 rows, 48 and 28).  The choice holds there all the
-// same: without the 256 tile whole forward passes take 451 us (ViT), 740 (mid), 477 (Zipf gate) and 23650 (131072 tokens, top-8)
-// against 434, 667, 392 and 18900, training steps 2404 and 20750 against 2035 and 16020.  64 x 128 (two blocks) came later, for the launches between: two products of
-// 8 experts x 96 rows, K = N = 2048: 68 (128 x 128) and 61 us (64 x 64) -> 53.
+// but for few rows of large weights (streamed tiles, below).  The shapes differ in how much of the chip a launch of few tiles uses, how finely
+// its work divides among the 256 compute units, and how fast a full unit runs: 256 x 256 (one block per unit) is 1.2-1.3 times as
+// fast as 128 x 128 (two) and 1.7-1.9 times as fast as 64 x 64 (three) once every unit has several tiles, and the slowest by up to
+// 3 times where it leaves most units idle.  128 x 256 (kHalf, two blocks, ffn_half.h) costs more per product than 256 x 256 and less per tile.
+//
+// The constants were fitted to launches by themselves.  With the kernels as they are, over launches drawn from 4-128 experts, 50-4200
+// rows each, K and N 256-4096, the choice is off the best tile by, on average: 3.2 % in 315 forward products (gathered with GELU, and
+// plain; 34 % for always the large tile), 4.1 % in 75 that keep their pre-activations (43 %), 2.8 and 5.3 % in 85 with B transposed, plain
+// and times act' (24, 30 %), 2.5 % in 205 weight gradients of slabs (28 %), 0.9 % in 205 gathered ones (9 %).  Products that follow each
+// other run at the board's power limit and take 1.2-1.7 times the estimate on the large tile; the choice holds in whole layers all the same.
+//   256 x 256: thr 1.1.  0.98, which its main loop reaches, took products from tiles that run them faster: 100 of those between the two
+//     with B transposed at 1.07 times their time (median, up to 1.6), 130 that keep their pre-activations at 1.28, 350 weight
+//     gradients of slabs at 1.21 (17 experts x 292 rows, 2560 x 1024: 55.7 and 41.4 us).  Gathered weight gradients have 0.98: of the same
+//     350 the large tile is the faster of nearly all (0.91; 52.4 and 56.7 us), and 0.98 chooses 0.8 % off the better, 1.1 11.6 %.
+//   128 x 256: a block that has its unit for itself takes 1.2 us per K-step of 64 (its ring holds 48 KB ahead), two together 1.6.  Over 1145
+//     forward products these constants choose 3.6 % off the best, 60 of them over 4 % slower than without this tile (1.29 at most) and
+//     292 as much faster (3.1 %, 33 and 259 over 940 drawn afterwards); with lat 0.33, thr 0.72 and margins instead it was 5.8 %, 137
+//     slower (up to 1.64: 48 experts x 190 rows, 4096 x 512, 105 us here and 67 on 128 x 128) and 329 faster.  Rows that a 64-row tile holds never come here: half of the tile
+//     would be padding.  (Over 79 such products it would choose 5.2 % off the best instead of 6.5 %, but take up to 1.19 times their
+//     time: 96 experts x 53 rows, 2560 x 1280, 157 us here and 132 on 64 x 128.)
+//     32 experts x 784 rows, 768 x 3072, two products: 331 us on the large tile, 285 here; 8 x 2048, 2048 x 2048: 245 and 269.
+//     Forward products only: with a transposed B (64-byte pieces of k, where the large tile loads 128) it is the slower at nearly
+//     every size (backward of 32 x 784 rows: 251 and 198 us against 226 and 171), and a training step's first product, which
+//     writes twice, gains nothing (216 against 212).
+//   64 x 128 (two blocks) is for the launches between: two products of 8 experts x 96 rows, K = N = 2048: 68 us on 128 x 128 and 61
+//     on 64 x 64 -> 53.
 //
 // Experts of so few rows that one tile holds them read their weights once, and that is all their launch does: 64 x 128 with the
 // nontemporal hint on the weights, 64 experts x 16 rows, 1024 x 4096, two products 221 -> 189 us (5.2 -> 6.1 TB/s over both; the
 // hint alone 202).  Where that leaves units without a block, 64 x 64 one stage deeper (8 experts x 16 rows, 2048 x 2048: 40 -> 33 us).
 // Weights below 48 MB keep the plain loads: they may stay in the caches from one call to the next (17 experts, 776 x 1544,
 // 32 rows: 39 us plain, 41 streamed).
-// The large tile has a half, 128 x 256 with two blocks to a unit (ffn_half.h), which costs more per product and less per tile.  Its constants were fitted with the others' held to 143 pairs of products (4-64 experts, 150-4130
-// rows each, 512-4096 wide), over which the choice among the three was 0.9 % off the best, against 3.5 % without it: 32 experts x
-// 784 rows, 768 x 3072: 331 -> 285 us; 8 x 1100, 2048 x 2048: 176 -> 166; but 8 x 2048, 2048 x 2048: 245 on the large one, 269 here.
-// The large tile's thr was 1.1 until its loads were spread over the K-step; with 0.98 the choice between the two is 0.5 % off the
-// better over 38 pairs of the same ranges (1.1: 1.1 %; 128 experts x 2048 rows, 1024 x 4096 went to the half: the pair 3915 us, 3667 now).
-// With an operand transposed 1.1 stays: with 0.98 the large tile took, of the products between the two, 100 with B transposed (4-128
-// experts, 50-4200 rows, 256-4096 wide) at 1.07 times the time of the smaller tile (median, up to 1.6), and 350 weight gradients of
-// dispatched slabs at 1.21 times (17 experts x 292 rows, 2560 x 1024: 55.7 and 41.4 us).  A gathered weight gradient is another matter:
-// of the same 350 the large tile is the faster of nearly all (0.91 times; 52.4 and 56.7 us), and 0.98 chooses 0.8 % off the better, 1.1 11.6 %.
-// Forward products only: with a transposed B (64-byte pieces of k, where the large tile loads 128) it is the slower at nearly every size
-// (backward of 32 x 784 rows: 251 and 198 us against 226 and 171), and a training step's first product, which writes twice, gains nothing (216 against 212).
 enum class Tile { k256, k128, k64x128, k64, k64x128_stream, k64_stream, kHalf };
 
 static inline double tile_cost(Tile tile, int mode, int64_t E, int64_t rows, double mean_rows, int64_t K, int64_t N, bool gathered) {
@@ -126,8 +130,8 @@ static inline double tile_cost(Tile tile, int mode, int64_t E, int64_t rows, dou
   switch (tile) {
     // kTN: with the launch that pads its last K-step, and, where its rows are gathered, less against the 128 x 128 tile, whose K-step
     // fetches row numbers in front of every load
-    case Tile::k256: return cost(256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, mode == kNN || (mode == kTN && gathered) ? 0.98 : 1.1);
-    case Tile::kHalf: return cost(128, 256, 2, 2.0, 4.0, 0.33, 0.72);
+    case Tile::k256: return cost(256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, mode == kTN && gathered ? 0.98 : 1.1);
+    case Tile::kHalf: return cost(128, 256, 2, 2.0, 3.0, 1.2, 0.8);
     case Tile::k64x128: return cost(64, 128, 2, 2.5, 2.5, 0.3, 0.44);
     case Tile::k64: return cost(64, 64, 3, 3.0, 1.5, 0.3, 0.235);
     default: return cost(128, 128, 2, 1.5, 3.5, 0.3, 0.56);
@@ -140,20 +144,15 @@ static inline Tile choose_tile(int mode, bool large_ok, bool half_ok, int64_t E,
   auto estimate = [&](Tile t) { return tile_cost(t, mode, E, rows, mean_rows, K, N, gathered); };
   Tile best = Tile::k128;
   double least = estimate(best);
-  auto consider = [&](Tile t, double c) { if (c < least) { least = c; best = t; } };
-  if (large_ok) {
-    const double whole = estimate(Tile::k256), half = half_ok ? estimate(Tile::kHalf) : whole;
-    // against the smaller tiles the half has to be clearly ahead.  By its estimate alone it took 34 pairs of short products (K from 256
-    // on, 20-180 us a pair) from them of which 15 got slower, by up to 18 % (48 experts x 196 rows, 384 x 512: 27.5 -> 32.5 us;
-    // 8 x 730, 256 x 1280: 26.3 -> 28.4); so it keeps those it gains on (8 x 21056, 512 x 256: 179 -> 145) and loses 2 % at most.  Rows that a 64-row tile
-    // holds stay there: their launch reads weights, and half of this tile would be padding (32 x 52, 3328 x 1792: 167 us there, 178-192 here)
-    const double ahead = 1.1 * half + 3.0;
-    if (half < whole) consider(Tile::kHalf, mean_rows > 64.0 && ahead < whole ? ahead : whole);
-    else consider(Tile::k256, whole);
-  }
+  auto consider = [&](Tile t) {
+    const double c = estimate(t);
+    if (c < least) { least = c; best = t; }
+  };
+  if (large_ok) consider(Tile::k256);
+  if (large_ok && half_ok && mean_rows > 64.0) consider(Tile::kHalf);
   if (mode != kTN) {                                                // 64 x 64 was the best tile for one of 278 weight gradients
-    consider(Tile::k64x128, estimate(Tile::k64x128));
-    consider(Tile::k64, estimate(Tile::k64));
+    consider(Tile::k64x128);
+    consider(Tile::k64);
   }
   return best;
 }

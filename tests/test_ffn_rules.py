@@ -71,6 +71,19 @@ def test_half_tile_only_where_it_may_run(ffn_rules, seed):
     assert other > 100                                 # products that do run on the half without either
 
 
+def test_half_tile_not_alone_on_its_unit(ffn_rules):
+    """Products of few tiles, whose blocks have a unit each for themselves, run longer on the half tile than on a smaller one
+    (microseconds: there, here); rows that a 64-row tile holds never take it; those it is for do."""
+    for E, C, mean, K, N in ((48, 190, 190, 4096, 512),          # 67, 105
+                             (24, 105, 105, 2560, 1536),         # 42, 62
+                             (32, 144, 115, 2048, 1024),         # 38, 52
+                             (20, 178, 89, 3072, 2560),          # 73, 115
+                             (12, 118, 59, 3072, 4096), (128, 128, 64, 3072, 2048), (96, 64, 64, 1280, 3072)):
+        assert ffn_rules.tile(0, E, C, K, N, mean, 0) != KHALF, (E, C, K, N)
+    for E, C, mean, K, N in ((32, 980, 784, 768, 3072), (32, 980, 784, 3072, 768), (8, 1100, 1100, 2048, 2048), (8, 21056, 21056, 512, 256)):
+        assert ffn_rules.tile(0, E, C, K, N, mean, 0) == KHALF, (E, C, K, N)
+
+
 def test_tile_of_transposed_operands(ffn_rules):
     """Products with B transposed, and weight gradients of dispatched slabs, that a smaller tile runs faster (second figure) than the
     large one (first); the same weight gradients with gathered rows, which are the faster on the large one."""

@@ -1015,7 +1015,7 @@ def test_expert_ffn_fp32_split(moe, ffn_rules, E, C, M, H, use_counts):
     test_expert_ffn_backward(moe, synth.DT_F32, E, C, M, H, O.ACT_SILU, True, use_counts)
 
 
-@pytest.mark.parametrize("E,C,M,H", [(64, 1500, 64, 256), (64, 900, 256, 256), (40, 385, 1024, 256), (32, 784, 768, 3072)])
+@pytest.mark.parametrize("E,C,M,H", [(64, 1500, 64, 256), (64, 900, 256, 256), (48, 385, 1024, 768), (32, 784, 768, 3072)])
 def test_expert_ffn_half_tile(moe, ffn_rules, E, C, M, H):
     """The 128 x 256 tile: reductions of 2 to 96 K-steps (fewer than its ring, and more), row tiles of 1 to 8 live 16-row pieces and
     none, from the dispatch buffer and gathered, against the oracle."""
