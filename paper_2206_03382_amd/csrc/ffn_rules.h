@@ -161,9 +161,11 @@ static inline Tile choose_tile(int mode, bool large_ok, bool half_ok, int64_t E,
 // tile's reduction over four waves.  On 64 x 64 such a launch is one chain of fp32 matrix instructions per wave on a part of the units.  Two
 // products: 4 experts x 256 rows, 256 x 512 (512 and 256 tiles): 22.0 -> 15.4 us; 8 x 32, 1024 x 2048: 61 -> 34; 8 x 16, 2048 x 2048: 81 -> 56.
 // With a second round of blocks 64 x 64, which loads half as much per product, is the faster: 4 x 512, 256 x 512 (1024 and 512 tiles):
-// 23.5 there, 25.0 here; 8 x 512: 28.5 and 44.9.  Only the sizes of the buffers decide, so that every route to a product sums alike.
+// 23.5 there, 25.0 here; 8 x 512: 28.5 and 44.9.  Up to 64 k, which is two K-steps for four waves, 64 x 64 is the faster, too: 4 x 256 rows,
+// N = 512: K = 32 4.8 us there, 5.5 here, 64 5.5 and 5.9, 96 6.0 and 6.0, 128 6.5 and 6.3, 256 8.6 and 7.7.  Only the sizes of the buffers
+// decide, so that every route to a product sums alike.
 constexpr int kSplitTile = 32, kSplitParts = 4;
-static inline bool fp32_split(int64_t E, int64_t C, int64_t N) { return E * tiles_in(C, kSplitTile) * tiles_in(N, kSplitTile) <= 512; }
+static inline bool fp32_split(int64_t E, int64_t C, int64_t K, int64_t N) { return K > 64 && E * tiles_in(C, kSplitTile) * tiles_in(N, kSplitTile) <= 512; }
 
 // Rows an expert holds on average: the caller's hint, or all of them.
 static inline double mean_or(int64_t rows_hint, int64_t C) { return (double)(rows_hint > 0 && rows_hint < C ? rows_hint : C); }

@@ -493,7 +493,7 @@ static hipError_t launch_tile(TileArgs p, int64_t total, hipStream_t s) {
 template <int MODE>
 static hipError_t launch_small(int dtype, Tile tile, const TileArgs& p, int64_t total, hipStream_t s) {
   if constexpr (MODE != kTN) {
-    if (dtype == MOE_F32 && fp32_split(p.E, p.C, p.N)) return launch_tile<float, MODE, kSplitTile, kSplitTile, 2, false, kSplitParts>(p, total, s);
+    if (dtype == MOE_F32 && fp32_split(p.E, p.C, p.K, p.N)) return launch_tile<float, MODE, kSplitTile, kSplitTile, 2, false, kSplitParts>(p, total, s);
   }
   if (dtype == MOE_F32) return launch_tile<float, MODE, 64, 64, 2>(p, total, s);
   if constexpr (MODE != kTN) {

@@ -35,7 +35,7 @@ int tile_keeping_pre(int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hi
 double tile_cost(int tile, int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
   return moe::tile_cost((moe::Tile)tile, mode, E, C, moe::mean_or(rows_hint, mode == moe::kTN ? K : C), K, N, gather_rows > 0);
 }
-int split(int64_t E, int64_t C, int64_t N) { return moe::fp32_split(E, C, N); }
+int split(int64_t E, int64_t C, int64_t K, int64_t N) { return moe::fp32_split(E, C, K, N); }
 int dx_tokens(int64_t T, int64_t row_bytes) { return moe::gate_dx_tokens(T, row_bytes); }
 int64_t backward_tokens(int64_t T, int64_t E, int bias) { return moe::gate_backward_token_block(T, E, bias); }
 int64_t wide_logits(int64_t T, int64_t E, int vecw) { return moe::gate_logits_wide_experts(T, E, vecw); }
@@ -54,7 +54,7 @@ def ffn_rules(tmp_path_factory):
     lib = ctypes.CDLL(str(d / "rules.so"))
     lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
-    lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 3
+    lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 4
     lib.tile_keeping_pre.restype, lib.tile_keeping_pre.argtypes = ctypes.c_int, [ctypes.c_int64] * 6
     lib.tile_cost.restype, lib.tile_cost.argtypes = ctypes.c_double, [ctypes.c_int] * 2 + [ctypes.c_int64] * 6
     lib.one_launch.restype, lib.one_launch.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]

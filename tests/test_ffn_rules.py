@@ -115,6 +115,13 @@ def test_tile_of_tokens_beyond_4_gib(ffn_rules):
     assert ffn_rules.tile(0, E, T // E, M, H, T // E, 2 ** 23) != K256       # 64 GiB: beyond the kernel's offsets
 
 
+def test_fp32_split_where_it_is_the_faster(ffn_rules):
+    """The split 32 x 32 tile only for reductions of three K-steps and more (4 experts x 256 rows, N = 512: K = 32 4.8 us without and 5.5
+    with it, 64 5.5 and 5.9, 128 6.5 and 6.3), and only where all its tiles are on the chip at once."""
+    for K in (8, 32, 64, 72, 96, 512):
+        assert ffn_rules.split(4, 256, K, 512) == (K > 64) and not ffn_rules.split(4, 257, K, 512)
+
+
 def test_slots_in_one_launch_where_it_is_the_faster(ffn_rules):
     """Scan and assignment in one launch only where that measured faster than two (both sides beside the rule)."""
     for T, E, k in ((64, 8, 2), (2048, 8, 2), (8192, 8, 1), (4096, 8, 2), (1024, 32, 2), (512, 64, 2), (64, 16, 4)):
