@@ -23,8 +23,8 @@ RULES_SOURCE = r"""
 #include "paper_2206_03382_amd/csrc/ffn_rules.h"
 #include "paper_2206_03382_amd/csrc/gate_rules.h"
 extern "C" {
-int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total) {
-  return moe::tile_grid(E, moe::tiles_in(C, tile), NT, moe::live_row_tiles(E, C, total, tile));
+int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total, int half) {
+  return moe::tile_grid(E, moe::tiles_in(C, tile), NT, moe::live_row_tiles(E, C, total, tile), half ? moe::kHalfGroupShift : 0);
 }
 int tile(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
   return (int)moe::tile_of(mode, E, C, K, N, rows_hint, gather_rows, false);
@@ -52,7 +52,7 @@ def ffn_rules(tmp_path_factory):
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
     lib = ctypes.CDLL(str(d / "rules.so"))
-    lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5
+    lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5 + [ctypes.c_int]
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
     lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 4
     lib.tile_keeping_pre.restype, lib.tile_keeping_pre.argtypes = ctypes.c_int, [ctypes.c_int64] * 6

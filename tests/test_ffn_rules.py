@@ -3,22 +3,23 @@ import numpy as np
 import pytest
 
 
-def blocks_needed(tiles, NT):
+def blocks_needed(tiles, NT, half):
     """Blocks the kernels' tile search can ask for when expert e has tiles[e] live row tiles of NT tiles each: whole groups first,
-    a short one per expert with a remainder, dealt to 8 XCDs."""
-    live = int(tiles.sum()) * NT
-    G = 32 if live >= 1024 else (16 if live >= 512 else 8)
+    a short one per expert with a remainder, dealt to 8 XCDs.  The half tile's groups hold twice as many tiles."""
+    live = int(tiles.sum()) * NT // (2 if half else 1)
+    G = (32 if live >= 1024 else (16 if live >= 512 else 8)) * (2 if half else 1)
     per = tiles * NT
     groups = int((per // G).sum() + (per % G > 0).sum())
     return -(-groups // 8) * 8 * G
 
 
+@pytest.mark.parametrize("half", [0, 1])
 @pytest.mark.parametrize("seed", range(8))
-def test_grid_reaches_every_tile(ffn_rules, seed):
+def test_grid_reaches_every_tile(ffn_rules, seed, half):
     """Whatever the fills are, as long as they keep to the total the caller promises, in all and expert by expert."""
     rng = np.random.default_rng(seed)
     for _ in range(3000):
-        E, tile = int(rng.integers(1, 513)), int(rng.choice([64, 128, 256]))
+        E, tile = int(rng.integers(1, 513)), int(rng.choice([64, 128, 256])) if not half else 128
         C, NT = int(2 ** rng.uniform(0, 14)), int(2 ** rng.uniform(0, 7))
         total = int(rng.integers(1, E * C + 1)) if rng.random() < 0.5 else E * int(rng.integers(1, C + 1))
         kind = rng.integers(4)
@@ -33,8 +34,8 @@ def test_grid_reaches_every_tile(ffn_rules, seed):
             fills = rng.integers(0, C + 1, size=E)
         fills = np.minimum(fills, np.maximum(total - (np.cumsum(fills) - fills), 0))      # within the total
         assert fills.sum() <= total
-        grid = ffn_rules.grid(E, C, tile, NT, total)
-        assert grid >= blocks_needed(-(-fills // tile), NT), (E, C, tile, NT, total)
+        grid = ffn_rules.grid(E, C, tile, NT, total, half)
+        assert grid >= blocks_needed(-(-fills // tile), NT, half), (E, C, tile, NT, total)
 
 
 def test_grid_is_bounded_by_the_rows_that_exist(ffn_rules):
@@ -42,8 +43,10 @@ def test_grid_is_bounded_by_the_rows_that_exist(ffn_rules):
     E, T, k = 128, 2048, 2
     for tile, NT in ((64, 8), (64, 32), (128, 16), (256, 4)):
         live = (T * k // tile + E) * NT
-        assert ffn_rules.grid(E, T, tile, NT, T * k) <= live + 32 * (E + 8)
-        assert ffn_rules.grid(E, T, tile, NT, E * T) >= E * T // tile * NT
+        assert ffn_rules.grid(E, T, tile, NT, T * k, 0) <= live + 32 * (E + 8)
+        assert ffn_rules.grid(E, T, tile, NT, E * T, 0) >= E * T // tile * NT
+    live = (T * k // 128 + E) * 16
+    assert ffn_rules.grid(E, T, 128, 16, T * k, 1) <= live + 64 * (E + 8)
 
 
 K256, K128, K64X128, K64, K64X128_STREAM, K64_STREAM, KHALF = range(7)

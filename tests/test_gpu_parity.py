@@ -485,12 +485,16 @@ def test_layer_streamed_weights(moe, ffn_rules, M):
     test_layer_forward_backward(moe, cfg)
 
 
+K256, K128, K64X128, K64, KHALF = 0, 1, 2, 3, 6                               # Tile of csrc/ffn_rules.h
+
+
 # The grouped GEMM deals its live tiles to the XCDs in groups of 32, 16 or 8, chosen on the device from the number of
-# live tiles (below 512: 8; below 1024: 16): fills that put the first product exactly at, just below and between the
-# thresholds, with ragged last row tiles and an empty expert.  H = 1024 gives the first product
-# four column tiles per row tile and the second one.
-@pytest.mark.parametrize("row_tiles", [127, 128, 200, 255, 256])
-def test_expert_ffn_tile_group_sizes(moe, row_tiles):
+# live tiles (below 512: 8; below 1024: 16); its half tile in groups of 64, 32 or 16 (below 1024, below 2048).  Fills that put the first
+# product exactly at, just below and between the thresholds, with ragged last row tiles and an empty expert: on the half tile, of which
+# there are 8 row_tiles - 8 (129 and 257 rows reach its thresholds, 128 and 256 are a row tile short), and, where the pre-activations are
+# kept, on the whole one (4 row_tiles).  H = 1024 gives the first product four column tiles per row tile and the second one.
+@pytest.mark.parametrize("row_tiles", [127, 128, 129, 200, 255, 256, 257])
+def test_expert_ffn_tile_group_sizes(moe, ffn_rules, row_tiles):
     dtype, E, M, H, act = synth.DT_BF16, 6, 256, 1024, O.ACT_SILU
     tiles = np.array([row_tiles - 3 * (row_tiles // 4) - 1, row_tiles // 4, 0, row_tiles // 4, 1, row_tiles // 4])   # per expert
     assert tiles.sum() == row_tiles and (tiles >= 0).all()
@@ -498,19 +502,66 @@ def test_expert_ffn_tile_group_sizes(moe, row_tiles):
     counts = (tiles * 256 + np.where(tiles > 0, ragged, 0)).astype(np.int32)
     C = int(counts.max())
     live = int(((counts + 255) // 256).sum())
-    assert live == row_tiles
+    assert live == row_tiles and int(((counts + 127) // 128).sum()) == 2 * row_tiles - 2
+    assert ffn_rules.tile(0, E, C, M, H, 0, 0) == KHALF
+    assert ffn_rules.tile_keeping_pre(E, C, M, H, 0, 0) == (K256 if row_tiles >= 128 else K128)
     cfg = synth.CONFIGS[1].scaled(T=E * C, M=M, H=H, E=E, dtype=dtype, cfg_id=45)
     inp = synth.make_inputs(cfg, seed=row_tiles, bias_std=0.5)
     Z = inp["x"].reshape(E, C, M)
     ref = O.expert_ffn(Z, inp["W1"], inp["b1"], inp["W2"], inp["b2"], act, rows=counts)
     Yd = torch.full((E, C, M), float("nan"), device="cuda").to(torch.bfloat16)
-    moe.expert_ffn(dev(Z, dtype), dev(inp["W1"], dtype), dev(inp["b1"], dtype), dev(inp["W2"], dtype), dev(inp["b2"], dtype), act,
-                   torch.from_numpy(counts).cuda(), Y=Yd)
+    Zd, W1, b1, W2, b2 = (dev(a, dtype) for a in (Z, inp["W1"], inp["b1"], inp["W2"], inp["b2"]))
+    c = torch.from_numpy(counts).cuda()
+    moe.expert_ffn(Zd, W1, b1, W2, b2, act, c, Y=Yd)
     got = host(Yd)
     rows = np.minimum(counts, C)
     mask = np.arange(C)[None, :] < rows[:, None]
     assert_close(got[mask], ref[mask], dtype, "ffn (filled rows)")
     assert np.isnan(got[~mask]).all(), "rows past counts[e] must be left untouched"
+    kept = host(moe.expert_ffn_train(Zd, W1, b1, W2, b2, act, counts=c)[0])
+    assert np.array_equal(kept[mask].view(np.uint32), got[mask].view(np.uint32))
+
+
+# Capacities that give the same rows the 64 x 64, 128 x 128, 64 x 128, 256 x 256 and 128 x 256 tiles (64 slots and more), with sums of
+# exactly cancelling products: what is left of them is their rounding, which differs as soon as two kernels add in another order.
+@pytest.mark.parametrize("rows", [61, 93, 187])
+def test_expert_ffn_same_bits_on_every_tile(moe, ffn_rules, rows):
+    """Which tile a product runs on depends on buffers and hints, so every bf16 tile has to sum alike: the products of an expert layer
+    forward, kept for training, and backward are equal bit for bit whatever the capacity.  (The tiles use matrix instructions of
+    two shapes, 32x32x16 and 16x16x32.)"""
+    E, M, H, act = 24, 768, 768, O.ACT_SILU
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+
+    def rand(*shape):
+        return torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+
+    order = torch.randperm(M, generator=gen, device="cuda")
+    a, w = rand(E, rows, M // 2), rand(E, M // 2, H)
+    Z0, W1 = torch.cat([a, -a], 2)[:, :, order].contiguous(), torch.cat([w, w], 1)[:, order].contiguous()
+    W2, dY0 = rand(E, H, M), rand(E, rows, M)
+    c = torch.full((E,), rows, dtype=torch.int32, device="cuda")
+    ref, seen = None, set()
+    for C in (64, 96, 192, 576, 832):
+        if C < rows:
+            continue
+        seen |= {(0, ffn_rules.tile(0, E, C, M, H, 0, 0)), (0, ffn_rules.tile_keeping_pre(E, C, M, H, 0, 0)), (1, ffn_rules.tile(1, E, C, M, H, 0, 0)),
+                 (2, ffn_rules.tile(2, E, M, C, H, 0, 0))}
+        Z, dY = (torch.full((E, C, M), float("nan"), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        Z[:, :rows], dY[:, :rows] = Z0, dY0
+        hidden = torch.empty((E, C, H), device="cuda", dtype=torch.bfloat16)
+        Y = moe.expert_ffn(Z, W1, None, W2, None, act, counts=c, hidden=hidden)
+        Yt, hidden_t, pre = moe.expert_ffn_train(Z, W1, None, W2, None, act, counts=c)
+        g = moe.expert_ffn_backward(Z, W1, None, W2, hidden_t, dY, act, counts=c, pre=pre)
+        got = {"hidden": hidden[:, :rows], "Y": Y[:, :rows], "hidden_t": hidden_t[:, :rows], "Yt": Yt[:, :rows], "pre": pre[:, :rows],
+               "dZ": g["dZ"][:, :rows], "dW1": g["dW1"], "dW2": g["dW2"]}
+        assert pre[:, :rows].any() and pre[:, :rows].abs().max() < 1e-3       # nothing but rounding
+        if ref is None:
+            ref = {name: t.clone() for name, t in got.items()}
+            assert torch.equal(ref["hidden"], ref["hidden_t"]) and torch.equal(ref["Y"], ref["Yt"])
+        for name, t in got.items():
+            assert torch.equal(t, ref[name]), (C, name)
+    tiles = {61: (K256, K128, K64X128, K64, KHALF), 93: (K256, K128, K64X128, KHALF), 187: (K256, K64X128, KHALF)}[rows]
+    assert {(0, t) for t in tiles} | {(1, t) for t in tiles if t != KHALF} | {(2, K256), (2, K128)} <= seen
 
 
 def test_expert_ffn_gelu_epilogue_range(moe):
@@ -861,6 +912,7 @@ def test_layer_train_step_on_the_large_tile(moe, ffn_rules):
     for hint, rows in ((T // E, T), (0, 0)):                                  # the layer; the stage entry points
         for mode, a, b in ((0, M, H), (0, H, M), (1, M, H), (1, H, M)):
             assert ffn_rules.tile(mode, E, C, a, b, hint, rows if a == M and mode == 0 else 0) == 0
+        assert ffn_rules.tile_keeping_pre(E, C, M, H, hint, rows) == 0
         assert ffn_rules.tile(2, E, H, C, M, hint, 0) == 0 and ffn_rules.tile(2, E, M, C, H, hint, rows) == 0
     fills = [0, 1, 63, 64, 65, 128, 129, 192, 193, 31, 33, 95, 97, 127, 160, 224, 255, 256, 257, 321]
     fills += [(T - sum(fills)) // 4 + i for i in (-3, -1, 1, 3)]
@@ -969,8 +1021,6 @@ def test_layer_forward_in_hip_graph(moe):
 # ----------------------------------------------------------------------------------------------------------------
 # dispatch fused into the first expert GEMM: same results as encode + FFN on the rows that exist
 # ----------------------------------------------------------------------------------------------------------------
-K256, KHALF = 0, 6                                                            # Tile of csrc/ffn_rules.h
-
 FUSED_LAYERS = [
     synth.CONFIGS[1].scaled(T=1500, M=256, H=512, E=8),
     synth.CONFIGS[2].scaled(T=1960, M=768, H=1024, E=32),
@@ -1016,21 +1066,27 @@ def test_expert_ffn_fp32_split(moe, ffn_rules, E, C, M, H, use_counts):
     test_expert_ffn_backward(moe, synth.DT_F32, E, C, M, H, O.ACT_SILU, True, use_counts)
 
 
-@pytest.mark.parametrize("E,C,M,H", [(64, 1500, 64, 256), (64, 900, 256, 256), (48, 385, 1024, 768), (32, 784, 768, 3072)])
-def test_expert_ffn_half_tile(moe, ffn_rules, E, C, M, H):
+@pytest.mark.parametrize("E,C,M,H,act,bias,use_counts", [(64, 1500, 64, 256, O.ACT_GELU, True, True), (64, 900, 256, 256, O.ACT_GELU, True, True),
+                                                         (48, 385, 1024, 768, O.ACT_GELU, True, True), (32, 784, 768, 3072, O.ACT_GELU, True, True),
+                                                         (48, 385, 1024, 768, O.ACT_SILU, False, True), (64, 900, 256, 256, O.ACT_RELU, True, False),
+                                                         (64, 900, 256, 256, O.ACT_SILU, False, False)])
+def test_expert_ffn_half_tile(moe, ffn_rules, E, C, M, H, act, bias, use_counts):
     """The 128 x 256 tile: reductions of 2 to 96 K-steps (fewer than its ring, and more), row tiles of 1 to 8 live 16-row pieces and
-    none, from the dispatch buffer and gathered, against the oracle."""
-    dtype, act = synth.DT_BF16, O.ACT_GELU
+    none, from the dispatch buffer and gathered, with every activation (the second products have none), against the oracle."""
+    dtype = synth.DT_BF16
     assert ffn_rules.tile(0, E, C, M, H, 0, 0) == KHALF
     edges = [0, 1, 15, 16, 17, 32, 33, 64, 95, 97, 112, 113, 127, 128, 129, 255, 256, 257, C - 1, C, C + 5]
     counts = np.array([edges[e % len(edges)] for e in range(E)], dtype=np.int32)
+    if not use_counts:
+        counts[:] = C
     cfg = synth.CONFIGS[1].scaled(T=E * C, M=M, H=H, E=E, dtype=dtype, cfg_id=47)
-    inp = synth.make_inputs(cfg, seed=M, bias_std=0.5)
+    inp = synth.make_inputs(cfg, seed=M, bias_std=0.5 if bias else 0.0)
     Z = inp["x"].reshape(E, C, M)
     some = np.arange(len(edges))                                              # every edge once: the oracle's share
-    ref = O.expert_ffn(Z[some], inp["W1"][some], inp["b1"][some], inp["W2"][some], inp["b2"][some], act, rows=counts[some])
+    b1, b2 = (None if inp[n] is None else inp[n][some] for n in ("b1", "b2"))
+    ref = O.expert_ffn(Z[some], inp["W1"][some], b1, inp["W2"][some], b2, act, rows=counts[some])
     x, W1, b1, W2, b2 = (dev(inp[n], dtype) for n in ("x", "W1", "b1", "W2", "b2"))
-    c = torch.from_numpy(counts).cuda()
+    c = torch.from_numpy(counts).cuda() if use_counts else None
     Yd = torch.full((E, C, M), float("nan"), device="cuda").to(torch.bfloat16)
     moe.expert_ffn(x.view(E, C, M), W1, b1, W2, b2, act, c, Y=Yd)
     got = host(Yd)
