@@ -70,7 +70,8 @@ constexpr int kRingBytes = 5 * kTileBytes;
 // behind every eighth from there on.  All sixteen behind the barrier, every fourth product: 2-5 % slower, with or without the third stage
 // of B loaded a K-step further ahead; A's behind every fourth or sixth product: up to 1 %; reads over 40 or 56 products and the barrier
 // moved with them: 1-2 %.  With gathered rows of a transposed A both operands' loads stay behind the barrier, because the wait for
-// the row indices ahead of it would wait for B's as well.
+// the row indices ahead of it would wait for B's as well: sixteen behind every fourth product, A's first.  (A's behind every eighth and B's
+// between their second half: 3 % slower over 16 weight gradients, 128 experts x 2048 rows, 4096 x 1024 2235 -> 2136 us.)
 constexpr int kReadSpan = 48, kBarrierAt = 56, kLoadEveryA = 8, kLoadEveryB = 6, kLoadEveryGathered = 4;
 #define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
 #define PIN() __builtin_amdgcn_sched_barrier(0)
@@ -349,11 +350,15 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
     auto read_at = [&](int m) { const int r = (m * NR + kReadSpan - 1) / kReadSpan; return r < ((m + 1) * NR + kReadSpan - 1) / kReadSpan ? r : NR; };
     auto loads = [&](int m) {                                       // m: products of this K-step so far
       if (!DMA) return;
-      const int p = GK ? m - kBarrierAt - 32 : m;
-      constexpr int every = GK ? kLoadEveryGathered : kLoadEveryB;
-      if (p >= 0 && p % every == 1 && p / every < 8) dma_b(p / every, b_fill);
-      const int pa = m - kBarrierAt;
-      if (pa >= 0 && pa % kLoadEveryA == 1 && pa / kLoadEveryA < 8) dma_a(pa / kLoadEveryA, kt + 2);
+      const int p = m - kBarrierAt;
+      if (GK) {
+        const int n = p >= 0 && p % kLoadEveryGathered == 1 ? p / kLoadEveryGathered : 16;
+        if (n < 8) dma_a(n, kt + 2);
+        else if (n < 16) dma_b(n - 8, b_fill);
+        return;
+      }
+      if (m % kLoadEveryB == 1 && m / kLoadEveryB < 8) dma_b(m / kLoadEveryB, b_fill);
+      if (p >= 0 && p % kLoadEveryA == 1 && p / kLoadEveryA < 8) dma_a(p / kLoadEveryA, kt + 2);
     };
 #pragma unroll
     for (int m = 0; m < 64; ++m) {
