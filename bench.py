@@ -7,8 +7,8 @@ of seeded synthetic input that is already resident in HBM.  The bench line is th
   value      layer forward tokens/s (T / mean step time)
   roofline   the dominant kernel (grouped bf16 MFMA GEMM of the expert FFN): algorithmic FLOP per launch divided by
              its mean launch time, measured with HIP events recorded on the library's stream inside the timed loop
-             (on every fifth timed step: the event records themselves cost stream time); `traffic` is read from the
-             rocprofv3 counter summary of the same workload under profiles/ (null where none is recorded)
+             (on every fifth timed step: the event records themselves cost stream time); `kernel` and `traffic` are read from
+             the rocprofv3 counter summary of the same workload under profiles/ (traffic null where none is recorded)
   stages     per-stage mean milliseconds and, for encode/decode, algorithmic HBM GB/s
   cpu_baseline  the CPU oracle timed on this machine's host cores on a bounded sample of the same workload
   fused_dispatch  the same step through moe_layer_forward_fused (the first expert GEMM gathers its rows from the tokens on
@@ -47,13 +47,16 @@ def to_device(a, dtype_code):
     return torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
 
 
-def recorded_gemm_traffic(workload: str):
-    """HBM bytes per grouped-GEMM launch from the rocprofv3 --pmc summary of this workload under profiles/, or None."""
+def recorded_gemm(workload: str):
+    """From the rocprofv3 --pmc summary of this workload under profiles/: the grouped-GEMM kernels its two products ran on, and the
+    HBM bytes per launch; (None, None) where nothing is recorded."""
     path = os.path.join(ROOT, "profiles", f"bench_{workload}_hbm_traffic.txt")
     if not os.path.exists(path):
-        return None
-    m = re.search(r"^gemm_traffic_bytes_per_launch:\s*(\d+)", open(path).read(), flags=re.M)
-    return int(m.group(1)) if m else None
+        return None, None
+    text = open(path).read()
+    kernels = re.search(r"^gemm_kernels:\s*(.+)$", text, flags=re.M)
+    traffic = re.search(r"^gemm_traffic_bytes_per_launch:\s*(\d+)", text, flags=re.M)
+    return kernels.group(1).strip() if kernels else None, int(traffic.group(1)) if traffic else None
 
 
 def workload_name(cfg, C):
@@ -134,6 +137,7 @@ def measure(cfg, inp, steps: int, warmup: int, cold: bool = True):
     dec_bytes = (R + T) * M * es + 12 * T * k                    # read each kept expert-output row once, write [T,M]
     logit_bytes = T * M * es + M * E * es + 4 * T * E            # read every token row once, write the logits
     topk_bytes = 4 * T * E + 12 * T * k + 4 * E + 4 * E * C
+    gemm_kernels, gemm_traffic = recorded_gemm(cfg.name)
     stages = {name: round(float(ms), 5) for name, ms in zip(moe.STAGE_NAMES, stage_ms)}
     stages["gate_logits_frac_hbm"] = round(logit_bytes / (stage_ms[0] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)
     stages["gate_topk_frac_hbm"] = round(topk_bytes / (stage_ms[1] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)
@@ -173,10 +177,10 @@ def measure(cfg, inp, steps: int, warmup: int, cold: bool = True):
     res = {
         "workload": workload_name(cfg, C), "filled_slots": R, "slots": E * C,
         "ms_per_step": round(ms_per_step, 5), "tokens_per_s": round(T / (ms_per_step * 1e-3), 1),
-        "roofline": {"bound": "mfma" if bf16 else "alu", "kernel": "grouped_gemm_mfma_kernel" if bf16 else "grouped_gemm_tile_kernel",
+        "roofline": {"bound": "mfma" if bf16 else "alu", "kernel": gemm_kernels or ("grouped_gemm_mfma_kernel" if bf16 else "grouped_gemm_tile_kernel"),
                      "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                      "flop_per_launch": flop_per_gemm, "avg_launch_ms": round(gemm_ms, 5),
-                     "traffic": recorded_gemm_traffic(cfg.name)},
+                     "traffic": gemm_traffic},
         "stages": stages,
         "layer_roofline": {"t_roofline_ms": round(t_roof_ms, 5), "frac": round(t_roof_ms / ms_per_step, 4),
                            "step_ms_median": round(float(np.median(step_from_events)), 5),

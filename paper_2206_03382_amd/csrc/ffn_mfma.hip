@@ -10,13 +10,17 @@
 // steps of 64 through LDS rings of two stages for A and three for B (5 x 32 KB, all of a unit's LDS) filled by direct global->LDS
 // loads (16 bytes per lane, no staging registers).  Within a wave every MFMA is followed by at most one LDS read and one direct load, so the
 // data movement of the next sub-step hides in the shadow of the current sub-step's MFMAs; one workgroup barrier per
-// K-step hands the LDS stages over.  With 4 x 4 tiles of v_mfma_f32_32x32x16_bf16, which takes more power for the same
-// product, the same schedule ran at 1.63 GHz where this one runs at 1.95: 8192^3 (two products) 1528 -> 1448 us, 8 experts x
-// 4096 rows, 2048 x 2048 483 -> 467 us, 32 experts x 8192 rows, 4096 x 1024 3994 -> 3857 us.  What bounded it then was the way from L2
-// into LDS (without the direct loads the same products took 0.79 of the time): with two stages of each operand all sixteen loads of
-// a K-step crowd into the half of a K-step between the barrier that frees their stage and its end.  The third stage of B lets its loads go
-// out before the barrier and A's after it, one in 6 to 8 products throughout: the same shapes 1496 -> 1467 us, 475 -> 446, 3865 ->
-// 3604 (1.5, 1.23 and 1.22 PFLOP/s; a tile of 16 to 64 K-steps spends 8 to 10 us outside the loop).
+// K-step hands the LDS stages over.
+//
+// What bounds it is the board's power limit, and next to it the way from L2 into LDS.  4 x 4 tiles of v_mfma_f32_32x32x16_bf16 take
+// more power for the same product; on the same two stages of each operand 8192^3 (two products) took 1528 us so and 1448 in this form, 8
+// experts x 4096 rows, 2048 x 2048 483 and 467, 32 x 8192, 4096 x 1024 3994 and 3857.  With two stages of each operand all sixteen
+// loads of a K-step crowd into the half of a K-step between the barrier that frees their stage and its end.  The third stage of B
+// lets its loads go out before the barrier and A's after it, one in 6 to 8 products throughout: the same shapes, on another board,
+// 1496 -> 1467 us, 475 -> 446, 3865 -> 3604 (1.5, 1.23 and 1.22 PFLOP/s; a tile of 16 to 64 K-steps spends 8 to 10 us outside the loop).  By counters, 128 experts x 8192 rows, 4096 x 1024, before
+// both and now: matrix cores busy 0.68 -> 0.71 of the time at 1.60 -> 1.64 GHz, and 0.51 -> 0.54 at 1.82 -> 1.89 in the
+// second product.  Weight gradients with few K-steps or few tiles per unit, which the power limit does not bind, were up to 8 %
+// faster on the former loop (16 experts x 495 slots, 1536 x 3072: 104 and 109 us), the others are up to 14 % faster on this one.
 //
 // LDS layouts (both written by the direct loads, which place lane l's 16 bytes at base + 16 l):
 //   A tile  [256 rows][8 chunks of 8 k]:   chunk g of row r is stored at chunk position g ^ ((r / 2) % 8), so the 16 lanes
@@ -601,10 +605,10 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
 #undef MOE_TILE_LOOP
 
   // ---- epilogue: activation, bf16; transposed through LDS so that global stores are 16 bytes per lane and a
-  // wave's store covers 4 rows x 256 contiguous bytes.  After the last barrier of the main loop no wave reads the
-  // stages and no direct load is in flight, so wave w may use the 32 KB at smem + 32 KB * w as its own
-  // [128 rows][16 chunks of 8 columns]; chunk c of row r sits at position c ^ (r % 16), which makes both the 8-byte
-  // writes (32 rows per instruction) and the 16-byte row-contiguous reads conflict-free.
+  // wave's store covers 4 rows x 256 contiguous bytes.  After the last barrier of the main loop no direct load is in flight and no
+  // wave reads the stages, but for what the last K-step reads ahead and nobody uses, so wave w may use the 32 KB at
+  // smem + 32 KB * w as its own [128 rows][16 chunks of 8 columns]; chunk c of row r sits at position c ^ (r % 16), which makes
+  // both the 8-byte writes (16 rows per instruction) and the 16-byte row-contiguous reads conflict-free.
   // A DUAL kernel writes the tile twice: first the values before the activation (what a training step keeps for the
   // backward pass), then the activated ones.
   char* wtile = smem + wave * 32768;

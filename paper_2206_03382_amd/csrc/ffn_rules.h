@@ -101,7 +101,8 @@ static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M,
 //     slower (up to 1.64: 48 experts x 190 rows, 4096 x 512, 105 us here and 67 on 128 x 128) and 329 faster.  Rows that a 64-row tile holds never come here: half of the tile
 //     would be padding.  (Over 79 such products it would choose 5.2 % off the best instead of 6.5 %, but take up to 1.19 times their
 //     time: 96 experts x 53 rows, 2560 x 1280, 157 us here and 132 on 64 x 128.)
-//     32 experts x 784 rows, 768 x 3072, two products: 331 us on the large tile, 285 here; 8 x 2048, 2048 x 2048: 245 and 269.
+//     Two products, on the large tile and here: 8 experts x 1100 rows, 2048 x 2048 181 and 165 us; 8 x 2048 239 and 268; 32 x 784, 768 x
+//     3072 327 and 315, with 784 rows on average 335 and 349 (whole ViT passes 390 and 385, 634 and 635).
 //     Forward products only: with a transposed B (64-byte pieces of k, where the large tile loads 128) it is the slower at nearly
 //     every size (backward of 32 x 784 rows: 251 and 198 us against 226 and 171), and a training step's first product, which
 //     writes twice, gains nothing (216 against 212).
