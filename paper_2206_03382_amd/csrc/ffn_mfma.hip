@@ -46,21 +46,9 @@
 // The two MFMA operands are passed swapped (B fragment first), so that a lane's accumulator registers hold four
 // consecutive output columns of one row: D'[n][m] with m = lane % 16, n = 4 (lane/16) + v.  The
 // epilogue packs them to 8 bytes, transposes the wave's 128 x 128 tile through LDS and stores whole 256-byte row pieces.
-#include <cmath>
-#include <type_traits>
-
-#include "common.h"
-#include "ffn_rules.h"
+#include "ffn_device.h"
 
 namespace moe {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) short short4v;
-typedef __attribute__((ext_vector_type(8))) short short8v;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 namespace {
 
@@ -77,20 +65,6 @@ constexpr int kRingBytes = 5 * kTileBytes;
 // the row indices ahead of it would wait for B's as well: sixteen behind every fourth product, A's first.  (A's behind every eighth and B's
 // between their second half: 3 % slower over 16 weight gradients, 128 experts x 2048 rows, 4096 x 1024 2235 -> 2136 us.)
 constexpr int kReadSpan = 48, kBarrierAt = 56, kLoadEveryA = 8, kLoadEveryB = 6, kLoadEveryGathered = 4;
-#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
-#define PIN() __builtin_amdgcn_sched_barrier(0)
-
-// Direct global->LDS load of 16 bytes per lane from base + voff: lane l's data lands at lds_addr + 16 l.  Written as
-// inline assembly so that the compiler does not serialise the prefetch against the LDS reads of the other stage;
-// completion is tracked by hand (s_waitcnt vmcnt + barrier before a stage is read).
-__device__ __forceinline__ void global_to_lds_16(const char* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds_addr) : "memory", "m0");
-}
-// The same from an address of the lane's own; STREAM: with the nontemporal hint, for data that is read once.
-template <bool STREAM = false> __device__ __forceinline__ void global_to_lds_16(const char* addr, uint32_t lds_addr) {
-  if constexpr (STREAM) asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(addr), "s"(lds_addr) : "memory", "m0");
-  else asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(addr), "s"(lds_addr) : "memory", "m0");
-}
 
 // Branch-free activations for the bf16 epilogue.  gelu(v) = v Phi(v) with Phi(-y) = erfc(y / sqrt 2) / 2 for y = |v|:
 // e = 2^-P(y) with a degree-5 polynomial P fitted to -log2 erfc(y / sqrt 2) (weighted least squares on [0, 9] with P(0) = 0;
@@ -143,84 +117,7 @@ struct Frags {
   bf16x8 a[8], b[8];
 };
 
-// Inclusive prefix sum over the 64 lanes with data-parallel primitives (shifts inside rows of 16 lanes, then the rows'
-// totals broadcast forward): no trip through the LDS crossbar, a few cycles per step.
-__device__ __forceinline__ int wave_inclusive_scan(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);    // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);    // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);    // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);    // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
 }  // namespace
-
-// Which tile block number b works on (see the numbering described in the kernel below).  Returns kTileNone past the last
-// live group, kTileIdle for an idle slot of a short group, kTileLive otherwise with the expert, its row and column tile and
-// the expert's number of real rows.
-constexpr int kTileLive = 0, kTileIdle = 1, kTileNone = 2;
-template <int TILE_ROWS, int GROUP_SHIFT = 0>
-__device__ __forceinline__ int find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
-                                         int& e_out, int& mt_out, int& nt_out, int& rows_out) {
-  auto live_rows = [&](int el) -> int {                             // rows of expert el that exist (its fill, at most C)
-    if (el >= E) return 0;
-    int64_t r = C;
-    if (counts) { const int64_t c = counts[el]; r = c < C ? (c > 0 ? c : 0) : C; }
-    return (int)r;
-  };
-  constexpr int kChunks = kMaxExperts / 64;
-  int rowsv[kChunks], mtv[kChunks];                                 // lane l of chunk c: rows / live row tiles of expert 64 c + l
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) rowsv[c] = c * 64 < E ? live_rows(c * 64 + lane) : 0;      // all loads in flight at once
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) mtv[c] = (rowsv[c] + TILE_ROWS - 1) / TILE_ROWS;
-  int live_tiles = 0;                                               // live tiles of all experts
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) {
-    if (c * 64 >= E) break;
-    live_tiles += __builtin_amdgcn_readlane(wave_inclusive_scan(mtv[c] * NT), 63);
-  }
-  const int gs = group_size_log2(live_tiles >> GROUP_SHIFT) + GROUP_SHIFT, G = 1 << gs;   // tiles per group
-  const int group = ((b / 8) >> gs) * 8 + b % 8, slot = (b / 8) & (G - 1);
-  int total_full = 0;                                               // full groups of all experts
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) {
-    if (c * 64 >= E) break;
-    total_full += __builtin_amdgcn_readlane(wave_inclusive_scan((mtv[c] * NT) >> gs), 63);
-  }
-  const bool short_group = group >= total_full;
-  const int target = short_group ? group - total_full : group;
-  int e = -1, mte = 0, rank = 0, rows_e = 0;                        // expert, its live row tiles, group's rank among its own, its rows
-  int base = 0;
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) {
-    if (c * 64 >= E || e >= 0) break;
-    const int mt_l = mtv[c];
-    const int ng_l = short_group ? (((mt_l * NT) & (G - 1)) != 0 ? 1 : 0) : (mt_l * NT) >> gs;
-    const int inc = wave_inclusive_scan(ng_l);                      // inclusive prefix sum over the wave
-    const int tot = __builtin_amdgcn_readlane(inc, 63);
-    if (target < base + tot) {
-      const unsigned long long hit = __ballot(base + inc > target);
-      const int l = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
-      e = c * 64 + l;                                               // the same in every lane: keep them in scalar registers
-      mte = __builtin_amdgcn_readlane(mt_l, l);
-      rows_e = __builtin_amdgcn_readlane(rowsv[c], l);
-      rank = target - (base + __builtin_amdgcn_readlane(inc - ng_l, l));
-    }
-    base += tot;
-  }
-  if (e < 0) return kTileNone;                                      // past the last live group
-  const int q = ((short_group ? (mte * NT) >> gs : rank) << gs) + slot;
-  if (q >= mte * NT) return kTileIdle;                              // idle slot of a short group
-  const int full = (NT / 8) * mte * 8;                              // live tiles of this expert in full 8-column blocks
-  int mt, nt;
-  if (q < full) { mt = (q % (mte * 8)) / 8; nt = (q / (mte * 8)) * 8 + q % 8; }
-  else { const int w = NT % 8, r = q - full; mt = r / w; nt = (NT / 8) * 8 + r % w; }
-  e_out = e; mt_out = mt; nt_out = nt; rows_out = rows_e;
-  return kTileLive;
-}
 
 #include "ffn_tile.h"
 #include "ffn_half.h"
@@ -483,19 +380,9 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
                                                                      uint16_t* __restrict__ pre_out) {
   __shared__ __attribute__((aligned(1024))) char smem[kRingBytes];
 
-  // ---- which tile -------------------------------------------------------------------------------------------------
-  // An expert's live tiles (row tiles below its fill x all column tiles) are numbered by blocks of 8 tile columns and,
-  // inside a block, row by row: 32 consecutive numbers are 4 row tiles x 8 column tiles that share A rows and B
-  // columns.  Each expert's numbering is cut into groups of 32; the full groups of all experts are numbered first,
-  // then the short last groups (ragged tails), and this sequence is dealt round-robin to the 8 XCDs: hardware deals
-  // blocks round-robin, so block b runs on XCD b % 8, whose 32 CUs hold one group at a time in their own L2.  Counting
-  // only live groups, full ones first, keeps the XCDs evenly loaded whatever the experts' fills are.  Every wave finds
-  // its group by prefix sums over the experts' group counts, 64 experts per step.  A launch with few live tiles (a
-  // couple of rounds per compute unit or less) cuts groups of 16 or 8 instead: whole groups go to one XCD, and with 32
-  // per group a handful of them would leave some XCDs with twice the work of others.
   const int lane = threadIdx.x & 63;
   int e, mt, nt, rows_e;
-  if (find_tile<BM>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e) != kTileLive) return;
+  if (!find_tile<BM>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e)) return;
   const int64_t rows = rows_e;                                      // already here from the search: no second trip to memory
   const int64_t m0 = (int64_t)mt * BM;
   if (m0 >= rows) return;                                           // cannot happen (mt < mte); keeps every access in the slab

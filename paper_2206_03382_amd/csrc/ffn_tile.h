@@ -23,29 +23,9 @@
 
 namespace {
 
-struct TileArgs {
-  const void* A;
-  const void* B;
-  const void* bias;
-  const int32_t* counts;
-  const int32_t* gather;        // slot -> row [E, slots]: A is one matrix of gather_rows rows, [., K] (kNN) or [., C] (kTN, GK)
-  int64_t gather_rows;
-  int64_t C;                    // rows of A (kNN, kNT) or its width (kTN)
-  int64_t K;                    // length of the reduction; slots per expert (kTN)
-  int N, E, MT, NT;
-  int plain;                    // block y, x = expert, tile of it; else the numbering of find_tile in x
-  void* out;
-  const int32_t* kfill;         // kTN: live slots per expert
-  const void* pre;              // kNT: multiply by act'(pre) (act >= 0) or add pre (act < 0)
-  void* pre_out;                // kNN: the values before the activation go here as well
-  int act;                      // MOE_ACT_*, + kFullAct (bf16 results) for the form with erf and true divisions; < 0: none
-  int64_t ktotal;               // PART: length of the whole reduction, of which every "expert" is K consecutive k
-};
-
 // The activations of bf16 results.  The fit behind epilogue_act is good to 6e-7, which is below a bf16 rounding except where GeLU
 // itself is small: at -4 it is off by 0.4 %, twice that rounding, and the erf form by 0.02 %.  Widths the large tile does not
 // take have always had the erf form (and true divisions) and keep it, whichever tile they run on; widths it takes keep the fit.
-constexpr int kFullAct = 4;
 template <int ACT> __device__ __forceinline__ float tile_act(float v) {
   if constexpr (ACT >= kFullAct) return apply_act(v, ACT - kFullAct);
   else return epilogue_act<ACT>(v);
@@ -62,8 +42,6 @@ template <int MOST, int L> __device__ __forceinline__ void wait_for_loads(int la
   }
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(MOST * L) : "memory");
 }
-
-__device__ __align__(256) uint4 g_zero_piece[16];                   // stays zero: where pieces past the reduction's end are read
 
 // GK (kTN): A's k rows (slots) are gathered; the row numbers of a K-step are fetched a K-step before its loads go out.
 // PART (kTN): one long product cut along its reduction: "expert" e reduces k = e K .. e K + K - 1, and the sums leave as fp32.
@@ -102,7 +80,7 @@ __global__ __launch_bounds__(WR * WC * KS * 64, 2) void grouped_gemm_tile_kernel
   // ---- which tile: the search of the large kernel, or plain numbering where that does not do ---------------------
   int e, mt, nt, rows;
   if (!p.plain) {
-    if (find_tile<BM>(blockIdx.x, lane, p.E, p.C, p.counts, p.NT, e, mt, nt, rows) != kTileLive) return;
+    if (!find_tile<BM>(blockIdx.x, lane, p.E, p.C, p.counts, p.NT, e, mt, nt, rows)) return;
   } else {
     e = blockIdx.y;
     mt = blockIdx.x / p.NT;
