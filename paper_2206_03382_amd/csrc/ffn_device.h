@@ -47,6 +47,13 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
 
 }  // namespace
 
+// Rows of expert e that exist: its fill, at most C.
+__device__ __forceinline__ int live_rows_of(int e, int64_t C, const int32_t* __restrict__ counts) {
+  if (!counts) return (int)C;
+  const int64_t c = counts[e];
+  return (int)(c < C ? (c > 0 ? c : 0) : C);
+}
+
 // Which tile block number b works on, or false where there is none for it.
 // An expert's live tiles (row tiles below its fill x all column tiles) are numbered by blocks of 8 tile columns and, inside a block,
 // row by row, so that 32 consecutive numbers are 4 row tiles x 8 column tiles that share A rows and B columns; the experts follow
@@ -55,16 +62,10 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
 template <int TILE_ROWS>
 __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
                                           int& e_out, int& mt_out, int& nt_out, int& rows_out) {
-  auto live_rows = [&](int el) -> int {                             // rows of expert el that exist (its fill, at most C)
-    if (el >= E) return 0;
-    int64_t r = C;
-    if (counts) { const int64_t c = counts[el]; r = c < C ? (c > 0 ? c : 0) : C; }
-    return (int)r;
-  };
   constexpr int kChunks = kMaxExperts / 64;
   int rowsv[kChunks], upto[kChunks];                                // lane l of chunk c: rows of expert 64 c + l; live tiles up to it
 #pragma unroll
-  for (int c = 0; c < kChunks; ++c) rowsv[c] = c * 64 < E ? live_rows(c * 64 + lane) : 0;      // all loads in flight at once
+  for (int c = 0; c < kChunks; ++c) rowsv[c] = c * 64 + lane < E ? live_rows_of(c * 64 + lane, C, counts) : 0;      // all loads in flight at once
   int live = 0;                                                     // live tiles of all experts
 #pragma unroll
   for (int c = 0; c < kChunks; ++c) {
@@ -116,6 +117,19 @@ struct TileArgs {
   int act;                      // MOE_ACT_*, + kFullAct (bf16 results) for the form with erf and true divisions; < 0: none
   int64_t ktotal;               // PART: length of the whole reduction, of which every "expert" is K consecutive k
 };
+
+// Fills in the tile counts and the grid of a launch on tiles of bm x bn (total: rows of all experts that exist, at most); false
+// where no grid holds it.
+static inline bool tile_launch(TileArgs& p, int bm, int bn, int64_t total, dim3& grid) {
+  p.MT = (int)ceil_div(p.C, bm);
+  p.NT = (int)ceil_div(p.N, bn);
+  // more experts than the search takes, or more blocks than a grid dimension holds (2^32 threads: launches beyond run cut short)
+  int64_t blocks = tile_grid(p.E, p.MT, p.NT, live_row_tiles(p.E, p.C, total, bm));
+  p.plain = p.E > kMaxExperts || blocks >= kMaxBlocks;
+  if (p.plain) blocks = (int64_t)p.MT * p.NT;
+  grid = dim3((unsigned)blocks, p.plain ? (unsigned)p.E : 1);
+  return blocks < kMaxBlocks;
+}
 
 // TileArgs::act of bf16 results: the form of the activations with erf and true divisions.
 constexpr int kFullAct = 4;

@@ -1,5 +1,5 @@
-// The grouped GEMM of ffn_mfma.hip for what its 256 x 256 tile does not cover or does not suit: fp32 storage, bf16 with any
-// K and N that are multiples of 8, and launches with few tiles.  Included by ffn_mfma.hip (same helpers, same operand layouts).
+// The grouped GEMM of ffn_mfma.hip for what its larger tiles do not cover or do not suit: fp32 storage, and bf16 launches with few
+// tiles, with any K and N that are multiples of 8.  Included by ffn_mfma.hip (same helpers, same operand layouts).
 //
 //   out[e] = epilogue(A[e] * B[e] + bias[e]) in the layouts kNN, kNT and kTN, bf16 (v_mfma_f32_32x32x16_bf16) or fp32
 //   (v_mfma_f32_32x32x2_f32: full fp32 products and sums), fp32 accumulation.
@@ -12,28 +12,16 @@
 //   k-contiguous operand: [rows][8 pieces of 16 bytes], piece g of row r at position g ^ ((r / 2) % 8)  (ds_read_b128)
 //   k-slow operand:       [k rows][width], bf16 pieces swizzled for ds_read_b64_tr_b16, fp32 read as single words
 // Several blocks share a compute unit (72 KB of LDS or less each), so that one block's matrix instructions cover another's
-// barrier, load latency, tile search and epilogue; what is left binds by LDS reads (128 x 128: about three quarters of
-// the LDS rate at the matrix cores' peak) and, for few tiles, by how evenly they divide among the units.
+// barrier, load latency, tile search and epilogue; what is left binds by LDS reads and, for few tiles, by how evenly they divide
+// among the units.
 //
 // What it replaced was an fp32 FMA kernel on operands transposed and padded in memory, at 12 TFLOP/s in either type.
 // Measured, training step of 17 experts x 353 rows, M = 776, H = 1544, bf16: the six products 645-700 us -> 35-57 us each,
-// step 5060 -> 337 us with all its other kernels.  8 experts x 1024 rows, M = 512, H = 1024, fp32: products 166-228 us -> 72-95 us
+// step 5060 -> 304 us with all its other kernels.  8 experts x 1024 rows, M = 512, H = 1024, fp32: products 166-228 us -> 72-95 us
 // (117 TFLOP/s in the weight gradients; fp32 matrix peak 157), step 1585 -> 603 us.  8 experts x 4 rows, M = H = 2048, bf16: 29 us
 // on the large tile -> 13 us (67 MB of weights: 5.1 TB/s), layer 121 -> 51 us.
 
 namespace {
-
-// The activations of bf16 results.  The fit behind epilogue_act is good to 6e-7, which is below a bf16 rounding except where GeLU
-// itself is small: at -4 it is off by 0.4 %, twice that rounding, and the erf form by 0.02 %.  Widths the large tile does not
-// take have always had the erf form (and true divisions) and keep it, whichever tile they run on; widths it takes keep the fit.
-template <int ACT> __device__ __forceinline__ float tile_act(float v) {
-  if constexpr (ACT >= kFullAct) return apply_act(v, ACT - kFullAct);
-  else return epilogue_act<ACT>(v);
-}
-template <int ACT> __device__ __forceinline__ float tile_act_grad(float p) {
-  if constexpr (ACT >= kFullAct) return apply_act_grad(p, ACT - kFullAct);
-  else return epilogue_act_grad<ACT>(p);
-}
 
 // Waits until at most min(later, MOST) K-steps' loads, L of them each, are outstanding.
 template <int MOST, int L> __device__ __forceinline__ void wait_for_loads(int later) {
@@ -85,9 +73,7 @@ __global__ __launch_bounds__(WR * WC * KS * 64, 2) void grouped_gemm_tile_kernel
     e = blockIdx.y;
     mt = blockIdx.x / p.NT;
     nt = blockIdx.x % p.NT;
-    int64_t r = p.C;
-    if (p.counts) { const int64_t c = p.counts[e]; r = c < p.C ? (c > 0 ? c : 0) : p.C; }
-    rows = (int)r;
+    rows = live_rows_of(e, p.C, p.counts);
   }
   const int64_t m0 = (int64_t)mt * BM;
   if (m0 >= rows) return;
@@ -446,14 +432,8 @@ __global__ __launch_bounds__(WR * WC * KS * 64, 2) void grouped_gemm_tile_kernel
 
 template <typename ET, int MODE, int BM, int BN, int NS, bool STREAM = false, int KS = 1>
 static hipError_t launch_tile(TileArgs p, int64_t total, hipStream_t s) {
-  p.MT = (int)ceil_div(p.C, BM);
-  p.NT = (int)ceil_div(p.N, BN);
-  // more experts than the search takes, or more blocks than a grid dimension holds (2^32 threads: launches beyond run cut short)
-  int64_t blocks = tile_grid(p.E, p.MT, p.NT, live_row_tiles(p.E, p.C, total, BM));
-  p.plain = p.E > kMaxExperts || blocks >= kMaxBlocks;
-  if (p.plain) blocks = (int64_t)p.MT * p.NT;
-  if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks, p.plain ? (unsigned)p.E : 1);
+  dim3 grid;
+  if (!tile_launch(p, BM, BN, total, grid)) return hipErrorInvalidValue;
   if constexpr (MODE == kTN) {
     if (p.gather) {
       grouped_gemm_tile_kernel<ET, MODE, BM, BN, 2, 2, NS, true><<<grid, dim3(256), 0, s>>>(p);
@@ -483,5 +463,5 @@ static hipError_t launch_small(int dtype, Tile tile, const TileArgs& p, int64_t 
       default: break;
     }
   }
-  return launch_tile<uint16_t, MODE, 128, 128, 2>(p, total, s);
+  return launch_ring<MODE, 128, 128>(p, total, s);
 }

@@ -564,6 +564,23 @@ def test_expert_ffn_same_bits_on_every_tile(moe, ffn_rules, rows):
     assert {(0, t) for t in tiles} | {(1, t) for t in tiles if t != KHALF} | {(2, K256), (2, K128)} <= seen
 
 
+@pytest.mark.parametrize("E,C,M,H", [(96, 257, 136, 264), (64, 130, 200, 776), (128, 193, 136, 136), (24, 129, 264, 2056), (520, 70, 72, 136)])
+def test_expert_ffn_ring_tile(moe, ffn_rules, E, C, M, H):
+    """The 128 x 128 tile in every layout: one row, column or reduction step past a tile, reductions shorter than its lookahead of two
+    K-steps, experts without rows and with all, and (weight gradients) more experts than the tile search takes."""
+    dtype = synth.DT_BF16
+    assert ffn_rules.tile(2, E, M, C, H, 0, 0) == K128 and ffn_rules.tile(2, E, H, C, M, 0, 0) == K128
+    assert E > 512 or ffn_rules.tile(0, E, C, M, H, 0, 0) == ffn_rules.tile_keeping_pre(E, C, M, H, 0, 0) == ffn_rules.tile(1, E, C, M, H, 0, 0) == K128
+    test_expert_ffn_backward(moe, dtype, E, C, M, H, O.ACT_GELU, True, True)
+
+
+def test_layer_ring_tile_gathers(moe, ffn_rules):
+    """A training step whose weight gradient gathers its rows on the 128 x 128 tile, and whose first product does."""
+    cfg = synth.CONFIGS[1].scaled(T=5000, M=136, H=520, E=32, k=2, f=1.0)
+    assert ffn_rules.tile(2, 32, 136, 313, 520, 313, 5000) == ffn_rules.tile_keeping_pre(32, 313, 136, 520, 313, 5000) == K128
+    test_layer_forward_backward(moe, cfg)
+
+
 def test_expert_ffn_gelu_epilogue_range(moe):
     """The matrix-core GEMM's GeLU epilogue through the kernel itself: one expert whose first layer is 6 x identity on
     inputs spanning [-1, 1] (so the pre-activations span [-6, 6], each an exact bf16 product) and whose second layer
