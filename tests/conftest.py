@@ -40,6 +40,7 @@ int split(int64_t E, int64_t C, int64_t K, int64_t N) { return moe::fp32_split(E
 int dx_tokens(int64_t T, int64_t row_bytes) { return moe::gate_dx_tokens(T, row_bytes); }
 int64_t backward_tokens(int64_t T, int64_t E, int bias) { return moe::gate_backward_token_block(T, E, bias); }
 int64_t wide_logits(int64_t T, int64_t E, int vecw) { return moe::gate_logits_wide_experts(T, E, vecw); }
+int one_block(int64_t T, int64_t E, int k, int64_t marked_C) { return moe::gate_in_one_block(T, E, k, marked_C); }
 int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T + 63) / 64, E, k); }
 }
 """
@@ -48,7 +49,7 @@ int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T
 @pytest.fixture(scope="session")
 def ffn_rules(tmp_path_factory):
     """The host rules of the grouped GEMM: grid(), tile_number(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, the same for a
-    product that keeps its pre-activations, tile_cost() and split(); and of the gate: one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
+    product that keeps its pre-activations, tile_cost() and split(); and of the gate: one_block(), one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
@@ -59,6 +60,7 @@ def ffn_rules(tmp_path_factory):
     lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 4
     lib.tile_keeping_pre.restype, lib.tile_keeping_pre.argtypes = ctypes.c_int, [ctypes.c_int64] * 6
     lib.tile_cost.restype, lib.tile_cost.argtypes = ctypes.c_double, [ctypes.c_int] * 2 + [ctypes.c_int64] * 6
+    lib.one_block.restype, lib.one_block.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int64]
     lib.one_launch.restype, lib.one_launch.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     lib.dx_tokens.restype, lib.dx_tokens.argtypes = ctypes.c_int, [ctypes.c_int64] * 2
     lib.backward_tokens.restype, lib.backward_tokens.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]

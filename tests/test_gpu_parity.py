@@ -142,6 +142,27 @@ def test_gate_topk_kernel_switches(moe, T, E, k):
     assert np.array_equal(got["slot_src"].cpu().numpy(), O.slot_source(ref["idx"], ref["loc"], E, C))
 
 
+@pytest.mark.parametrize("T,E,k,block", [(1, 1, 1, 1), (63, 2, 2, 1), (65, 5, 5, 1), (256, 13, 2, 1), (257, 13, 2, 0), (1023, 16, 2, 1), (1024, 8, 4, 1),
+                                         (1025, 8, 4, 0), (64, 16, 3, 0), (500, 4, 3, 1), (64, 17, 1, 0)])
+def test_gate_topk_in_one_block(moe, ffn_rules, T, E, k, block):
+    """Around the tokens, experts and choices up to which a gate is one block, in both arrival orders; infinite logits (a token
+    whose values are all -inf takes the first expert), and far more capacity than tokens."""
+    assert ffn_rules.one_block(T, E, k, -(-T * k // E)) == block
+    test_gate_topk_kernel_switches(moe, T, E, k) if E > 1 else test_gate_topk(moe, T, E, k, 1.0, 0, 0.5)
+    test_gate_topk_batch_prioritized(moe, T, E, k, 0.7, 1, 0.25)
+    logits = synth.make_logits(T, E, seed=T, quantum=0.25)
+    logits[::3] = -np.inf
+    logits[1::5, 0] = -np.inf
+    C = 4 * T
+    got = moe.gate_topk(torch.from_numpy(logits).cuda(), k, C, 0)
+    idx = np.argsort(-logits, axis=1, kind="stable")[:, :k]
+    finite = np.isfinite(np.take_along_axis(logits, idx, 1)).all(1)
+    assert finite.any() == (T > 1) and np.array_equal(got["idx"].cpu().numpy()[finite], idx[finite])
+    assert (got["idx"].cpu().numpy()[::3] == 0).all()
+    ref_slots = O.slot_source(got["idx"].cpu().numpy(), got["loc"].cpu().numpy(), E, C)
+    assert np.array_equal(got["slot_src"].cpu().numpy(), ref_slots) and int(got["counts"].sum()) == T * k
+
+
 @pytest.mark.parametrize("T,E,k", [(4096, 8, 2), (4097, 8, 2), (8193, 8, 1), (512, 64, 2), (500, 65, 2), (64, 16, 8), (64, 17, 2), (1000, 43, 3)])
 def test_gate_topk_slots_in_one_launch(moe, T, E, k):
     """Around the counts of counters, pairs and experts up to which scan and assignment are one launch."""
