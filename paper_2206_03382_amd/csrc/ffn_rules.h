@@ -23,24 +23,7 @@ static inline int64_t tiles_in(int64_t n, int64_t tile) { return (n + tile - 1) 
 // from the side buffers, which also covers an expert without any slot (one K-step of zeros).
 MOE_HOST_DEVICE inline int slot_ksteps(int64_t fill) { return fill > 0 ? (int)((fill + kLargeK - 1) / kLargeK) : 1; }
 
-// Tile that block b works on when `live` tiles exist, or -1.  The tiles are cut into 8 runs of equal length (to a tile), one to an
-// XCD: hardware deals blocks round-robin, so block b runs on XCD b % 8 and takes tile b / 8 of its run, and the tiles that an XCD holds
-// at one time are neighbours in its own L2.  Runs are even whatever the fills are.  Groups of 8 to 32 tiles of one expert, dealt round-robin,
-// were not: 17 experts x 14 tiles left an XCD with five groups of 8 for its 32 units, two rounds instead of one (42 us, 24 so).
-// Whole passes: ViT layer of 32 experts x 784 rows 396 -> 350 us, training step of 17 x 353 rows 340 -> 309, four drawn ones 1.03 to
-// 1.11 times as fast.  From kDealtTiles tiles on whole rounds of 32 tiles to an XCD are dealt instead, so that the XCDs work next to each
-// other and share what they read beyond their L2 (128 experts x 8192 rows, 4096 x 1024: layer 17.41 ms in eighths, 17.15 in groups,
-// 17.35 so on a board that had 17.38 in groups); with fewer, eighths are as good or better (17 x 353 rows: 328 us dealt).
-constexpr int kDealtTiles = 4096;
-MOE_HOST_DEVICE inline int tile_number(int b, int live) {
-  const int x = b % 8, i = b / 8;                                   // XCD, which of its tiles
-  const int left = live < kDealtTiles ? live : live & 255, dealt = (live - left) / 8;
-  if (i < dealt) return ((i >> 5) * 8 + x) * 32 + (i & 31);
-  const int t = x * left / 8 + i - dealt;
-  return t < (x + 1) * left / 8 ? 8 * dealt + t : -1;
-}
-
-// Blocks are counted as for tiles numbered in groups, which tile_number needs no more: 32 tiles to a group when the launch has several
+// Blocks are counted as for tiles numbered in groups throughout, which find_tile needs no more: 32 tiles to a group when the launch has several
 // rounds of tiles for every compute unit, fewer when it has not.
 constexpr int64_t kTilesForGroups16 = 512, kTilesForGroups32 = 1024;
 static inline int group_size_log2(int64_t live_tiles) {
@@ -58,7 +41,7 @@ constexpr int kHalfGroupShift = 1;
 
 // Blocks to launch so that every tile is reached whatever the fills turn out to be: E experts of at most MT x NT tiles, of which at
 // most `row_tiles` row tiles are live in all.  Counts a group's G blocks whole, 8 XCDs evenly, one short group to an expert: at
-// least the live tiles and a multiple of 8, which is what tile_number asks for.
+// least the live tiles and a multiple of 8, which is what find_tile (ffn_device.h) asks for.
 // The layer knows its total (every choice is one row).  Without it the grid has to hold C rows of every expert, and where the
 // capacity is far above the mean fill nearly all blocks find nothing to do, each after a tile search and holding its LDS: dynamic
 // capacity, buffers for all 2048 tokens, 128 experts, M = 4096, H = 1024: layer 746 us, 487 with the bound.

@@ -49,16 +49,6 @@ def test_grid_is_bounded_by_the_rows_that_exist(ffn_rules):
     assert ffn_rules.grid(E, T, 128, 16, T * k, 1) <= live + 64 * (E + 8)
 
 
-@pytest.mark.parametrize("live", [0, 1, 7, 8, 9, 238, 255, 256, 663, 4095, 4096, 4097, 4351, 4352, 16640, 66561])
-def test_every_tile_has_one_block(ffn_rules, live):
-    """Blocks 0 .. 8 ceil(live / 8) - 1 reach every live tile once, blocks past them none; no XCD has a tile more than another but for one."""
-    blocks = -(-live // 8) * 8
-    tiles = [ffn_rules.tile_number(b, live) for b in range(blocks + 64)]
-    assert sorted(t for t in tiles[:blocks] if t >= 0) == list(range(live)) and all(t == -1 for t in tiles[blocks:])
-    per = [sum(t >= 0 for t in tiles[x::8]) for x in range(8)]
-    assert max(per) - min(per) <= 1
-
-
 K256, K128, K64X128, K64, K64X128_STREAM, K64_STREAM, KHALF = range(7)
 
 

@@ -585,6 +585,23 @@ def test_expert_ffn_same_bits_on_every_tile(moe, ffn_rules, rows):
     assert {(0, t) for t in tiles} | {(1, t) for t in tiles if t != KHALF} | {(2, K256), (2, K128)} <= seen
 
 
+@pytest.mark.parametrize("E,C,H", [(70, 700, 1032), (513, 70, 264), (3, 3000, 4104), (9, 300, 776), (200, 130, 2056), (65, 66, 520)])
+def test_expert_ffn_every_tile_once(moe, E, C, H):
+    """Fills of every kind (none, one row, around row tiles, all, random) in launches below and beyond the tiles from which whole groups are
+    dealt to the XCDs, with more than 64 experts to search and more than the search takes.  Small integers: exact."""
+    M = 64
+    rng = np.random.default_rng(E)
+    fills = rng.integers(0, C + 1, size=E)
+    fills[:8] = np.minimum([0, 1, 64, 65, 128, 129, C, 0], C)[:E]
+    rows = torch.from_numpy(fills.astype(np.int32)).cuda()
+    Z, W1 = (torch.randint(-2, 3, s, device="cuda").to(torch.bfloat16) for s in ((E, C, M), (E, M, H)))
+    hidden = torch.full((E, C, H), float("nan"), device="cuda", dtype=torch.bfloat16)
+    moe.expert_ffn(Z, W1, None, torch.zeros((E, H, M), device="cuda", dtype=torch.bfloat16), None, O.ACT_RELU, counts=rows, hidden=hidden)
+    live = torch.arange(C, device="cuda")[None, :] < rows[:, None]
+    want = torch.bmm(Z.float(), W1.float()).clamp(min=0).to(torch.bfloat16)
+    assert torch.equal(hidden[live], want[live]) and bool(hidden[~live].isnan().all())
+
+
 @pytest.mark.parametrize("E,C,M,H", [(96, 257, 136, 264), (64, 130, 200, 776), (128, 193, 136, 136), (24, 129, 264, 2056), (520, 70, 72, 136)])
 def test_expert_ffn_ring_tile(moe, ffn_rules, E, C, M, H):
     """The 128 x 128 tile in every layout: one row, column or reduction step past a tile, reductions shorter than its lookahead of two
