@@ -602,6 +602,22 @@ def test_expert_ffn_every_tile_once(moe, E, C, H):
     assert torch.equal(hidden[live], want[live]) and bool(hidden[~live].isnan().all())
 
 
+def test_expert_ffn_backward_streamed_column_sums(moe):
+    """db2 of slabs beyond 1 GiB, whose column sums are streamed: a ragged last block of columns, rows that end inside a batch of eight and an
+    expert without any.  Bound: chains of rows / 32 + 32 additions in fp32, and one rounding to bf16."""
+    E, C, M, H = 3, 45000, 4104, 8
+    assert E * C * M * 2 >= 2 ** 30
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    Z, dY, hidden = (torch.randn((E, C, w), generator=gen, device="cuda", dtype=torch.bfloat16) for w in (M, M, H))
+    W1, W2 = (torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16) for s in ((E, M, H), (E, H, M)))
+    rows = [C, 0, 777]
+    g = moe.expert_ffn_backward(Z, W1, None, W2, hidden, dY, O.ACT_RELU, counts=torch.tensor(rows, dtype=torch.int32, device="cuda"), pre=hidden)
+    for e, n in enumerate(rows):
+        v = dY[e, :n].double()
+        ref, bound = v.sum(0), (n / 32 + 32) * 2.0 ** -24 * v.abs().sum(0)
+        assert bool(((g["db2"][e].double() - ref).abs() <= bound + 2.0 ** -8 * ref.abs()).all()), e
+
+
 @pytest.mark.parametrize("E,C,M,H", [(96, 257, 136, 264), (64, 130, 200, 776), (128, 193, 136, 136), (24, 129, 264, 2056), (520, 70, 72, 136)])
 def test_expert_ffn_ring_tile(moe, ffn_rules, E, C, M, H):
     """The 128 x 128 tile in every layout: one row, column or reduction step past a tile, reductions shorter than its lookahead of two
