@@ -163,6 +163,12 @@ def test_gate_topk_in_one_block(moe, ffn_rules, T, E, k, block):
     assert np.array_equal(got["slot_src"].cpu().numpy(), ref_slots) and int(got["counts"].sum()) == T * k
 
 
+@pytest.mark.parametrize("T,E,k", [(49088, 64, 5), (49089, 64, 5), (65472, 65, 5), (65473, 65, 5), (32705, 65, 4)])
+def test_gate_topk_lane_line(moe, T, E, k):
+    """Around the counts of 64-token blocks from which a gate of many choices decides with one lane per token."""
+    test_gate_topk_kernel_switches(moe, T, E, k)
+
+
 @pytest.mark.parametrize("T,E,k", [(4096, 8, 2), (4097, 8, 2), (8193, 8, 1), (512, 64, 2), (500, 65, 2), (64, 16, 8), (64, 17, 2), (1000, 43, 3)])
 def test_gate_topk_slots_in_one_launch(moe, T, E, k):
     """Around the counts of counters, pairs and experts up to which scan and assignment are one launch."""
