@@ -64,7 +64,9 @@ __device__ __forceinline__ int live_rows_of(int e, int64_t C, const int32_t* __r
 // left XCDs with up to a round of tiles more than others: 17 experts x 14 tiles 42 us, 24 so; ViT layer of 32 experts x 784 rows 386 ->
 // 353, training step of 17 x 353 rows 340 -> 309.  Runs of an eighth for every launch cost where XCDs next to each other
 // share what they read beyond their L2: 8 experts x 4096 rows, 2048 x 2048 (1088 tiles) layer 592 us in groups, 604 in eighths, 603 in
-// rounds of 32 cut without regard to experts, 0.996 of the rate in groups so; 17 x 353 (663 tiles) 328 in such rounds.
+// rounds of 32 cut without regard to experts, 0.996 of the rate in groups so; 17 x 353 (663 tiles) 328 in such rounds.  Experts of fewer than
+// four row tiles on average have nothing for several XCDs to share and stay in eighths: 64 experts x 16 rows, 1024 x 4096 212.0 us
+// dealt, 210.3 so.
 // Every wave finds its tile by prefix sums over the experts, 64 to a step; no host has to know the fills.
 constexpr int kDealtTiles = 1024;
 template <int TILE_ROWS>
@@ -84,7 +86,7 @@ __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, con
   // tiles of expert l that are dealt in whole groups, and what of its tiles is left
   const int x = b % 8, i = b / 8;
   int rounds = 0, groups[kChunks];                                  // lane l of chunk c: full groups up to expert 64 c + l
-  if (live >= kDealtTiles) {
+  if (live >= kDealtTiles && live >= 4 * E * NT) {
     int full = 0;
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) {
