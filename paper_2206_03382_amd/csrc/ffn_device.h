@@ -55,8 +55,7 @@ __device__ __forceinline__ int live_rows_of(int e, int64_t C, const int32_t* __r
 }
 
 // Which tile block number b works on, or false where there is none for it.
-// An expert's live tiles (row tiles below its fill x all column tiles) are numbered by blocks of 8 tile columns and, inside a block,
-// row by row, so that 32 consecutive numbers are 4 row tiles x 8 column tiles that share A rows and B columns.  Hardware deals blocks
+// An expert's live tiles (row tiles below its fill x all column tiles) are numbered as tile_in_expert says.  Hardware deals blocks
 // round-robin, so block b runs on XCD b % 8, as the b / 8-th of its tiles, and the tiles that an XCD holds at one time should be neighbours
 // in its own L2.  Launches of kDealtTiles tiles and more deal whole groups of 32 tiles of an expert to the XCDs in turn, in as many rounds as
 // there are full ones for all eight.  Everything left (all of a smaller launch) is one sequence, expert by expert, cut into 8 runs of
@@ -69,9 +68,19 @@ __device__ __forceinline__ int live_rows_of(int e, int64_t C, const int32_t* __r
 // dealt, 210.3 so.
 // Every wave finds its tile by prefix sums over the experts, 64 to a step; no host has to know the fills.
 constexpr int kDealtTiles = 1024;
-template <int TILE_ROWS>
+// EQUAL: every expert has all of its C rows (weight gradients), see equal_tile.
+template <int TILE_ROWS, bool EQUAL = false>
 __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
                                           int& e_out, int& mt_out, int& nt_out, int& rows_out) {
+  if (EQUAL) {
+    TileAt at;
+    if (!equal_tile(b, E, (int)((C + TILE_ROWS - 1) / TILE_ROWS), NT, at)) return false;
+    e_out = at.e;
+    mt_out = at.mt;
+    nt_out = at.nt;
+    rows_out = (int)C;
+    return true;
+  }
   constexpr int kChunks = kMaxExperts / 64;
   int rowsv[kChunks], upto[kChunks];                                // lane l of chunk c: rows of expert 64 c + l; live tiles up to it
 #pragma unroll
@@ -118,17 +127,11 @@ __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, con
     const int rows = __builtin_amdgcn_readlane(rowsv[c], l), mte = (rows + TILE_ROWS - 1) / TILE_ROWS;
     const int in = __builtin_amdgcn_readlane(inc, l), all = mte * NT, gone = __builtin_amdgcn_readlane(mine, l);
     const int q = dealt ? (target - (in - (all >> 5))) * 32 + (i & 31) : 32 * gone + target - (in - (all - 32 * gone));
-    const int fullc = (NT / 8) * mte * 8;                           // its tiles in full 8-column blocks
-    e_out = c * 64 + l;                                             // the same in every lane: in scalar registers
+    const TileAt at = tile_in_expert(c * 64 + l, q, mte, NT);
+    e_out = at.e;                                                   // the same in every lane: in scalar registers
+    mt_out = at.mt;
+    nt_out = at.nt;
     rows_out = rows;
-    if (q < fullc) {
-      mt_out = (q % (mte * 8)) / 8;
-      nt_out = (q / (mte * 8)) * 8 + q % 8;
-    } else {
-      const int w = NT % 8, r = q - fullc;
-      mt_out = r / w;
-      nt_out = (NT / 8) * 8 + r % w;
-    }
     return true;
   }
   return false;

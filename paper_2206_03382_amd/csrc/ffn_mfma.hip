@@ -395,7 +395,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
 
   const int lane = threadIdx.x & 63;
   int e, mt, nt, rows_e;
-  if (!find_tile<BM>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e)) return;
+  if (!find_tile<BM, MODE == kTN>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e)) return;
   const int64_t rows = rows_e;                                      // already here from the search: no second trip to memory
   const int64_t m0 = (int64_t)mt * BM;
   if (m0 >= rows) return;                                           // cannot happen (mt < mte); keeps every access in the slab

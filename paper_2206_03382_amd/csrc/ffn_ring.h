@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256, 2 * ring_bytes(TM, TN) <= 163840 ? 2 : 1) void
   const int wm = wave >> 1, wn = wave & 1, kq = lane >> 4;
   int e, mt, nt, rows;
   if (!p.plain) {
-    if (!find_tile<TM>(blockIdx.x, lane, p.E, p.C, p.counts, p.NT, e, mt, nt, rows)) return;
+    if (!find_tile<TM, MODE == kTN>(blockIdx.x, lane, p.E, p.C, p.counts, p.NT, e, mt, nt, rows)) return;
   } else {
     e = blockIdx.y;
     mt = blockIdx.x / p.NT;

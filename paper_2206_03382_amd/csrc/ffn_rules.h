@@ -23,11 +23,60 @@ static inline int64_t tiles_in(int64_t n, int64_t tile) { return (n + tile - 1) 
 // from the side buffers, which also covers an expert without any slot (one K-step of zeros).
 MOE_HOST_DEVICE inline int slot_ksteps(int64_t fill) { return fill > 0 ? (int)((fill + kLargeK - 1) / kLargeK) : 1; }
 
-// Blocks are counted as for tiles numbered in groups throughout, which find_tile needs no more: 32 tiles to a group when the launch has several
-// rounds of tiles for every compute unit, fewer when it has not.
+// Tiles per group (log2) of numberings that deal whole groups to the XCDs: 32 when the launch has several rounds of tiles for every compute
+// unit; fewer when it has not, so that the groups still spread evenly.  Blocks are counted so for every launch (tile_grid).
 constexpr int64_t kTilesForGroups16 = 512, kTilesForGroups32 = 1024;
-static inline int group_size_log2(int64_t live_tiles) {
+MOE_HOST_DEVICE inline int group_size_log2(int64_t live_tiles) {
   return live_tiles >= kTilesForGroups32 ? 5 : (live_tiles >= kTilesForGroups16 ? 4 : 3);
+}
+
+struct TileAt { int e, mt, nt; };           // expert, row tile, column tile
+
+// Tile q of the rows x NT ones of expert e: by blocks of 8 tile columns and, inside a block, row by row, so that 32 consecutive ones are 4 row
+// tiles x 8 column tiles that share A rows and B columns.
+MOE_HOST_DEVICE inline TileAt tile_in_expert(int e, int q, int rows, int NT) {
+  const int full = (NT / 8) * rows * 8;                             // its tiles in full 8-column blocks
+  if (q < full) return {e, (q % (rows * 8)) / 8, (q / (rows * 8)) * 8 + q % 8};
+  const int w = NT % 8, r = q - full;
+  return {e, r / w, (NT / 8) * 8 + r % w};
+}
+
+// Which tile block b of a weight-gradient launch (kTN) works on, E experts of MT x NT tiles each; false where there is none for it.
+// Hardware deals blocks round-robin: block b runs on XCD b % 8, as the b / 8-th of its tiles.  All experts have the same number of tiles, but a
+// tile of an expert with many rows takes several times that of one with few, so every XCD has to get its share of each expert: whole groups of an
+// expert's tiles are dealt to the XCDs in turn, then whole tails (what an expert has beyond its groups), and only the groups and tails of the
+// last rounds, fewer than eight, are cut into 8 runs of equal length (to a tile).  Runs of an eighth of all tiles gave
+// the experts with many rows to one XCD.  Imbalanced gate (Zipf), two products of 8 experts, 8192 tokens, 2048 x 2048: 218 us in groups throughout,
+// 417 in eighths, 215 so (training step 800, 986 and 761); 64 experts, 16384 tokens, 1024 x 1024: step 415, 475 and 397.  Even gate, 17 experts x
+// 353 rows, 776 x 1544: 81 us in groups throughout, 79 with the tails in eighths, 75 so.
+// No prefix sums over the experts, either, which every tile of a short reduction would pay for.
+MOE_HOST_DEVICE inline bool equal_tile(int b, int E, int MT, int NT, TileAt& at) {
+  const int n = MT * NT, gs = group_size_log2((int64_t)E * n), x = b % 8, i = b / 8;
+  const int own = n >> gs, tail = n - (own << gs), rounds = (E * own) >> 3, dealt = rounds << gs, tails = (E >> 3) * tail;   // an XCD's
+  int e, q;
+  if (i < dealt) {
+    const int g = (i >> gs) * 8 + x;
+    e = g / own;
+    q = ((g - e * own) << gs) + (i & ((1 << gs) - 1));
+  } else if (i < dealt + tails) {
+    const int j = i - dealt, r = j / tail;
+    e = r * 8 + x;
+    q = (own << gs) + j - r * tail;
+  } else {
+    const int rest = E * n - 8 * (dealt + tails), t = x * rest / 8 + i - dealt - tails, of_tails = (E & 7) * tail;
+    if (t >= (x + 1) * rest / 8) return false;
+    if (t < of_tails) {
+      const int r = t / tail;
+      e = (E & ~7) + r;
+      q = (own << gs) + t - r * tail;
+    } else {
+      const int g = 8 * rounds + ((t - of_tails) >> gs);
+      e = g / own;
+      q = ((g - e * own) << gs) + ((t - of_tails) & ((1 << gs) - 1));
+    }
+  }
+  at = tile_in_expert(e, q, MT, NT);
+  return true;
 }
 
 // Row tiles that hold rows, at most, when the experts hold `total` rows among them, each at most C.

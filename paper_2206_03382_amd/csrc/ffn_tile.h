@@ -68,7 +68,7 @@ __global__ __launch_bounds__(WR * WC * KS * 64, 2) void grouped_gemm_tile_kernel
   // ---- which tile: the search of the large kernel, or plain numbering where that does not do ---------------------
   int e, mt, nt, rows;
   if (!p.plain) {
-    if (!find_tile<BM>(blockIdx.x, lane, p.E, p.C, p.counts, p.NT, e, mt, nt, rows)) return;
+    if (!find_tile<BM, MODE == kTN>(blockIdx.x, lane, p.E, p.C, p.counts, p.NT, e, mt, nt, rows)) return;
   } else {
     e = blockIdx.y;
     mt = blockIdx.x / p.NT;

@@ -26,6 +26,12 @@ extern "C" {
 int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total, int half) {
   return moe::tile_grid(E, moe::tiles_in(C, tile), NT, moe::live_row_tiles(E, C, total, tile), half ? moe::kHalfGroupShift : 0);
 }
+int equal_tile(int b, int E, int MT, int NT, int* at) {
+  moe::TileAt t;
+  if (!moe::equal_tile(b, E, MT, NT, t)) return 0;
+  at[0] = t.e; at[1] = t.mt; at[2] = t.nt;
+  return 1;
+}
 int tile(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
   return (int)moe::tile_of(mode, E, C, K, N, rows_hint, gather_rows, false);
 }
@@ -47,13 +53,14 @@ int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T
 
 @pytest.fixture(scope="session")
 def ffn_rules(tmp_path_factory):
-    """The host rules of the grouped GEMM: grid(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, the same for a
+    """The host rules of the grouped GEMM: grid(), equal_tile(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, the same for a
     product that keeps its pre-activations, tile_cost() and split(); and of the gate: one_block(), one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
     lib = ctypes.CDLL(str(d / "rules.so"))
     lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5 + [ctypes.c_int]
+    lib.equal_tile.restype, lib.equal_tile.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
     lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 4
     lib.tile_keeping_pre.restype, lib.tile_keeping_pre.argtypes = ctypes.c_int, [ctypes.c_int64] * 6

@@ -1,4 +1,6 @@
 """The host rules of the grouped GEMM and of the gate (csrc/ffn_rules.h, csrc/gate_rules.h), compiled on their own: no GPU needed."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -47,6 +49,41 @@ def test_grid_is_bounded_by_the_rows_that_exist(ffn_rules):
         assert ffn_rules.grid(E, T, tile, NT, E * T, 0) >= E * T // tile * NT
     live = (T * k // 128 + E) * 16
     assert ffn_rules.grid(E, T, 128, 16, T * k, 1) <= live + 64 * (E + 8)
+
+
+def tiles_of_xcds(find, blocks):
+    """What find(b), a tile or None, gives for blocks 0 .. blocks - 1, XCD by XCD; none past them."""
+    assert all(find(b) is None for b in range(blocks, blocks + 64))
+    return [[t for t in (find(b) for b in range(x, blocks, 8)) if t is not None] for x in range(8)]
+
+
+def equal_tiles(ffn_rules, E, MT, NT):
+    at = (ctypes.c_int * 3)()
+    find = lambda b: tuple(at) if ffn_rules.equal_tile(b, E, MT, NT, at) else None
+    return tiles_of_xcds(find, -(-E * MT * NT // 8) * 8)
+
+
+@pytest.mark.parametrize("E", [1, 3, 7, 8, 9, 17, 64, 65, 512])
+def test_weight_gradient_tiles_once(ffn_rules, E):
+    """Every tile of a weight-gradient launch has one block, below and beyond each group size, and no XCD a tile more than another but for one."""
+    for MT, NT in [(1, 1), (1, 7), (2, 8), (3, 4), (5, 9), (8, 8), (7, 13), (19, 16)]:
+        if E * MT * NT > 40000:
+            continue
+        per = equal_tiles(ffn_rules, E, MT, NT)
+        assert sorted(sum(per, [])) == [(e, m, n) for e in range(E) for m in range(MT) for n in range(NT)]
+        assert max(map(len, per)) - min(map(len, per)) <= 1
+
+
+@pytest.mark.parametrize("E,MT,NT", [(8, 8, 8), (8, 6, 8), (16, 4, 16), (32, 12, 4), (32, 3, 12), (64, 4, 4), (64, 8, 16)])
+def test_weight_gradient_work_is_even_on_imbalanced_experts(ffn_rules, E, MT, NT):
+    """A Zipf-shaped gate: the first experts are full, the last nearly empty.  A tile costs its reduction (up to 32 K-steps) and a fixed
+    part of 8.  No XCD has more than 1.25 times the mean (runs of an eighth of the tiles: more than twice)."""
+    cost = [8 + min(32, max(1, round(64 / (e * 8 / E + 1) ** 1.5))) for e in range(E)]
+    per = [sum(cost[t[0]] for t in x) for x in equal_tiles(ffn_rules, E, MT, NT)]
+    assert max(per) <= 1.25 * sum(per) / 8
+    order = sorted((e, m, n) for e in range(E) for m in range(MT) for n in range(NT))
+    eighths = [sum(cost[t[0]] for t in order[x * len(order) // 8:(x + 1) * len(order) // 8]) for x in range(8)]
+    assert max(eighths) > 1.5 * sum(eighths) / 8
 
 
 K256, K128, K64X128, K64, K64X128_STREAM, K64_STREAM, KHALF = range(7)
