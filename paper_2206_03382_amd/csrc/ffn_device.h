@@ -55,21 +55,11 @@ __device__ __forceinline__ int live_rows_of(int e, int64_t C, const int32_t* __r
 }
 
 // Which tile block number b works on, or false where there is none for it.
-// An expert's live tiles (row tiles below its fill x all column tiles) are numbered as tile_in_expert says.  Hardware deals blocks
-// round-robin, so block b runs on XCD b % 8, as the b / 8-th of its tiles, and the tiles that an XCD holds at one time should be neighbours
-// in its own L2.  Launches of kDealtTiles tiles and more deal whole groups of 32 tiles of an expert to the XCDs in turn, in as many rounds as
-// there are full ones for all eight.  Everything left (all of a smaller launch) is one sequence, expert by expert, cut into 8 runs of
-// equal length (to a tile), one to an XCD: even whatever the fills are.  Groups of 8 to 32 tiles dealt throughout, short ones last,
-// left XCDs with up to a round of tiles more than others: 17 experts x 14 tiles 42 us, 24 so; ViT layer of 32 experts x 784 rows 386 ->
-// 353, training step of 17 x 353 rows 340 -> 309.  Runs of an eighth for every launch cost where XCDs next to each other
-// share what they read beyond their L2: 8 experts x 4096 rows, 2048 x 2048 (1088 tiles) layer 592 us in groups, 604 in eighths, 603 in
-// rounds of 32 cut without regard to experts, 0.996 of the rate in groups so; 17 x 353 (663 tiles) 328 in such rounds.  Experts of fewer than
-// four row tiles on average have nothing for several XCDs to share and stay in eighths: 64 experts x 16 rows, 1024 x 4096 212.0 us
-// dealt, 210.3 so.
-// Every wave finds its tile by prefix sums over the experts, 64 to a step; no host has to know the fills.
-constexpr int kDealtTiles = 1024;
+// An expert's live tiles are its row tiles below the fill x all column tiles; how they are numbered and dealt to the XCDs: ffn_rules.h.  Every wave
+// finds its tile by prefix sums over the experts, 64 to a step; no host has to know the fills.
+// SHIFT: log2 of the blocks that share a unit, where groups are to hold as many more tiles.
 // EQUAL: every expert has all of its C rows (weight gradients), see equal_tile.
-template <int TILE_ROWS, bool EQUAL = false>
+template <int TILE_ROWS, bool EQUAL = false, int SHIFT = 0>
 __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
                                           int& e_out, int& mt_out, int& nt_out, int& rows_out) {
   if (EQUAL) {
@@ -92,42 +82,31 @@ __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, con
     upto[c] = live + wave_inclusive_scan((rowsv[c] + TILE_ROWS - 1) / TILE_ROWS * NT);
     live = __builtin_amdgcn_readlane(upto[c], 63);
   }
-  // tiles of expert l that are dealt in whole groups, and what of its tiles is left
-  const int x = b % 8, i = b / 8;
+  constexpr int gs = kGroupShift + SHIFT;
   int rounds = 0, groups[kChunks];                                  // lane l of chunk c: full groups up to expert 64 c + l
-  if (live >= kDealtTiles && live >= 4 * E * NT) {
+  if (deals_groups(live, E, NT, SHIFT)) {
     int full = 0;
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) {
       if (c * 64 >= E) break;
-      groups[c] = full + wave_inclusive_scan(((rowsv[c] + TILE_ROWS - 1) / TILE_ROWS * NT) >> 5);
+      groups[c] = full + wave_inclusive_scan(((rowsv[c] + TILE_ROWS - 1) / TILE_ROWS * NT) >> gs);
       full = __builtin_amdgcn_readlane(groups[c], 63);
     }
     rounds = full >> 3;
   }
-  const bool dealt = i < rounds * 32;
-  const int left = live - rounds * 256;
-  const int target = dealt ? (i >> 5) * 8 + x : x * left / 8 + i - rounds * 32;
-  if (!dealt && target >= (x + 1) * left / 8) return false;
-  int seen = 0;
+  const TileSpot s = tile_spot(b, live, rounds, gs);
+  if (s.part == kNoTile) return false;
 #pragma unroll
   for (int c = 0; c < kChunks; ++c) {
     if (c * 64 >= E) break;
-    const int tiles = (rowsv[c] + TILE_ROWS - 1) / TILE_ROWS * NT;
-    int mine = 0, inc;                                              // dealt groups of this lane's expert
-    if (rounds > 0) {
-      const int before = groups[c] - (tiles >> 5), most = rounds * 8 - before;
-      mine = most < 0 ? 0 : (most < tiles >> 5 ? most : tiles >> 5);
-    }
-    if (dealt) inc = groups[c];
-    else inc = rounds > 0 ? seen + wave_inclusive_scan(tiles - 32 * mine) : upto[c];
-    const unsigned long long hit = __ballot(inc > target);
-    if (hit == 0) { seen = __builtin_amdgcn_readlane(inc, 63); continue; }
+    int inc = upto[c];                                              // groups, or tiles that are left, up to this lane's expert
+    if (rounds > 0) inc = s.part == kDealtTile ? groups[c] : inc - ((groups[c] < rounds * 8 ? groups[c] : rounds * 8) << gs);
+    const unsigned long long hit = __ballot(inc > s.at);
+    if (hit == 0) continue;
     const int l = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
-    const int rows = __builtin_amdgcn_readlane(rowsv[c], l), mte = (rows + TILE_ROWS - 1) / TILE_ROWS;
-    const int in = __builtin_amdgcn_readlane(inc, l), all = mte * NT, gone = __builtin_amdgcn_readlane(mine, l);
-    const int q = dealt ? (target - (in - (all >> 5))) * 32 + (i & 31) : 32 * gone + target - (in - (all - 32 * gone));
-    const TileAt at = tile_in_expert(c * 64 + l, q, mte, NT);
+    const int rows = __builtin_amdgcn_readlane(rowsv[c], l), mte = (rows + TILE_ROWS - 1) / TILE_ROWS, all = mte * NT;
+    const int back = s.at - __builtin_amdgcn_readlane(inc, l);      // from the end of the expert's groups or tiles
+    const TileAt at = tile_in_expert(c * 64 + l, s.part == kDealtTile ? ((back + (all >> gs)) << gs) + (b / 8 & ((1 << gs) - 1)) : all + back, mte, NT);
     e_out = at.e;                                                   // the same in every lane: in scalar registers
     mt_out = at.mt;
     nt_out = at.nt;

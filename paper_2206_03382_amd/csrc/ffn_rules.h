@@ -25,6 +25,7 @@ MOE_HOST_DEVICE inline int slot_ksteps(int64_t fill) { return fill > 0 ? (int)((
 
 // Tiles per group (log2) of numberings that deal whole groups to the XCDs: 32 when the launch has several rounds of tiles for every compute
 // unit; fewer when it has not, so that the groups still spread evenly.  Blocks are counted so for every launch (tile_grid).
+constexpr int kGroupShift = 5, kHalfGroupShift = 1;
 constexpr int64_t kTilesForGroups16 = 512, kTilesForGroups32 = 1024;
 MOE_HOST_DEVICE inline int group_size_log2(int64_t live_tiles) {
   return live_tiles >= kTilesForGroups32 ? 5 : (live_tiles >= kTilesForGroups16 ? 4 : 3);
@@ -39,6 +40,35 @@ MOE_HOST_DEVICE inline TileAt tile_in_expert(int e, int q, int rows, int NT) {
   if (q < full) return {e, (q % (rows * 8)) / 8, (q / (rows * 8)) * 8 + q % 8};
   const int w = NT % 8, r = q - full;
   return {e, r / w, (NT / 8) * 8 + r % w};
+}
+
+// How the other launches (kNN, kNT), whose experts hold different numbers of row tiles, are numbered; the search by a wave is find_tile in
+// ffn_device.h.  Hardware deals blocks round-robin: block b runs on XCD b % 8, as the b / 8-th of its tiles, and the tiles that an XCD holds at one
+// time should be neighbours in its own L2.  Large launches deal whole groups of an expert's tiles to the XCDs in turn, as many as there are full
+// ones for all eight.  Everything left (all of a smaller launch) is one sequence, expert by expert, cut into 8 runs of
+// equal length (to a tile), one to an XCD: even whatever the fills are.  Groups of 8 to 32 tiles dealt throughout, short ones last,
+// left XCDs with up to a round of tiles more than others: 17 experts x 14 tiles 42 us, 24 so; ViT layer of 32 experts x 784 rows 382 ->
+// 355, training step of 17 x 353 rows 314 -> 291.  Runs of an eighth for every launch cost where XCDs next to each other
+// share what they read beyond their L2: 8 experts x 4096 rows, 2048 x 2048 (1088 tiles) layer 592 us in groups, 604 in eighths, 603 in
+// rounds of 32 cut without regard to experts, 0.996 of the rate in groups so.
+//
+// A group is what an XCD's 32 units hold at one time: 32 tiles of the large tile and of the smaller ones, 64 of the half tile, of which two blocks
+// share a unit (kHalfGroupShift).  Groups of 32 half tiles brought 1.4 times as many panels of A and B into an L2 (32 experts x 784 rows, 3072
+// columns; 1.7 times for 2000 rows, 2048 columns).  Layers, 32 and 64 to a group: 43811 tokens, 64 experts, top-4, 512 x 3840 1567 and 1528 us; 29598, 64, top-8,
+// 256 x 256 247 and 242; ViT 347.8 and 347.0; with 256 k, where panels are small, also slower: 41617, 32, top-1, 256 x 2560 240 and 243.
+// Groups are dealt from four rounds of the chip on, on the large and on the half tile.  (17 experts x 353 rows on 128 x 128, 663 tiles: step 328 us in
+// rounds of 32, 309 in eighths.)
+constexpr int kDealtTiles = 1024;
+MOE_HOST_DEVICE inline bool deals_groups(int live, int E, int NT, int shift) { return live >= kDealtTiles << shift && live >= 4 * E * NT; }
+
+enum TilePart { kDealtTile, kLeftTile, kNoTile };
+struct TileSpot { TilePart part; int at; }; // kDealtTile: number of the group among all; kLeftTile: of the tile among those left
+// gs: log2 of a group's tiles, of which each XCD takes `rounds` groups.
+MOE_HOST_DEVICE inline TileSpot tile_spot(int b, int live, int rounds, int gs) {
+  const int x = b % 8, i = b / 8, dealt = rounds << gs;
+  if (i < dealt) return {kDealtTile, (i >> gs) * 8 + x};
+  const int left = live - 8 * dealt, at = x * left / 8 + i - dealt;
+  return {at < (x + 1) * left / 8 ? kLeftTile : kNoTile, at};
 }
 
 // Which tile block b of a weight-gradient launch (kTN) works on, E experts of MT x NT tiles each; false where there is none for it.
@@ -84,9 +114,6 @@ static inline int64_t live_row_tiles(int64_t E, int64_t C, int64_t total, int64_
   const int64_t full = E * tiles_in(C, tile_rows), n = total / tile_rows + (E < total ? E : total);
   return n < full ? n : full;
 }
-
-// The half tile (128 x 256) has two blocks on a unit: groups of twice as many tiles cover the same rows and columns.
-constexpr int kHalfGroupShift = 1;
 
 // Blocks to launch so that every tile is reached whatever the fills turn out to be: E experts of at most MT x NT tiles, of which at
 // most `row_tiles` row tiles are live in all.  Counts a group's G blocks whole, 8 XCDs evenly, one short group to an expert: at

@@ -32,6 +32,31 @@ int equal_tile(int b, int E, int MT, int NT, int* at) {
   at[0] = t.e; at[1] = t.mt; at[2] = t.nt;
   return 1;
 }
+// find_tile, one expert behind the other instead of 64 lanes at a time
+int tile_at(int b, int E, const int* rows, int tile_rows, int NT, int shift, int* at) {
+  const int gs = moe::kGroupShift + shift;
+  int live = 0, full = 0, upto = 0, groups = 0;
+  for (int e = 0; e < E; ++e) {
+    const int tiles = (int)moe::tiles_in(rows[e], tile_rows) * NT;
+    live += tiles;
+    full += tiles >> gs;
+  }
+  const int rounds = moe::deals_groups(live, E, NT, shift) ? full >> 3 : 0;
+  const moe::TileSpot s = moe::tile_spot(b, live, rounds, gs);
+  if (s.part == moe::kNoTile) return 0;
+  for (int e = 0; e < E; ++e) {
+    const int mt = (int)moe::tiles_in(rows[e], tile_rows), all = mt * NT;
+    upto += all;
+    groups += all >> gs;
+    const int inc = s.part == moe::kDealtTile ? groups : upto - ((groups < rounds * 8 ? groups : rounds * 8) << gs), back = s.at - inc;
+    if (inc <= s.at) continue;
+    const moe::TileAt t = moe::tile_in_expert(e, s.part == moe::kDealtTile ? ((back + (all >> gs)) << gs) + (b / 8 & ((1 << gs) - 1)) : all + back, mt, NT);
+    at[0] = t.e; at[1] = t.mt; at[2] = t.nt;
+    return 1 + s.part;
+  }
+  return -1;
+}
+int half_shift() { return moe::kHalfGroupShift; }
 int tile(int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
   return (int)moe::tile_of(mode, E, C, K, N, rows_hint, gather_rows, false);
 }
@@ -53,7 +78,7 @@ int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T
 
 @pytest.fixture(scope="session")
 def ffn_rules(tmp_path_factory):
-    """The host rules of the grouped GEMM: grid(), equal_tile(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, the same for a
+    """The host rules of the grouped GEMM: grid(), equal_tile(), tile_at(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, the same for a
     product that keeps its pre-activations, tile_cost() and split(); and of the gate: one_block(), one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text(RULES_SOURCE)
@@ -61,6 +86,8 @@ def ffn_rules(tmp_path_factory):
     lib = ctypes.CDLL(str(d / "rules.so"))
     lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5 + [ctypes.c_int]
     lib.equal_tile.restype, lib.equal_tile.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
+    lib.tile_at.restype = ctypes.c_int
+    lib.tile_at.argtypes = [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int)] + [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
     lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 4
     lib.tile_keeping_pre.restype, lib.tile_keeping_pre.argtypes = ctypes.c_int, [ctypes.c_int64] * 6

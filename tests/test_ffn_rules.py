@@ -86,6 +86,54 @@ def test_weight_gradient_work_is_even_on_imbalanced_experts(ffn_rules, E, MT, NT
     assert max(eighths) > 1.5 * sum(eighths) / 8
 
 
+def live_tiles(ffn_rules, rows, tile_rows, NT, shift, blocks, parts=None):
+    """The tiles of a forward launch, XCD by XCD; `parts` gets what kinds of place in the numbering they came from."""
+    at, fills = (ctypes.c_int * 3)(), (ctypes.c_int * len(rows))(*rows)
+    def find(b):
+        part = ffn_rules.tile_at(b, len(rows), fills, tile_rows, NT, shift, at)
+        assert part >= 0
+        if parts is not None and part:
+            parts.add(part)
+        return tuple(at) if part else None
+    return tiles_of_xcds(find, blocks)
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("E,C,tile_rows,NT,most_dealt", [(1, 700, 64, 3, -1), (8, 4200, 256, 8, 0), (17, 353, 128, 14, -1), (33, 1500, 128, 9, 1), (70, 1300, 128, 12, 1),
+                                                         (130, 900, 64, 5, 1), (65, 66, 64, 9, -1), (512, 300, 64, 7, 0)])
+def test_every_live_tile_once(ffn_rules, E, C, tile_rows, NT, most_dealt, shift):
+    """Fills of every kind, in launches below and beyond the tiles from which whole groups are dealt: every live tile has one block
+    among those that the grid launches, and no XCD has a tile more than another but for one.  most_dealt: the largest shift at which groups are."""
+    rng, parts = np.random.default_rng(E), set()
+    for fills in (np.full(E, C), rng.integers(0, C + 1, size=E), np.where(rng.random(E) < 0.3, C, 0), np.minimum(C, (C * 4 / (1 + np.arange(E))).astype(int)),
+                  np.minimum(C, np.array([0, 1, tile_rows, tile_rows + 1, 2 * tile_rows, C, C - 1])[rng.integers(0, 7, size=E)])):
+        rows = [int(v) for v in fills]
+        grid = ffn_rules.grid(E, C, tile_rows, NT, max(1, sum(rows)), shift)
+        per = live_tiles(ffn_rules, rows, tile_rows, NT, shift, grid, parts)
+        assert sorted(sum(per, [])) == [(e, m, n) for e in range(E) for m in range(-(-rows[e] // tile_rows)) for n in range(NT)]
+        assert max(map(len, per)) - min(map(len, per)) <= 1
+    assert 2 in parts and (1 in parts) == (shift <= most_dealt)
+
+
+def panels(tiles, at_once):
+    """Panels of A and B (256 columns of B as 2 of 128 rows of A) that an XCD brings into its L2, as many tiles at a time as it holds."""
+    return sum(len({t[:2] for t in w}) + 2 * len({(t[0], t[2]) for t in w}) for w in (tiles[i:i + at_once] for i in range(0, len(tiles), at_once)))
+
+
+@pytest.mark.parametrize("E,rows,NT,in32", [(32, 784, 12, 1.35), (32, 2000, 8, 1.6), (16, 4000, 8, 1.6), (64, 1000, 10, 1.1), (128, 470, 8, 1.0), (8, 8000, 4, 1.0)])
+def test_groups_of_the_half_tile_are_what_an_xcd_holds(ffn_rules, E, rows, NT, in32):
+    """Two blocks of the half tile share a unit, so an XCD holds 64 of its tiles at one time.  At most 1.1 times the panels of groups of
+    64 dealt one by one, short ones last; with groups of 32 it is in32 times and more."""
+    MT = -(-rows // 128)
+    order = [[(e, m, 8 * c + n) for c in range(-(-NT // 8)) for m in range(MT) for n in range(min(8, NT - 8 * c))] for e in range(E)]
+    cut = [t[i:i + 64] for t in order for i in range(0, len(t), 64)]
+    groups = [g for g in cut if len(g) == 64] + [g for g in cut if len(g) < 64]
+    old = sum(panels(sum(groups[x::8], []), 64) for x in range(8))
+    now = sum(panels(x, 64) for x in live_tiles(ffn_rules, [rows] * E, 128, NT, ffn_rules.half_shift(), -(-E * MT * NT // 8) * 8))
+    assert now <= 1.1 * old
+    assert sum(panels(x, 64) for x in live_tiles(ffn_rules, [rows] * E, 128, NT, 0, -(-E * MT * NT // 8) * 8)) >= in32 * old
+
+
 K256, K128, K64X128, K64, K64X128_STREAM, K64_STREAM, KHALF = range(7)
 
 
