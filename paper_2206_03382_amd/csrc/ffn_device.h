@@ -141,7 +141,7 @@ static inline bool tile_launch(TileArgs& p, int bm, int bn, int64_t total, dim3&
   p.MT = (int)ceil_div(p.C, bm);
   p.NT = (int)ceil_div(p.N, bn);
   // more experts than the search takes, or more blocks than a grid dimension holds (2^32 threads: launches beyond run cut short)
-  int64_t blocks = tile_grid(p.E, p.MT, p.NT, live_row_tiles(p.E, p.C, total, bm));
+  int64_t blocks = tile_grid(p.NT, live_row_tiles(p.E, p.C, total, bm));
   p.plain = p.E > kMaxExperts || blocks >= kMaxBlocks;
   if (p.plain) blocks = (int64_t)p.MT * p.NT;
   grid = dim3((unsigned)blocks, p.plain ? (unsigned)p.E : 1);

@@ -602,7 +602,7 @@ static hipError_t launch_large_nn(const void* A, const void* B, const void* bias
                                   const int32_t* gather, int64_t gather_rows, void* pre_out) {
   const int64_t bm = half ? BM / 2 : BM;
   const int MT = (int)ceil_div(C, bm), NT = (int)(N / BN);
-  const int64_t blocks = tile_grid(E, MT, NT, live_row_tiles(E, C, total, bm), half ? kHalfGroupShift : 0);
+  const int64_t blocks = tile_grid(NT, live_row_tiles(E, C, total, bm));
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
 #define MOE_LAUNCH_GEMM_AT(ACT, DUAL, FAR)                                                                            \
@@ -642,7 +642,7 @@ static hipError_t launch_large_nn(const void* A, const void* B, const void* bias
 static hipError_t launch_large_nt(const void* A, const void* Bt, const int32_t* counts, int64_t E, int64_t C,
                                   int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s, int64_t total) {
   const int MT = (int)ceil_div(C, BM), NT = (int)(N / BN);
-  const int64_t blocks = tile_grid(E, MT, NT, live_row_tiles(E, C, total, BM));
+  const int64_t blocks = tile_grid(NT, live_row_tiles(E, C, total, BM));
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
 #define MOE_LAUNCH_GEMM(ACT, GRAD)                                                                                    \
@@ -672,7 +672,7 @@ static hipError_t launch_large_tn(const void* At, const void* B, const int32_t* 
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   const int MT = (int)(R / BM), NT = (int)(N / BN);
-  const int64_t blocks = tile_grid(E, MT, NT, E * MT);
+  const int64_t blocks = tile_grid(NT, E * MT);
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
 #define MOE_LAUNCH_GATHERED(FAR)                                                                                        \
@@ -742,7 +742,7 @@ template <typename ET, int BM, int BN, int WR, int WC>
 static hipError_t launch_slices(TileArgs p, hipStream_t s) {
   p.MT = (int)ceil_div(p.C, BM);
   p.NT = (int)ceil_div(p.N, BN);
-  const int64_t blocks = tile_grid(p.E, p.MT, p.NT, (int64_t)p.E * p.MT);
+  const int64_t blocks = tile_grid(p.NT, (int64_t)p.E * p.MT);
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   grouped_gemm_tile_kernel<ET, kTN, BM, BN, WR, WC, 2, false, true><<<dim3((unsigned)blocks), dim3(256), 0, s>>>(p);
   return hipGetLastError();

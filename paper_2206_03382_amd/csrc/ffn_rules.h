@@ -23,14 +23,6 @@ static inline int64_t tiles_in(int64_t n, int64_t tile) { return (n + tile - 1) 
 // from the side buffers, which also covers an expert without any slot (one K-step of zeros).
 MOE_HOST_DEVICE inline int slot_ksteps(int64_t fill) { return fill > 0 ? (int)((fill + kLargeK - 1) / kLargeK) : 1; }
 
-// Tiles per group (log2) of numberings that deal whole groups to the XCDs: 32 when the launch has several rounds of tiles for every compute
-// unit; fewer when it has not, so that the groups still spread evenly.  Blocks are counted so for every launch (tile_grid).
-constexpr int kGroupShift = 5, kHalfGroupShift = 1;
-constexpr int64_t kTilesForGroups16 = 512, kTilesForGroups32 = 1024;
-MOE_HOST_DEVICE inline int group_size_log2(int64_t live_tiles) {
-  return live_tiles >= kTilesForGroups32 ? 5 : (live_tiles >= kTilesForGroups16 ? 4 : 3);
-}
-
 struct TileAt { int e, mt, nt; };           // expert, row tile, column tile
 
 // Tile q of the rows x NT ones of expert e: by blocks of 8 tile columns and, inside a block, row by row, so that 32 consecutive ones are 4 row
@@ -58,7 +50,7 @@ MOE_HOST_DEVICE inline TileAt tile_in_expert(int e, int q, int rows, int NT) {
 // 256 x 256 247 and 242; ViT 347.8 and 347.0; with 256 k, where panels are small, also slower: 41617, 32, top-1, 256 x 2560 240 and 243.
 // Groups are dealt from four rounds of the chip on, on the large and on the half tile.  (17 experts x 353 rows on 128 x 128, 663 tiles: step 328 us in
 // rounds of 32, 309 in eighths.)
-constexpr int kDealtTiles = 1024;
+constexpr int kGroupShift = 5, kHalfGroupShift = 1, kDealtTiles = 1024;
 MOE_HOST_DEVICE inline bool deals_groups(int live, int E, int NT, int shift) { return live >= kDealtTiles << shift && live >= 4 * E * NT; }
 
 enum TilePart { kDealtTile, kLeftTile, kNoTile };
@@ -74,14 +66,15 @@ MOE_HOST_DEVICE inline TileSpot tile_spot(int b, int live, int rounds, int gs) {
 // Which tile block b of a weight-gradient launch (kTN) works on, E experts of MT x NT tiles each; false where there is none for it.
 // Hardware deals blocks round-robin: block b runs on XCD b % 8, as the b / 8-th of its tiles.  All experts have the same number of tiles, but a
 // tile of an expert with many rows takes several times that of one with few, so every XCD has to get its share of each expert: whole groups of an
-// expert's tiles are dealt to the XCDs in turn, then whole tails (what an expert has beyond its groups), and only the groups and tails of the
+// expert's tiles (32 when the launch has several rounds of tiles for every compute unit; fewer when it has not, so that they still spread evenly) are dealt
+// to the XCDs in turn, then whole tails (what an expert has beyond its groups), and only the groups and tails of the
 // last rounds, fewer than eight, are cut into 8 runs of equal length (to a tile).  Runs of an eighth of all tiles gave
 // the experts with many rows to one XCD.  Imbalanced gate (Zipf), two products of 8 experts, 8192 tokens, 2048 x 2048: 218 us in groups throughout,
 // 417 in eighths, 215 so (training step 800, 986 and 761); 64 experts, 16384 tokens, 1024 x 1024: step 415, 475 and 397.  Even gate, 17 experts x
 // 353 rows, 776 x 1544: 81 us in groups throughout, 79 with the tails in eighths, 75 so.
 // No prefix sums over the experts, either, which every tile of a short reduction would pay for.
 MOE_HOST_DEVICE inline bool equal_tile(int b, int E, int MT, int NT, TileAt& at) {
-  const int n = MT * NT, gs = group_size_log2((int64_t)E * n), x = b % 8, i = b / 8;
+  const int n = MT * NT, gs = E * n >= 1024 ? 5 : (E * n >= 512 ? 4 : 3), x = b % 8, i = b / 8;
   const int own = n >> gs, tail = n - (own << gs), rounds = (E * own) >> 3, dealt = rounds << gs, tails = (E >> 3) * tail;   // an XCD's
   int e, q;
   if (i < dealt) {
@@ -115,25 +108,12 @@ static inline int64_t live_row_tiles(int64_t E, int64_t C, int64_t total, int64_
   return n < full ? n : full;
 }
 
-// Blocks to launch so that every tile is reached whatever the fills turn out to be: E experts of at most MT x NT tiles, of which at
-// most `row_tiles` row tiles are live in all.  Counts a group's G blocks whole, 8 XCDs evenly, one short group to an expert: at
-// least the live tiles and a multiple of 8, which is what find_tile (ffn_device.h) asks for.
+// Blocks to launch so that every tile is reached whatever the fills turn out to be: of the row tiles of NT tiles each, at most `row_tiles`
+// are live in all, and their tiles are dealt evenly to the 8 XCDs.
 // The layer knows its total (every choice is one row).  Without it the grid has to hold C rows of every expert, and where the
 // capacity is far above the mean fill nearly all blocks find nothing to do, each after a tile search and holding its LDS: dynamic
 // capacity, buffers for all 2048 tokens, 128 experts, M = 4096, H = 1024: layer 746 us, 487 with the bound.
-static inline int64_t tile_grid(int64_t E, int64_t MT, int64_t NT, int64_t row_tiles, int shift = 0) {
-  const int64_t most = row_tiles * NT;                              // live tiles
-  int64_t blocks = 0;
-  for (int gs = 3; gs <= 5; ++gs) {
-    if (gs > group_size_log2(most >> shift)) break;                 // too few tiles for this group size
-    const int64_t limit = gs == 3 ? (kTilesForGroups16 << shift) - 1 : (gs == 4 ? (kTilesForGroups32 << shift) - 1 : most);
-    const int64_t live = most < limit ? most : limit, G = (int64_t)1 << (gs + shift);
-    const int64_t full = E * tiles_in(MT * NT, G), n = live / G + (E < live ? E : live), groups = n < full ? n : full;
-    const int64_t b = tiles_in(groups, 8) * 8 * G;
-    blocks = b > blocks ? b : blocks;
-  }
-  return blocks;
-}
+static inline int64_t tile_grid(int64_t NT, int64_t row_tiles) { return tiles_in(row_tiles * NT, 8) * 8; }
 
 // Shapes the 256 x 256 tile takes in the forward layout; gather_rows > 0: A's rows are gathered from that many.
 static inline bool large_tile_supports(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows) {

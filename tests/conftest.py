@@ -23,8 +23,8 @@ RULES_SOURCE = r"""
 #include "paper_2206_03382_amd/csrc/ffn_rules.h"
 #include "paper_2206_03382_amd/csrc/gate_rules.h"
 extern "C" {
-int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total, int half) {
-  return moe::tile_grid(E, moe::tiles_in(C, tile), NT, moe::live_row_tiles(E, C, total, tile), half ? moe::kHalfGroupShift : 0);
+int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total) {
+  return moe::tile_grid(NT, moe::live_row_tiles(E, C, total, tile));
 }
 int equal_tile(int b, int E, int MT, int NT, int* at) {
   moe::TileAt t;
@@ -84,7 +84,7 @@ def ffn_rules(tmp_path_factory):
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
     lib = ctypes.CDLL(str(d / "rules.so"))
-    lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5 + [ctypes.c_int]
+    lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5
     lib.equal_tile.restype, lib.equal_tile.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
     lib.tile_at.restype = ctypes.c_int
     lib.tile_at.argtypes = [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int)] + [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]

@@ -5,14 +5,9 @@ import numpy as np
 import pytest
 
 
-def blocks_needed(tiles, NT, half):
-    """Blocks the kernels' tile search can ask for when expert e has tiles[e] live row tiles of NT tiles each: whole groups first,
-    a short one per expert with a remainder, dealt to 8 XCDs.  The half tile's groups hold twice as many tiles."""
-    live = int(tiles.sum()) * NT // (2 if half else 1)
-    G = (32 if live >= 1024 else (16 if live >= 512 else 8)) * (2 if half else 1)
-    per = tiles * NT
-    groups = int((per // G).sum() + (per % G > 0).sum())
-    return -(-groups // 8) * 8 * G
+def blocks_needed(tiles, NT):
+    """Blocks the kernels' tile search can ask for when expert e has tiles[e] live row tiles of NT tiles each: as many for each of 8 XCDs."""
+    return -(-int(tiles.sum()) * NT // 8) * 8
 
 
 @pytest.mark.parametrize("half", [0, 1])
@@ -36,8 +31,8 @@ def test_grid_reaches_every_tile(ffn_rules, seed, half):
             fills = rng.integers(0, C + 1, size=E)
         fills = np.minimum(fills, np.maximum(total - (np.cumsum(fills) - fills), 0))      # within the total
         assert fills.sum() <= total
-        grid = ffn_rules.grid(E, C, tile, NT, total, half)
-        assert grid >= blocks_needed(-(-fills // tile), NT, half), (E, C, tile, NT, total)
+        grid = ffn_rules.grid(E, C, tile, NT, total)
+        assert grid >= blocks_needed(-(-fills // tile), NT), (E, C, tile, NT, total)
 
 
 def test_grid_is_bounded_by_the_rows_that_exist(ffn_rules):
@@ -45,10 +40,8 @@ def test_grid_is_bounded_by_the_rows_that_exist(ffn_rules):
     E, T, k = 128, 2048, 2
     for tile, NT in ((64, 8), (64, 32), (128, 16), (256, 4)):
         live = (T * k // tile + E) * NT
-        assert ffn_rules.grid(E, T, tile, NT, T * k, 0) <= live + 32 * (E + 8)
-        assert ffn_rules.grid(E, T, tile, NT, E * T, 0) >= E * T // tile * NT
-    live = (T * k // 128 + E) * 16
-    assert ffn_rules.grid(E, T, 128, 16, T * k, 1) <= live + 64 * (E + 8)
+        assert ffn_rules.grid(E, T, tile, NT, T * k) <= live + 7
+        assert E * T // tile * NT <= ffn_rules.grid(E, T, tile, NT, E * T) <= E * T // tile * NT + 7
 
 
 def tiles_of_xcds(find, blocks):
@@ -108,7 +101,7 @@ def test_every_live_tile_once(ffn_rules, E, C, tile_rows, NT, most_dealt, shift)
     for fills in (np.full(E, C), rng.integers(0, C + 1, size=E), np.where(rng.random(E) < 0.3, C, 0), np.minimum(C, (C * 4 / (1 + np.arange(E))).astype(int)),
                   np.minimum(C, np.array([0, 1, tile_rows, tile_rows + 1, 2 * tile_rows, C, C - 1])[rng.integers(0, 7, size=E)])):
         rows = [int(v) for v in fills]
-        grid = ffn_rules.grid(E, C, tile_rows, NT, max(1, sum(rows)), shift)
+        grid = ffn_rules.grid(E, C, tile_rows, NT, max(1, sum(rows)))
         per = live_tiles(ffn_rules, rows, tile_rows, NT, shift, grid, parts)
         assert sorted(sum(per, [])) == [(e, m, n) for e in range(E) for m in range(-(-rows[e] // tile_rows)) for n in range(NT)]
         assert max(map(len, per)) - min(map(len, per)) <= 1
