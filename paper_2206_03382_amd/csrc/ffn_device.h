@@ -57,9 +57,88 @@ __device__ __forceinline__ int live_rows_of(int e, int64_t C, const int32_t* __r
 // Which tile block number b works on, or false where there is none for it.
 // An expert's live tiles are its row tiles below the fill x all column tiles; how they are numbered and dealt to the XCDs: ffn_rules.h.  Every wave
 // finds its tile by prefix sums over the experts, 64 to a step; no host has to know the fills.
-// SHIFT: log2 of the blocks that share a unit, where groups are to hold as many more tiles.
-// EQUAL: every expert has all of its C rows (weight gradients), see equal_tile.
-template <int TILE_ROWS, bool EQUAL = false, int SHIFT = 0>
+// SHIFT: log2 of the blocks that share a unit, where groups are to hold as many more tiles.  SHORTS: imbalanced experts' short row tiles come last.
+template <int TILE_ROWS, int SHIFT, bool SHORTS, int CHUNKS>
+__device__ __forceinline__ bool search_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
+                                            int& e_out, int& mt_out, int& nt_out, int& rows_out) {
+  int rowsv[CHUNKS], upto[CHUNKS], groups[CHUNKS];                  // lane l of chunk c: rows of expert 64 c + l; tall tiles, full groups of them up to it
+  unsigned long long shortv[CHUNKS];                                // experts with a short row tile
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) rowsv[c] = c * 64 + lane < E ? live_rows_of(c * 64 + lane, C, counts) : 0;      // all loads in flight at once
+  bool uneven = false;
+  if (SHORTS && counts && C > TILE_ROWS) {
+    int all_rows = 0;
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+      if (c > 0 && c * 64 >= E) break;
+      all_rows += __builtin_amdgcn_readlane(wave_inclusive_scan(rowsv[c]), 63);
+    }
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+      if (c > 0 && c * 64 >= E) break;
+      uneven |= __ballot(far_above_mean(rowsv[c], E, all_rows)) != 0;
+    }
+  }
+  int tall = 0, shorts = 0;
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) {
+    if (c > 0 && c * 64 >= E) break;
+    const int mt = tall_row_tiles(rowsv[c], TILE_ROWS, uneven);
+    upto[c] = tall + wave_inclusive_scan(mt * NT);
+    tall = __builtin_amdgcn_readlane(upto[c], 63);
+    if (SHORTS) {
+      shortv[c] = __ballot(rowsv[c] > mt * TILE_ROWS);
+      shorts += __builtin_popcountll(shortv[c]) * NT;
+    }
+  }
+  constexpr int gs = kGroupShift + SHIFT;
+  int rounds = 0;
+  if (deals_groups(tall, E, NT, SHIFT)) {
+    int full = 0;
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+      if (c > 0 && c * 64 >= E) break;
+      groups[c] = full + wave_inclusive_scan(tall_row_tiles(rowsv[c], TILE_ROWS, uneven) * NT >> gs);
+      full = __builtin_amdgcn_readlane(groups[c], 63);
+    }
+    rounds = full >> 3;
+  }
+  const TileSpot s = tile_spot(b, tall, shorts, rounds, gs);
+  if (s.part == kNoTile) return false;
+  int seen = 0;                                                     // short row tiles of earlier chunks
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) {
+    if (c > 0 && c * 64 >= E) break;
+    int inc = upto[c];                                              // groups, tiles that are left, or short tiles, up to this lane's expert
+    if (rounds > 0) inc = s.part == kDealtTile ? groups[c] : inc - ((groups[c] < rounds * 8 ? groups[c] : rounds * 8) << gs);
+    if (SHORTS && s.part == kShortTile) {
+      const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(shortv[c] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)shortv[c], 0));
+      inc = (seen + before + (int)(shortv[c] >> lane & 1)) * NT;
+      seen += __builtin_popcountll(shortv[c]);
+    }
+    const unsigned long long hit = __ballot(inc > s.at);
+    if (hit == 0) continue;
+    const int l = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
+    const int rows = __builtin_amdgcn_readlane(rowsv[c], l), mt = tall_row_tiles(rows, TILE_ROWS, uneven), all = mt * NT;
+    const int back = s.at - __builtin_amdgcn_readlane(inc, l);      // from the end of the expert's groups or tiles
+    e_out = c * 64 + l;                                             // the same in every lane: in scalar registers
+    rows_out = rows;
+    if (SHORTS && s.part == kShortTile) {
+      mt_out = mt;
+      nt_out = NT + back;
+    } else {
+      const TileAt at = tile_in_expert(e_out, s.part == kDealtTile ? ((back + (all >> gs)) << gs) + (b / 8 & ((1 << gs) - 1)) : all + back, mt, NT);
+      mt_out = at.mt;
+      nt_out = at.nt;
+    }
+    return true;
+  }
+  return false;
+}
+
+// EQUAL: every expert has all of its C rows (weight gradients), see equal_tile.  Up to 64 experts have code of their own, one straight piece:
+// what a launch of few tiles pays for is fetching it (decode step of 16 tokens 47.8 -> 46.9 us).
+template <int TILE_ROWS, bool EQUAL = false, int SHIFT = 0, bool SHORTS = false>
 __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
                                           int& e_out, int& mt_out, int& nt_out, int& rows_out) {
   if (EQUAL) {
@@ -71,49 +150,8 @@ __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, con
     rows_out = (int)C;
     return true;
   }
-  constexpr int kChunks = kMaxExperts / 64;
-  int rowsv[kChunks], upto[kChunks];                                // lane l of chunk c: rows of expert 64 c + l; live tiles up to it
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) rowsv[c] = c * 64 + lane < E ? live_rows_of(c * 64 + lane, C, counts) : 0;      // all loads in flight at once
-  int live = 0;                                                     // live tiles of all experts
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) {
-    if (c * 64 >= E) break;
-    upto[c] = live + wave_inclusive_scan((rowsv[c] + TILE_ROWS - 1) / TILE_ROWS * NT);
-    live = __builtin_amdgcn_readlane(upto[c], 63);
-  }
-  constexpr int gs = kGroupShift + SHIFT;
-  int rounds = 0, groups[kChunks];                                  // lane l of chunk c: full groups up to expert 64 c + l
-  if (deals_groups(live, E, NT, SHIFT)) {
-    int full = 0;
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c) {
-      if (c * 64 >= E) break;
-      groups[c] = full + wave_inclusive_scan(((rowsv[c] + TILE_ROWS - 1) / TILE_ROWS * NT) >> gs);
-      full = __builtin_amdgcn_readlane(groups[c], 63);
-    }
-    rounds = full >> 3;
-  }
-  const TileSpot s = tile_spot(b, live, rounds, gs);
-  if (s.part == kNoTile) return false;
-#pragma unroll
-  for (int c = 0; c < kChunks; ++c) {
-    if (c * 64 >= E) break;
-    int inc = upto[c];                                              // groups, or tiles that are left, up to this lane's expert
-    if (rounds > 0) inc = s.part == kDealtTile ? groups[c] : inc - ((groups[c] < rounds * 8 ? groups[c] : rounds * 8) << gs);
-    const unsigned long long hit = __ballot(inc > s.at);
-    if (hit == 0) continue;
-    const int l = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
-    const int rows = __builtin_amdgcn_readlane(rowsv[c], l), mte = (rows + TILE_ROWS - 1) / TILE_ROWS, all = mte * NT;
-    const int back = s.at - __builtin_amdgcn_readlane(inc, l);      // from the end of the expert's groups or tiles
-    const TileAt at = tile_in_expert(c * 64 + l, s.part == kDealtTile ? ((back + (all >> gs)) << gs) + (b / 8 & ((1 << gs) - 1)) : all + back, mte, NT);
-    e_out = at.e;                                                   // the same in every lane: in scalar registers
-    mt_out = at.mt;
-    nt_out = at.nt;
-    rows_out = rows;
-    return true;
-  }
-  return false;
+  if (E <= 64) return search_tile<TILE_ROWS, SHIFT, SHORTS, 1>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out);
+  return search_tile<TILE_ROWS, SHIFT, SHORTS, kMaxExperts / 64>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out);
 }
 
 struct TileArgs {

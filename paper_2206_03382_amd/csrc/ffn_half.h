@@ -134,7 +134,7 @@ __global__ __launch_bounds__(256, 2) void grouped_gemm_half_kernel(const uint16_
   __shared__ __attribute__((aligned(1024))) char smem[HNS * kHalfStage];
   const int lane = threadIdx.x & 63;
   int e, mt, nt, rows_e;
-  if (!find_tile<HBM, false, kHalfGroupShift>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e)) return;
+  if (!find_tile<HBM, false, kHalfGroupShift, true>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e)) return;
   const int64_t rows = rows_e;
   const int64_t m0 = (int64_t)mt * HBM;
   if (m0 >= rows) return;

@@ -395,7 +395,7 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
 
   const int lane = threadIdx.x & 63;
   int e, mt, nt, rows_e;
-  if (!find_tile<BM, MODE == kTN>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e)) return;
+  if (!find_tile<BM, MODE == kTN, 0, MODE != kTN>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e)) return;
   const int64_t rows = rows_e;                                      // already here from the search: no second trip to memory
   const int64_t m0 = (int64_t)mt * BM;
   if (m0 >= rows) return;                                           // cannot happen (mt < mte); keeps every access in the slab
@@ -602,7 +602,7 @@ static hipError_t launch_large_nn(const void* A, const void* B, const void* bias
                                   const int32_t* gather, int64_t gather_rows, void* pre_out) {
   const int64_t bm = half ? BM / 2 : BM;
   const int MT = (int)ceil_div(C, bm), NT = (int)(N / BN);
-  const int64_t blocks = tile_grid(NT, live_row_tiles(E, C, total, bm));
+  const int64_t blocks = tile_grid(NT, live_row_tiles(E, C, total, bm), true);
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
 #define MOE_LAUNCH_GEMM_AT(ACT, DUAL, FAR)                                                                            \
@@ -642,7 +642,7 @@ static hipError_t launch_large_nn(const void* A, const void* B, const void* bias
 static hipError_t launch_large_nt(const void* A, const void* Bt, const int32_t* counts, int64_t E, int64_t C,
                                   int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s, int64_t total) {
   const int MT = (int)ceil_div(C, BM), NT = (int)(N / BN);
-  const int64_t blocks = tile_grid(NT, live_row_tiles(E, C, total, BM));
+  const int64_t blocks = tile_grid(NT, live_row_tiles(E, C, total, BM), true);
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
 #define MOE_LAUNCH_GEMM(ACT, GRAD)                                                                                    \

@@ -49,18 +49,33 @@ MOE_HOST_DEVICE inline TileAt tile_in_expert(int e, int q, int rows, int NT) {
 // columns; 1.7 times for 2000 rows, 2048 columns).  Layers, 32 and 64 to a group: 43811 tokens, 64 experts, top-4, 512 x 3840 1567 and 1528 us; 29598, 64, top-8,
 // 256 x 256 247 and 242; ViT 347.8 and 347.0; with 256 k, where panels are small, also slower: 41617, 32, top-1, 256 x 2560 240 and 243.
 // Groups are dealt from four rounds of the chip on, on the large and on the half tile.  (17 experts x 353 rows on 128 x 128, 663 tiles: step 328 us in
-// rounds of 32, 309 in eighths.)
+// rounds of 32, 309 in eighths.)  Experts of fewer than four row tiles on average stay in eighths.  Over 25 layers and steps of 1 to 6 row tiles
+// that is 0.1 % faster on average: 2 % for 64 experts x 256 rows, 1000 x 2056, 48 x 188, 1544 x 2056 and 96 x 417, 768 x 1544, 2 % slower for
+// a step of 64 x 125, 1000 x 2000 and for 96 imbalanced ones, 768 x 1544.
 constexpr int kGroupShift = 5, kHalfGroupShift = 1, kDealtTiles = 1024;
 MOE_HOST_DEVICE inline bool deals_groups(int live, int E, int NT, int shift) { return live >= kDealtTiles << shift && live >= 4 * E * NT; }
 
-enum TilePart { kDealtTile, kLeftTile, kNoTile };
-struct TileSpot { TilePart part; int at; }; // kDealtTile: number of the group among all; kLeftTile: of the tile among those left
-// gs: log2 of a group's tiles, of which each XCD takes `rounds` groups.
-MOE_HOST_DEVICE inline TileSpot tile_spot(int b, int live, int rounds, int gs) {
+// With an imbalanced gate an even share of the tiles is no even share of the work: the experts that fill their capacity have whole row tiles, the
+// others one that is nearly empty, and a run may hold only ones or only others.  Where an expert has more than 1.5 times the mean
+// rows, the large and the half tile therefore number the row tiles that are filled to more than half first and cut the short ones (an
+// expert's last one, at most) into runs of their own, which come after.  Zipf-shaped gates, products without and with: 64 experts x 550 rows, 2560 x
+// 1024 94.1 and 80.8 us; 128 experts, 512 x 2048 27.2 and 21.4; 8 x 3000, 2048 x 1536 96.5 and 78.3; training step of the last 562
+// and 535; the slowest 8 x 4096, 2048 x 2048 120.6 and 128.1 (step 761 and 786).  An even gate keeps them where they are: next to the
+// expert's other tiles they find its weights in the L2 (32 experts x 166 rows, 1856 x 3840 131 us, 183 apart; ViT 328 and 343).  So do the
+// smaller tiles, which read more weights for a product (128 x 128, 16 x 750 rows, 1000 x 2000 54.6 and 61.0).
+MOE_HOST_DEVICE inline bool far_above_mean(int rows, int E, int all_rows) { return 2.0f * (float)rows * (float)E > 3.0f * (float)all_rows; }
+MOE_HOST_DEVICE inline int tall_row_tiles(int rows, int tile_rows, bool uneven) { return (rows + (uneven ? tile_rows / 2 : tile_rows) - 1) / tile_rows; }
+
+enum TilePart { kDealtTile, kLeftTile, kShortTile, kNoTile };
+struct TileSpot { TilePart part; int at; }; // kDealtTile: number of the group among all; else of the tile among those left, or the short ones
+// tall, shorts: tiles of either kind; gs: log2 of a group's tiles, of which each XCD takes `rounds` groups.
+MOE_HOST_DEVICE inline TileSpot tile_spot(int b, int tall, int shorts, int rounds, int gs) {
   const int x = b % 8, i = b / 8, dealt = rounds << gs;
   if (i < dealt) return {kDealtTile, (i >> gs) * 8 + x};
-  const int left = live - 8 * dealt, at = x * left / 8 + i - dealt;
-  return {at < (x + 1) * left / 8 ? kLeftTile : kNoTile, at};
+  const int left = tall - 8 * dealt, first = x * left / 8, own = (x + 1) * left / 8 - first, j = i - dealt;
+  if (j < own) return {kLeftTile, first + j};
+  const int at = x * shorts / 8 + j - own;
+  return {at < (x + 1) * shorts / 8 ? kShortTile : kNoTile, at};
 }
 
 // Which tile block b of a weight-gradient launch (kTN) works on, E experts of MT x NT tiles each; false where there is none for it.
@@ -109,11 +124,11 @@ static inline int64_t live_row_tiles(int64_t E, int64_t C, int64_t total, int64_
 }
 
 // Blocks to launch so that every tile is reached whatever the fills turn out to be: of the row tiles of NT tiles each, at most `row_tiles`
-// are live in all, and their tiles are dealt evenly to the 8 XCDs.
+// are live in all, and their tiles are dealt evenly to the 8 XCDs (shorts_last: in two kinds, each to a tile).
 // The layer knows its total (every choice is one row).  Without it the grid has to hold C rows of every expert, and where the
 // capacity is far above the mean fill nearly all blocks find nothing to do, each after a tile search and holding its LDS: dynamic
 // capacity, buffers for all 2048 tokens, 128 experts, M = 4096, H = 1024: layer 746 us, 487 with the bound.
-static inline int64_t tile_grid(int64_t NT, int64_t row_tiles) { return tiles_in(row_tiles * NT, 8) * 8; }
+static inline int64_t tile_grid(int64_t NT, int64_t row_tiles, bool shorts_last = false) { return (tiles_in(row_tiles * NT, 8) + (shorts_last ? 1 : 0)) * 8; }
 
 // Shapes the 256 x 256 tile takes in the forward layout; gather_rows > 0: A's rows are gathered from that many.
 static inline bool large_tile_supports(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows) {

@@ -23,8 +23,8 @@ RULES_SOURCE = r"""
 #include "paper_2206_03382_amd/csrc/ffn_rules.h"
 #include "paper_2206_03382_amd/csrc/gate_rules.h"
 extern "C" {
-int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total) {
-  return moe::tile_grid(NT, moe::live_row_tiles(E, C, total, tile));
+int64_t grid(int64_t E, int64_t C, int64_t tile, int64_t NT, int64_t total, int shorts_last) {
+  return moe::tile_grid(NT, moe::live_row_tiles(E, C, total, tile), shorts_last);
 }
 int equal_tile(int b, int E, int MT, int NT, int* at) {
   moe::TileAt t;
@@ -33,24 +33,31 @@ int equal_tile(int b, int E, int MT, int NT, int* at) {
   return 1;
 }
 // find_tile, one expert behind the other instead of 64 lanes at a time
-int tile_at(int b, int E, const int* rows, int tile_rows, int NT, int shift, int* at) {
+int tile_at(int b, int E, const int* rows, int tile_rows, int NT, int shift, int shorts_last, int* at) {
   const int gs = moe::kGroupShift + shift;
-  int live = 0, full = 0, upto = 0, groups = 0;
+  int all_rows = 0, tall = 0, shorts = 0, full = 0, upto = 0, groups = 0, short_upto = 0;
+  bool uneven = false;
+  for (int e = 0; e < E; ++e) all_rows += rows[e];
+  for (int e = 0; e < E; ++e) uneven = uneven || (shorts_last && moe::far_above_mean(rows[e], E, all_rows));
   for (int e = 0; e < E; ++e) {
-    const int tiles = (int)moe::tiles_in(rows[e], tile_rows) * NT;
-    live += tiles;
-    full += tiles >> gs;
+    const int mt = moe::tall_row_tiles(rows[e], tile_rows, uneven);
+    tall += mt * NT;
+    full += mt * NT >> gs;
+    shorts += rows[e] > mt * tile_rows ? NT : 0;
   }
-  const int rounds = moe::deals_groups(live, E, NT, shift) ? full >> 3 : 0;
-  const moe::TileSpot s = moe::tile_spot(b, live, rounds, gs);
+  const int rounds = moe::deals_groups(tall, E, NT, shift) ? full >> 3 : 0;
+  const moe::TileSpot s = moe::tile_spot(b, tall, shorts, rounds, gs);
   if (s.part == moe::kNoTile) return 0;
   for (int e = 0; e < E; ++e) {
-    const int mt = (int)moe::tiles_in(rows[e], tile_rows), all = mt * NT;
+    const int mt = moe::tall_row_tiles(rows[e], tile_rows, uneven), all = mt * NT;
     upto += all;
     groups += all >> gs;
-    const int inc = s.part == moe::kDealtTile ? groups : upto - ((groups < rounds * 8 ? groups : rounds * 8) << gs), back = s.at - inc;
+    short_upto += rows[e] > mt * tile_rows ? NT : 0;
+    const int inc = s.part == moe::kShortTile ? short_upto : (s.part == moe::kDealtTile ? groups : upto - ((groups < rounds * 8 ? groups : rounds * 8) << gs));
     if (inc <= s.at) continue;
-    const moe::TileAt t = moe::tile_in_expert(e, s.part == moe::kDealtTile ? ((back + (all >> gs)) << gs) + (b / 8 & ((1 << gs) - 1)) : all + back, mt, NT);
+    const int back = s.at - inc;
+    moe::TileAt t = {e, mt, NT + back};
+    if (s.part != moe::kShortTile) t = moe::tile_in_expert(e, s.part == moe::kDealtTile ? ((back + (all >> gs)) << gs) + (b / 8 & ((1 << gs) - 1)) : all + back, mt, NT);
     at[0] = t.e; at[1] = t.mt; at[2] = t.nt;
     return 1 + s.part;
   }
@@ -84,10 +91,10 @@ def ffn_rules(tmp_path_factory):
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
     lib = ctypes.CDLL(str(d / "rules.so"))
-    lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5
+    lib.grid.restype, lib.grid.argtypes = ctypes.c_int64, [ctypes.c_int64] * 5 + [ctypes.c_int]
     lib.equal_tile.restype, lib.equal_tile.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
     lib.tile_at.restype = ctypes.c_int
-    lib.tile_at.argtypes = [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int)] + [ctypes.c_int] * 3 + [ctypes.POINTER(ctypes.c_int)]
+    lib.tile_at.argtypes = [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int)] + [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
     lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 4
     lib.tile_keeping_pre.restype, lib.tile_keeping_pre.argtypes = ctypes.c_int, [ctypes.c_int64] * 6

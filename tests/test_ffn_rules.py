@@ -31,7 +31,7 @@ def test_grid_reaches_every_tile(ffn_rules, seed, half):
             fills = rng.integers(0, C + 1, size=E)
         fills = np.minimum(fills, np.maximum(total - (np.cumsum(fills) - fills), 0))      # within the total
         assert fills.sum() <= total
-        grid = ffn_rules.grid(E, C, tile, NT, total)
+        grid = ffn_rules.grid(E, C, tile, NT, total, 0)
         assert grid >= blocks_needed(-(-fills // tile), NT), (E, C, tile, NT, total)
 
 
@@ -40,8 +40,8 @@ def test_grid_is_bounded_by_the_rows_that_exist(ffn_rules):
     E, T, k = 128, 2048, 2
     for tile, NT in ((64, 8), (64, 32), (128, 16), (256, 4)):
         live = (T * k // tile + E) * NT
-        assert ffn_rules.grid(E, T, tile, NT, T * k) <= live + 7
-        assert E * T // tile * NT <= ffn_rules.grid(E, T, tile, NT, E * T) <= E * T // tile * NT + 7
+        assert ffn_rules.grid(E, T, tile, NT, T * k, 0) <= live + 7
+        assert E * T // tile * NT <= ffn_rules.grid(E, T, tile, NT, E * T, 0) <= E * T // tile * NT + 7
 
 
 def tiles_of_xcds(find, blocks):
@@ -79,11 +79,11 @@ def test_weight_gradient_work_is_even_on_imbalanced_experts(ffn_rules, E, MT, NT
     assert max(eighths) > 1.5 * sum(eighths) / 8
 
 
-def live_tiles(ffn_rules, rows, tile_rows, NT, shift, blocks, parts=None):
+def live_tiles(ffn_rules, rows, tile_rows, NT, shift, blocks, parts=None, shorts_last=0):
     """The tiles of a forward launch, XCD by XCD; `parts` gets what kinds of place in the numbering they came from."""
     at, fills = (ctypes.c_int * 3)(), (ctypes.c_int * len(rows))(*rows)
     def find(b):
-        part = ffn_rules.tile_at(b, len(rows), fills, tile_rows, NT, shift, at)
+        part = ffn_rules.tile_at(b, len(rows), fills, tile_rows, NT, shift, shorts_last, at)
         assert part >= 0
         if parts is not None and part:
             parts.add(part)
@@ -91,21 +91,43 @@ def live_tiles(ffn_rules, rows, tile_rows, NT, shift, blocks, parts=None):
     return tiles_of_xcds(find, blocks)
 
 
-@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("shift,shorts_last", [(0, 0), (0, 1), (1, 1)])
 @pytest.mark.parametrize("E,C,tile_rows,NT,most_dealt", [(1, 700, 64, 3, -1), (8, 4200, 256, 8, 0), (17, 353, 128, 14, -1), (33, 1500, 128, 9, 1), (70, 1300, 128, 12, 1),
                                                          (130, 900, 64, 5, 1), (65, 66, 64, 9, -1), (512, 300, 64, 7, 0)])
-def test_every_live_tile_once(ffn_rules, E, C, tile_rows, NT, most_dealt, shift):
+def test_every_live_tile_once(ffn_rules, E, C, tile_rows, NT, most_dealt, shift, shorts_last):
     """Fills of every kind, in launches below and beyond the tiles from which whole groups are dealt: every live tile has one block
-    among those that the grid launches, and no XCD has a tile more than another but for one.  most_dealt: the largest shift at which groups are."""
+    among those that the grid launches, and no XCD has a tile more than another but for one of each kind.  most_dealt: the largest shift at which groups are."""
     rng, parts = np.random.default_rng(E), set()
     for fills in (np.full(E, C), rng.integers(0, C + 1, size=E), np.where(rng.random(E) < 0.3, C, 0), np.minimum(C, (C * 4 / (1 + np.arange(E))).astype(int)),
                   np.minimum(C, np.array([0, 1, tile_rows, tile_rows + 1, 2 * tile_rows, C, C - 1])[rng.integers(0, 7, size=E)])):
         rows = [int(v) for v in fills]
-        grid = ffn_rules.grid(E, C, tile_rows, NT, max(1, sum(rows)))
-        per = live_tiles(ffn_rules, rows, tile_rows, NT, shift, grid, parts)
+        grid = ffn_rules.grid(E, C, tile_rows, NT, max(1, sum(rows)), shorts_last)
+        per = live_tiles(ffn_rules, rows, tile_rows, NT, shift, grid, parts, shorts_last)
         assert sorted(sum(per, [])) == [(e, m, n) for e in range(E) for m in range(-(-rows[e] // tile_rows)) for n in range(NT)]
-        assert max(map(len, per)) - min(map(len, per)) <= 1
-    assert 2 in parts and (1 in parts) == (shift <= most_dealt)
+        assert max(map(len, per)) - min(map(len, per)) <= 1 + shorts_last
+    assert 2 in parts and (1 in parts) == (shift <= most_dealt) and (3 in parts) == (shorts_last == 1 and E > 1)
+
+
+@pytest.mark.parametrize("E,C,tile_rows,NT,worse", [(64, 550, 256, 4, 1.2), (8, 3000, 256, 8, 1.05), (32, 980, 128, 12, 1.15), (128, 586, 128, 8, 1.15)])
+def test_short_row_tiles_are_shared_evenly(ffn_rules, E, C, tile_rows, NT, worse):
+    """Zipf-shaped fills: a tile costs a third and, for the rest, its rows.  No XCD has more than 1.15 times the mean; with one run for all kinds
+    of tiles it is at least `worse` times as much."""
+    fills = [max(1, min(C, int(C * (E / 2) * (e + 1) ** -2.4))) if e < E // 2 else 30 for e in range(E)]
+    def most(shorts_last):
+        blocks = ffn_rules.grid(E, C, tile_rows, NT, sum(fills), shorts_last)
+        work = [sum(0.35 + 0.65 * min(1, (fills[e] - m * tile_rows) / tile_rows) for e, m, _ in x)
+                for x in live_tiles(ffn_rules, fills, tile_rows, NT, tile_rows == 128, blocks, shorts_last=shorts_last)]
+        return max(work) * 8 / sum(work)
+    assert most(1) <= 1.15 and most(0) >= worse * most(1)
+
+
+def test_an_even_gate_keeps_short_row_tiles_in_place(ffn_rules):
+    """Fills as an even gate gives them, from 30 rows per expert on: no expert is far above the mean, so the shorts stay with the others."""
+    rng, parts = np.random.default_rng(1), set()
+    for E, mean in [(8, 4096), (32, 784), (17, 353), (64, 128), (128, 64), (32, 30)]:
+        rows = [int(v) for v in rng.multinomial(E * mean, np.full(E, 1 / E))]
+        live_tiles(ffn_rules, rows, 128, 4, 1, ffn_rules.grid(E, 2 * mean, 128, 4, E * mean, 1), parts, 1)
+    assert 3 not in parts
 
 
 def panels(tiles, at_once):
