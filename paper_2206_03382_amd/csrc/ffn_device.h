@@ -57,7 +57,7 @@ __device__ __forceinline__ int live_rows_of(int e, int64_t C, const int32_t* __r
 // Which tile block number b works on, or false where there is none for it.
 // An expert's live tiles are its row tiles below the fill x all column tiles; how they are numbered and dealt to the XCDs: ffn_rules.h.  Every wave
 // finds its tile by prefix sums over the experts, 64 to a step; no host has to know the fills.
-// SHIFT: log2 of the blocks that share a unit, where groups are to hold as many more tiles.  SHORTS: imbalanced experts' short row tiles come last.
+// SHIFT: log2 of the blocks that share a unit, where groups are to hold as many more tiles.  SHORTS: short row tiles may come last.
 template <int TILE_ROWS, int SHIFT, bool SHORTS, int CHUNKS>
 __device__ __forceinline__ bool search_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
                                             int& e_out, int& mt_out, int& nt_out, int& rows_out) {
@@ -65,30 +65,38 @@ __device__ __forceinline__ bool search_tile(int b, int lane, int E, int64_t C, c
   unsigned long long shortv[CHUNKS];                                // experts with a short row tile
 #pragma unroll
   for (int c = 0; c < CHUNKS; ++c) rowsv[c] = c * 64 + lane < E ? live_rows_of(c * 64 + lane, C, counts) : 0;      // all loads in flight at once
-  bool uneven = false;
+  int tall = 0, shorts = 0;
+#pragma unroll
+  for (int c = 0; c < CHUNKS; ++c) {                                // as if all row tiles were tall
+    if (c > 0 && c * 64 >= E) break;
+    upto[c] = tall + wave_inclusive_scan((rowsv[c] + TILE_ROWS - 1) / TILE_ROWS * NT);
+    tall = __builtin_amdgcn_readlane(upto[c], 63);
+  }
+  bool apart = false;                                               // short row tiles come last
   if (SHORTS && counts && C > TILE_ROWS) {
-    int all_rows = 0;
+    int all_rows = 0, without = 0, upto_without[CHUNKS];
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c) {
       if (c > 0 && c * 64 >= E) break;
       all_rows += __builtin_amdgcn_readlane(wave_inclusive_scan(rowsv[c]), 63);
+      upto_without[c] = without + wave_inclusive_scan(tall_row_tiles(rowsv[c], TILE_ROWS, true) * NT);
+      without = __builtin_amdgcn_readlane(upto_without[c], 63);
     }
+    apart = opens_a_round(without, tall, SHIFT);
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c) {
       if (c > 0 && c * 64 >= E) break;
-      uneven |= __ballot(far_above_mean(rowsv[c], E, all_rows)) != 0;
+      apart |= __ballot(far_above_mean(rowsv[c], E, all_rows)) != 0;
     }
-  }
-  int tall = 0, shorts = 0;
+    if (apart) {
+      shorts = tall - without;
+      tall = without;
 #pragma unroll
-  for (int c = 0; c < CHUNKS; ++c) {
-    if (c > 0 && c * 64 >= E) break;
-    const int mt = tall_row_tiles(rowsv[c], TILE_ROWS, uneven);
-    upto[c] = tall + wave_inclusive_scan(mt * NT);
-    tall = __builtin_amdgcn_readlane(upto[c], 63);
-    if (SHORTS) {
-      shortv[c] = __ballot(rowsv[c] > mt * TILE_ROWS);
-      shorts += __builtin_popcountll(shortv[c]) * NT;
+      for (int c = 0; c < CHUNKS; ++c) {
+        if (c > 0 && c * 64 >= E) break;
+        upto[c] = upto_without[c];
+        shortv[c] = __ballot(rowsv[c] > tall_row_tiles(rowsv[c], TILE_ROWS, true) * TILE_ROWS);
+      }
     }
   }
   constexpr int gs = kGroupShift + SHIFT;
@@ -98,7 +106,7 @@ __device__ __forceinline__ bool search_tile(int b, int lane, int E, int64_t C, c
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c) {
       if (c > 0 && c * 64 >= E) break;
-      groups[c] = full + wave_inclusive_scan(tall_row_tiles(rowsv[c], TILE_ROWS, uneven) * NT >> gs);
+      groups[c] = full + wave_inclusive_scan(tall_row_tiles(rowsv[c], TILE_ROWS, apart) * NT >> gs);
       full = __builtin_amdgcn_readlane(groups[c], 63);
     }
     rounds = full >> 3;
@@ -119,7 +127,7 @@ __device__ __forceinline__ bool search_tile(int b, int lane, int E, int64_t C, c
     const unsigned long long hit = __ballot(inc > s.at);
     if (hit == 0) continue;
     const int l = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
-    const int rows = __builtin_amdgcn_readlane(rowsv[c], l), mt = tall_row_tiles(rows, TILE_ROWS, uneven), all = mt * NT;
+    const int rows = __builtin_amdgcn_readlane(rowsv[c], l), mt = tall_row_tiles(rows, TILE_ROWS, apart), all = mt * NT;
     const int back = s.at - __builtin_amdgcn_readlane(inc, l);      // from the end of the expert's groups or tiles
     e_out = c * 64 + l;                                             // the same in every lane: in scalar registers
     rows_out = rows;

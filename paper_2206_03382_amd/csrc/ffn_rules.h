@@ -63,8 +63,15 @@ MOE_HOST_DEVICE inline bool deals_groups(int live, int E, int NT, int shift) { r
 // and 535; the slowest 8 x 4096, 2048 x 2048 120.6 and 128.1 (step 761 and 786).  An even gate keeps them where they are: next to the
 // expert's other tiles they find its weights in the L2 (32 experts x 166 rows, 1856 x 3840 131 us, 183 apart; ViT 328 and 343).  So do the
 // smaller tiles, which read more weights for a product (128 x 128, 16 x 750 rows, 1000 x 2000 54.6 and 61.0).
+// The exception are few short tiles that alone open another round of the chip, the second or third: 32 experts x 500 rows, 2048 x 2048, layer 392
+// and 361 us; 64 x 246, 768 x 1024 145 and 135; 16 x 237, 3072 x 4096 340 and 321; the slowest of 14 such, 64 x 121, 2560 x 3840, 723 and 738.
+// Many of them cost what they read (48 x 160, 2304 x 2816, as many shorts as others: 431 and 568), and with more rounds there is no difference.
+MOE_HOST_DEVICE inline bool opens_a_round(int tall, int all, int shift) {
+  const int places = 256 << shift;
+  return (all - tall) * 3 <= tall && tall <= 2 * places && (tall + places - 1) / places < (all + places - 1) / places;
+}
 MOE_HOST_DEVICE inline bool far_above_mean(int rows, int E, int all_rows) { return 2.0f * (float)rows * (float)E > 3.0f * (float)all_rows; }
-MOE_HOST_DEVICE inline int tall_row_tiles(int rows, int tile_rows, bool uneven) { return (rows + (uneven ? tile_rows / 2 : tile_rows) - 1) / tile_rows; }
+MOE_HOST_DEVICE inline int tall_row_tiles(int rows, int tile_rows, bool apart) { return (rows + (apart ? tile_rows / 2 : tile_rows) - 1) / tile_rows; }
 
 enum TilePart { kDealtTile, kLeftTile, kShortTile, kNoTile };
 struct TileSpot { TilePart part; int at; }; // kDealtTile: number of the group among all; else of the tile among those left, or the short ones

@@ -35,12 +35,17 @@ int equal_tile(int b, int E, int MT, int NT, int* at) {
 // find_tile, one expert behind the other instead of 64 lanes at a time
 int tile_at(int b, int E, const int* rows, int tile_rows, int NT, int shift, int shorts_last, int* at) {
   const int gs = moe::kGroupShift + shift;
-  int all_rows = 0, tall = 0, shorts = 0, full = 0, upto = 0, groups = 0, short_upto = 0;
-  bool uneven = false;
-  for (int e = 0; e < E; ++e) all_rows += rows[e];
-  for (int e = 0; e < E; ++e) uneven = uneven || (shorts_last && moe::far_above_mean(rows[e], E, all_rows));
+  int all_rows = 0, all_tiles = 0, without = 0, tall = 0, shorts = 0, full = 0, upto = 0, groups = 0, short_upto = 0;
   for (int e = 0; e < E; ++e) {
-    const int mt = moe::tall_row_tiles(rows[e], tile_rows, uneven);
+    all_rows += rows[e];
+    all_tiles += moe::tall_row_tiles(rows[e], tile_rows, false) * NT;
+    without += moe::tall_row_tiles(rows[e], tile_rows, true) * NT;
+  }
+  bool apart = moe::opens_a_round(without, all_tiles, shift);
+  for (int e = 0; e < E; ++e) apart = apart || moe::far_above_mean(rows[e], E, all_rows);
+  apart = apart && shorts_last;
+  for (int e = 0; e < E; ++e) {
+    const int mt = moe::tall_row_tiles(rows[e], tile_rows, apart);
     tall += mt * NT;
     full += mt * NT >> gs;
     shorts += rows[e] > mt * tile_rows ? NT : 0;
@@ -49,7 +54,7 @@ int tile_at(int b, int E, const int* rows, int tile_rows, int NT, int shift, int
   const moe::TileSpot s = moe::tile_spot(b, tall, shorts, rounds, gs);
   if (s.part == moe::kNoTile) return 0;
   for (int e = 0; e < E; ++e) {
-    const int mt = moe::tall_row_tiles(rows[e], tile_rows, uneven), all = mt * NT;
+    const int mt = moe::tall_row_tiles(rows[e], tile_rows, apart), all = mt * NT;
     upto += all;
     groups += all >> gs;
     short_upto += rows[e] > mt * tile_rows ? NT : 0;

@@ -122,12 +122,18 @@ def test_short_row_tiles_are_shared_evenly(ffn_rules, E, C, tile_rows, NT, worse
 
 
 def test_an_even_gate_keeps_short_row_tiles_in_place(ffn_rules):
-    """Fills as an even gate gives them, from 30 rows per expert on: no expert is far above the mean, so the shorts stay with the others."""
+    """Fills as an even gate gives them, from 30 rows per expert on: no expert is far above the mean, so the shorts stay with the others.  They come
+    last where they alone open the second or third round of the chip and are few."""
     rng, parts = np.random.default_rng(1), set()
     for E, mean in [(8, 4096), (32, 784), (17, 353), (64, 128), (128, 64), (32, 30)]:
         rows = [int(v) for v in rng.multinomial(E * mean, np.full(E, 1 / E))]
-        live_tiles(ffn_rules, rows, 128, 4, 1, ffn_rules.grid(E, 2 * mean, 128, 4, E * mean, 1), parts, 1)
+        live_tiles(ffn_rules, rows, 128, 6, 1, ffn_rules.grid(E, 2 * mean, 128, 6, E * mean, 1), parts, 1)
     assert 3 not in parts
+    for E, mean, tile_rows, NT, apart in [(32, 500, 256, 8, True), (32, 256, 128, 8, True), (64, 166, 128, 8, False), (32, 450, 256, 8, False), (32, 1000, 256, 8, False)]:
+        rows, parts = [mean + (16 if e % 4 == 0 else -16) for e in range(E)], set()
+        per = live_tiles(ffn_rules, rows, tile_rows, NT, int(tile_rows == 128), ffn_rules.grid(E, 2 * mean, tile_rows, NT, sum(rows), 1), parts, 1)
+        assert sorted(sum(per, [])) == [(e, m, n) for e in range(E) for m in range(-(-rows[e] // tile_rows)) for n in range(NT)]
+        assert (3 in parts) == apart, (E, mean)
 
 
 def panels(tiles, at_once):
