@@ -3,6 +3,8 @@
 Bars: routing integers (idx, loc, kept, counts, slot_src) bit-exact; encode bit-exact; floating-point outputs within
 max-abs-error <= 1e-5 * max|ref| (fp32 storage) or 2e-2 * max|ref| (bf16 storage) of the fp64 oracle.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -593,8 +595,8 @@ def test_expert_ffn_same_bits_on_every_tile(moe, ffn_rules, rows):
 
 @pytest.mark.parametrize("E,C,H", [(70, 700, 1032), (513, 70, 264), (3, 3000, 4104), (9, 300, 776), (200, 130, 2056), (65, 66, 520)])
 def test_expert_ffn_every_tile_once(moe, E, C, H):
-    """Fills of every kind (none, one row, around row tiles, all, random) in launches below and beyond the tiles from which whole groups are
-    dealt to the XCDs, with more than 64 experts to search and more than the search takes.  Small integers: exact."""
+    """Fills of every kind (none, one row, around row tiles, all, random) in launches whose tiles are one sequence in eighths, with more than 64
+    experts to search and more than the search takes.  Small integers: exact."""
     M = 64
     rng = np.random.default_rng(E)
     fills = rng.integers(0, C + 1, size=E)
@@ -606,6 +608,30 @@ def test_expert_ffn_every_tile_once(moe, E, C, H):
     live = torch.arange(C, device="cuda")[None, :] < rows[:, None]
     want = torch.bmm(Z.float(), W1.float()).clamp(min=0).to(torch.bfloat16)
     assert torch.equal(hidden[live], want[live]) and bool(hidden[~live].isnan().all())
+
+
+@pytest.mark.parametrize("E,C,M,H,low,dtype,tile,parts", [
+    (12, 8000, 1024, 2048, 0, torch.bfloat16, 0, {1, 2, 3}), (12, 9000, 64, 2048, 0, torch.bfloat16, 6, {1, 2, 3}), (66, 1500, 64, 2048, 0, torch.bfloat16, 6, {2, 3}),
+    (66, 1300, 64, 2048, 1100, torch.bfloat16, 6, {1, 2}), (70, 1400, 64, 1032, 1000, torch.bfloat16, 1, {1, 2}), (70, 700, 72, 200, 500, torch.float32, 3, {1, 2})])
+def test_expert_ffn_every_tile_once_in_groups(moe, ffn_rules, E, C, M, H, low, dtype, tile, parts):
+    """The same where whole groups are dealt to the XCDs, what is left comes in eighths, and short row tiles come last (parts: which of
+    the three a launch has, by the rules themselves), on each tile that has them, up to 64 experts and beyond.  low 0: Zipf-shaped fills."""
+    rng = np.random.default_rng(E)
+    fills = rng.integers(low, C + 1, size=E) if low else np.minimum(C, C * 8 // (1 + np.arange(E)))
+    fills[:8] = np.minimum([0, 1, 64, 65, 128, 129, C, 0], C)
+    tile_rows, width, shift, shorts_last = {0: (256, 256, 0, 1), 1: (128, 128, 0, 0), 3: (64, 64, 0, 0), 6: (128, 256, 1, 1)}[tile]
+    if dtype == torch.bfloat16:
+        assert ffn_rules.tile(0, E, C, M, H, 0, 0) == tile
+    at, f, NT = (ctypes.c_int * 3)(), (ctypes.c_int * E)(*[int(v) for v in fills]), -(-H // width)
+    blocks = ffn_rules.grid(E, C, tile_rows, NT, E * C, shorts_last)
+    assert {ffn_rules.tile_at(b, E, f, tile_rows, NT, shift, shorts_last, at) for b in range(blocks)} - {0} == parts
+    rows = torch.from_numpy(fills.astype(np.int32)).cuda()
+    Z, W1 = (torch.randint(-2, 3, s, device="cuda").to(dtype) for s in ((E, C, M), (E, M, H)))
+    hidden = torch.full((E, C, H), float("nan"), device="cuda", dtype=dtype)
+    moe.expert_ffn(Z, W1, None, torch.zeros((E, H, M), device="cuda", dtype=dtype), None, O.ACT_RELU, counts=rows, hidden=hidden)
+    for e, n in enumerate(fills):
+        want = (Z[e, :n].float() @ W1[e].float()).clamp(min=0).to(dtype)
+        assert torch.equal(hidden[e, :n], want) and bool(hidden[e, n:].isnan().all()), e
 
 
 def test_expert_ffn_backward_streamed_column_sums(moe):
