@@ -6,6 +6,7 @@
 // as stored for the products with W^T, the activations as stored for the weight gradients (reduction over an expert's slots
 // up to its fill), and act' is applied in the epilogue of the dH product; nothing is copied, padded or transposed in memory.
 #include "common.h"
+#include "ffn_rules.h"
 
 namespace moe {
 
@@ -112,10 +113,7 @@ static hipError_t ffn_backward_t(const void* Z, const void* W1, const void* b1, 
   }
   auto colsums = [&]() -> hipError_t {
     const int cprH = (int)(H * es / 16), cprM = (int)(M * es / 16);
-    // Slabs beyond the caches are streamed, in pieces of 256 bytes to a row instead of 128: 128 experts x 2048 rows of 1024 and 4096 columns
-    // 542 -> 458 us (5.9 TB/s).  In the caches the hint would cost, and launches of few blocks need them all (8 x 4096 rows,
-    // 2048 and 2048: 52 us either way).
-    const bool stream = (double)E * C * (M > H ? M : H) * es >= 1073741824.0;
+    const bool stream = colsum_streams(E, counts ? mean_or(rows_hint, C) : (double)C, db1 ? H * es : 0, db2 ? M * es : 0);
     const int np = stream ? 16 : 8;
     const ColsumJob<ET> j1 = {(const uint4*)dP, (ET*)db1, cprH, db1 ? (int)ceil_div(cprH, np) : 0};
     const ColsumJob<ET> j2 = {(const uint4*)dY, (ET*)db2, cprM, db2 ? (int)ceil_div(cprM, np) : 0};

@@ -261,4 +261,14 @@ static inline Tile tile_of(int mode, int64_t E, int64_t C, int64_t K, int64_t N,
   return choose_tile(mode, large_ok, half_ok, E, C, mean_or(rows_hint, C), K, N, gather_rows > 0);
 }
 
+// Whether the column sums (ffn_backward.hip) of E slabs each, of so many rows on average and of the given bytes (0: not summed), are streamed, in
+// pieces of 256 bytes to a row instead of 128: where the rows that are expected lie far beyond the caches and half as many blocks still fill the chip.
+// Without and with, both sums: 128 experts x 2048 rows, 4096 and 1024 columns 537 and 475 us; 64 x 4096, 2048 and 2048 416 and 330; fewer blocks than
+// units: 8 x 16384, 1024 and 1024 (128) 103 and 108, 4 x 32768, 1024 and 1024 (64) 141 and 185, 5 x 78643, 256 and 256 (10) 244 and 371.  The
+// capacity says little: of 64 x 2560, 1024 and 1024, a Zipf-shaped gate fills 77 MB, which the caches hold, 12.9 and 16.0.  With an even
+// gate the line could lie at 256 MB (8 x 4096, 2048 and 2048 54 and 44; 134 MB of 8 x 4096, 1024 and 1024 22.5 and 23.0).
+static inline bool colsum_streams(int64_t E, double rows, int64_t row_bytes1, int64_t row_bytes2) {
+  return (double)E * rows * (double)(row_bytes1 + row_bytes2) >= 1073741824.0 && E * (tiles_in(row_bytes1, 256) + tiles_in(row_bytes2, 256)) >= 256;
+}
+
 }  // namespace moe

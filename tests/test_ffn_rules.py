@@ -155,6 +155,15 @@ def test_groups_of_the_half_tile_are_what_an_xcd_holds(ffn_rules, E, rows, NT, i
     assert sum(panels(x, 64) for x in live_tiles(ffn_rules, [rows] * E, 128, NT, 0, -(-E * MT * NT // 8) * 8)) >= in32 * old
 
 
+def test_column_sums_stream_what_is_expected_and_summed(ffn_rules):
+    """The rows expected, not the capacity, of the slabs whose sum is asked for, and only with a block for every unit."""
+    big = dict(E=128, M=8192, H=2048)                                # bytes of a row, 2048 rows expected of 4096
+    assert ffn_rules.colsum_streams(big["E"], 2048, big["H"], big["M"])
+    assert not ffn_rules.colsum_streams(big["E"], 200, big["H"], big["M"])       # the same buffers, mostly empty
+    assert not ffn_rules.colsum_streams(big["E"], 2048, big["H"], 0)             # the wide slab's sum is not asked for
+    assert not ffn_rules.colsum_streams(4, 131072, 2048, 2048)                   # 64 blocks
+
+
 K256, K128, K64X128, K64, K64X128_STREAM, K64_STREAM, KHALF = range(7)
 
 

@@ -634,20 +634,27 @@ def test_expert_ffn_every_tile_once_in_groups(moe, ffn_rules, E, C, M, H, low, d
         assert torch.equal(hidden[e, :n], want) and bool(hidden[e, n:].isnan().all()), e
 
 
-def test_expert_ffn_backward_streamed_column_sums(moe):
-    """db2 of slabs beyond 1 GiB, whose column sums are streamed: a ragged last block of columns, rows that end inside a batch of eight and an
-    expert without any.  Bound: chains of rows / 32 + 32 additions in fp32, and one rounding to bf16."""
-    E, C, M, H = 3, 45000, 4104, 8
-    assert E * C * M * 2 >= 2 ** 30
+@pytest.mark.parametrize("dtype,E,C,M,H", [(torch.bfloat16, 9, 15000, 4104, 8), (torch.bfloat16, 10, 15000, 2056, 2056), (torch.float32, 9, 7500, 4104, 8)])
+def test_expert_ffn_backward_streamed_column_sums(moe, ffn_rules, dtype, E, C, M, H):
+    """db1 and db2 of slabs beyond 1 GiB, whose column sums are streamed: ragged last blocks of columns, rows that end inside a batch of eight, an
+    expert without any and some with a few.  db1 sums dP = dY W2^T where the pre-activations are positive.  Bounds: chains of rows / 32 + 32 additions
+    in fp32 and, in bf16, one rounding of the sum and one of every dP (a sum of M products in fp32)."""
+    es = 2 if dtype == torch.bfloat16 else 4
+    assert ffn_rules.colsum_streams(E, C, H * es, M * es) and not ffn_rules.colsum_streams(E, C / 8, H * es, M * es)
     gen = torch.Generator(device="cuda").manual_seed(5)
-    Z, dY, hidden = (torch.randn((E, C, w), generator=gen, device="cuda", dtype=torch.bfloat16) for w in (M, M, H))
-    W1, W2 = (torch.randn(s, generator=gen, device="cuda", dtype=torch.bfloat16) for s in ((E, M, H), (E, H, M)))
-    rows = [C, 0, 777]
+    Z, dY, hidden = (torch.randn((E, C, w), generator=gen, device="cuda").to(dtype) for w in (M, M, H))
+    W1, W2 = (torch.randn(s, generator=gen, device="cuda").to(dtype) for s in ((E, M, H), (E, H, M)))
+    rows = [C, 0, 777, 1, 255, 256, 257, C - 1, 8 * 32 + 31, C][:E]
     g = moe.expert_ffn_backward(Z, W1, None, W2, hidden, dY, O.ACT_RELU, counts=torch.tensor(rows, dtype=torch.int32, device="cuda"), pre=hidden)
+    ulp = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -23
     for e, n in enumerate(rows):
         v = dY[e, :n].double()
         ref, bound = v.sum(0), (n / 32 + 32) * 2.0 ** -24 * v.abs().sum(0)
-        assert bool(((g["db2"][e].double() - ref).abs() <= bound + 2.0 ** -8 * ref.abs()).all()), e
+        assert bool(((g["db2"][e].double() - ref).abs() <= bound + ulp * ref.abs()).all()), e
+        dP = (v @ W2[e].double().T) * (hidden[e, :n] > 0)
+        mag = (v.abs() @ W2[e].double().abs().T) * (hidden[e, :n] > 0)
+        ref, bound = dP.sum(0), (n / 32 + 32) * 2.0 ** -24 * dP.abs().sum(0) + ulp * dP.abs().sum(0) + M * 2.0 ** -24 * mag.sum(0)
+        assert bool(((g["db1"][e].double() - ref).abs() <= bound + ulp * ref.abs()).all()), e
 
 
 @pytest.mark.parametrize("E,C,M,H", [(96, 257, 136, 264), (64, 130, 200, 776), (128, 193, 136, 136), (24, 129, 264, 2056), (520, 70, 72, 136)])
