@@ -17,15 +17,6 @@
 namespace moe {
 
 typedef __attribute__((ext_vector_type(4))) double f64x4;
-// Blocks of 64 tokens from which wide gates decide with one lane per token.  Below, a token's lane group spreads a block's work
-// over more of the chip: 6000 tokens, 64 experts, top-4: 19 us against 23 (51 against 73 with near-tie repairs); 65536
-// tokens, top-2: 27 against 21.  At the line itself (32768 tokens) the two are alike for up to four choices (top-1 of 32 12.4 and 11.0 us,
-// top-4 of 64 24.1 and 23.3).  With more choices and their repairs the line lies further out, whole gates, group and lane: 32768 tokens,
-// M = 4096, top-8 of 128 172 and 260 us; M = 1024, top-8 of 64 92 and 115; 49152, M = 2048, top-8 of 128 177 and 209; M = 1024, top-5 of 64
-// 94 and 91; 65472, M = 4096, top-6 of 128 288 and 310; M = 1024, top-8 of 64 161 and 126.  Top-k alone of 131072 tokens, top-8 of 128: 147 and 103.
-constexpr int kLaneTopkMinBlocks = 512;
-static bool lane_topk(int64_t blocks, int64_t E, int k) { return blocks >= (k <= 4 ? kLaneTopkMinBlocks : (E <= 64 ? 768 : 1024)); }
-
 
 // ---------------------------------------------------------------------------------------------------------------
 // logits[t,e] = sum_m x[t,m] Wg[m,e] + bias[e], fp64 accumulate (v_mfma_f64_16x16x4_f64), one rounding to fp32.
@@ -1038,7 +1029,7 @@ hipError_t launch_gate_topk(float* logits, int64_t T, int64_t E, int k, int64_t 
   } while (0)
   // wide gates with few choices: one lane per token (its LDS footprint, 4 waves x (8.25 KB + k E bytes), must fit 64 KB);
   // tokens in a caller-given order (perm) keep the lane-group kernel
-  const bool lane_kernel = !perm && lane_topk(NB, E, k) && E > 16 && k <= 32 && (size_t)k * E <= 7936;
+  const bool lane_kernel = !perm && NB >= gate_lane_topk_blocks(E, k, repair ? repair->M : 0) && E > 16 && k <= 32 && (size_t)k * E <= 7936;
   if (lane_kernel) {
     if (k <= 1) MOE_TOPK_LANE(1); else if (k <= 2) MOE_TOPK_LANE(2); else if (k <= 4) MOE_TOPK_LANE(4);
     else if (k <= 8) MOE_TOPK_LANE(8); else if (k <= 16) MOE_TOPK_LANE(16); else MOE_TOPK_LANE(32);

@@ -27,6 +27,23 @@ inline bool gate_in_one_block(int64_t T, int64_t E, int k, int64_t marked_C) {
   return T <= ((E & (E - 1)) == 0 ? kSmallGateTokens : 256) && E <= 16 && E * k <= kSmallGatePairs && E * marked_C <= 16 * kSmallGateTokens;
 }
 
+// Blocks of 64 tokens from which wide gates decide with one lane per token (M: length of the products that repair near-ties; 0: none are
+// repaired).  Below, a token's lane group spreads a block's work over more of the chip: 6000 tokens, 64 experts, top-4: 19 us against 23 (51 against 73
+// with repairs); 65536 tokens, top-2: 27 against 21.  At the line itself (32768 tokens) the two are alike for up to four choices (top-1 of
+// 32 12.4 and 11.0 us, top-4 of 64 24.1 and 23.3).  More choices have more near-ties, and a lane's repairs are a wave's serial
+// part, so with repairs the line lies further out, the longer a product is.  Whole gates with top-5 and top-8 of 24 to 256 experts, 32768 to 65472 tokens,
+// group and lane: 32768 tokens, M = 4096, top-8 of 128 170 and 264 us; M = 1024, top-8 of 64 95 and 117; 49152, M = 4096, top-8 of 256 491 and 558;
+// 65472, M = 4096, top-8 of 64 292 and 318, but M = 1024 165 and 152, M = 512, top-8 of 256 1.20 times as long in groups; of 32 experts 40000, M = 1024 108 and 91.
+// Over 260 such gates this line is 0.4 % off the better form on average (10 % at most), 512 for all 6.8 %, 768 and 1024 by the number of experts 3.8 %.
+// Without repairs 512 is 3.2 % off over 92 gates and 768 and 1024 20 %: lanes are the faster from there on for nearly all (top-8 of 160 92 and
+// 64 us, 65472 tokens 172 and 79; top-5 of 24 38 and 28), though not for a few choices of many experts (32768 tokens, top-5 of 128 32 and
+// 46, of 512 87 and 141).
+inline int64_t gate_lane_topk_blocks(int64_t E, int k, int64_t M) {
+  if (k <= 4 || M == 0) return 512;
+  const int64_t line = E <= 32 ? 256 + M / 8 : 448 + M / 6;
+  return line < 512 ? 512 : (line > 1024 ? 1024 : line);
+}
+
 // Experts whose exact logits the wide kernel takes, in blocks of 128 (vecw: its 16-byte pieces of Wg's rows are whole); the narrow
 // kernel takes the others, 64 at a time.  Blocks of 128 fill badly with few tokens or with a remainder: fp32, M = 2048, narrow and
 // wide 4096 tokens, 128 experts 56 and 132 us, 16384 168 and 189, 65536 661 and 630; 12000, 512 502 and 484; 65536, 96 520 and 628;

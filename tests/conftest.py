@@ -84,6 +84,7 @@ int dx_tokens(int64_t T, int64_t row_bytes) { return moe::gate_dx_tokens(T, row_
 int64_t backward_tokens(int64_t T, int64_t E, int bias) { return moe::gate_backward_token_block(T, E, bias); }
 int64_t wide_logits(int64_t T, int64_t E, int vecw) { return moe::gate_logits_wide_experts(T, E, vecw); }
 int one_block(int64_t T, int64_t E, int k, int64_t marked_C) { return moe::gate_in_one_block(T, E, k, marked_C); }
+int64_t lane_topk_blocks(int64_t E, int k, int64_t M) { return moe::gate_lane_topk_blocks(E, k, M); }
 int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T + 63) / 64, E, k); }
 }
 """
@@ -92,7 +93,7 @@ int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T
 @pytest.fixture(scope="session")
 def ffn_rules(tmp_path_factory):
     """The host rules of the grouped GEMM: grid(), equal_tile(), tile_at(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, the same for a
-    product that keeps its pre-activations, tile_cost(), colsum_streams() and split(); and of the gate: one_block(), one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
+    product that keeps its pre-activations, tile_cost(), colsum_streams() and split(); and of the gate: one_block(), lane_topk_blocks(), one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
@@ -107,6 +108,7 @@ def ffn_rules(tmp_path_factory):
     lib.tile_keeping_pre.restype, lib.tile_keeping_pre.argtypes = ctypes.c_int, [ctypes.c_int64] * 6
     lib.tile_cost.restype, lib.tile_cost.argtypes = ctypes.c_double, [ctypes.c_int] * 2 + [ctypes.c_int64] * 6
     lib.one_block.restype, lib.one_block.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_int64]
+    lib.lane_topk_blocks.restype, lib.lane_topk_blocks.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_int, ctypes.c_int64]
     lib.one_launch.restype, lib.one_launch.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     lib.dx_tokens.restype, lib.dx_tokens.argtypes = ctypes.c_int, [ctypes.c_int64] * 2
     lib.backward_tokens.restype, lib.backward_tokens.argtypes = ctypes.c_int64, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]

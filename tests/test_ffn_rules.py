@@ -274,3 +274,14 @@ def test_wide_logits(ffn_rules):
                        (8200, 136, 0), (16384, 128, 0), (25088, 256, 256), (65536, 64, 0)):
         assert ffn_rules.wide_logits(T, E, 1) == wide, (T, E)
     assert ffn_rules.wide_logits(65536, 129, 0) == 0
+
+
+def test_lane_topk_line(ffn_rules):
+    """512 blocks of 64 tokens for few choices and without repairs; with repairs further out the longer their products, sooner for few experts."""
+    line = ffn_rules.lane_topk_blocks
+    assert {line(E, k, M) for E in (17, 64, 128, 512) for k, M in ((1, 4096), (4, 4096), (5, 0), (32, 0))} == {512}
+    assert line(32, 8, 1024) == 512 and line(128, 8, 4096) == 1024
+    for E, k in ((32, 5), (64, 8), (512, 16)):
+        lines = [line(E, k, M) for M in range(256, 16384, 256)]
+        assert lines == sorted(lines) and lines[0] == 512 and lines[-1] == 1024
+        assert line(32, k, 2048) <= line(64, k, 2048)

@@ -165,10 +165,18 @@ def test_gate_topk_in_one_block(moe, ffn_rules, T, E, k, block):
     assert np.array_equal(got["slot_src"].cpu().numpy(), ref_slots) and int(got["counts"].sum()) == T * k
 
 
-@pytest.mark.parametrize("T,E,k", [(49088, 64, 5), (49089, 64, 5), (65472, 65, 5), (65473, 65, 5), (32705, 65, 4)])
+@pytest.mark.parametrize("T,E,k", [(49088, 64, 5), (49089, 64, 5), (65472, 65, 5), (65473, 65, 5), (32705, 65, 4), (32704, 65, 5), (32705, 65, 5),
+                                   (32704, 160, 8), (32705, 160, 8), (32705, 300, 5), (32705, 24, 16)])
 def test_gate_topk_lane_line(moe, T, E, k):
     """Around the counts of 64-token blocks from which a gate of many choices decides with one lane per token."""
     test_gate_topk_kernel_switches(moe, T, E, k)
+
+
+@pytest.mark.parametrize("T,M,E,k,lane", [(34048, 512, 64, 5, 0), (34049, 512, 64, 5, 1), (32704, 256, 136, 6, 0), (32705, 256, 136, 6, 1), (32705, 512, 32, 5, 1)])
+def test_gate_route_lane_line(moe, ffn_rules, T, M, E, k, lane):
+    """The same where near-ties are repaired, of up to 128 experts (four repairs side by side in a wave) and more (one by one)."""
+    assert (-(-T // 64) >= ffn_rules.lane_topk_blocks(E, k, M)) == lane
+    test_gate_route_near_ties(moe, T, M, E, k)
 
 
 @pytest.mark.parametrize("T,E,k", [(4096, 8, 2), (4097, 8, 2), (8193, 8, 1), (512, 64, 2), (500, 65, 2), (64, 16, 8), (64, 17, 2), (1000, 43, 3)])
