@@ -896,8 +896,10 @@ __global__ __launch_bounds__(kSmallGateTokens) void gate_small_kernel(const floa
                                                                       int32_t* __restrict__ slot_src, int mark_unfilled,
                                                                       const int32_t* __restrict__ perm) {
   constexpr int W = kSmallGateTokens / kWave;
-  __shared__ int cnt[G * G][W + 1], total[G * G];                   // [expert * k + rank]: arrivals by wave, then of earlier waves
-  __shared__ float prob[G][kSmallGateTokens];
+  // pairs and choices that the rule lets in, with more than G / 2 experts
+  constexpr int P = G * G < kSmallGatePairs ? G * G : kSmallGatePairs, R = kSmallGatePairs / (G / 2 + 1) < G ? kSmallGatePairs / (G / 2 + 1) : G;
+  __shared__ int cnt[P][W + 1], total[P];                           // [expert * k + rank]: arrivals by wave, then of earlier waves
+  __shared__ float prob[R][kSmallGateTokens];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, tv = (int)threadIdx.x, pairs = E * k;
   const int waves = (int)blockDim.x >> 6;
   const bool valid = tv < T;

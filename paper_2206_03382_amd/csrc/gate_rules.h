@@ -19,7 +19,7 @@ inline bool slots_in_one_launch(int64_t token_blocks, int64_t E, int k) {
 // Whether top-k, scan and assignment all run in one block (gate_small_kernel: a lane per token, its logits in registers).  marked_C:
 // slots per expert that have to be marked unfilled, which one block does slowly where they are many; 0 if none are.  Measured in captured
 // graphs, two or three launches and this one: 64 tokens, 3 experts, top-3 6.2 and 4.3 us, 256, 16, 2 7.5 and 5.1, 512, 8, 4 8.0
-// and 5.7, 1024, 16, 1 6.4 and 5.8, 1024, 8, 4 8.5 and 8.7.  Many ranks are its serial part: 64, 16, 4 10.1 and 10.5, 1024, 16, 8 16.5 and
+// and 5.7, 1024, 16, 1 6.5 and 5.8, 1024, 8, 4 8.6 and 8.6.  Many ranks are its serial part: 64, 16, 4 10.1 and 10.5, 1024, 16, 8 16.5 and
 // 23.4.  Rows that are not a power of two long come value by value, which many waves on one unit do slowly: 24, 6, 2 5.9 and 4.6, 64,
 // 5, 5 8.2 and 7.1, but 1000, 13, 1 6.3 and 8.3.
 constexpr int kSmallGateTokens = 1024, kSmallGatePairs = 32;
