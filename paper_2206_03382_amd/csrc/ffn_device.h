@@ -74,28 +74,35 @@ __device__ __forceinline__ bool search_tile(int b, int lane, int E, int64_t C, c
   }
   bool apart = false;                                               // short row tiles come last
   if (SHORTS && counts && C > TILE_ROWS) {
-    int all_rows = 0, without = 0, upto_without[CHUNKS];
+    int all_rows = 0;
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c) {
       if (c > 0 && c * 64 >= E) break;
       all_rows += __builtin_amdgcn_readlane(wave_inclusive_scan(rowsv[c]), 63);
-      upto_without[c] = without + wave_inclusive_scan(tall_row_tiles(rowsv[c], TILE_ROWS, true) * NT);
-      without = __builtin_amdgcn_readlane(upto_without[c], 63);
     }
-    apart = opens_a_round(without, tall, SHIFT);
 #pragma unroll
     for (int c = 0; c < CHUNKS; ++c) {
       if (c > 0 && c * 64 >= E) break;
       apart |= __ballot(far_above_mean(rowsv[c], E, all_rows)) != 0;
     }
-    if (apart) {
-      shorts = tall - without;
-      tall = without;
+    if (apart || may_open_a_round(tall, SHIFT)) {
+      int without = 0, upto_without[CHUNKS];
 #pragma unroll
       for (int c = 0; c < CHUNKS; ++c) {
         if (c > 0 && c * 64 >= E) break;
-        upto[c] = upto_without[c];
-        shortv[c] = __ballot(rowsv[c] > tall_row_tiles(rowsv[c], TILE_ROWS, true) * TILE_ROWS);
+        upto_without[c] = without + wave_inclusive_scan(tall_row_tiles(rowsv[c], TILE_ROWS, true) * NT);
+        without = __builtin_amdgcn_readlane(upto_without[c], 63);
+      }
+      apart |= opens_a_round(without, tall, SHIFT);
+      if (apart) {
+        shorts = tall - without;
+        tall = without;
+#pragma unroll
+        for (int c = 0; c < CHUNKS; ++c) {
+          if (c > 0 && c * 64 >= E) break;
+          upto[c] = upto_without[c];
+          shortv[c] = __ballot(rowsv[c] > tall_row_tiles(rowsv[c], TILE_ROWS, true) * TILE_ROWS);
+        }
       }
     }
   }
@@ -144,8 +151,9 @@ __device__ __forceinline__ bool search_tile(int b, int lane, int E, int64_t C, c
   return false;
 }
 
-// EQUAL: every expert has all of its C rows (weight gradients), see equal_tile.  Up to 64 experts have code of their own, one straight piece:
-// what a launch of few tiles pays for is fetching it (decode step of 16 tokens 47.8 -> 46.9 us).
+// EQUAL: every expert has all of its C rows (weight gradients), see equal_tile.  Up to 64 experts, and up to 128, have code of their own, nearly one
+// straight piece: what a launch of few tiles pays for is fetching it (decode step of 16 tokens 47.8 -> 46.9 us; second product of 128 experts x 8192 rows, 264
+// tiles to a unit, 8150 -> 8080).
 template <int TILE_ROWS, bool EQUAL = false, int SHIFT = 0, bool SHORTS = false>
 __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
                                           int& e_out, int& mt_out, int& nt_out, int& rows_out) {
@@ -159,6 +167,7 @@ __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, con
     return true;
   }
   if (E <= 64) return search_tile<TILE_ROWS, SHIFT, SHORTS, 1>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out);
+  if (E <= 128) return search_tile<TILE_ROWS, SHIFT, SHORTS, 2>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out);
   return search_tile<TILE_ROWS, SHIFT, SHORTS, kMaxExperts / 64>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out);
 }
 

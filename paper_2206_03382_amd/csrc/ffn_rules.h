@@ -70,6 +70,7 @@ MOE_HOST_DEVICE inline bool opens_a_round(int tall, int all, int shift) {
   const int places = 256 << shift;
   return (all - tall) * 3 <= tall && tall <= 2 * places && (tall + places - 1) / places < (all + places - 1) / places;
 }
+MOE_HOST_DEVICE inline bool may_open_a_round(int all, int shift) { return all <= 3 * (256 << shift); }   // spares larger launches the count: 4/3 of two rounds, at most
 MOE_HOST_DEVICE inline bool far_above_mean(int rows, int E, int all_rows) { return 2.0f * (float)rows * (float)E > 3.0f * (float)all_rows; }
 MOE_HOST_DEVICE inline int tall_row_tiles(int rows, int tile_rows, bool apart) { return (rows + (apart ? tile_rows / 2 : tile_rows) - 1) / tile_rows; }
 

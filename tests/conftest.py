@@ -41,7 +41,7 @@ int tile_at(int b, int E, const int* rows, int tile_rows, int NT, int shift, int
     all_tiles += moe::tall_row_tiles(rows[e], tile_rows, false) * NT;
     without += moe::tall_row_tiles(rows[e], tile_rows, true) * NT;
   }
-  bool apart = moe::opens_a_round(without, all_tiles, shift);
+  bool apart = moe::may_open_a_round(all_tiles, shift) && moe::opens_a_round(without, all_tiles, shift);
   for (int e = 0; e < E; ++e) apart = apart || moe::far_above_mean(rows[e], E, all_rows);
   apart = apart && shorts_last;
   for (int e = 0; e < E; ++e) {
