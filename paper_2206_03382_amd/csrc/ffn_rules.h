@@ -89,16 +89,21 @@ MOE_HOST_DEVICE inline TileSpot tile_spot(int b, int tall, int shorts, int round
 // Which tile block b of a weight-gradient launch (kTN) works on, E experts of MT x NT tiles each; false where there is none for it.
 // Hardware deals blocks round-robin: block b runs on XCD b % 8, as the b / 8-th of its tiles.  All experts have the same number of tiles, but a
 // tile of an expert with many rows takes several times that of one with few, so every XCD has to get its share of each expert: whole groups of an
-// expert's tiles (32 when the launch has several rounds of tiles for every compute unit; fewer when it has not, so that they still spread evenly) are dealt
+// expert's tiles (32 from 1024 tiles on, 16 below, so that they still spread evenly) are dealt
 // to the XCDs in turn, then whole tails (what an expert has beyond its groups), and only the groups and tails of the
 // last rounds, fewer than eight, are cut into 8 runs of equal length (to a tile).  Runs of an eighth of all tiles gave
 // the experts with many rows to one XCD.  Imbalanced gate (Zipf), two products of 8 experts, 8192 tokens, 2048 x 2048: 218 us in groups throughout,
 // 417 in eighths, 215 so (training step 800, 986 and 761); 64 experts, 16384 tokens, 1024 x 1024: step 415, 475 and 397.  Even gate, 17 experts x
 // 353 rows, 776 x 1544: 81 us in groups throughout, 79 with the tails in eighths, 75 so.
+// A launch of one tile to a unit is as long as its slowest tile however it is dealt, and is cut in eighths throughout.  Groups of 8 below 512 tiles
+// seldom share a panel: 4 experts, 32895 tokens, 2048 x 768 (384 tiles) step 1186 us, 1169 with 16, 1164 in eighths; imbalanced, 16384, 1024 x 1536
+// 355, 347 and 376; 256 tiles, 8192, 1024 x 1024 265 in groups of 8, 258 in eighths.
 // No prefix sums over the experts, either, which every tile of a short reduction would pay for.
 MOE_HOST_DEVICE inline bool equal_tile(int b, int E, int MT, int NT, TileAt& at) {
-  const int n = MT * NT, gs = E * n >= 1024 ? 5 : (E * n >= 512 ? 4 : 3), x = b % 8, i = b / 8;
-  const int own = n >> gs, tail = n - (own << gs), rounds = (E * own) >> 3, dealt = rounds << gs, tails = (E >> 3) * tail;   // an XCD's
+  const int n = MT * NT, gs = E * n >= 1024 ? 5 : 4, x = b % 8, i = b / 8;
+  const bool deal = E * n > 256;
+  const int own = deal ? n >> gs : 0, tail = n - (own << gs), whole = deal ? E >> 3 : 0;        // an expert's groups and what is beyond; rounds of tails
+  const int rounds = (E * own) >> 3, dealt = rounds << gs, tails = whole * tail;                // an XCD's
   int e, q;
   if (i < dealt) {
     const int g = (i >> gs) * 8 + x;
@@ -109,11 +114,11 @@ MOE_HOST_DEVICE inline bool equal_tile(int b, int E, int MT, int NT, TileAt& at)
     e = r * 8 + x;
     q = (own << gs) + j - r * tail;
   } else {
-    const int rest = E * n - 8 * (dealt + tails), t = x * rest / 8 + i - dealt - tails, of_tails = (E & 7) * tail;
+    const int rest = E * n - 8 * (dealt + tails), t = x * rest / 8 + i - dealt - tails, of_tails = (E - 8 * whole) * tail;
     if (t >= (x + 1) * rest / 8) return false;
     if (t < of_tails) {
       const int r = t / tail;
-      e = (E & ~7) + r;
+      e = 8 * whole + r;
       q = (own << gs) + t - r * tail;
     } else {
       const int g = 8 * rounds + ((t - of_tails) >> gs);
