@@ -12,7 +12,7 @@
 //
 // What bounds it is the way from L2 into LDS: 24 KB per 128 x 256 x 32 products, half as much again as the large tile, so that
 // tile stays the faster where its rounds are full (8 experts x 2048 rows, 2048 x 2048, two products: 239 us there, 268 here), and this one is
-// where they are not (8 x 1100: 181 and 165; 32 x 784, 768 x 3072: 327 and 315).
+// where they are not (8 x 1100: 181 and 165; 32 x 784, 768 x 3072: 327 and 315; numbered in groups throughout).
 //
 // LDS layouts: A [rows][4 pieces of 8 k], piece g of row r at g ^ (-(r / 4) % 4): the lanes that share a cycle of a
 // ds_read_b128 (0-3, 12-15, 20-27 and so on) then cover all 64 banks; with g ^ (r / 4 % 4) two of them meet in every bank.  B

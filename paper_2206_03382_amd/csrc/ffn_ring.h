@@ -15,7 +15,7 @@
 // from L2.  Against 128 x 128 as 32 x 32 x 16 instructions on two stages of both operands, product by product (62 to 68 shapes each off and on
 // the large tile's grid, 3e8 to 1.5e11 flop): forward 0.94 of the time, with kept pre-activations 0.95, B transposed 0.92, with the act'
 // epilogue 0.87 and 0.82, weight gradients of slabs 0.99, gathered 0.92 (slowest 1.10: 125 experts x 76 rows, 512 x 768).  Whole training
-// steps: 87913 tokens, 4 experts, 512 x 512 2735 -> 2408 us, 17 x 353 rows, 776 x 1544 309 -> 304.
+// steps: 87913 tokens, 4 experts, 512 x 512 2735 -> 2408 us, 17 x 353 rows, 776 x 1544 309 -> 304 on one board.
 //
 // LDS layouts: a k-contiguous operand as in the large tile.  A k-slow operand of width W is [64 k][W / 8 pieces]; a transposing
 // read takes 32 bytes of each of 4 k rows, and two of its 16-lane blocks, 8 k apart, share a cycle.  Their eight pieces of 32

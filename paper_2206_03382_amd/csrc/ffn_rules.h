@@ -166,12 +166,14 @@ static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M,
 // Which tile a bf16 launch takes: the one with the least estimated time among those it may run on (tile_of), in microseconds
 //   base + fix * rounds + ksteps * max(lat * rounds, thr * tiles per unit),    rounds = tiles per unit / blocks per unit
 // but for few rows of large weights (streamed tiles, below).  The shapes differ in how much of the chip a launch of few tiles uses, how finely
-// its work divides among the 256 compute units, and how fast a full unit runs: 256 x 256 (one block per unit) is 1.2-1.3 times as
-// fast as 128 x 128 (two) and 1.7-1.9 times as fast as 64 x 64 (three) once every unit has several tiles, and the slowest by up to
+// its work divides among the 256 compute units, and how fast a full unit runs: 256 x 256 (one block per unit) was 1.2-1.3 times as
+// fast as 128 x 128 (two) with the kernel that the constants were fitted on, and is 1.7-1.9 times as fast as 64 x 64 (three) once every unit has several tiles, and the slowest by up to
 // 3 times where it leaves most units idle.  128 x 256 (kHalf, two blocks, ffn_half.h) costs more per product than 256 x 256 and less per tile.
 //
-// The constants were fitted to launches by themselves.  With the kernels as they are, over launches drawn from 4-128 experts, 50-4200
-// rows each, K and N 256-4096, the choice is off the best tile by, on average: 3.2 % in 315 forward products (gathered with GELU, and
+// The constants were fitted to launches by themselves, with a 128 x 128 kernel of 32 x 32 x 16 instructions (the present one takes 0.82 to 0.99 of
+// its time, by layout: ffn_ring.h) and tiles numbered in groups throughout, and so are all distances and times of this comment: with
+// the kernels as they are they have not been taken again.  Over launches drawn from 4-128 experts, 50-4200
+// rows each, K and N 256-4096, the choice was off the best tile by, on average: 3.2 % in 315 forward products (gathered with GELU, and
 // plain; 34 % for always the large tile), 4.1 % in 75 that keep their pre-activations (43 %), 2.8 and 5.3 % in 85 with B transposed, plain
 // and times act' (24, 30 %), 2.5 % in 205 weight gradients of slabs (28 %), 0.9 % in 205 gathered ones (9 %).  Products that follow each
 // other run at the board's power limit and take 1.2-1.7 times the estimate on the large tile; the choice holds in whole layers all the same.
@@ -213,8 +215,7 @@ static inline double tile_cost(Tile tile, int mode, int64_t E, int64_t rows, dou
     return base + fix * rounds + ksteps * (lat * rounds > thr * q ? lat * rounds : thr * q);
   };
   switch (tile) {
-    // kTN: with the launch that pads its last K-step, and, where its rows are gathered, less against the 128 x 128 tile, whose K-step
-    // fetches row numbers in front of every load
+    // kTN: with the launch that pads its last K-step, and, where its rows are gathered, less (see above)
     case Tile::k256: return cost(256, 256, 1, mode == kTN ? 10.0 : 1.0, 9.0, 0.0, mode == kTN && gathered ? 0.98 : 1.1);
     case Tile::kHalf: return cost(128, 256, 2, 2.0, 3.0, 1.2, 0.8);
     case Tile::k64x128: return cost(64, 128, 2, 2.5, 2.5, 0.3, 0.44);

@@ -16,8 +16,8 @@
 // among the units.
 //
 // What it replaced was an fp32 FMA kernel on operands transposed and padded in memory, at 12 TFLOP/s in either type.
-// Measured, training step of 17 experts x 353 rows, M = 776, H = 1544, bf16: the six products 645-700 us -> 35-57 us each,
-// step 5060 -> 304 us with all its other kernels.  8 experts x 1024 rows, M = 512, H = 1024, fp32: products 166-228 us -> 72-95 us
+// Measured, training step of 17 experts x 353 rows, M = 776, H = 1544, bf16: the six products 645-700 us -> 35-57 us each
+// (33-43 on the 128 x 128 tile of ffn_ring.h, which takes them now), step 5060 -> 340 us.  8 experts x 1024 rows, M = 512, H = 1024, fp32: products 166-228 us -> 72-95 us
 // (117 TFLOP/s in the weight gradients; fp32 matrix peak 157), step 1585 -> 603 us.  8 experts x 4 rows, M = H = 2048, bf16: 29 us
 // on the large tile -> 13 us (67 MB of weights: 5.1 TB/s), layer 121 -> 51 us.
 
