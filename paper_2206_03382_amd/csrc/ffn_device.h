@@ -58,9 +58,9 @@ __device__ __forceinline__ int live_rows_of(int e, int64_t C, const int32_t* __r
 // An expert's live tiles are its row tiles below the fill x all column tiles; how they are numbered and dealt to the XCDs: ffn_rules.h.  Every wave
 // finds its tile by prefix sums over the experts, 64 to a step; no host has to know the fills.
 // SHIFT: log2 of the blocks that share a unit, where groups are to hold as many more tiles.  SHORTS: short row tiles may come last.
-template <int TILE_ROWS, int SHIFT, bool SHORTS, int CHUNKS>
+template <int TILE_ROWS, int SHIFT, bool SHORTS, bool CUTS, int CHUNKS>
 __device__ __forceinline__ bool search_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
-                                            int& e_out, int& mt_out, int& nt_out, int& rows_out) {
+                                            int& e_out, int& mt_out, int& nt_out, int& rows_out, TileHalf& half) {
   int rowsv[CHUNKS], upto[CHUNKS], groups[CHUNKS];                  // lane l of chunk c: rows of expert 64 c + l; tall tiles, full groups of them up to it
   unsigned long long shortv[CHUNKS];                                // experts with a short row tile
 #pragma unroll
@@ -118,6 +118,8 @@ __device__ __forceinline__ bool search_tile(int b, int lane, int E, int64_t C, c
     }
     rounds = full >> 3;
   }
+  half = {-1, -1};
+  if (CUTS && __builtin_expect(may_be_cut(b, gridDim.x, tall + shorts), 0) && !cut_tile(b, gridDim.x, tall, shorts, half)) return false;
   const TileSpot s = tile_spot(b, tall, shorts, rounds, gs);
   if (s.part == kNoTile) return false;
   int seen = 0;                                                     // short row tiles of earlier chunks
@@ -154,9 +156,9 @@ __device__ __forceinline__ bool search_tile(int b, int lane, int E, int64_t C, c
 // EQUAL: every expert has all of its C rows (weight gradients), see equal_tile.  Up to 64 experts, and up to 128, have code of their own, nearly one
 // straight piece: what a launch of few tiles pays for is fetching it (decode step of 16 tokens 47.8 -> 46.9 us; second product of 128 experts x 8192 rows, 264
 // tiles to a unit, 8150 -> 8080).
-template <int TILE_ROWS, bool EQUAL = false, int SHIFT = 0, bool SHORTS = false>
+template <int TILE_ROWS, bool EQUAL = false, int SHIFT = 0, bool SHORTS = false, bool CUTS = false>
 __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
-                                          int& e_out, int& mt_out, int& nt_out, int& rows_out) {
+                                          int& e_out, int& mt_out, int& nt_out, int& rows_out, TileHalf& half) {
   if (EQUAL) {
     TileAt at;
     if (!equal_tile(b, E, (int)((C + TILE_ROWS - 1) / TILE_ROWS), NT, at)) return false;
@@ -164,11 +166,19 @@ __device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, con
     mt_out = at.mt;
     nt_out = at.nt;
     rows_out = (int)C;
+    half = {-1, -1};
     return true;
   }
-  if (E <= 64) return search_tile<TILE_ROWS, SHIFT, SHORTS, 1>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out);
-  if (E <= 128) return search_tile<TILE_ROWS, SHIFT, SHORTS, 2>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out);
-  return search_tile<TILE_ROWS, SHIFT, SHORTS, kMaxExperts / 64>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out);
+  if (E <= 64) return search_tile<TILE_ROWS, SHIFT, SHORTS, CUTS, 1>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out, half);
+  if (E <= 128) return search_tile<TILE_ROWS, SHIFT, SHORTS, CUTS, 2>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out, half);
+  return search_tile<TILE_ROWS, SHIFT, SHORTS, CUTS, kMaxExperts / 64>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out, half);
+}
+
+template <int TILE_ROWS, bool EQUAL = false, int SHIFT = 0, bool SHORTS = false>
+__device__ __forceinline__ bool find_tile(int b, int lane, int E, int64_t C, const int32_t* __restrict__ counts, int NT,
+                                          int& e_out, int& mt_out, int& nt_out, int& rows_out) {
+  TileHalf half;
+  return find_tile<TILE_ROWS, EQUAL, SHIFT, SHORTS>(b, lane, E, C, counts, NT, e_out, mt_out, nt_out, rows_out, half);
 }
 
 struct TileArgs {

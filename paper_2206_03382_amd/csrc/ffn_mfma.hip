@@ -134,6 +134,7 @@ struct Frags {
 #include "ffn_ring.h"
 #include "ffn_tile.h"
 #include "ffn_half.h"
+#include "ffn_piece.h"
 
 
 // ---- main loop -------------------------------------------------------------------------------------------------
@@ -378,7 +379,8 @@ __device__ __forceinline__ void tile_main_loop(char* smem, const char* a_base, c
 // GK (kTN only): A's k-rows (slots) are gathered through `gather` [E, K] from the matrix A [gather_rows, C] (the token
 // matrix, for the first layer's weight gradient when the dispatch buffer was never written).
 // FAR (with a gathered A only): see tile_main_loop.
-template <int ACT, int MODE, bool GRAD, bool DUAL = false, bool GK = false, bool FAR = false>
+// CUT (not kTN, not FAR): the tiles of the last round may be cut, see cut_tile in ffn_rules.h.
+template <int ACT, int MODE, bool GRAD, bool DUAL = false, bool GK = false, bool FAR = false, bool CUT = false>
 __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint16_t* __restrict__ A,
                                                                      const uint16_t* __restrict__ B,
                                                                      const uint16_t* __restrict__ bias,
@@ -395,11 +397,36 @@ __global__ __launch_bounds__(kThreads) void grouped_gemm_mfma_kernel(const uint1
 
   const int lane = threadIdx.x & 63;
   int e, mt, nt, rows_e;
-  if (!find_tile<BM, MODE == kTN, 0, MODE != kTN>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e)) return;
+  TileHalf half;
+  if (!find_tile<BM, MODE == kTN, 0, MODE != kTN, CUT>(blockIdx.x, lane, E, C, counts, NT, e, mt, nt, rows_e, half)) return;
   const int64_t rows = rows_e;                                      // already here from the search: no second trip to memory
   const int64_t m0 = (int64_t)mt * BM;
   if (m0 >= rows) return;                                           // cannot happen (mt < mte); keeps every access in the slab
   const int n0 = nt * BN;
+
+  if (CUT && half.col >= 0) {
+    const bool tall = rows - m0 > 128;
+    if (half.row == 1 && !tall) return;                            // a short tile has no lower half
+    Piece p;
+    p.m0 = m0 + (half.row == 1 ? 128 : 0);
+    p.A = gather ? A : A + (int64_t)e * C * K;
+    p.B = B + (int64_t)e * K * N;
+    p.n0 = n0 + half.col * 128;
+    p.bias = bias ? bias + (int64_t)e * N + p.n0 : nullptr;
+    p.gather = gather ? gather + (int64_t)e * C + p.m0 : nullptr;
+    p.gather_rows = gather_rows;
+    p.rows = (int)(rows - p.m0 < 256 ? rows - p.m0 : 256);
+    p.K = K;
+    p.N = N;
+    p.out = ((int64_t)e * C + p.m0) * N + p.n0;
+    if (half.row < 0 && tall) {
+      run_piece<256, 128, 3, ACT, MODE, GRAD, DUAL>(smem, p, out, pre, pre_out);
+    } else {
+      p.rows = p.rows < 128 ? p.rows : 128;
+      run_piece<128, 128, 5, ACT, MODE, GRAD, DUAL>(smem, p, out, pre, pre_out);
+    }
+    return;
+  }
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
@@ -599,14 +626,15 @@ __global__ __launch_bounds__(256) void tail_rows_kernel(const TailRows a, const 
 // `half`: on the half tile; `total`: rows of all experts that exist, at most.
 static hipError_t launch_large_nn(const void* A, const void* B, const void* bias, int act, const int32_t* counts,
                                   int64_t E, int64_t C, int64_t K, int64_t N, void* out, hipStream_t s, bool half, int64_t total,
-                                  const int32_t* gather, int64_t gather_rows, void* pre_out) {
+                                  int64_t rows_hint, const int32_t* gather, int64_t gather_rows, void* pre_out) {
   const int64_t bm = half ? BM / 2 : BM;
   const int MT = (int)ceil_div(C, bm), NT = (int)(N / BN);
-  const int64_t blocks = tile_grid(NT, live_row_tiles(E, C, total, bm), true);
+  const bool cut = !half && !far_rows(gather_rows, K) && cuts_last_round(E, C, mean_or(rows_hint, C), counts, NT);
+  const int64_t blocks = tile_grid(NT, live_row_tiles(E, C, total, bm), true, cut);
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
-#define MOE_LAUNCH_GEMM_AT(ACT, DUAL, FAR)                                                                            \
-  grouped_gemm_mfma_kernel<ACT, kNN, false, DUAL, false, FAR><<<grid, block, 0, s>>>(                                 \
+#define MOE_LAUNCH_GEMM_AT(ACT, DUAL, FAR, CUT)                                                                       \
+  grouped_gemm_mfma_kernel<ACT, kNN, false, DUAL, false, FAR, CUT><<<grid, block, 0, s>>>(                                 \
       (const uint16_t*)A, (const uint16_t*)B, (const uint16_t*)bias, counts, gather, (int)gather_rows, (int)E, C,     \
       (int)K, (int)N, MT, NT, (uint16_t*)out, nullptr, nullptr, nullptr, nullptr,                                       \
       (uint16_t*)pre_out)
@@ -615,8 +643,9 @@ static hipError_t launch_large_nn(const void* A, const void* B, const void* bias
     if (half)                                                                                                         \
       grouped_gemm_half_kernel<ACT><<<grid, block, 0, s>>>((const uint16_t*)A, (const uint16_t*)B, (const uint16_t*)bias, \
                                                            counts, gather, (int)gather_rows, (int)E, C, (int)K, (int)N, MT, NT, (uint16_t*)out); \
-    else if (far_rows(gather_rows, K)) MOE_LAUNCH_GEMM_AT(ACT, DUAL, true);                                            \
-    else MOE_LAUNCH_GEMM_AT(ACT, DUAL, false);                                                                        \
+    else if (far_rows(gather_rows, K)) MOE_LAUNCH_GEMM_AT(ACT, DUAL, true, false);                                     \
+    else if (cut) MOE_LAUNCH_GEMM_AT(ACT, DUAL, false, true);                                                         \
+    else MOE_LAUNCH_GEMM_AT(ACT, DUAL, false, false);                                                                 \
   } while (0)
   if (pre_out && act >= 0) {
     switch (act) {
@@ -640,15 +669,21 @@ static hipError_t launch_large_nn(const void* A, const void* B, const void* bias
 // out[e] = A[e] (rows_e x K) * Bt[e]^T, Bt [E, N, K]; with `pre` [E, C, N] the result is multiplied by act'(pre), or,
 // with act < 0, has `pre` added (pre == out accumulates in place).
 static hipError_t launch_large_nt(const void* A, const void* Bt, const int32_t* counts, int64_t E, int64_t C,
-                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s, int64_t total) {
+                                  int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s, int64_t total, int64_t rows_hint) {
   const int MT = (int)ceil_div(C, BM), NT = (int)(N / BN);
-  const int64_t blocks = tile_grid(NT, live_row_tiles(E, C, total, BM), true);
+  const bool cut = cuts_last_round(E, C, mean_or(rows_hint, C), counts, NT);
+  const int64_t blocks = tile_grid(NT, live_row_tiles(E, C, total, BM), true, cut);
   if (blocks >= kMaxBlocks) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kThreads);
-#define MOE_LAUNCH_GEMM(ACT, GRAD)                                                                                    \
-  grouped_gemm_mfma_kernel<ACT, kNT, GRAD><<<grid, block, 0, s>>>(                                                    \
+#define MOE_LAUNCH_GEMM_AT(ACT, GRAD, CUT)                                                                            \
+  grouped_gemm_mfma_kernel<ACT, kNT, GRAD, false, false, false, CUT><<<grid, block, 0, s>>>(                          \
       (const uint16_t*)A, (const uint16_t*)Bt, nullptr, counts, nullptr, 0, (int)E, C, (int)K, (int)N, MT, NT,        \
       (uint16_t*)out, nullptr, nullptr, nullptr, (const uint16_t*)pre, nullptr)
+#define MOE_LAUNCH_GEMM(ACT, GRAD)                                                                                    \
+  do {                                                                                                                \
+    if (cut) MOE_LAUNCH_GEMM_AT(ACT, GRAD, true);                                                                     \
+    else MOE_LAUNCH_GEMM_AT(ACT, GRAD, false);                                                                        \
+  } while (0)
   if (!pre) MOE_LAUNCH_GEMM(-1, false);
   else if (act < 0) MOE_LAUNCH_GEMM(-1, true);                      // out = product + pre
   else switch (act) {
@@ -657,6 +692,7 @@ static hipError_t launch_large_nt(const void* A, const void* Bt, const int32_t* 
     default: MOE_LAUNCH_GEMM(MOE_ACT_SILU, true); break;
   }
 #undef MOE_LAUNCH_GEMM
+#undef MOE_LAUNCH_GEMM_AT
   return hipGetLastError();
 }
 
@@ -705,7 +741,7 @@ hipError_t launch_grouped_gemm(const void* A, const void* B, const void* bias, i
   const Tile tile = dtype == MOE_BF16 ? tile_of(kNN, E, C, K, N, rows_hint, gather ? gather_rows : 0, pre_out != nullptr) : Tile::k64;
   const int64_t total = total_rows(counts, E, C, rows_hint);
   if (tile == Tile::k256 || tile == Tile::kHalf)
-    return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, tile == Tile::kHalf, total, gather, gather_rows, pre_out);
+    return launch_large_nn(A, B, bias, act, counts, E, C, K, N, out, s, tile == Tile::kHalf, total, rows_hint, gather, gather_rows, pre_out);
   if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports(E, C, K, N, 0)) act += kFullAct;
   const TileArgs p = {A, B, bias, counts, gather, gather_rows, C, K, (int)N, (int)E, 0, 0, 0, out, nullptr, nullptr, pre_out, act, 0};
   return launch_small<kNN>(dtype, tile, p, total, s);
@@ -717,7 +753,7 @@ hipError_t launch_grouped_gemm_nt(const void* A, const void* Bt, int dtype, cons
                                   int64_t K, int64_t N, void* out, const void* pre, int act, hipStream_t s, int64_t rows_hint) {
   const Tile tile = dtype == MOE_BF16 ? tile_of(kNT, E, C, K, N, rows_hint, 0, false) : Tile::k64;
   const int64_t total = total_rows(counts, E, C, rows_hint);
-  if (tile == Tile::k256) return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s, total);
+  if (tile == Tile::k256) return launch_large_nt(A, Bt, counts, E, C, K, N, out, pre, act, s, total, rows_hint);
   if (dtype == MOE_BF16 && act > MOE_ACT_RELU && !large_tile_supports_backward(E, C, K, N)) act += kFullAct;
   const TileArgs p = {A, Bt, nullptr, counts, nullptr, 0, C, K, (int)N, (int)E, 0, 0, 0, out, nullptr, pre, nullptr, pre ? act : -1, 0};
   return launch_small<kNT>(dtype, tile, p, total, s);

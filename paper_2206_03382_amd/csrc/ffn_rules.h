@@ -86,6 +86,38 @@ MOE_HOST_DEVICE inline TileSpot tile_spot(int b, int tall, int shorts, int round
   return {at < (x + 1) * shorts / 8 ? kShortTile : kNoTile, at};
 }
 
+// On the large tile a launch's last round may be cut (forward and transposed-B products).  What an XCD has beyond whole rounds of its 32 units would
+// hold them all for a tile's time: up to 8 tiles go out as quarters of 128 x 128, up to 16 as halves of 256 x 128 columns (ffn_piece.h), which
+// end 0.25-0.45 and 0.65 of a tile's time later.  Two products of 8 experts, 2048 x 2048: 4096 rows and one expert of 4352 518 us whole, 481 cut; 7
+// of them 531 and 503 (nine to sixteen tiles: 4352 rows and one of 4608 531 in whole tiles, 514 in halves; 7 of those 536 and 529, 549 in quarters);
+// 1100 rows each 196 and 153; 4096 rows and one 4126, 492 and 481.  From 17 tiles on both forms take as long as the tiles themselves.
+// Blocks that find no tile cost a unit 0.38 us each, and after a partial round they run on the units that it leaves idle; after pieces none is idle.
+// So launches with more than 2048 of them (imbalanced gates) stay whole: 64 experts, 65536 tokens, Zipf, 1024 x 4096, 8200 blocks for 848 tiles 143 us, 147 cut.
+constexpr int kCutQuarters = 8, kCutHalves = 16, kCutSurplus = 2048;
+struct TileHalf { int row, col; };          // the half of a tile that a block computes, 0 or 1, or -1: both
+// Whether block b may have a part of a tile, in a launch of so many blocks: a test for nearly all of them to fail early.
+MOE_HOST_DEVICE inline bool may_be_cut(int b, int blocks, int tiles) { return b / 8 >= ((tiles / 8 - 1) & ~31) && blocks - tiles <= kCutSurplus; }
+// What it works on: turns b into the number of the block that would have the whole tile, of which it takes `half`; false where there is nothing for it.
+MOE_HOST_DEVICE inline bool cut_tile(int& b, int blocks, int tall, int shorts, TileHalf& half) {
+  const int x = b % 8, n = (x + 1) * tall / 8 - x * tall / 8 + (x + 1) * shorts / 8 - x * shorts / 8, over = n % 32, j = b / 8 - (n - over);
+  const bool quarters = over <= kCutQuarters;
+  const int parts = quarters ? 4 * over : 2 * over;
+  if (j < 0 || over > kCutHalves || n - over + parts > blocks / 8) return true;
+  if (j >= parts) return false;
+  const int low = quarters && j >= 2 * over, k = j - low * 2 * over;           // upper halves first: a short tile has no lower one
+  half = {quarters ? low : -1, k % 2};
+  b = (n - over + k / 2) * 8 + x;
+  return true;
+}
+// Whether a launch gets the kernel that can cut, and the blocks for it: by the tiles of an XCD if every expert has `rows` rows (up to) on average, give or
+// take a standard deviation of even choices.  One that has nothing to cut would pay 0.5-1 us for the longer kernel and the blocks (64 experts x 283 rows, 768 x 512:
+// second product 25.0 us, 25.9 so); beyond 16 rounds a part of the last one is no more than that either.
+static inline bool cuts_last_round(int64_t E, int64_t C, double rows, bool up_to, int64_t NT) {
+  const double off = up_to ? sqrt(rows) : 0.0, low = rows - off > 1.0 ? rows - off : 1.0, high = rows + off < (double)C ? rows + off : (double)C;
+  const double n = (double)(E * NT) * (ceil(low / kLargeTile) + ceil(high / kLargeTile)) / 16.0;
+  return n <= 512.0 && n - 32.0 * floor(n / 32.0) >= 0.5 && n - 32.0 * floor(n / 32.0) <= kCutHalves + 2.0;
+}
+
 // Which tile block b of a weight-gradient launch (kTN) works on, E experts of MT x NT tiles each; false where there is none for it.
 // Hardware deals blocks round-robin: block b runs on XCD b % 8, as the b / 8-th of its tiles.  All experts have the same number of tiles, but a
 // tile of an expert with many rows takes several times that of one with few, so every XCD has to get its share of each expert: whole groups of an
@@ -141,7 +173,9 @@ static inline int64_t live_row_tiles(int64_t E, int64_t C, int64_t total, int64_
 // The layer knows its total (every choice is one row).  Without it the grid has to hold C rows of every expert, and where the
 // capacity is far above the mean fill nearly all blocks find nothing to do, each after a tile search and holding its LDS: dynamic
 // capacity, buffers for all 2048 tokens, 128 experts, M = 4096, H = 1024: layer 746 us, 487 with the bound.
-static inline int64_t tile_grid(int64_t NT, int64_t row_tiles, bool shorts_last = false) { return (tiles_in(row_tiles * NT, 8) + (shorts_last ? 1 : 0)) * 8; }
+static inline int64_t tile_grid(int64_t NT, int64_t row_tiles, bool shorts_last = false, bool cuts = false) {
+  return (tiles_in(row_tiles * NT, 8) + (shorts_last ? 1 : 0) + (cuts ? 3 * kCutQuarters : 0)) * 8;
+}
 
 // Shapes the 256 x 256 tile takes in the forward layout; gather_rows > 0: A's rows are gathered from that many.
 static inline bool large_tile_supports(int64_t E, int64_t C, int64_t K, int64_t N, int64_t gather_rows) {
