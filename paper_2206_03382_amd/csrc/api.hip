@@ -3,6 +3,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "gate_rules.h"
 
 namespace moe {
 namespace {
@@ -31,7 +32,8 @@ inline int row_shape_status(int64_t M) {
 
 // The gating function from the tokens: logits, then decisions and slots.  bf16 gates take the fast logits kernel and
 // the top-k kernel's exact repair of near-ties; everything else the fp64 logits kernel.  Workspace: the arrival
-// counters, then (fast path) the transposed gate weights, their norms and the per-token error bounds.
+// counters, then (fast path) the transposed gate weights, their norms and the per-token error bounds.  staged: after_logits records an event
+// between the two, so they are launches of their own.
 bool gate_uses_fast_logits(int dtype, int64_t T, int64_t M, int64_t E) { return gate_logits_fast_supports(dtype, T, M, E); }
 
 size_t gate_route_workspace(int64_t T, int64_t M, int64_t E, int k, int dtype) {
@@ -43,7 +45,7 @@ size_t gate_route_workspace(int64_t T, int64_t M, int64_t E, int k, int dtype) {
 template <typename F>
 hipError_t run_gate(const void* x, const void* Wg, const float* bias, int dtype, int64_t T, int64_t M, int64_t E, int k, int64_t C,
                     int normalize, float* logits, int32_t* idx, float* gate_w, int32_t* loc, int32_t* counts, int32_t* slot_src,
-                    void* ws, hipStream_t s, F&& after_logits, bool mark_unfilled = true) {
+                    void* ws, hipStream_t s, F&& after_logits, bool mark_unfilled = true, bool staged = false) {
   int32_t* counters = (int32_t*)ws;
   if (gate_uses_fast_logits(dtype, T, M, E)) {
     const GateFastWorkspace f = gate_fast_layout((char*)ws + align_up(moe_gate_workspace_bytes(T, E, k), 256), T, M, E);
@@ -53,6 +55,8 @@ hipError_t run_gate(const void* x, const void* Wg, const float* bias, int dtype,
     const GateRepair repair = {f.margin, x, f.Wt, bias, M, f.Mp};
     return launch_gate_topk(logits, T, E, k, C, normalize, idx, gate_w, loc, counts, slot_src, counters, s, nullptr, &repair, mark_unfilled);
   }
+  if (!staged && gate_of_few_tokens(T, E, k, slot_src && mark_unfilled ? C : 0))
+    return launch_gate_few_tokens(x, Wg, bias, dtype, T, M, E, logits, k, C, normalize, idx, gate_w, loc, counts, slot_src, mark_unfilled, s);
   hipError_t err = launch_gate_logits(x, Wg, bias, dtype, T, M, E, logits, s);
   if (err != hipSuccess) return err;
   if (!after_logits()) return hipErrorUnknown;
@@ -442,7 +446,7 @@ int layer_forward(const void* x, const void* Wg, const float* gate_bias, const v
   auto mark = [&]() -> bool { return !stage_events || hipEventRecord((hipEvent_t)stage_events[stage++], s) == hipSuccess; };
 
   if (!mark()) return MOE_HIP_ERROR;
-  if (run_gate(x, Wg, gate_bias, dtype, T, M, E, k, C, normalize, d_logits, d_idx, d_gw, d_loc, d_counts, d_src, d_gws, s, mark) != hipSuccess ||
+  if (run_gate(x, Wg, gate_bias, dtype, T, M, E, k, C, normalize, d_logits, d_idx, d_gw, d_loc, d_counts, d_src, d_gws, s, mark, true, stage_events) != hipSuccess ||
       !mark())
     return MOE_HIP_ERROR;
   const int64_t mean = mean_fill(T, E, k);

@@ -63,15 +63,12 @@ template <typename XT, int N> struct RawN {
 // Measured against four waves on fp64 weights staged through LDS, in a captured graph with its launch: 512 tokens, M = 1024,
 // 64 experts, fp32 53 -> 17 us; 64 tokens, M = 4096, 64 experts 180 -> 20; 16384 tokens, M = 2048, 8 experts 41 -> 35.
 template <typename XT, int NT, int KS, int TW>
-__global__ __launch_bounds__(64 * KS) void gate_logits_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
-                                                              const float* __restrict__ bias, int64_t T, int M, int E,
-                                                              int e_base, float* __restrict__ logits) {
+__device__ __forceinline__ void logits_of_tiles(const XT* __restrict__ x, const XT* __restrict__ Wg, const float* __restrict__ bias, int64_t T, int M,
+                                                int E, int64_t t0, int e0, float* __restrict__ logits) {
   constexpr int PF = 2;
   __shared__ double red[KS - 1][TW * NT][4][64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, kq = lane >> 4;
-  const int64_t t0 = (int64_t)blockIdx.x * (16 * TW);
-  const int e0 = e_base + blockIdx.y * (16 * NT);
   const int passes = (M + 31) / 32, per = (passes + KS - 1) / KS;
   const int p0 = wave * per, p1 = p0 + per < passes ? p0 + per : passes;   // this wave's passes (possibly none)
   const XT* xrow[TW];
@@ -155,6 +152,13 @@ __global__ __launch_bounds__(64 * KS) void gate_logits_kernel(const XT* __restri
       }
     }
   }
+}
+
+template <typename XT, int NT, int KS, int TW>
+__global__ __launch_bounds__(64 * KS) void gate_logits_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
+                                                              const float* __restrict__ bias, int64_t T, int M, int E,
+                                                              int e_base, float* __restrict__ logits) {
+  logits_of_tiles<XT, NT, KS, TW>(x, Wg, bias, T, M, E, (int64_t)blockIdx.x * (16 * TW), e_base + blockIdx.y * (16 * NT), logits);
 }
 
 // Wide gates of many tokens (the cosine router's projection; the rule: gate_rules.h): a block's 2 x 2 waves own 32 tokens x 128 experts, a wave
@@ -890,11 +894,9 @@ __global__ __launch_bounds__(256) void gate_slots_kernel(const int32_t* __restri
 // among its wave's comes from ballots as in gate_assign_kernel.  Such a gate is launches that wait for each other, not work: captured,
 // top-k on: 16 tokens, 8 experts, top-2 6.1 -> 4.9 us; 512 tokens, 4 experts, top-1 5.4 -> 2.9; 1024 tokens 5.4 -> 3.3.
 template <int G>
-__global__ __launch_bounds__(kSmallGateTokens) void gate_small_kernel(const float* __restrict__ logits, int T, int E, int bits, int k, int64_t C,
-                                                                      int normalize, int32_t* __restrict__ idx, float* __restrict__ gate_w,
-                                                                      int32_t* __restrict__ loc, int32_t* __restrict__ counts,
-                                                                      int32_t* __restrict__ slot_src, int mark_unfilled,
-                                                                      const int32_t* __restrict__ perm) {
+__device__ __forceinline__ void decide_small_gate(const float* logits, int T, int E, int bits, int k, int64_t C, int normalize, int32_t* __restrict__ idx,
+                                                  float* __restrict__ gate_w, int32_t* __restrict__ loc, int32_t* __restrict__ counts,
+                                                  int32_t* __restrict__ slot_src, int mark_unfilled, const int32_t* __restrict__ perm) {
   constexpr int W = kSmallGateTokens / kWave;
   // pairs and choices that the rule lets in, with more than G / 2 experts
   constexpr int P = G * G < kSmallGatePairs ? G * G : kSmallGatePairs, R = kSmallGatePairs / (G / 2 + 1) < G ? kSmallGatePairs / (G / 2 + 1) : G;
@@ -986,6 +988,50 @@ __global__ __launch_bounds__(kSmallGateTokens) void gate_small_kernel(const floa
     if (mark_unfilled && slot_src)
       for (int64_t c = (n < C ? n : C) + lane; c < C; c += kWave) slot_src[(int64_t)e * C + c] = -1;
   }
+}
+
+template <int G>
+__global__ __launch_bounds__(kSmallGateTokens) void gate_small_kernel(const float* __restrict__ logits, int T, int E, int bits, int k, int64_t C,
+                                                                      int normalize, int32_t* __restrict__ idx, float* __restrict__ gate_w,
+                                                                      int32_t* __restrict__ loc, int32_t* __restrict__ counts,
+                                                                      int32_t* __restrict__ slot_src, int mark_unfilled,
+                                                                      const int32_t* __restrict__ perm) {
+  decide_small_gate<G>(logits, T, E, bits, k, C, normalize, idx, gate_w, loc, counts, slot_src, mark_unfilled, perm);
+}
+
+// The whole gate of up to 16 tokens (the rule: gate_rules.h): the one tile of logits_of_tiles and, in the same block, the decisions on it.  A decode step
+// is launches that wait for each other: logits 8.2 us and decisions 4.9 in two launches, 12.3 so by the profiler, and a launch less to wait for (16 tokens, 8 experts
+// 2048 x 2048, whole pass 47.4 -> 46.0; 256 x 256, 4 experts 19.0 -> 17.1).  What binds is one unit's fp64 matrix pipe (M / 4 instructions of 64
+// cycles over four of them) and two trips to memory; with four passes in flight instead of two 12.8.
+template <typename XT, int G>
+__global__ __launch_bounds__(64 * 16) void gate_few_tokens_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg, const float* __restrict__ bias, int T,
+                                                                  int M, int E, float* logits, int bits, int k, int64_t C, int normalize,
+                                                                  int32_t* __restrict__ idx, float* __restrict__ gate_w, int32_t* __restrict__ loc,
+                                                                  int32_t* __restrict__ counts, int32_t* __restrict__ slot_src, int mark_unfilled) {
+  logits_of_tiles<XT, 1, 16, 1>(x, Wg, bias, T, M, E, 0, 0, logits);
+  __syncthreads();
+  decide_small_gate<G>(logits, T, E, bits, k, C, normalize, idx, gate_w, loc, counts, slot_src, mark_unfilled, nullptr);
+}
+
+hipError_t launch_gate_few_tokens(const void* x, const void* Wg, const float* bias, int dtype, int64_t T, int64_t M, int64_t E, float* logits, int k,
+                                  int64_t C, int normalize, int32_t* idx, float* gate_w, int32_t* loc, int32_t* counts, int32_t* slot_src,
+                                  bool mark_unfilled, hipStream_t s) {
+  int bits = 0;
+  while ((1 << bits) < E) ++bits;
+#define MOE_FEW(XT, GG)                                                                                                                   \
+  gate_few_tokens_kernel<XT, GG><<<dim3(1), dim3(64 * 16), 0, s>>>((const XT*)x, (const XT*)Wg, bias, (int)T, (int)M, (int)E, logits, bits, k, C, \
+                                                                   normalize, idx, gate_w, loc, counts, slot_src, mark_unfilled)
+#define MOE_FEW_G(XT)                 \
+  do {                                \
+    if (E <= 4) MOE_FEW(XT, 4);       \
+    else if (E <= 8) MOE_FEW(XT, 8);  \
+    else MOE_FEW(XT, 16);             \
+  } while (0)
+  if (dtype == MOE_F32) MOE_FEW_G(float);
+  else MOE_FEW_G(uint16_t);
+#undef MOE_FEW_G
+#undef MOE_FEW
+  return hipGetLastError();
 }
 
 hipError_t launch_gate_topk(float* logits, int64_t T, int64_t E, int k, int64_t C, int normalize, int32_t* idx,

@@ -27,6 +27,13 @@ inline bool gate_in_one_block(int64_t T, int64_t E, int k, int64_t marked_C) {
   return T <= ((E & (E - 1)) == 0 ? kSmallGateTokens : 256) && E <= 16 && E * k <= kSmallGatePairs && E * marked_C <= 16 * kSmallGateTokens;
 }
 
+// Whether such a gate's logits are computed by that block as well (gate_few_tokens_kernel): where they are one tile of 16 tokens x 16 experts, which one block
+// computes anyhow.  (More tokens are more tiles, which as many units compute at once.)  One or two experts stay with two launches.
+constexpr int64_t kFewGateTokens = 16;
+inline bool gate_of_few_tokens(int64_t T, int64_t E, int k, int64_t marked_C) {
+  return T <= kFewGateTokens && E > 2 && gate_in_one_block(T, E, k, marked_C);
+}
+
 // Blocks of 64 tokens from which wide gates decide with one lane per token (M: length of the products that repair near-ties; 0: none are
 // repaired).  Below, a token's lane group spreads a block's work over more of the chip: 6000 tokens, 64 experts, top-4: 19 us against 23 (51 against 73
 // with repairs); 65536 tokens, top-2: 27 against 21.  At the line itself (32768 tokens) the two are alike for up to four choices (top-1 of
