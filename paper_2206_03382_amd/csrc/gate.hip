@@ -161,22 +161,31 @@ __global__ __launch_bounds__(64 * KS) void gate_logits_kernel(const XT* __restri
   logits_of_tiles<XT, NT, KS, TW>(x, Wg, bias, T, M, E, (int64_t)blockIdx.x * (16 * TW), e_base + blockIdx.y * (16 * NT), logits);
 }
 
-// Wide gates of many tokens (the cosine router's projection; the rule: gate_rules.h): a block's 2 x 2 waves own 32 tokens x 128 experts, a wave
-// 16 x 64 as four accumulator tiles.  Both operands go through LDS as fp32, 32 k at a time (the next 32 k are fetched to
-// registers meanwhile), and are widened on the way out: per 32 k a wave issues 32 matrix instructions of 64 cycles against
-// 34 LDS reads and 40 conversions, which hide behind them, and 21 KB of LDS let seven blocks share a unit and cover each
-// other's staging.  What binds is the fp64 matrix pipe.  Blocks are small because the count of blocks per unit is what
-// divides unevenly; all expert blocks go in one launch.  Replaced four waves of 16 tokens x 128 experts on fp64 weights in LDS,
-// one launch per 128 experts: 25088 tokens, M = 768, 256 columns
-// 275 -> 211 us (47 TFLOP/s; the fp64 matrix pipe alone sustains 67). Seven blocks per unit need 72 registers: at 96 the blocks past
-// the fifth of a unit run by themselves at the end, 229 us.
-// LDS rows: 36 floats per token (16 rows x 4 groups of a ds_read_b128 spread over all banks), 130 per k of the weights (the
+// Wide gates of many tokens (the cosine router's projection; the rule: gate_rules.h): a block's 2 x 2 waves own 32 tokens x 64 experts, a wave
+// 16 x 32 as two accumulator tiles.  Both operands go through LDS in 32 bits, 32 k at a time (the next 32 k are fetched to
+// registers meanwhile): fp32 values are widened on the way out; of bf16 values, widened on the way in, LDS holds the upper half of the fp64.  Per 32 k a
+// wave issues 16 matrix instructions of 64 cycles against 18 LDS reads, which hide behind them, and 13 KB of LDS let eight blocks share a unit and cover each
+// other's staging.  What binds is the fp64 matrix pipe and beside it the conversions.  Blocks are small because the count of blocks per unit is what
+// divides unevenly; all expert blocks go in one launch.  Replaced blocks of 128 experts, seven to a unit, both operands in fp32: 25088 tokens, M = 768, 256
+// columns 203 -> 186 us (53 TFLOP/s; the fp64 matrix pipe alone sustains 67), of which the conversions 3 us by the profiler; fp32, 65536 tokens, M = 2048, 128
+// experts 632 -> 598; 131072, M = 1024, 96 492 and 493.  (Those replaced four waves of 16 tokens x 128 experts on fp64 weights in LDS, 275 us.)
+// LDS rows: 36 values per token (16 rows x 4 groups of a ds_read_b128 spread over all banks), 66 per k of the weights (the
 // four k of an operand read lie 16 banks apart).
-constexpr int kWideTokens = 32, kWideExperts = 128, kWideK = 32, kWideLdx = 36, kWideLdw = 130;
+constexpr int kWideTokens = 32, kWideExperts = 64, kWideK = 32, kWideLdx = 36, kWideLdw = 66;
+
+// What LDS holds of an operand, in 32 bits: of a bf16 value widened to fp64 the upper half (the lower one is zero), else the fp32 value.
+template <typename XT> __device__ __forceinline__ float wide_store(float v) {
+  if constexpr (sizeof(XT) == 2) return __uint_as_float((uint32_t)(__builtin_bit_cast(uint64_t, (double)v) >> 32));
+  else return v;
+}
+template <typename XT> __device__ __forceinline__ double wide_load(float v) {
+  if constexpr (sizeof(XT) == 2) return __builtin_bit_cast(double, (uint64_t)__float_as_uint(v) << 32);
+  else return (double)v;
+}
 
 // E a multiple of 8 and Wg 16-byte aligned.
 template <typename XT>
-__global__ __launch_bounds__(256, sizeof(XT) == 2 ? 7 : 4) void gate_logits_wide_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
+__global__ __launch_bounds__(256, sizeof(XT) == 2 ? 8 : 6) void gate_logits_wide_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
                                                                const float* __restrict__ bias, int64_t T, int M, int E,
                                                                int expert_blocks, float* __restrict__ logits) {
   __shared__ __attribute__((aligned(16))) float xs[kWideTokens * kWideLdx];
@@ -186,53 +195,46 @@ __global__ __launch_bounds__(256, sizeof(XT) == 2 ? 7 : 4) void gate_logits_wide
   const int64_t t0 = (int64_t)(blockIdx.x / expert_blocks) * kWideTokens;       // the blocks that share tokens run together
   const int e0 = (int)(blockIdx.x % expert_blocks) * kWideExperts;
 
-  // staging: thread i brings 4 values of token i / 8 and 16 of k row i / 8
+  // staging: thread i brings 4 values of token i / 8 and 8 of k row i / 8
   const int srow = threadIdx.x >> 3, sp = threadIdx.x & 7;
   const int64_t st = t0 + srow < T ? t0 + srow : T - 1;
   const XT* xsrc = x + st * (int64_t)M + sp * 4;
-  const int we0 = e0 + sp * 16;                                     // first expert of this thread's 16
+  const int we0 = e0 + sp * 8;                                      // first expert of this thread's 8
   RawN<XT, 4> xr;
-  RawN<XT, 8> wr[2];
+  RawN<XT, 8> wr;
   auto fetch = [&](int k0) __attribute__((always_inline)) {          // M is a multiple of 8: four values are all inside or all outside
     const bool live = k0 + sp * 4 < M;
     xr.load_vec(live ? xsrc + k0 : xsrc - sp * 4);
     xr.keep_if(live);
     const bool wlive = k0 + srow < M;
     const XT* row = Wg + (int64_t)(wlive ? k0 + srow : 0) * E;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int e = we0 + 8 * h;
-      wr[h].load_vec(row + (e < E ? e : 0));
-      wr[h].keep_if(wlive && e < E);
-    }
+    wr.load_vec(row + (we0 < E ? we0 : 0));
+    wr.keep_if(wlive && we0 < E);
   };
-  f64x4 acc[4];
+  f64x4 acc[2];
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) acc[nt] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int nt = 0; nt < 2; ++nt) acc[nt] = f64x4{0.0, 0.0, 0.0, 0.0};
   fetch(0);
   for (int k0 = 0; k0 < M; k0 += kWideK) {
     __syncthreads();                                                // the previous chunk has been read
-    *reinterpret_cast<float4*>(&xs[srow * kWideLdx + sp * 4]) = make_float4(xr.get(0), xr.get(1), xr.get(2), xr.get(3));
+    *reinterpret_cast<float4*>(&xs[srow * kWideLdx + sp * 4]) = make_float4(wide_store<XT>(xr.get(0)), wide_store<XT>(xr.get(1)), wide_store<XT>(xr.get(2)), wide_store<XT>(xr.get(3)));
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int u = 0; u < 8; u += 2)
-        *reinterpret_cast<float2*>(&ws[srow * kWideLdw + sp * 16 + 8 * h + u]) = make_float2(wr[h].get(u), wr[h].get(u + 1));
+    for (int u = 0; u < 8; u += 2) *reinterpret_cast<float2*>(&ws[srow * kWideLdw + sp * 8 + u]) = make_float2(wide_store<XT>(wr.get(u)), wide_store<XT>(wr.get(u + 1)));
     __syncthreads();
     if (k0 + kWideK < M) fetch(k0 + kWideK);
     const float* xa = &xs[(wt * 16 + r) * kWideLdx + kq * 8];
     const float4 a0 = *reinterpret_cast<const float4*>(xa), a1 = *reinterpret_cast<const float4*>(xa + 4);
     const float av[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-    const float* wb = &ws[kq * 8 * kWideLdw + we * 64 + r];
+    const float* wb = &ws[kq * 8 * kWideLdw + we * 32 + r];
 #pragma unroll
     for (int s = 0; s < 8; ++s)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt)
-        acc[nt] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av[s], (double)wb[s * kWideLdw + nt * 16], acc[nt], 0, 0, 0);
+      for (int nt = 0; nt < 2; ++nt)
+        acc[nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(wide_load<XT>(av[s]), wide_load<XT>(wb[s * kWideLdw + nt * 16]), acc[nt], 0, 0, 0);
   }
 #pragma unroll
-  for (int nt = 0; nt < 4; ++nt) {
-    const int e = e0 + we * 64 + nt * 16 + r;
+  for (int nt = 0; nt < 2; ++nt) {
+    const int e = e0 + we * 32 + nt * 16 + r;
     if (e >= E) continue;
     const double be = bias ? (double)bias[e] : 0.0;
 #pragma unroll
@@ -252,7 +254,7 @@ static void launch_gate_logits_one(const XT* x, const XT* Wg, const float* bias,
 }
 
 // Tokens to a launch: a grid dimension holds fewer than 2^32 threads, 256 to every 16 tokens or, for wide gates, to every 32
-// tokens and 128 experts.
+// tokens and 64 experts.
 static int64_t gate_logits_tokens_per_launch(int64_t E) {
   const int64_t n = ((int64_t)1 << 27) / (E > 64 ? ceil_div(E, kWideExperts) : 1) / kWideTokens * kWideTokens;
   return n > kWideTokens ? n : kWideTokens;

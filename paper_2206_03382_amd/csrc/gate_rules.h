@@ -52,7 +52,8 @@ inline int64_t gate_lane_topk_blocks(int64_t E, int k, int64_t M) {
 }
 
 // Experts whose exact logits the wide kernel takes, in blocks of 128 (vecw: its 16-byte pieces of Wg's rows are whole); the narrow
-// kernel takes the others, 64 at a time.  Blocks of 128 fill badly with few tokens or with a remainder: fp32, M = 2048, narrow and
+// kernel takes the others, 64 at a time.  The line was drawn with blocks of 128 (they are 64 wide now, and 4 to 8 % faster where they run), which
+// fill badly with few tokens or with a remainder: fp32, M = 2048, narrow and
 // wide 4096 tokens, 128 experts 56 and 132 us, 16384 168 and 189, 65536 661 and 630; 12000, 512 502 and 484; 65536, 96 520 and 628;
 // 136 (128 + 8 against 256) 766 and 1210; 120 697 and 629.
 inline int64_t gate_logits_wide_experts(int64_t T, int64_t E, bool vecw) {
