@@ -109,13 +109,69 @@ MOE_HOST_DEVICE inline bool cut_tile(int& b, int blocks, int tall, int shorts, T
   b = (n - over + k / 2) * 8 + x;
   return true;
 }
+// The units of an XCD by when they are free, in twentieths of a whole tile's time.
+struct UnitsFree {
+  int at[512] = {32}, now = 0, last = 0;
+  void take(int n, int time) {                                      // so many tiles or parts, each on the first unit that is free
+    while (n > 0) {
+      while (at[now] == 0) ++now;
+      const int m = n < at[now] ? n : at[now];
+      at[now] -= m;
+      at[now + time] += m;
+      if (now + time > last) last = now + time;
+      n -= m;
+    }
+  }
+};
+// Whether cut tiles end clearly later than whole ones where every expert's last row tile holds up to 32 rows.  Such a tile takes less than half of a whole one's time, and
+// its unit goes on to the next: the whole tiles beyond the full rounds may start long before these end, and their halves, one behind the other on
+// the few units that are free early, end later than they would; and halves of such a tile, which both load the rows, take longer than it does.  With a
+// multiple of 8 experts every XCD has the same sequence of tiles (apart: the short ones last); this walks it both ways, with what 1300 launches took.  Products whole
+// and cut: 16 experts x 516 rows, K = 1536, N = 2048 64.1 and 75.1 us; 8 x 516, 2048 x 3840 80.0 and 89.3; 8 x 1028, 1024 x 4096 92.5 and 100.3; but 32 x 544, 1536 x 1024 82.8 and 70.2.
+// Over those launches cutting all is 1.0 % off the better form on average (19 % at most), cutting none 3 %, this 0.4 % (7 % at most where it cuts, 9 % where it does not).
+static inline bool cut_short_tiles_end_later(int experts, int row_tiles, int NT, bool apart) {
+  constexpr int kTall = 20, kShort = 8, kTallPart[2] = {10, 13}, kShortPart[2] = {6, 11};   // parts: quarters, halves
+  const int n = experts * row_tiles * NT, over = n % 32, halves = over > kCutQuarters;
+  UnitsFree whole;
+  int rest[2 * kCutHalves], runs = 0, done = 0;                     // runs of tiles beyond the full rounds, tall and short in turn
+  auto run = [&](int of, bool tall) {
+    const int full = n - over - done, early = full > of ? of : (full > 0 ? full : 0);
+    done += of;
+    whole.take(early, tall ? kTall : kShort);
+    if (of == early) return;
+    if ((runs % 2 == 0) != tall) rest[runs++] = 0;
+    rest[runs++] = of - early;
+  };
+  if (apart) {
+    run(experts * NT * (row_tiles - 1), true);
+    run(experts * NT, false);
+  } else {
+    for (int e = 0; e < experts; ++e)
+      for (int c = 0; c < NT; c += 8) {
+        const int w = NT - c < 8 ? NT - c : 8;
+        run(w * (row_tiles - 1), true);
+        run(w, false);
+      }
+  }
+  UnitsFree cut = whole;
+  for (int r = 0; r < runs; ++r) {
+    whole.take(rest[r], r % 2 == 0 ? kTall : kShort);
+    cut.take(2 * rest[r], r % 2 == 0 ? kTallPart[halves] : kShortPart[halves]);
+  }
+  for (int r = 0; r < runs && !halves; r += 2) cut.take(2 * rest[r], kTallPart[0]);        // lower halves, which short tiles do not have
+  return 20 * cut.last >= 21 * whole.last;
+}
 // Whether a launch gets the kernel that can cut, and the blocks for it: by the tiles of an XCD if every expert has `rows` rows (up to) on average, give or
 // take a standard deviation of even choices.  One that has nothing to cut would pay 0.5-1 us for the longer kernel and the blocks (64 experts x 283 rows, 768 x 512:
 // second product 25.0 us, 25.9 so); beyond 16 rounds a part of the last one is no more than that either.
 static inline bool cuts_last_round(int64_t E, int64_t C, double rows, bool up_to, int64_t NT) {
   const double off = up_to ? sqrt(rows) : 0.0, low = rows - off > 1.0 ? rows - off : 1.0, high = rows + off < (double)C ? rows + off : (double)C;
   const double n = (double)(E * NT) * (ceil(low / kLargeTile) + ceil(high / kLargeTile)) / 16.0;
-  return n <= 512.0 && n - 32.0 * floor(n / 32.0) >= 0.5 && n - 32.0 * floor(n / 32.0) <= kCutHalves + 2.0;
+  if (!(n <= 512.0 && n - 32.0 * floor(n / 32.0) >= 0.5 && n - 32.0 * floor(n / 32.0) <= kCutHalves + 2.0)) return false;
+  if (up_to || E % 8 != 0 || C <= kLargeTile || C % kLargeTile == 0 || C % kLargeTile > 32 || (int)n % 32 > kCutHalves) return true;
+  const int row_tiles = (int)tiles_in(C, kLargeTile), all = (int)(E * NT) * row_tiles, tall = all - (int)(E * NT);
+  if (deals_groups(all, (int)E, (int)NT, 0)) return true;           // another sequence
+  return !cut_short_tiles_end_later((int)(E / 8), row_tiles, (int)NT, may_open_a_round(all, 0) && opens_a_round(tall, all, 0));
 }
 
 // Which tile block b of a weight-gradient launch (kTN) works on, E experts of MT x NT tiles each; false where there is none for it.

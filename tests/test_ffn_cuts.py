@@ -1,5 +1,7 @@
 """The parts of tiles that the large tile's last round is cut into (cut_tile in csrc/ffn_rules.h, csrc/ffn_piece.h)."""
 import ctypes
+import heapq
+import itertools
 import os
 import subprocess
 
@@ -63,6 +65,44 @@ def test_launches_that_cut(rules):
         assert rules.cuts(E, C, rows, up_to, NT), (E, C, rows)
     for E, C, rows, up_to, NT in ((8, 4096, 4096, 0, 8), (64, 283, 283, 1, 2), (64, 2048, 2048, 1, 16), (128, 16384, 8192, 1, 16), (8, 1600, 1500, 1, 8)):
         assert not rules.cuts(E, C, rows, up_to, NT), (E, C, rows)
+
+
+def cut_ends_later(E, rows, NT, apart):
+    """An XCD's tiles in turn on 32 units, by a heap of the times at which these are free, whole and with the last, partial round in parts."""
+    heights = -(-rows // 256)
+    tall = ([True] * (E // 8 * NT * (heights - 1)) + [False] * (E // 8 * NT) if apart else
+            [kind for _ in range(E // 8) for c in range(0, NT, 8) for kind, n in ((True, heights - 1), (False, 1)) for _ in range(n * min(8, NT - c))])
+    over = len(tall) % 32
+    def end(tasks):
+        units = [0] * 32
+        for t in tasks:
+            heapq.heapreplace(units, units[0] + t)
+        return max(units)
+    first, rest = [20 if t else 8 for t in tall[:len(tall) - over]], tall[len(tall) - over:]
+    if over > 8:
+        parts = [13 if t else 11 for t in rest for _ in range(2)]
+    else:
+        parts = [10 if t else 6 for t in rest for _ in range(2)] + [10 for t in rest if t for _ in range(2)]
+    return 20 * end(first + parts) >= 21 * end(first + [20 if t else 8 for t in rest])
+
+
+def test_whole_tiles_where_short_ones_make_room(rules):
+    """Every expert full, its last row tile of a few rows: products that took up to 1.17 times as long cut as whole stay whole, those that cutting makes faster
+    are cut; everywhere as a plain walk over the tiles has it."""
+    for E, rows, NT in ((16, 516, 8), (24, 516, 5), (8, 516, 15), (8, 528, 16), (8, 1028, 16), (16, 1027, 8), (8, 1537, 16)):
+        assert not rules.cuts(E, rows, rows, 0, NT), (E, rows, NT)
+    for E, rows, NT in ((32, 544, 4), (16, 272, 10), (24, 800, 3), (40, 784, 2), (32, 528, 3), (8, 612, 16), (8, 1152, 8), (12, 516, 8)):
+        assert rules.cuts(E, rows, rows, 0, NT), (E, rows, NT)
+    seen = set()
+    for E, heights, NT in itertools.product((8, 16, 24, 40, 64), range(2, 14), range(1, 19)):
+        n, tall = E * heights * NT // 8, E * (heights - 1) * NT
+        if not 1 <= n % 32 <= 16 or n > 512 or (8 * n >= 1024 and heights >= 4):      # those deal whole groups, cut as they are
+            continue
+        apart = E * heights * NT <= 768 and 3 * E * NT <= tall <= 512 and -(-tall // 256) < -(-E * heights * NT // 256)
+        for rows in (256 * heights - 255, 256 * heights - 224):
+            assert rules.cuts(E, rows, rows, 0, NT) != cut_ends_later(E, rows, NT, apart), (E, rows, NT)
+        seen.add((apart, n % 32 > 8, rules.cuts(E, rows, rows, 0, NT)))
+    assert len(seen) >= 7
 
 
 FILLS = {                                              # row tiles x 6 column tiles over 8 XCDs: tiles of an XCD
