@@ -78,6 +78,7 @@ int tile_keeping_pre(int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hi
 double tile_cost(int tile, int mode, int64_t E, int64_t C, int64_t K, int64_t N, int64_t rows_hint, int64_t gather_rows) {
   return moe::tile_cost((moe::Tile)tile, mode, E, C, moe::mean_or(rows_hint, mode == moe::kTN ? K : C), K, N, gather_rows > 0);
 }
+int cuts(int64_t E, int64_t C, double rows, int up_to, int64_t NT) { return moe::cuts_last_round(E, C, rows, up_to, NT); }
 int colsum_streams(int64_t E, double rows, int64_t b1, int64_t b2) { return moe::colsum_streams(E, rows, b1, b2); }
 int split(int64_t E, int64_t C, int64_t K, int64_t N) { return moe::fp32_split(E, C, K, N); }
 int dx_tokens(int64_t T, int64_t row_bytes) { return moe::gate_dx_tokens(T, row_bytes); }
@@ -93,7 +94,7 @@ int one_launch(int64_t T, int64_t E, int k) { return moe::slots_in_one_launch((T
 @pytest.fixture(scope="session")
 def ffn_rules(tmp_path_factory):
     """The host rules of the grouped GEMM: grid(), equal_tile(), tile_at(), tile(), whose results are numbered as the enum in csrc/ffn_rules.h is, the same for a
-    product that keeps its pre-activations, tile_cost(), colsum_streams() and split(); and of the gate: one_block(), lane_topk_blocks(), one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
+    product that keeps its pre-activations, tile_cost(), cuts(), colsum_streams() and split(); and of the gate: one_block(), lane_topk_blocks(), one_launch(), dx_tokens(), backward_tokens(), wide_logits()."""
     d = tmp_path_factory.mktemp("rules")
     (d / "rules.cpp").write_text(RULES_SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", ROOT, str(d / "rules.cpp"), "-o", str(d / "rules.so")], check=True)
@@ -103,6 +104,7 @@ def ffn_rules(tmp_path_factory):
     lib.tile_at.restype = ctypes.c_int
     lib.tile_at.argtypes = [ctypes.c_int] * 2 + [ctypes.POINTER(ctypes.c_int)] + [ctypes.c_int] * 4 + [ctypes.POINTER(ctypes.c_int)]
     lib.tile.restype, lib.tile.argtypes = ctypes.c_int, [ctypes.c_int] + [ctypes.c_int64] * 6
+    lib.cuts.restype, lib.cuts.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_double, ctypes.c_int, ctypes.c_int64]
     lib.colsum_streams.restype, lib.colsum_streams.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_double] + [ctypes.c_int64] * 2
     lib.split.restype, lib.split.argtypes = ctypes.c_int, [ctypes.c_int64] * 4
     lib.tile_keeping_pre.restype, lib.tile_keeping_pre.argtypes = ctypes.c_int, [ctypes.c_int64] * 6

@@ -19,11 +19,11 @@ extern "C" {
 int64_t grid(int64_t tiles) { return moe::tile_grid(1, tiles, true, true); }
 int cuts(int64_t E, int64_t C, double rows, int up_to, int64_t NT) { return moe::cuts_last_round(E, C, rows, up_to, NT); }
 // as the kernel's search does it: the block whose tile block b works on, row and column half; false where there is nothing for b
-int part(int b, int blocks, int tall, int shorts, int* at) {
+int part(int b, int blocks, int tall, int shorts, int rounds, int* at) {
   moe::TileHalf half = {-1, -1};
   if (moe::may_be_cut(b, blocks, tall + shorts) && !moe::cut_tile(b, blocks, tall, shorts, half)) return 0;
-  at[0] = b; at[1] = half.row; at[2] = half.col;
-  return moe::tile_spot(b, tall, shorts, 0, moe::kGroupShift).part != moe::kNoTile;
+  at[0] = b; at[1] = half.row; at[2] = half.col; at[3] = moe::tile_spot(b, tall, shorts, rounds, moe::kGroupShift).part == moe::kDealtTile;
+  return moe::tile_spot(b, tall, shorts, rounds, moe::kGroupShift).part != moe::kNoTile;
 }
 }
 """
@@ -41,22 +41,24 @@ def rules(tmp_path_factory):
 
 
 def test_every_quarter_of_every_tile_once(rules):
-    """Any number of tall and short tiles, in a grid for just those and in one with room: every tile is computed whole or in all its parts, once."""
-    rng, at, seen = np.random.default_rng(0), (ctypes.c_int * 3)(), set()
-    for case in range(400):
-        tall, shorts = int(rng.integers(0, 900)), int(rng.integers(0, 200)) if case % 2 else 0
+    """Any number of tall and short tiles, with any number of whole groups dealt first, in a grid for just those and in one with room: every tile is computed
+    whole or in all its parts, once, and those of dealt groups whole."""
+    rng, at, seen = np.random.default_rng(0), (ctypes.c_int * 4)(), set()
+    for case in range(600):
+        tall, shorts = int(rng.integers(0, 900 if case < 400 else 4100)), int(rng.integers(0, 200)) if case % 2 else 0
+        rounds = int(rng.integers(0, tall // 256 + 1)) if case >= 400 else 0
         blocks = rules.grid(tall + shorts + (0 if case % 4 < 2 else int(rng.integers(0, 3000))))
         covered = {}
         for b in range(blocks + 64):
-            if not rules.part(b, blocks, tall, shorts, at):
+            if not rules.part(b, blocks, tall, shorts, rounds, at):
                 continue
-            assert b < blocks
+            assert b < blocks and not (at[3] and at[2] >= 0)
             rows, cols = ([v] if v >= 0 else [0, 1] for v in (at[1], at[2]))
-            seen.add((at[1] >= 0, at[2] >= 0))
+            seen.add((at[1] >= 0, at[2] >= 0, rounds > 0))
             for q in ((r, c) for r in rows for c in cols):
                 covered[at[0], q] = covered.get((at[0], q), 0) + 1
         assert set(covered.values()) <= {1} and len(covered) == 4 * (tall + shorts)
-    assert seen == {(False, False), (False, True), (True, True)}
+    assert seen == {(*parts, dealt) for parts in ((False, False), (False, True), (True, True)) for dealt in (False, True)}
 
 
 def test_launches_that_cut(rules):
@@ -115,20 +117,17 @@ FILLS = {                                              # row tiles x 6 column ti
 }
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("act", [O.ACT_RELU, O.ACT_GELU, O.ACT_SILU])
-@pytest.mark.parametrize("fills", FILLS, ids=str)
-def test_cut_products_have_the_same_bits(rules, ffn_rules, fills, act):
-    """The forward (plain, gathered, keeping its pre-activations) and the products with B transposed, all experts in one launch whose last round is
-    cut, against a launch for every expert on slabs of just its rows: the sums run in the same order, so the bits are equal.  Slots past
-    the fill are not written."""
+def check_cut_products(rules, fills, act, M, H, bias=True):
+    """All experts in one launch whose last round is cut against a launch for every expert on slabs of just its rows, none of which is cut: the sums run in the same order,
+    so the bits are equal.  Slots past the fill are not written."""
     from paper_2206_03382_amd import moe
-    E, C, M, H = 5, 2100, 1536, 1536
+    E, C = 5, 2100
     assert rules.cuts(E, C, C, 1, H // 256)
-    assert {ffn_rules.tile(0, E, C, M, H, 0, 0), ffn_rules.tile_keeping_pre(E, C, M, H, 0, 0), ffn_rules.tile(1, E, C, M, H, 0, 0)} == {0}
     gen = torch.Generator(device="cuda").manual_seed(len(fills) + act)
     rand = lambda *shape, std=1.0: (torch.randn(shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
     W1, W2, b1, b2 = rand(E, M, H, std=M ** -0.5), rand(E, H, M, std=H ** -0.5), rand(E, H), rand(E, M)
+    if not bias:
+        b1 = b2 = None
     T = 4000
     x, dY = rand(T, M), rand(E, C, M)
     slots = torch.randint(0, T, (E, C), generator=gen, device="cuda", dtype=torch.int32)
@@ -146,7 +145,7 @@ def test_cut_products_have_the_same_bits(rules, ffn_rules, fills, act):
         if n == 0:
             continue
         one = lambda t: t[e:e + 1, :n].contiguous()
-        w = [t[e:e + 1] for t in (W1, b1, W2, b2)]
+        w = [None if t is None else t[e:e + 1] for t in (W1, b1, W2, b2)]
         want_Y, want_hidden, want_pre = moe.expert_ffn_train(one(Z), *w, act)
         want = moe.expert_ffn_backward(one(Z), w[0], w[1], w[2], want_hidden, one(dY), act, pre=want_pre)
         for name, got, ref in (("hidden", hidden, want_hidden), ("Y", Y, want_Y), ("gathered", Yg, want_Y), ("Yt", Yt, want_Y), ("hidden_t", hidden_t, want_hidden),
@@ -154,3 +153,35 @@ def test_cut_products_have_the_same_bits(rules, ffn_rules, fills, act):
             assert torch.equal(got[e, :n], ref[0]), (name, e, n)
         for name in ("dW1", "dW2"):                    # of dP and hidden: dP is a product with B transposed
             assert torch.equal(g[name][e], want[name][0]), (name, e, n)
+
+
+def large_uncut(ffn_rules, rules, E, C, M, H):
+    """Which of the products on C rows (forward, keeping its pre-activations, B transposed; over M) run on the large tile; those that a launch of one expert cuts."""
+    tiles = (ffn_rules.tile(0, E, C, M, H, 0, 0), ffn_rules.tile_keeping_pre(E, C, M, H, 0, 0), ffn_rules.tile(1, E, C, M, H, 0, 0))
+    return [t == 0 for t in tiles], [t == 0 and E == 1 and bool(rules.cuts(1, C, C, 0, H // 256)) for t in tiles]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("act", [O.ACT_RELU, O.ACT_GELU, O.ACT_SILU])
+@pytest.mark.parametrize("fills", FILLS, ids=str)
+def test_cut_products_have_the_same_bits(rules, ffn_rules, fills, act):
+    """The forward (plain, gathered, keeping its pre-activations) and the products with B transposed."""
+    assert large_uncut(ffn_rules, rules, 5, 2100, 1536, 1536)[0] == [True] * 3
+    check_cut_products(rules, fills, act, 1536, 1536)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fills", ["quarters", "halves", "one row tile"])
+@pytest.mark.parametrize("K", [64, 128, 192, 256, 320])
+def test_cut_products_of_short_reductions(rules, ffn_rules, K, fills):
+    """One to five K-steps, fewer than, as many as and more than the rings of the parts hold (five and three): the product that keeps its pre-activations and the one with B transposed;
+    without biases, too.  (Off the grid of 256 the derivative of GELU has two forms, by the tile, which differ in the last bit: ReLU there.)"""
+    assert large_uncut(ffn_rules, rules, 5, 2100, K, 1536)[0][1:] == [True] * 2
+    check_cut_products(rules, fills, O.ACT_GELU if K == 256 else O.ACT_RELU, K, 1536, bias=K != 192)
+
+
+def test_single_launches_are_not_cut(rules, ffn_rules):
+    """What the tests above compare with: a launch of one expert on any of their fills takes another tile, or leaves whole rounds."""
+    for M in (64, 128, 192, 256, 320, 1536):
+        for n in {n for f in FILLS.values() for n in f if n}:
+            assert large_uncut(ffn_rules, rules, 1, n, M, 1536)[1] == [False] * 3, (M, n)

@@ -827,6 +827,15 @@ def test_gate_backward_few_tokens(moe, T, M, E):
     test_gate_backward(moe, synth.DT_BF16, T, M, E, 3, 1)
 
 
+@pytest.mark.parametrize("E", [64, 128])
+def test_gate_backward_last_round_in_parts(moe, ffn_rules, E):
+    """dx of a wide gate is a product on the large tile with B transposed, over one or two K-steps, that adds to what is there: with a last round that is
+    cut into parts, the last row tile of 25 rows."""
+    T, M = 16409, 1024
+    assert ffn_rules.tile(1, 1, T, E, M, 0, 0) == 0 and ffn_rules.cuts(1, T, T, 0, M // 256)
+    test_gate_backward(moe, synth.DT_BF16, T, M, E, 3, 1)
+
+
 # ----------------------------------------------------------------------------------------------------------------
 # moe_expert_ffn_backward
 # ----------------------------------------------------------------------------------------------------------------
