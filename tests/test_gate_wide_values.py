@@ -1,17 +1,18 @@
-"""Values at the ends of the storage types through the wide exact-logits kernel, which holds bf16 operands as the upper halves of fp64 values."""
+"""Values at the ends of the storage types through the exact-logits kernels; the wide one holds bf16 operands as the upper halves of fp64 values."""
 import pytest
 import torch
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("M,E", [(8, 72), (40, 128)])
-def test_wide_logits_of_extreme_values(dtype, M, E):
-    """Zeros of both signs, subnormals, the largest values, infinities and NaN against fp64: not-a-number and infinite where that is, else within one
+@pytest.mark.parametrize("M,E,wide", [(8, 72, 0), (8, 120, 120), (40, 128, 128), (40, 232, 232), (24, 136, 128)])
+def test_wide_logits_of_extreme_values(ffn_rules, dtype, M, E, wide):
+    """`wide` of the experts on the wide kernel (blocks of 64, the last one partly filled; part of a chunk of 32 k), the others on the narrow one.  Zeros of both signs, subnormals, the largest values, infinities and NaN against fp64: not-a-number and infinite where that is, else within one
     rounding (2^-23: the sums themselves err by M 2^-53 of the largest term, and no two large terms cancel.  A large weight beside the large tokens does
     not belong here: products of 4e38 of either sign leave what the others sum to within 8 * 2^-53 * 4e38, any order being as good)."""
     from paper_2206_03382_amd import moe
     T = 2 ** 22 // E + 33
+    assert ffn_rules.wide_logits(T, E, 1) == wide
     gen = torch.Generator(device="cuda").manual_seed(E)
     x, Wg = (torch.rand(s, generator=gen, device="cuda") + 0.5 for s in ((T, M), (M, E)))
     big, tiny = float(torch.finfo(dtype).max), float(torch.finfo(dtype).smallest_normal)

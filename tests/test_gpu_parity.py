@@ -291,8 +291,8 @@ def test_gate_logits(moe, dtype, T, M, E, bias):
 @pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16])
 @pytest.mark.parametrize("T,M,E", [(1, 8, 65), (31, 24, 72), (32, 32, 128), (33, 40, 129), (97, 72, 192), (64, 256, 136)])
 def test_gate_logits_wide_edges(moe, dtype, T, M, E):
-    """Gates beyond 64 experts around the block (32 tokens x 128 experts) and the chunk (32 k); Wg also at an address that
-    is aligned to one element only.  Bound: as above."""
+    """Gates beyond 64 experts of few tokens, which the wide kernel does not take, around a tile (16 tokens x 16 experts) and a pass (32 k); Wg also at an
+    address that is aligned to one element only.  Bound: as above."""
     cfg = synth.CONFIGS[1].scaled(T=T, M=M, H=8, E=E, dtype=dtype, cfg_id=44)
     inp = synth.make_inputs(cfg, seed=T + E)
     ref = O.gate_logits(inp["x"], inp["Wg"], None)
@@ -309,7 +309,7 @@ def test_gate_logits_wide_edges(moe, dtype, T, M, E):
 @pytest.mark.parametrize("T,M,E", [(8200, 40, 65), (8200, 72, 100), (32768, 24, 128), (32767, 24, 128), (30850, 32, 136), (32776, 40, 232), (16400, 24, 40),
                                    (16384, 40, 24), (9000, 1032, 130)])
 def test_gate_logits_wide_and_narrow(moe, dtype, T, M, E):
-    """Around the counts of tokens and experts that send blocks of 128 experts to the wide kernel and the rest to the narrow one,
+    """Around the counts of tokens and experts that send whole 128s of experts to the wide kernel and the rest to the narrow one,
     in its forms of one and two token tiles.  Bound: as above."""
     test_gate_logits(moe, dtype, T, M, E, True)
 
