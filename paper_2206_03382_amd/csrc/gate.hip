@@ -168,7 +168,7 @@ __global__ __launch_bounds__(64 * KS) void gate_logits_kernel(const XT* __restri
 // other's staging.  What binds is the fp64 matrix pipe and beside it the conversions.  Blocks are small because the count of blocks per unit is what
 // divides unevenly; all expert blocks go in one launch.  Replaced blocks of 128 experts, seven to a unit, both operands in fp32: 25088 tokens, M = 768, 256
 // columns 203 -> 186 us (53 TFLOP/s; the fp64 matrix pipe alone sustains 67), of which the conversions 3 us by the profiler; fp32, 65536 tokens, M = 2048, 128
-// experts 632 -> 598; 131072, M = 1024, 96 492 and 493.  (Those replaced four waves of 16 tokens x 128 experts on fp64 weights in LDS, 275 us.)
+// experts 632 -> 598; over 300 gates of 104 to 512 experts between 0.87 and 1.01 of their time from M = 256 on, with M = 64 up to 1.03 (201650 tokens, 104 experts 68.6 and 70.7).  (Those replaced four waves of 16 tokens x 128 experts on fp64 weights in LDS, 275 us.)
 // LDS rows: 36 values per token (16 rows x 4 groups of a ds_read_b128 spread over all banks), 66 per k of the weights (the
 // four k of an operand read lie 16 banks apart).
 constexpr int kWideTokens = 32, kWideExperts = 64, kWideK = 32, kWideLdx = 36, kWideLdw = 66;
@@ -185,7 +185,7 @@ template <typename XT> __device__ __forceinline__ double wide_load(float v) {
 
 // E a multiple of 8 and Wg 16-byte aligned.
 template <typename XT>
-__global__ __launch_bounds__(256, sizeof(XT) == 2 ? 8 : 6) void gate_logits_wide_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
+__global__ __launch_bounds__(256, 8) void gate_logits_wide_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg,
                                                                const float* __restrict__ bias, int64_t T, int M, int E,
                                                                int expert_blocks, float* __restrict__ logits) {
   __shared__ __attribute__((aligned(16))) float xs[kWideTokens * kWideLdx];
@@ -1003,8 +1003,9 @@ __global__ __launch_bounds__(kSmallGateTokens) void gate_small_kernel(const floa
 
 // The whole gate of up to 16 tokens (the rule: gate_rules.h): the one tile of logits_of_tiles and, in the same block, the decisions on it.  A decode step
 // is launches that wait for each other: logits 8.2 us and decisions 4.9 in two launches, 12.3 so by the profiler, and a launch less to wait for (16 tokens, 8 experts
-// 2048 x 2048, whole pass 47.4 -> 46.0; 256 x 256, 4 experts 19.0 -> 17.1).  What binds is one unit's fp64 matrix pipe (M / 4 instructions of 64
-// cycles over four of them) and two trips to memory; with four passes in flight instead of two 12.8.
+// 2048 x 2048, whole pass 47.4 -> 46.0; 256 x 256, 4 experts 19.0 -> 17.1).  Of the 12 us 5.9 do not depend on M (launch, the sums through LDS, the decisions, their stores: captured, M = 8),
+// and each 1024 k are another 2.9, of which one unit's fp64 matrix pipes take 1.7 (M / 4 instructions of 64 cycles over four of them at 2.4 GHz) and the passes' trips to memory the
+// rest; with four passes in flight instead of two 12.8.
 template <typename XT, int G>
 __global__ __launch_bounds__(64 * 16) void gate_few_tokens_kernel(const XT* __restrict__ x, const XT* __restrict__ Wg, const float* __restrict__ bias, int T,
                                                                   int M, int E, float* logits, int bits, int k, int64_t C, int normalize,

@@ -28,7 +28,8 @@ inline bool gate_in_one_block(int64_t T, int64_t E, int k, int64_t marked_C) {
 }
 
 // Whether such a gate's logits are computed by that block as well (gate_few_tokens_kernel): where they are one tile of 16 tokens x 16 experts, which one block
-// computes anyhow.  (More tokens are more tiles, which as many units compute at once.)  One or two experts stay with two launches.
+// computes anyhow.  (More tokens are more tiles, which as many units compute at once.)  One or two experts, which have lane groups of
+// their own in the decisions, would need two more instantiations per type, for gates that leave little to choose: they stay with two launches.
 constexpr int64_t kFewGateTokens = 16;
 inline bool gate_of_few_tokens(int64_t T, int64_t E, int k, int64_t marked_C) {
   return T <= kFewGateTokens && E > 2 && gate_in_one_block(T, E, k, marked_C);
@@ -51,11 +52,11 @@ inline int64_t gate_lane_topk_blocks(int64_t E, int k, int64_t M) {
   return line < 512 ? 512 : (line > 1024 ? 1024 : line);
 }
 
-// Experts whose exact logits the wide kernel takes, in blocks of 128 (vecw: its 16-byte pieces of Wg's rows are whole); the narrow
-// kernel takes the others, 64 at a time.  The line was drawn with blocks of 128 (they are 64 wide now, and 4 to 8 % faster where they run), which
-// fill badly with few tokens or with a remainder: fp32, M = 2048, narrow and
-// wide 4096 tokens, 128 experts 56 and 132 us, 16384 168 and 189, 65536 661 and 630; 12000, 512 502 and 484; 65536, 96 520 and 628;
-// 136 (128 + 8 against 256) 766 and 1210; 120 697 and 629.
+// Experts whose exact logits the wide kernel takes (vecw: its 16-byte pieces of Wg's rows are whole): whole 128s, two of its blocks, and what is left
+// beyond them if it is more than 96; the narrow kernel takes the others, 64 at a time.  A block's 64 columns take the same time whether they are filled or not, and few
+// tokens leave units without a block.  fp32, M = 2048, all narrow and all wide: 4096 tokens, 128 experts 54 and 75 us, 16384 168 and 175, 32768 324 and 319, 65536 658 and
+// 610; 12000, 512 486 and 455; 65536, 72 468 and 602, 96 517 and 604, 104 688 and 605, 120 686 and 609; 136 722 as 128 + 8, 792 and 880; 160 774 as 128 + 32, 837 and 876.
+// Only at 64 beyond a 128 all wide would be the better: 192 936 as 128 + 64, 983 and 890 (32768 tokens 489, 486 and 463).
 inline int64_t gate_logits_wide_experts(int64_t T, int64_t E, bool vecw) {
   if (E <= 64 || !vecw || T * E < ((int64_t)1 << 22)) return 0;
   const int64_t left = E % 128;

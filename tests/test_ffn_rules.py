@@ -269,7 +269,7 @@ def test_gate_backward_tokens_per_block(ffn_rules):
 
 
 def test_wide_logits(ffn_rules):
-    """Blocks of 128 experts only where they measured faster than 64 at a time, and never for a remainder they would mostly pad."""
+    """Whole 128s of experts where they measured faster than 64 at a time on the narrow kernel, and never a remainder that would mostly be padding."""
     for T, E, wide in ((65536, 128, 128), (65536, 136, 128), (65536, 120, 120), (65536, 96, 0), (65536, 65, 0), (65536, 192, 128), (12000, 512, 512),
                        (8200, 136, 0), (16384, 128, 0), (25088, 256, 256), (65536, 64, 0)):
         assert ffn_rules.wide_logits(T, E, 1) == wide, (T, E)
