@@ -90,7 +90,7 @@ MOE_HOST_DEVICE inline TileSpot tile_spot(int b, int tall, int shorts, int round
 // hold them all for a tile's time: up to 8 tiles go out as quarters of 128 x 128, up to 16 as halves of 256 x 128 columns (ffn_piece.h), which
 // end 0.25-0.45 and 0.65 of a tile's time later.  Two products of 8 experts, 2048 x 2048: 4096 rows and one expert of 4352 518 us whole, 481 cut; 7
 // of them 531 and 503 (nine to sixteen tiles: 4352 rows and one of 4608 531 in whole tiles, 514 in halves; 7 of those 536 and 529, 549 in quarters);
-// 1100 rows each 196 and 153; 4096 rows and one 4126, 492 and 481.  From 17 tiles on both forms take as long as the tiles themselves.
+// 1100 rows each 196 and 153, forced onto this tile (tile_of gives them to the half tile, 162); 4096 rows and one 4126, 492 and 481.  From 17 tiles on both forms take as long as the tiles themselves.
 // Blocks that find no tile cost a unit 0.38 us each, and after a partial round they run on the units that it leaves idle; after pieces none is idle.
 // So launches with more than 2048 of them (imbalanced gates) stay whole: 64 experts, 65536 tokens, Zipf, 1024 x 4096, 8200 blocks for 848 tiles 143 us, 147 cut.
 constexpr int kCutQuarters = 8, kCutHalves = 16, kCutSurplus = 2048;
@@ -163,7 +163,8 @@ static inline bool cut_short_tiles_end_later(int experts, int row_tiles, int NT,
 }
 // Whether a launch gets the kernel that can cut, and the blocks for it: by the tiles of an XCD if every expert has `rows` rows (up to) on average, give or
 // take a standard deviation of even choices.  One that has nothing to cut would pay 0.5-1 us for the longer kernel and the blocks (64 experts x 283 rows, 768 x 512:
-// second product 25.0 us, 25.9 so); beyond 16 rounds a part of the last one is no more than that either.
+// second product 25.0 us, 25.9 so); beyond 16 rounds a part of the last one is no more than that either.  The reduction is not asked: 490 drawn products, all experts full or an even
+// gate, took 0.83 of the time cut for K = 64, 0.96 for 128 and 256, 0.92 for 384 to 1024 and 0.88 for 1536 and 2048, 240 with a Zipf-shaped gate 0.96, 0.96, 0.90 and 0.92.
 static inline bool cuts_last_round(int64_t E, int64_t C, double rows, bool up_to, int64_t NT) {
   const double off = up_to ? sqrt(rows) : 0.0, low = rows - off > 1.0 ? rows - off : 1.0, high = rows + off < (double)C ? rows + off : (double)C;
   const double n = (double)(E * NT) * (ceil(low / kLargeTile) + ceil(high / kLargeTile)) / 16.0;
@@ -282,6 +283,7 @@ static inline bool large_tile_supports_backward(int64_t E, int64_t C, int64_t M,
 //     Forward products only: with a transposed B (64-byte pieces of k, where the large tile loads 128) it is the slower at nearly
 //     every size (backward of 32 x 784 rows: 251 and 198 us against 226 and 171), and a training step's first product, which
 //     writes twice, gains nothing (216 against 212).
+// Where the large tile's last round is cut (cuts_last_round), the estimate still counts a whole one: what it says of such launches is too much.
 //   64 x 128 (two blocks) is for the launches between: two products of 8 experts x 96 rows, K = N = 2048: 68 us on 128 x 128 and 61
 //     on 64 x 64 -> 53.
 //
